@@ -17,8 +17,11 @@ namespace ihmc {
 // In the phi form the estimator slots hold the sums of t = tanh(h' + phi):
 // T_PSI sum t, T_PSIH sum h' t, T_UT t.K t, and `t2` is sum t^2 of the
 // proposal; the records then hold the spin expectations given phi.
+// `st` may be a copy of the state in LDS.  `r_acc`: the trajectory's accept
+// uniform, when the caller has drawn it already.
 __device__ __forceinline__ uint32_t finalize_trajectory(const ChainDev& cd, ChainState* st, int last_buf,
-                                                        const u128* sum, uint32_t bad, double t2 = 0.0) {
+                                                        const u128* sum, uint32_t bad, double t2 = 0.0,
+                                                        const double* r_acc = nullptr) {
   // Every field of the state that the step reads is loaded up front (one round
   // trip of independent loads rather than a chain of dependent ones) and the
   // changed ones are stored at the end.
@@ -46,7 +49,7 @@ __device__ __forceinline__ uint32_t finalize_trajectory(const ChainDev& cd, Chai
   if (cd.replay && t < cd.cap) {
     accept = cd.replay[t] != 0;
   } else {
-    const double r = uniform_at(cd, (uint32_t)t, TAG_ACC);
+    const double r = r_acc ? *r_acc : uniform_at(cd, (uint32_t)t, TAG_ACC);
     accept = finite && (dH <= 0.0 || r < exp(-dH));
   }
   if (finite && !cur_bad && counted) sum_exp_mdh += exp(-dH);

@@ -1,0 +1,114 @@
+// Per-site building blocks shared by the tiled and the LDS-resident lattice
+// kernels: vector accesses of the state arrays and the FP64 action terms.
+#pragma once
+
+#include "device_common.hpp"
+
+namespace ihmc {
+
+template <typename T>
+__device__ __forceinline__ T neg_if(T v, int sign) {
+  return sign < 0 ? -v : v;
+}
+
+// Four consecutive state values (16 bytes for FP32, 32 bytes for FP64).
+template <typename T>
+__device__ __forceinline__ void ld4(const T* __restrict__ p, T (&v)[4]);
+template <>
+__device__ __forceinline__ void ld4<float>(const float* __restrict__ p, float (&v)[4]) {
+  const float4 q = *reinterpret_cast<const float4*>(p);
+  v[0] = q.x;
+  v[1] = q.y;
+  v[2] = q.z;
+  v[3] = q.w;
+}
+template <>
+__device__ __forceinline__ void ld4<double>(const double* __restrict__ p, double (&v)[4]) {
+  const double2 a = reinterpret_cast<const double2*>(p)[0];
+  const double2 b = reinterpret_cast<const double2*>(p)[1];
+  v[0] = a.x;
+  v[1] = a.y;
+  v[2] = b.x;
+  v[3] = b.y;
+}
+// The state arrays that the chain table points to live in global memory.
+// Accessing them through pointers of the global address space lets the
+// compiler use global rather than flat memory instructions: a flat access
+// counts as an LDS access too, so every wait for LDS data would also wait for
+// the global loads still in flight.
+template <class T>
+using gmem = __attribute__((address_space(1))) T;
+typedef float vf4 __attribute__((ext_vector_type(4)));
+typedef double vd2 __attribute__((ext_vector_type(2)));
+
+template <typename T>
+__device__ __forceinline__ void ld4g(const gmem<T>* p, T (&v)[4]);
+template <>
+__device__ __forceinline__ void ld4g<float>(const gmem<float>* p, float (&v)[4]) {
+  const vf4 q = *(const gmem<vf4>*)p;
+  v[0] = q.x;
+  v[1] = q.y;
+  v[2] = q.z;
+  v[3] = q.w;
+}
+template <>
+__device__ __forceinline__ void ld4g<double>(const gmem<double>* p, double (&v)[4]) {
+  const vd2 a = ((const gmem<vd2>*)p)[0];
+  const vd2 b = ((const gmem<vd2>*)p)[1];
+  v[0] = a.x;
+  v[1] = a.y;
+  v[2] = b.x;
+  v[3] = b.y;
+}
+template <typename T>
+__device__ __forceinline__ void st4g(gmem<T>* p, const T (&v)[4]);
+template <>
+__device__ __forceinline__ void st4g<float>(gmem<float>* p, const float (&v)[4]) {
+  *(gmem<vf4>*)p = vf4{v[0], v[1], v[2], v[3]};
+}
+template <>
+__device__ __forceinline__ void st4g<double>(gmem<double>* p, const double (&v)[4]) {
+  ((gmem<vd2>*)p)[0] = vd2{v[0], v[1]};
+  ((gmem<vd2>*)p)[1] = vd2{v[2], v[3]};
+}
+
+template <typename T>
+__device__ __forceinline__ void st4(T* __restrict__ p, const T (&v)[4]);
+template <>
+__device__ __forceinline__ void st4<float>(float* __restrict__ p, const float (&v)[4]) {
+  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+}
+template <>
+__device__ __forceinline__ void st4<double>(double* __restrict__ p, const double (&v)[4]) {
+  reinterpret_cast<double2*>(p)[0] = make_double2(v[0], v[1]);
+  reinterpret_cast<double2*>(p)[1] = make_double2(v[2], v[3]);
+}
+
+// FP64 action and estimator terms of one site of the stored field: the integer
+// stencil weights are exact, C and sqrt(J') are the true FP64 constants.
+//   h[0]  S-density   1/2 psi u - psi h'/sqrt(J') - log cosh(sqrt(J') u)
+//   h[1]  psi
+//   h[2]  psi h'
+//   h[3]  u tanh(sqrt(J') u)
+// or, in the shifted form (b0 = 0, hw = h'), with y = sqrt(J') u + h':
+//   h[0] = 1/2 psi u - log cosh(y),  h[3] = y tanh(y).
+// `act` = the site belongs to the lattice (a quad may reach into the row
+// padding, a column into the plane padding): inactive sites give exact zeros.
+__device__ __forceinline__ void h_terms(const ChainDev& cd, double v, double nb, int64_t idx, bool act,
+                                        double (&h)[4]) {
+  const double u = cd.C * v + nb;
+  const double y = __builtin_fma(cd.sqJ, u, cd.hw);
+  double lc, th;
+  logcosh_tanh(y, lc, th);
+  double hpx = cd.hp0, bx = cd.b0;
+  if (cd.h_kind == 2) {
+    hpx = cd.hp[idx];
+    bx = hpx / cd.sqJ;
+  }
+  h[0] = act ? 0.5 * v * u - v * bx - lc : 0.0;
+  h[1] = act ? v : 0.0;
+  h[2] = act ? v * hpx : 0.0;
+  h[3] = act ? (cd.form == FORM_SHIFTED ? y : u) * th : 0.0;
+}
+
+}  // namespace ihmc

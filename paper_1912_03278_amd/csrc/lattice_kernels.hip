@@ -26,6 +26,7 @@
 // tile shape or on which chains share a launch.
 #include "chain_epilogue.hpp"
 #include "device_common.hpp"
+#include "lattice_common.hpp"
 #include "lattice_kernels.hpp"
 
 namespace ihmc {
@@ -47,72 +48,6 @@ __device__ __forceinline__ int wrap_any(int v, int L) {
 // the buffer addresses derived from them stay in scalar registers.
 __device__ __forceinline__ int32_t state_word(const int32_t* p) {
   return *(const __attribute__((address_space(4))) int32_t*)p;
-}
-
-template <typename T>
-__device__ __forceinline__ T neg_if(T v, int sign) {
-  return sign < 0 ? -v : v;
-}
-
-// Four consecutive state values (16 bytes for FP32, 32 bytes for FP64).
-template <typename T>
-__device__ __forceinline__ void ld4(const T* __restrict__ p, T (&v)[4]);
-template <>
-__device__ __forceinline__ void ld4<float>(const float* __restrict__ p, float (&v)[4]) {
-  const float4 q = *reinterpret_cast<const float4*>(p);
-  v[0] = q.x;
-  v[1] = q.y;
-  v[2] = q.z;
-  v[3] = q.w;
-}
-template <>
-__device__ __forceinline__ void ld4<double>(const double* __restrict__ p, double (&v)[4]) {
-  const double2 a = reinterpret_cast<const double2*>(p)[0];
-  const double2 b = reinterpret_cast<const double2*>(p)[1];
-  v[0] = a.x;
-  v[1] = a.y;
-  v[2] = b.x;
-  v[3] = b.y;
-}
-// The state arrays that the chain table points to live in global memory.
-// Accessing them through pointers of the global address space lets the
-// compiler use global rather than flat memory instructions: a flat access
-// counts as an LDS access too, so every wait for LDS data would also wait for
-// the global loads still in flight.
-template <class T>
-using gmem = __attribute__((address_space(1))) T;
-typedef float vf4 __attribute__((ext_vector_type(4)));
-typedef double vd2 __attribute__((ext_vector_type(2)));
-
-template <typename T>
-__device__ __forceinline__ void ld4g(const gmem<T>* p, T (&v)[4]);
-template <>
-__device__ __forceinline__ void ld4g<float>(const gmem<float>* p, float (&v)[4]) {
-  const vf4 q = *(const gmem<vf4>*)p;
-  v[0] = q.x;
-  v[1] = q.y;
-  v[2] = q.z;
-  v[3] = q.w;
-}
-template <>
-__device__ __forceinline__ void ld4g<double>(const gmem<double>* p, double (&v)[4]) {
-  const vd2 a = ((const gmem<vd2>*)p)[0];
-  const vd2 b = ((const gmem<vd2>*)p)[1];
-  v[0] = a.x;
-  v[1] = a.y;
-  v[2] = b.x;
-  v[3] = b.y;
-}
-template <typename T>
-__device__ __forceinline__ void st4g(gmem<T>* p, const T (&v)[4]);
-template <>
-__device__ __forceinline__ void st4g<float>(gmem<float>* p, const float (&v)[4]) {
-  *(gmem<vf4>*)p = vf4{v[0], v[1], v[2], v[3]};
-}
-template <>
-__device__ __forceinline__ void st4g<double>(gmem<double>* p, const double (&v)[4]) {
-  ((gmem<vd2>*)p)[0] = vd2{v[0], v[1]};
-  ((gmem<vd2>*)p)[1] = vd2{v[2], v[3]};
 }
 
 // Where a staging thread finds its 4-element chunk x .. x+3 of every row it
@@ -154,45 +89,6 @@ __device__ __forceinline__ void load_chunk(const gmem<T>* row, const ChunkPos& c
 // Element offset of a row from its index and the row pitch (both non-negative).
 __device__ __forceinline__ uint64_t row_offset(int idx, int64_t stride) {
   return (uint64_t)(uint32_t)idx * (uint64_t)stride;
-}
-
-template <typename T>
-__device__ __forceinline__ void st4(T* __restrict__ p, const T (&v)[4]);
-template <>
-__device__ __forceinline__ void st4<float>(float* __restrict__ p, const float (&v)[4]) {
-  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-}
-template <>
-__device__ __forceinline__ void st4<double>(double* __restrict__ p, const double (&v)[4]) {
-  reinterpret_cast<double2*>(p)[0] = make_double2(v[0], v[1]);
-  reinterpret_cast<double2*>(p)[1] = make_double2(v[2], v[3]);
-}
-
-// FP64 action and estimator terms of one site of the stored field: the integer
-// stencil weights are exact, C and sqrt(J') are the true FP64 constants.
-//   h[0]  S-density   1/2 psi u - psi h'/sqrt(J') - log cosh(sqrt(J') u)
-//   h[1]  psi
-//   h[2]  psi h'
-//   h[3]  u tanh(sqrt(J') u)
-// or, in the shifted form (b0 = 0, hw = h'), with y = sqrt(J') u + h':
-//   h[0] = 1/2 psi u - log cosh(y),  h[3] = y tanh(y).
-// `act` = the site belongs to the lattice (a quad may reach into the row
-// padding, a column into the plane padding): inactive sites give exact zeros.
-__device__ __forceinline__ void h_terms(const ChainDev& cd, double v, double nb, int64_t idx, bool act,
-                                        double (&h)[4]) {
-  const double u = cd.C * v + nb;
-  const double y = __builtin_fma(cd.sqJ, u, cd.hw);
-  double lc, th;
-  logcosh_tanh(y, lc, th);
-  double hpx = cd.hp0, bx = cd.b0;
-  if (cd.h_kind == 2) {
-    hpx = cd.hp[idx];
-    bx = hpx / cd.sqJ;
-  }
-  h[0] = act ? 0.5 * v * u - v * bx - lc : 0.0;
-  h[1] = act ? v : 0.0;
-  h[2] = act ? v * hpx : 0.0;
-  h[3] = act ? (cd.form == FORM_SHIFTED ? y : u) * th : 0.0;
 }
 
 // Workgroups are dealt to the eight XCDs round-robin (block b runs on XCD b % 8),
@@ -943,299 +839,6 @@ __global__ __launch_bounds__(64 * ZR, 8) void lattice_pass3t(const ChainDev* __r
   block_accumulate_ranks<MODE, NT / 64, NR>(cd, st, accR, bad, lat_in_buf(cur, k), tix);
 }
 
-// ---------------------------------------------------- LDS-resident chains ---
-//
-// One workgroup runs whole trajectories of one small chain (one Tile entry per
-// chain names it) with the accepted field, the working field, the momenta, w
-// and the per-site field held in LDS in logical site order: every pass of the
-// trajectory, its FP64 sums and the Metropolis step in one launch, with no
-// partial-sum table and no launch per pass.  The per-site arithmetic and the
-// grouping of the FP64 sums (in 2D 16 x-aligned sites as four quads; in 3D
-// x-aligned quads of columns, each column first summed over an aligned 4-plane
-// slab, in z order) are those of the tiled passes, so a resident chain's
-// trajectory is bit-identical to the tiled one.
-// n_traj = 0 measures S and the estimator sums of the accepted field (the
-// set-up pass) instead.
-constexpr int RES_THREADS = 256;
-// field arrays: under half of the 160 KiB LDS with the reduction scratch, so
-// two chains share a CU; 64 x 64 FP32 chains fit (without a per-site field)
-constexpr int RES_LDS_BYTES = 81408;
-
-int resident_max_sites(int precision, bool site_field) { return RES_LDS_BYTES / ((site_field ? 5 : 4) * precision); }
-
-// LDS a launch reserves beyond the kernel's own when it runs beside tiled
-// passes: enough that a CU holds one resident chain instead of two, so the
-// other half of the CU's LDS stays with the tiled blocks (as many of them fit
-// there as without it).
-constexpr int RES_SOLO_LDS_PAD = 1024;
-static_assert(2 * (RES_LDS_BYTES + RES_SOLO_LDS_PAD) > 160 * 1024, "one resident chain per CU");
-
-// Two workgroups per CU also need the registers of two waves per SIMD (at most
-// 256 per lane): left to itself the compiler spends more on the Metropolis
-// step and the FP64 draws, which run once per trajectory, and the CU then
-// holds one chain.  The bound keeps two, at the price of a few spilled FP64
-// constants reloaded at the trajectory's end.
-template <typename T, int NDIM>
-__global__ __launch_bounds__(RES_THREADS, 2) void lattice_resident(const ChainDev* __restrict__ chains,
-                                                                const Tile* __restrict__ tiles, int n_traj) {
-  __shared__ __align__(16) unsigned char lds[RES_LDS_BYTES];
-  __shared__ u128 sRed[RES_THREADS / 64][NTERM];
-  __shared__ uint32_t sBad[RES_THREADS / 64];
-  __shared__ int sSign, sTraj;
-  __shared__ uint32_t sFlags;
-  const ChainDev& cd = chains[tiles[blockIdx.x].chain];
-  ChainState* st = cd.st;
-  const int L0 = cd.L0, L1 = cd.L1, L2 = (NDIM == 3) ? cd.L2 : 1;
-  const int N = (int)cd.N;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const bool site_field = (cd.h_kind == 2);
-  T* sA = reinterpret_cast<T*>(lds);  // accepted field as stored (sign not applied)
-  T* sP = sA + N;                     // working field
-  T* sM = sP + N;                     // momenta
-  T* sW = sM + N;                     // w
-  T* sB = sW + N;                     // h'/sqrt(J') per site (site field only)
-  const int pitch = cd.pitch, plane = L0 * L1;
-  const int cur = st->cur;
-  gmem<T>* __restrict__ gpsi = (gmem<T>*)cd.psi + (int64_t)cur * cd.NP;
-  for (int i = tid; i < N; i += RES_THREADS) {
-    const int64_t g = (i % L0) + (int64_t)pitch * (i / L0);
-    sA[i] = gpsi[g];
-    if (site_field) sB[i] = ((const gmem<T>*)cd.b)[g];
-  }
-  const T b_uniform = (T)cd.b0;
-  const T Ct = (T)cd.C;
-  const T at = (T)cd.sqJ, hw = (T)cd.hw;
-
-  // periodic neighbours of logical site i = x + L0 (y + L1 z)
-  struct Nb {
-    int xm, xp, ym, yp, zm, zp;
-  };
-  auto nbrs = [&](int i, int x, int y, int z) {
-    Nb n;
-    n.xm = i + (x == 0 ? L0 - 1 : -1);
-    n.xp = i + (x == L0 - 1 ? 1 - L0 : 1);
-    n.ym = i + (y == 0 ? (L1 - 1) * L0 : -L0);
-    n.yp = i + (y == L1 - 1 ? -(L1 - 1) * L0 : L0);
-    n.zm = i, n.zp = i;
-    if (NDIM == 3) {
-      n.zm = i + (z == 0 ? (L2 - 1) * plane : -plane);
-      n.zp = i + (z == L2 - 1 ? -(L2 - 1) * plane : plane);
-    }
-    return n;
-  };
-  // FP64 sums of per-site terms into fixed point, grouped as in the tiled
-  // passes: per 16 x-aligned sites, as (q0 + q1) + (q2 + q3) of their quads
-  // (2D); per quad of columns each summed over an aligned 4-plane slab (3D).
-  // term(i, x, y, z, out) fills the K terms listed in `which`; sites past the
-  // row end contribute zeros.
-  constexpr int UQ = (NDIM == 2) ? 4 : 1;  // quads per unit
-  const int nq = (L0 + 4 * UQ - 1) / (4 * UQ), ns = (NDIM == 3) ? (L2 + 3) / 4 : 1;
-  const int n_units = nq * L1 * ns;
-  auto unit_sums = [&](auto term, const int* which, int K, u128* acc, uint32_t& bad) {
-    for (int u = tid; u < n_units; u += RES_THREADS) {
-      const int q = u % nq, r = u / nq, y = r % L1, sl = r / L1;
-      // unit total (q0 + q1) + (q2 + q3) over its quads, built as the quads come
-      double first[5], total[5];
-#pragma unroll 1
-      for (int g = 0; g < UQ; ++g) {
-        double col[5][4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-#pragma unroll
-          for (int a = 0; a < 5; ++a) col[a][e] = 0.0;
-          const int x = 4 * (UQ * q + g) + e;
-          if (x >= L0) continue;
-          const int z0 = 4 * sl, z1 = (NDIM == 3) ? min(z0 + 4, L2) : 1;
-          for (int z = z0; z < z1; ++z) {
-            double v[5];
-            term(x + L0 * (y + L1 * z), x, y, z, v);
-            for (int a = 0; a < K; ++a) col[a][e] = col[a][e] + v[a];
-          }
-        }
-#pragma unroll
-        for (int a = 0; a < 5; ++a) {
-          const double qv = quad_sum(col[a][0], col[a][1], col[a][2], col[a][3]);
-          if (UQ == 1) {
-            total[a] = qv;
-          } else if ((g & 1) == 0) {
-            first[a] = qv;
-          } else {
-            const double pr = first[a] + qv;
-            total[a] = (g == 1) ? pr : total[a] + pr;
-          }
-        }
-      }
-      for (int a = 0; a < K; ++a) acc[which[a]] = add128(acc[which[a]], to_fixed(total[a], bad));
-    }
-  };
-  // S-density, psi, psi h', u tanh(sqrt(J') u) of the field in sP (FP64)
-  auto action_terms = [&](int i, int x, int y, int z, double* v) {
-    const Nb n = nbrs(i, x, y, z);
-    double nb = ((double)sP[n.xm] + (double)sP[n.xp]) + ((double)sP[n.ym] + (double)sP[n.yp]);
-    if (NDIM == 3) nb = nb + ((double)sP[n.zm] + (double)sP[n.zp]);
-    double h[4];
-    h_terms(cd, (double)sP[i], nb, x + (int64_t)pitch * (y + (int64_t)L1 * z), true, h);
-    v[0] = h[0];
-    v[1] = h[1];
-    v[2] = h[2];
-    v[3] = h[3];
-  };
-  // the block's fixed-point totals, for thread 0
-  auto block_total = [&](const u128* acc, uint32_t bad, u128* sum) {
-#pragma unroll
-    for (int a = 0; a < NTERM; ++a) {
-      const u128 v = wave_sum128(acc[a]);
-      if (lane == 0) sRed[wave][a] = v;
-    }
-    const unsigned long long any = __ballot(bad != 0u);
-    if (lane == 0) sBad[wave] = any ? 1u : 0u;
-    __syncthreads();
-    uint32_t b = 0u;
-    if (tid == 0) {
-      for (int a = 0; a < NTERM; ++a) {
-        u128 v = sRed[0][a];
-        for (int w = 1; w < RES_THREADS / 64; ++w) v = add128(v, sRed[w][a]);
-        sum[a] = v;
-      }
-      for (int w = 0; w < RES_THREADS / 64; ++w) b |= sBad[w];
-    }
-    return b;
-  };
-  // The sites of a thread are tid, tid + NTHR, ...: their coordinates start
-  // from those of tid and advance by fixed steps with carries, which keeps
-  // integer division out of the pass loops.
-  struct Walk {
-    int x, y, z;
-  };
-  const int step_x = RES_THREADS % L0, step_r = RES_THREADS / L0;
-  const int step_y = step_r % L1, step_z = step_r / L1;
-  Walk w0;
-  w0.x = tid % L0;
-  w0.y = (tid / L0) % L1;
-  w0.z = (tid / L0) / L1;
-  auto advance_walk = [&](Walk& c) {
-    c.x += step_x;
-    int carry = 0;
-    if (c.x >= L0) {
-      c.x -= L0;
-      carry = 1;
-    }
-    c.y += step_y + carry;
-    carry = 0;
-    if (c.y >= L1) {
-      c.y -= L1;
-      carry = 1;
-    }
-    c.z += step_z + carry;
-  };
-
-  if (n_traj == 0) {  // set-up: S and the estimator sums of the accepted field
-    const int sign = st->sign;
-    for (int i = tid; i < N; i += RES_THREADS) sP[i] = neg_if(sA[i], sign);
-    __syncthreads();
-    u128 acc[NTERM];
-    for (int a = 0; a < NTERM; ++a) acc[a] = u128{0ull, 0ull};
-    uint32_t bad = 0u;
-    const int which[4] = {T_S, T_PSI, T_PSIH, T_UT};
-    unit_sums(action_terms, which, 4, acc, bad);
-    u128 sum[NTERM];
-    const uint32_t b = block_total(acc, bad, sum);
-    if (tid == 0) finalize_measure(st, sum, b);
-    return;
-  }
-
-  for (int t = 0; t < n_traj; ++t) {
-    if (tid == 0) {
-      sSign = st->sign;
-      sTraj = st->traj;
-    }
-    __syncthreads();
-    const int sign = sSign;
-    const uint32_t traj = (uint32_t)sTraj;
-    // working field; fresh momenta, one Philox draw per site pair
-    for (int i = tid; i < N; i += RES_THREADS) sP[i] = neg_if(sA[i], sign);
-    for (int pr = tid; 2 * pr < N; pr += RES_THREADS) {
-      T z0, z1;
-      normal_pair<T>(cd, traj, TAG_MOM, pr, z0, z1);
-      sM[2 * pr] = z0;
-      if (2 * pr + 1 < N) sM[2 * pr + 1] = z1;
-    }
-    __syncthreads();
-    u128 acc[NTERM];
-    for (int a = 0; a < NTERM; ++a) acc[a] = u128{0ull, 0ull};
-    uint32_t bad = 0u;
-    {
-      const int which[1] = {T_K0};
-      unit_sums([&](int i, int, int, int, double* v) {
-        const double pd = (double)sM[i];
-        v[0] = 0.5 * pd * pd;
-      }, which, 1, acc, bad);
-    }
-    // kick-drift passes; the last one kicks only
-    for (int j = 0; j < cd.n_pass; ++j) {
-      Walk cw = w0;
-      for (int i = tid; i < N; i += RES_THREADS, advance_walk(cw)) {
-        const Nb n = nbrs(i, cw.x, cw.y, cw.z);
-        const T c = sP[i];
-        T s = (sP[n.xm] + sP[n.xp]) + (sP[n.ym] + sP[n.yp]);
-        if (NDIM == 3) s = s + (sP[n.zm] + sP[n.zp]);
-        const T u = fma_t(Ct, c, s);
-        sW[i] = fma_t(at, tanh_state(fma_t(at, u, hw)), -c);
-      }
-      __syncthreads();
-      double kick_d = 0.0, drift_d = 0.0;
-      pass_coeffs(cd, j, kick_d, drift_d);
-      const T kick = (T)kick_d, drift = (T)drift_d;
-      const bool last = (j == cd.n_pass - 1);
-      Walk cu = w0;
-      for (int i = tid; i < N; i += RES_THREADS, advance_walk(cu)) {
-        const Nb n = nbrs(i, cu.x, cu.y, cu.z);
-        T sw = (sW[n.xm] + sW[n.xp]) + (sW[n.ym] + sW[n.yp]);
-        if (NDIM == 3) sw = sw + (sW[n.zm] + sW[n.zp]);
-        T F = fma_t(Ct, sW[i], sw);
-        F = F + (site_field ? sB[i] : b_uniform);
-        const T p = fma_t(kick, F, sM[i]);
-        sM[i] = p;
-        if (!last) sP[i] = fma_t(drift, p, sP[i]);
-      }
-      __syncthreads();
-    }
-    // final kinetic energy and the action terms of the proposal
-    {
-      const int which[5] = {T_K1, T_S, T_PSI, T_PSIH, T_UT};
-      unit_sums([&](int i, int x, int y, int z, double* v) {
-        const double pd = (double)sM[i];
-        v[0] = 0.5 * pd * pd;
-        action_terms(i, x, y, z, v + 1);
-      }, which, 5, acc, bad);
-    }
-    u128 sum[NTERM];
-    const uint32_t b = block_total(acc, bad, sum);
-    if (tid == 0) sFlags = finalize_trajectory(cd, st, cur, sum, b);
-    __syncthreads();
-    if (sFlags & REC_ACCEPT)
-      for (int i = tid; i < N; i += RES_THREADS) sA[i] = sP[i];
-    __syncthreads();
-  }
-  // the accepted field back to its buffer (finalize kept st->cur = cur)
-  for (int i = tid; i < N; i += RES_THREADS) gpsi[(i % L0) + (int64_t)pitch * (i / L0)] = sA[i];
-}
-
-hipError_t launch_lattice_resident(int precision, int ndim, const ChainDev* chains, const Tile* tiles, int n_chains,
-                                   int n_traj, int per_cu, hipStream_t s) {
-  if (n_chains <= 0) return hipSuccess;
-  if (per_cu != 1 && per_cu != 2) return hipErrorInvalidValue;
-  const size_t pad = per_cu == 1 ? RES_SOLO_LDS_PAD : 0;
-  if (precision == 4) {
-    if (ndim == 2) lattice_resident<float, 2><<<n_chains, RES_THREADS, pad, s>>>(chains, tiles, n_traj);
-    else lattice_resident<float, 3><<<n_chains, RES_THREADS, pad, s>>>(chains, tiles, n_traj);
-  } else {
-    if (ndim == 2) lattice_resident<double, 2><<<n_chains, RES_THREADS, pad, s>>>(chains, tiles, n_traj);
-    else lattice_resident<double, 3><<<n_chains, RES_THREADS, pad, s>>>(chains, tiles, n_traj);
-  }
-  return hipGetLastError();
-}
-
 // ------------------------------------------------------------------ launch ---
 
 // Threads that give every SIMD of the MI355X eight waves: 256 CUs x 4 SIMDs x
@@ -1341,11 +944,7 @@ TileShape tile_shape(int precision, int ndim, int cls) {
 
 hipError_t launch_lattice_pass(int precision, int ndim, int cls, int mode, const ChainDev* chains,
                                const Tile* tiles, int n_tiles, int j, int k, hipStream_t s) {
-  if (cls == RESIDENT_CLASS || cls == RESIDENT_PHI_CLASS) {  // whole trajectories only; set-up is n_traj = 0
-    if (mode != PASS_MEASURE) return hipErrorInvalidValue;
-    if (cls == RESIDENT_PHI_CLASS) return launch_lattice_resident_phi(ndim, chains, tiles, n_tiles, 0, s);
-    return launch_lattice_resident(precision, ndim, chains, tiles, n_tiles, 0, 2, s);
-  }
+  if (cls < 0) return hipErrorInvalidValue;  // resident chains run whole trajectories (launch_resident_group)
   if (precision == 4) {
     if (ndim == 2) {
       if (cls == 1) return launch_mode2v<float, 16, 16>(mode, chains, tiles, n_tiles, j, k, s);

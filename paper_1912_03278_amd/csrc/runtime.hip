@@ -378,6 +378,7 @@ void plan_groups(const std::vector<ChainDev>& cd, const std::vector<int>& member
       g.tile_begin.push_back((int)tiles.size() - base - g.tile_off);
       if (resident) {
         tiles.push_back(Tile{ci, 0, 0, 0});
+        resident_extend(g.res, c);
       } else {
         for (int z = 0; z < c.L2; z += (g.ndim == 3 ? ts.bz : 1))
           for (int y = 0; y < c.L1; y += ts.by)
@@ -733,10 +734,7 @@ int Chains::build(int32_t n_, const ihmc_lattice* lats, const ihmc_run* runs, in
     else k_init_psi<double><<<nblk(N), 256, 0, s>>>(d_cd, i, src, shift[i]);
     HIPCHK(hipGetLastError(), "k_init_psi");
   }
-  for (auto& g : groups) {
-    HIPCHK(launch_lattice_pass(g.prec, g.ndim, g.cls, PASS_MEASURE, d_cd, d_tiles + g.tile_off, g.tile_begin.back(), 0, 0, s),
-           "measure pass");
-  }
+  HIPCHK(launch_measure(groups, d_tiles, d_cd, s), "measure pass");
   hipError_t e = hipStreamSynchronize(s);
   // translated chains: delta and the action offset h'.Kt^-1 h'/(2J') on the host
   for (int i = 0; i < n && e == hipSuccess; ++i) {
@@ -753,11 +751,11 @@ int Chains::build(int32_t n_, const ihmc_lattice* lats, const ihmc_run* runs, in
 }
 
 // One launch running n_traj whole trajectories (0: the set-up measurement) of
-// every chain of an LDS-resident group; per_cu as in launch_lattice_resident.
+// every chain of an LDS-resident group.
 hipError_t launch_resident_group(const Group& g, const ChainDev* d_cd, const Tile* t, int n, int n_traj,
-                                 int per_cu, hipStream_t s) {
+                                 hipStream_t s) {
   if (g.cls == RESIDENT_PHI_CLASS) return launch_lattice_resident_phi(g.ndim, d_cd, t, n, n_traj, s);
-  return launch_lattice_resident(g.prec, g.ndim, d_cd, t, n, n_traj, per_cu, s);
+  return launch_lattice_resident(g.prec, g.ndim, g.res, d_cd, t, n, n_traj, s);
 }
 
 // Enqueue target of a round plan: the HIP stream operations, or (dry) a count
@@ -791,8 +789,8 @@ struct RoundSink {
                   hipStream_t st) {
     return pool ? launch_lattice_pass(g.prec, g.ndim, g.cls, mode, d_cd, t, n, j, k, st) : hipSuccess;
   }
-  hipError_t resident(const Group& g, const ChainDev* d_cd, const Tile* t, int n, int per_cu, hipStream_t st) {
-    return pool ? launch_resident_group(g, d_cd, t, n, 1, per_cu, st) : hipSuccess;
+  hipError_t resident(const Group& g, const ChainDev* d_cd, const Tile* t, int n, hipStream_t st) {
+    return pool ? launch_resident_group(g, d_cd, t, n, 1, st) : hipSuccess;
   }
 };
 
@@ -809,17 +807,13 @@ static hipError_t round_plan(const std::vector<Group>& groups, const Tile* d_til
   hipEvent_t fork;
   if ((e = sk.take(&fork)) != hipSuccess) return e;
   if ((e = sk.record(fork, s)) != hipSuccess) return e;
-  // resident launches beside tiled groups leave half of each CU to their passes
-  bool tiled = false;
-  for (const Group& g : groups) tiled = tiled || g.cls >= 0;
-  const int res_per_cu = tiled ? 1 : 2;
   for (size_t gi = 0; gi < groups.size(); ++gi) {
     const Group& g = groups[gi];
     hipStream_t gs = sk.pool ? side[gi] : nullptr;
     if ((e = sk.wait(gs, fork)) != hipSuccess) return e;
     const Tile* base = d_tiles + g.tile_off;
     if (g.cls < 0) {  // one launch runs the whole trajectory of every chain of the group
-      if ((e = sk.resident(g, d_cd, base, g.tile_begin.back(), res_per_cu, gs)) != hipSuccess) return e;
+      if ((e = sk.resident(g, d_cd, base, g.tile_begin.back(), gs)) != hipSuccess) return e;
       if ((e = sk.join(gs, s)) != hipSuccess) return e;
       continue;
     }
@@ -891,7 +885,7 @@ int Chains::advance(int32_t n_traj) {
       const Group& g = groups[gi];
       hipStream_t gs = fork ? side[gi] : s;
       if (fork) HIPCHK(hipStreamWaitEvent(gs, events[0], 0), "fork wait");
-      HIPCHK(launch_resident_group(g, d_cd, d_tiles + g.tile_off, g.tile_begin.back(), n_traj, 2, gs),
+      HIPCHK(launch_resident_group(g, d_cd, d_tiles + g.tile_off, g.tile_begin.back(), n_traj, gs),
              "resident launch");
       if (fork) {
         HIPCHK(hipEventRecord(events[1 + gi], gs), "join");
@@ -1685,8 +1679,10 @@ hipError_t launch_field_cg(ChainDev* d_cd, const int* which, int n, double* work
 }
 hipError_t launch_measure(const std::vector<Group>& groups, const Tile* d_tiles, const ChainDev* d_cd, hipStream_t s) {
   for (auto& g : groups) {
-    hipError_t e = launch_lattice_pass(g.prec, g.ndim, g.cls, PASS_MEASURE, d_cd, d_tiles + g.tile_off,
-                                       g.tile_begin.back(), 0, 0, s);
+    const Tile* t = d_tiles + g.tile_off;
+    const int n = g.tile_begin.back();
+    hipError_t e = g.cls < 0 ? launch_resident_group(g, d_cd, t, n, 0, s)
+                             : launch_lattice_pass(g.prec, g.ndim, g.cls, PASS_MEASURE, d_cd, t, n, 0, 0, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

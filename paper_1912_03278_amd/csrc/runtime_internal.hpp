@@ -10,6 +10,7 @@
 
 #include "../../include/ihmc.h"
 #include "ihmc_internal.hpp"
+#include "lattice_kernels.hpp"
 
 namespace ihmc {
 
@@ -94,6 +95,7 @@ int tune_load(TuneTable& t, const char* path);
 struct Group {
   int prec = 4, ndim = 2, cls = 0;
   bool pair = false;            // middle steps two per launch (PASS_PAIR)
+  ResidentShape res;            // resident groups: what the launch has to fit
   std::vector<int> order;       // chain indices, sorted by pass count (descending)
   std::vector<int> n_pass;      // pass count per position in `order`
   std::vector<int> tile_begin;  // first tile of each position, relative to tile_off; size+1
@@ -130,7 +132,7 @@ hipError_t launch_field_cg(ChainDev* d_cd, const int* which, int n, double* work
                            hipStream_t s);
 hipError_t launch_measure(const std::vector<Group>& groups, const Tile* d_tiles, const ChainDev* d_cd, hipStream_t s);
 hipError_t launch_resident_group(const Group& g, const ChainDev* d_cd, const Tile* t, int n, int n_traj,
-                                 int per_cu, hipStream_t s);
+                                 hipStream_t s);
 
 struct Chains {
   ihmc_ctx* ctx = nullptr;
