@@ -1,0 +1,219 @@
+// Kt x = h' for chains with a per-site field (set-up; Sec. 2, the remark after
+// eq. phi_psi_substitution): the estimator constants h'^T Kt^-1 h' and
+// 1^T Kt^-1 h', and x itself for chains that run in translated coordinates.
+//
+// On the periodic lattice Kt is diagonal in the real plane waves
+// prod_d cas(2 pi k_d x_d / L_d), cas = cos + sin (the shift operators along an
+// axis come in symmetric pairs, which have cos and sin of one frequency as
+// eigenvectors of the same eigenvalue), with eigenvalues
+//     lambda(k) = C + 2 sum_d cos(2 pi k_d / L_d)
+//               = (C - 2 ndim) + sum_d 4 cos^2(pi k_d / L_d),
+// the second form exact to rounding also where C barely exceeds 2 ndim.  So the
+// solve is a separable Hartley transform H of h', a division by lambda and (for
+// x) the same transform again, over N:
+//     h'^T Kt^-1 h' = sum_k H(k)^2 / (N lambda(k)),   1^T Kt^-1 h' = H(0) / (2 ndim + C).
+//
+// One axis of all chains is one launch: out[k] = sum_j cas(2 pi j k / L) in[j],
+// N L products per chain in FP64, tiles of 64 frequencies x 64 columns, 16
+// steps of j staged in LDS at a time.  Bound by FP64 issue for long axes and by
+// launches otherwise.  A call of 512 uneven 2D chains of 16 .. 256 sites a row
+// went from 180 to 105 ms: the solve took 76.7 ms as conjugate gradients with one
+// workgroup per chain (the largest chain's ~160 iterations over 2 MB of vectors
+// set it).  Every sum has an
+// order of its own chain, so the constants do not depend on which chains share
+// the launches.
+#include <algorithm>
+
+#include "device_common.hpp"
+#include "runtime_internal.hpp"
+
+namespace ihmc {
+
+namespace {
+
+constexpr int FT = 64, FJ = 16;     // tile (frequencies, columns), staged steps
+constexpr int FTHREADS = 256;
+constexpr int CHUNK = 1024;         // modes per partial sum of h' Kt^-1 h'
+constexpr unsigned MAX_GRID_X = 4096;
+
+// Work space of one chain (4 N values): two field arrays, then the tables
+// cas(2 pi m / L_d) of the axes, then the partial sums.
+__device__ __forceinline__ double* cas_table(double* w, const ChainDev& cd, int axis) {
+  return w + 2 * cd.N + (axis > 0 ? cd.L0 : 0) + (axis > 1 ? cd.L1 : 0);
+}
+__device__ __forceinline__ double* partials(double* w, const ChainDev& cd) {
+  return w + 2 * cd.N + cd.L0 + cd.L1 + (cd.ndim == 3 ? cd.L2 : 0);
+}
+
+// h' in site order into the first array, and the axes' tables.
+__global__ __launch_bounds__(FTHREADS) void k_fs_init(const ChainDev* __restrict__ cds, const int* __restrict__ which,
+                                                      double* work, const int64_t* __restrict__ woff) {
+  const ChainDev& cd = cds[which[blockIdx.y]];
+  double* w = work + woff[blockIdx.y];
+  const int64_t t0 = blockIdx.x * (int64_t)FTHREADS + threadIdx.x, stride = (int64_t)gridDim.x * FTHREADS;
+  for (int64_t i = t0; i < cd.N; i += stride) w[i] = cd.hp[stored_index(cd, i)];
+  for (int a = 0; a < cd.ndim; ++a) {
+    const int L = a == 0 ? cd.L0 : (a == 1 ? cd.L1 : cd.L2);
+    double* tab = cas_table(w, cd, a);
+    for (int64_t m = t0; m < L; m += stride) {
+      double sn, cs;
+      sincos_turn((double)m / (double)L, sn, cs);
+      tab[m] = cs + sn;
+    }
+  }
+}
+
+// One axis of every chain, from array `src` to the other.  Columns of axis 0 are
+// rows of L0 consecutive values; of axis a > 0, lines of stride prod_{b<a} L_b.
+__global__ __launch_bounds__(FTHREADS) void k_fs_axis(const ChainDev* __restrict__ cds, const int* __restrict__ which,
+                                                      double* work, const int64_t* __restrict__ woff, int axis,
+                                                      int src) {
+  __shared__ __align__(16) double sIn[FJ][FT + 2];
+  __shared__ __align__(16) double sC[FJ][FT];
+  const ChainDev& cd = cds[which[blockIdx.y]];
+  if (axis >= cd.ndim) {  // a 2D chain beside 3D ones: the array changes place all the same
+    const double* in = work + woff[blockIdx.y] + src * cd.N;
+    double* out = work + woff[blockIdx.y] + (1 - src) * cd.N;
+    for (int64_t i = blockIdx.x * (int64_t)FTHREADS + threadIdx.x; i < cd.N; i += (int64_t)gridDim.x * FTHREADS)
+      out[i] = in[i];
+    return;
+  }
+  double* w = work + woff[blockIdx.y];
+  const double* __restrict__ in = w + src * cd.N;
+  double* __restrict__ out = w + (1 - src) * cd.N;
+  const double* __restrict__ tab = cas_table(w, cd, axis);
+  const int L = axis == 0 ? cd.L0 : (axis == 1 ? cd.L1 : cd.L2);
+  const int64_t inner = axis == 0 ? 1 : (axis == 1 ? (int64_t)cd.L0 : (int64_t)cd.L0 * cd.L1);
+  const int64_t ncol = cd.N / L;
+  const int64_t kt = (L + FT - 1) / FT, ntile = kt * ((ncol + FT - 1) / FT);
+  const double rL = 1.0 / (double)L;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  auto offset = [&](int64_t c) { return axis == 0 ? c * L : (c / inner) * (L * inner) + c % inner; };
+  for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
+    const int k0 = (int)(tile % kt) * FT;
+    const int64_t c0 = (tile / kt) * FT;
+    double acc[FT / 4];
+#pragma unroll
+    for (int c = 0; c < FT / 4; ++c) acc[c] = 0.0;
+    for (int j0 = 0; j0 < L; j0 += FJ) {
+      // values (consecutive threads along the contiguous direction) and the tile of cas
+      for (int e = tid; e < FJ * FT; e += FTHREADS) {
+        const int jj = axis == 0 ? e % FJ : e / FT, cc = axis == 0 ? e / FJ : e % FT;
+        const bool ok = j0 + jj < L && c0 + cc < ncol;
+        sIn[jj][cc] = ok ? in[offset(c0 + cc) + (int64_t)(j0 + jj) * inner] : 0.0;
+      }
+      for (int e = tid; e < FJ * FT; e += FTHREADS) {
+        const int jj = e / FT, kk = e % FT;
+        double v = 0.0;
+        if (j0 + jj < L && k0 + kk < L) {
+          const int64_t p = (int64_t)(j0 + jj) * (k0 + kk);  // < 2^40: exact in FP64
+          int64_t m = p - (int64_t)((double)p * rL) * L;
+          m = m < 0 ? m + L : (m >= L ? m - L : m);
+          v = tab[m];
+        }
+        sC[jj][kk] = v;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int jj = 0; jj < FJ; ++jj) {
+        const double cs = sC[jj][lane];
+#pragma unroll
+        for (int c = 0; c < FT / 4; ++c) acc[c] = __builtin_fma(cs, sIn[jj][(FT / 4) * wv + c], acc[c]);
+      }
+      __syncthreads();
+    }
+    if (k0 + lane < L)
+#pragma unroll
+      for (int c = 0; c < FT / 4; ++c) {
+        const int64_t col = c0 + (FT / 4) * wv + c;
+        if (col < ncol) out[offset(col) + (int64_t)(k0 + lane) * inner] = acc[c];
+      }
+  }
+}
+
+// 4 cos^2(pi k / L): an axis' part of lambda + 2 ndim - C.
+__device__ __forceinline__ double axis_eig(int k, int L) {
+  double sn, cs;
+  sincos_turn((double)k / (2.0 * (double)L), sn, cs);
+  return 4.0 * (cs * cs);
+}
+
+// In array `src`: H(k) -> H(k) / (N lambda(k)); partial sums of H^2 / (N lambda)
+// over CHUNK modes each, one workgroup per chunk, in a fixed order.
+__global__ __launch_bounds__(FTHREADS) void k_fs_scale(ChainDev* __restrict__ cds, const int* __restrict__ which,
+                                                       double* work, const int64_t* __restrict__ woff, int src) {
+  __shared__ double sh[FTHREADS / 64];
+  ChainDev& cd = cds[which[blockIdx.y]];
+  double* w = work + woff[blockIdx.y];
+  double* H = w + src * cd.N;
+  const int64_t nchunk = (cd.N + CHUNK - 1) / CHUNK;
+  const double gap = cd.C - 2.0 * cd.ndim, n = (double)cd.N;
+  if (blockIdx.x == 0 && threadIdx.x == 0) cd.c_m = H[0] / (2.0 * cd.ndim + cd.C);
+  __syncthreads();
+  for (int64_t b = blockIdx.x; b < nchunk; b += gridDim.x) {
+    double s = 0.0;
+    for (int e = threadIdx.x; e < CHUNK; e += FTHREADS) {
+      const int64_t i = b * CHUNK + e;
+      if (i >= cd.N) continue;
+      const int x = (int)(i % cd.L0);
+      const int64_t r = i / cd.L0;
+      double lam = gap + axis_eig(x, cd.L0) + axis_eig((int)(r % cd.L1), cd.L1);
+      if (cd.ndim == 3) lam += axis_eig((int)(r / cd.L1), cd.L2);
+      const double h = H[i], y = h / (n * lam);
+      s += h * y;
+      H[i] = y;
+    }
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) partials(w, cd)[b] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    __syncthreads();
+  }
+}
+
+// c_e = the partial sums of a chain, in a fixed order (one wave per chain).
+__global__ __launch_bounds__(64) void k_fs_final(ChainDev* __restrict__ cds, const int* __restrict__ which,
+                                                 double* work, const int64_t* __restrict__ woff) {
+  ChainDev& cd = cds[which[blockIdx.x]];
+  const double* p = partials(work + woff[blockIdx.x], cd);
+  const int64_t nchunk = (cd.N + CHUNK - 1) / CHUNK;
+  double s = 0.0;
+  for (int64_t b = threadIdx.x; b < nchunk; b += 64) s += p[b];
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  if (threadIdx.x == 0) cd.c_e = s;
+}
+
+}  // namespace
+
+hipError_t launch_field_solve(ChainDev* d_cd, const std::vector<const ChainDev*>& host, const int* which, double* work,
+                              const int64_t* woff, bool need_x, hipStream_t s) {
+  if (host.empty()) return hipSuccess;
+  // largest number of tiles, sites and dimensions among the chains
+  int64_t tiles = 1, sites = 1;
+  int nd = 2;
+  for (const ChainDev* c : host) {
+    const int64_t L[3] = {c->L0, c->L1, c->L2};
+    for (int a = 0; a < c->ndim; ++a)
+      tiles = std::max(tiles, ((L[a] + FT - 1) / FT) * ((c->N / L[a] + FT - 1) / FT));
+    sites = std::max(sites, c->N);
+    nd = std::max(nd, c->ndim);
+  }
+  auto grid_x = [](int64_t n) { return (unsigned)std::min<int64_t>(n, MAX_GRID_X); };
+  // the chains fill grid.y, at most 65535 at a time
+  for (size_t c0 = 0; c0 < host.size(); c0 += 65535) {
+    const unsigned n = (unsigned)std::min<size_t>(host.size() - c0, 65535);
+    const int* wh = which + c0;
+    const int64_t* wo = woff + c0;
+    const dim3 gs(grid_x((sites + 4 * FTHREADS - 1) / (4 * FTHREADS)), n), gt(grid_x(tiles), n);
+    k_fs_init<<<gs, FTHREADS, 0, s>>>(d_cd, wh, work, wo);
+    for (int a = 0; a < nd; ++a) k_fs_axis<<<gt, FTHREADS, 0, s>>>(d_cd, wh, work, wo, a, a & 1);
+    const int at = nd & 1;  // the array that holds the transform
+    k_fs_scale<<<dim3(grid_x((sites + CHUNK - 1) / CHUNK), n), FTHREADS, 0, s>>>(d_cd, wh, work, wo, at);
+    k_fs_final<<<n, 64, 0, s>>>(d_cd, wh, work, wo);
+    if (need_x)  // back: ends in the first array
+      for (int a = 0; a < nd; ++a) k_fs_axis<<<gt, FTHREADS, 0, s>>>(d_cd, wh, work, wo, a, (at + a) & 1);
+  }
+  return hipGetLastError();
+}
+
+}  // namespace ihmc

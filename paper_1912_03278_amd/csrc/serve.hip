@@ -407,9 +407,9 @@ bool ihmc_server::admit_setup(std::vector<Request*>& fresh) {
     return p;
   };
   std::vector<Request*> ok;
-  std::vector<int> cg_slots;
-  std::vector<int64_t> cg_off;
-  int64_t cg_total = 0;
+  std::vector<int> fs_slots;
+  std::vector<int64_t> fs_off;
+  int64_t fs_total = 0;
   // the set-up runs with the device idle: the round in flight finishes first
   hipError_t e = hipStreamSynchronize(s);
   for (Request* r : fresh) {
@@ -462,9 +462,9 @@ bool ihmc_server::admit_setup(std::vector<Request*>& fresh) {
       if (!t) e = hipErrorOutOfMemory;
       if (e == hipSuccess) e = hipMemcpyAsync(t, r->h.data(), 8 * c.N, hipMemcpyHostToDevice, s);
       if (e == hipSuccess) e = launch_field_setup(d_cd, r->slot, t, r->lat.beta, c.N, c.precision, s);
-      cg_slots.push_back(r->slot);
-      cg_off.push_back(cg_total);
-      cg_total += 4 * c.N;
+      fs_slots.push_back(r->slot);
+      fs_off.push_back(fs_total);
+      fs_total += 4 * c.N;
     }
     const bool translated = r->run.form == FORM_SHIFTED && c.h_kind == 2;
     if (e == hipSuccess) {
@@ -475,29 +475,33 @@ bool ihmc_server::admit_setup(std::vector<Request*>& fresh) {
         if (e == hipSuccess) e = hipMemcpyAsync(t, r->psi0.data(), 8 * c.N, hipMemcpyHostToDevice, s);
         src = t;
       }
-      // a translated request's field starts after the CG below, with delta added
+      // a translated request's field starts after the solve below, with delta added
       if (e == hipSuccess && !translated) e = launch_init_psi(d_cd, r->slot, src, c.N, c.precision, s);
       if (translated) r->dshift = src;  // the staged psi0 (or null), for the later start
     }
     if (e != hipSuccess) break;
     ok.push_back(r);
   }
-  if (e == hipSuccess && !cg_slots.empty()) {
-    double* work = (double*)tmp(8 * (uint64_t)cg_total);
-    int* which = (int*)tmp(sizeof(int) * cg_slots.size());
-    int64_t* woff = (int64_t*)tmp(sizeof(int64_t) * cg_off.size());
+  if (e == hipSuccess && !fs_slots.empty()) {
+    double* work = (double*)tmp(8 * (uint64_t)fs_total);
+    int* which = (int*)tmp(sizeof(int) * fs_slots.size());
+    int64_t* woff = (int64_t*)tmp(sizeof(int64_t) * fs_off.size());
     if (!work || !which || !woff) e = hipErrorOutOfMemory;
-    if (e == hipSuccess) e = hipMemcpyAsync(which, cg_slots.data(), sizeof(int) * cg_slots.size(), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(woff, cg_off.data(), sizeof(int64_t) * cg_off.size(), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = launch_field_cg(d_cd, which, (int)cg_slots.size(), work, woff, s);
-    // translated requests: delta = x / sqrt(J') (x = Kt^-1 h' of the CG), then
+    if (e == hipSuccess) e = hipMemcpyAsync(which, fs_slots.data(), sizeof(int) * fs_slots.size(), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(woff, fs_off.data(), sizeof(int64_t) * fs_off.size(), hipMemcpyHostToDevice, s);
+    std::vector<const ChainDev*> host;
+    for (int slot : fs_slots) host.push_back(&cd_host[slot]);
+    bool translated = false;
+    for (Request* r : ok) translated = translated || (r->run.form == FORM_SHIFTED && r->cd.h_kind == 2);
+    if (e == hipSuccess) e = launch_field_solve(d_cd, host, which, work, woff, translated, s);
+    // translated requests: delta = x / sqrt(J') (x = Kt^-1 h' of the solve), then
     // the starting field psi0 + delta, as a chain set starts it
     for (Request* r : ok) {
       if (e != hipSuccess) break;
       if (!(r->run.form == FORM_SHIFTED && r->cd.h_kind == 2)) continue;
       size_t j = 0;
-      while (j < cg_slots.size() && cg_slots[j] != r->slot) ++j;
-      double* x = work + cg_off[j];
+      while (j < fs_slots.size() && fs_slots[j] != r->slot) ++j;
+      double* x = work + fs_off[j];
       e = launch_scale(x, r->cd.N, r->cd.sqJ, s);
       if (e == hipSuccess) e = launch_init_psi(d_cd, r->slot, r->dshift, r->cd.N, r->cd.precision, s, x);
       r->dshift = x;
