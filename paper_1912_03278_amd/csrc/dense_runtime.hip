@@ -376,16 +376,13 @@ int DenseChains::build(const ihmc_dense& md, int32_t n, const ihmc_run* runs, in
     c.b = bfield;
     c.hp = hp;
     if (!c.psi || !c.p || !c.rec || !c.st || !pblk) return nomem("chain state");
-    HIPCHK(setup_partials(c, pblk, s), "partials");
-    HIPCHK(hipMemsetAsync(c.psi, 0, 4 * 3 * (size_t)Np, s), "clear psi");
-    HIPCHK(hipMemsetAsync(c.p, 0, 4 * (size_t)Np, s), "clear p");
+    setup_partials(c, pblk);
     if (r.replay_accept && r.n_traj > 0) {
       uint8_t* d = (uint8_t*)dalloc((uint64_t)r.n_traj);
       if (!d) return nomem("replay");
       HIPCHK(hipMemcpyAsync(d, r.replay_accept, (size_t)r.n_traj, hipMemcpyHostToDevice, s), "replay upload");
       c.replay = d;
     }
-    HIPCHK(launch_zero_state(c.st, s), "state");
   }
 
   // ---- estimator constants: g = Kt^-1 1, and Kt^-1 h' for a per-site field
@@ -434,16 +431,25 @@ int DenseChains::build(const ihmc_dense& md, int32_t n, const ihmc_run* runs, in
   if (!d_cd) return nomem("chain table");
   HIPCHK(hipMemcpyAsync(d_cd, cd.data(), sizeof(ChainDev) * (size_t)B, hipMemcpyHostToDevice, s), "chain upload");
 
-  // ---- initial fields and their action
-  for (int i = 0; i < B; ++i) {
-    const double* src = nullptr;
-    if (runs[i].psi0) {
-      double* t = (double*)tmp_alloc(8 * (uint64_t)N);
-      if (!t) return nomem("psi0 staging");
-      HIPCHK(hipMemcpyAsync(t, runs[i].psi0, 8 * (size_t)N, hipMemcpyHostToDevice, s), "psi0 upload");
-      src = t;
+  // ---- states, initial fields and their action
+  HIPCHK(launch_reset(d_cd, B, 3 * Np, s), "chain states");
+  {
+    std::vector<StartField> start;
+    for (int i = 0; i < B; ++i) {
+      double* src = nullptr;
+      if (runs[i].psi0) {
+        src = (double*)tmp_alloc(8 * (uint64_t)N);
+        if (!src) return nomem("psi0 staging");
+        HIPCHK(hipMemcpyAsync(src, runs[i].psi0, 8 * (size_t)N, hipMemcpyHostToDevice, s), "psi0 upload");
+      }
+      start.push_back(StartField{src, nullptr, i});
     }
-    HIPCHK(launch_init_psi(d_cd, i, src, N, IHMC_F32, s), "initial field");
+    StartField* d_start = (StartField*)tmp_alloc(sizeof(StartField) * start.size());
+    if (!d_start) return nomem("starting fields");
+    HIPCHK(hipMemcpyAsync(d_start, start.data(), sizeof(StartField) * start.size(), hipMemcpyHostToDevice, s),
+           "start table");
+    HIPCHK(launch_start(d_cd, d_start, B, N, s), "initial fields");
+    HIPCHK(hipStreamSynchronize(s), "initial fields sync");  // `start` is read by the copy
   }
   HIPCHK(dense_gemm_f64(K64, d_cd, 0, 1, U64, Np, B, s), "measure product");
   HIPCHK(dense_h(PASS_MEASURE, d_cd, B, Np, U64, 0, s), "measure");
@@ -545,7 +551,9 @@ extern "C" int ihmc_dense_result(ihmc_dense_chains* ch, int32_t i, ihmc_result* 
   CTX_OK(ch->impl.ctx);
   DenseChains& d = ch->impl;
   if (i < 0 || i >= d.B) return set_error(IHMC_E_INVAL, "chain index %d out of range", i);
-  return result_from_device(d.ctx, d.cd[i], d.d_cd, i, out);
+  if (!out) return set_error(IHMC_E_INVAL, "out is NULL");
+  const int done = d.base[i] + d.enqueued;
+  return collect_results(d.ctx, d.cd, d.d_cd, i, 1, &done, out);
 }
 
 extern "C" int ihmc_dense_checkpoint(ihmc_dense_chains* ch, int32_t i, void* buf, uint64_t* bytes) {
@@ -635,7 +643,10 @@ extern "C" int ihmc_run_dense(ihmc_ctx* ctx, const ihmc_dense* model, int32_t n,
   for (int i = 0; i < n && rc == IHMC_OK; ++i)
     if (runs[i].n_traj != runs[0].n_traj) rc = set_error(IHMC_E_INVAL, "ihmc_run_dense: runs differ in n_traj");
   if (rc == IHMC_OK) rc = c->impl.advance(runs[0].n_traj);
-  for (int i = 0; i < n && rc == IHMC_OK; ++i) rc = result_from_device(ctx, c->impl.cd[i], c->impl.d_cd, i, &outs[i]);
+  if (rc == IHMC_OK) {
+    const std::vector<int> done((size_t)n, runs[0].n_traj);
+    rc = collect_results(ctx, c->impl.cd, c->impl.d_cd, 0, n, done.data(), outs);
+  }
   ihmc_dense_destroy(c);
   return rc;
 }

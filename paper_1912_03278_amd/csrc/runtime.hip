@@ -439,6 +439,7 @@ extern "C" void ihmc_ctx_destroy(ihmc_ctx* c) {
   hipSetDevice(c->device);
   hipStreamSynchronize(c->stream);
   hipStreamDestroy(c->stream);
+  stage_destroy(c->stage);
   if (c->af) c->ff(c->arena.base, c->user);
   else hipFree(c->arena.base);
   delete c;
@@ -526,7 +527,7 @@ int Chains::build(int32_t n_, const ihmc_lattice* lats, const ihmc_run* runs, in
     c.rec = (TrajRecord*)dalloc(sizeof(TrajRecord) * (uint64_t)std::max(1, r.n_traj));
     c.st = (ChainState*)dalloc(sizeof(ChainState));
     void* pblk = dalloc(partials_bytes(c.n_tiles));
-    if (pblk) HIPCHK(setup_partials(c, pblk, s), "partials");
+    if (pblk) setup_partials(c, pblk);
     if (!c.psi || !c.p || !c.rec || !c.st || !pblk) {
       cleanup();
       return set_error(IHMC_E_NOMEM, "chain %d: device arena exhausted (%llu of %llu bytes in use)", i,
@@ -549,7 +550,6 @@ int Chains::build(int32_t n_, const ihmc_lattice* lats, const ihmc_run* runs, in
         return set_error(IHMC_E_NOMEM, "chain %d: arena exhausted", i);
       }
     }
-    k_zero_state<<<1, 256, 0, s>>>(c.st);
   }
   d_cd = (ChainDev*)dalloc(sizeof(ChainDev) * (uint64_t)n);
   if (!d_cd) {
@@ -586,37 +586,32 @@ int Chains::build(int32_t n_, const ihmc_lattice* lats, const ihmc_run* runs, in
   HIPCHK(hipMemcpyAsync(d_tiles, all_tiles.data(), sizeof(Tile) * all_tiles.size(), hipMemcpyHostToDevice, s),
          "tile upload");
   HIPCHK(hipMemcpyAsync(d_cd, cd.data(), sizeof(ChainDev) * (uint64_t)n, hipMemcpyHostToDevice, s), "chain upload");
+  HIPCHK(launch_reset(d_cd, n, 0, s), "chain states");
 
   // ---- per-site fields into the stored layout
-  for (int i = 0; i < n; ++i) {
-    if (cd[i].h_kind != 2) continue;
-    const int64_t N = cd[i].N;
-    double* t = (double*)tmp_alloc(8 * (uint64_t)N);
-    if (!t) {
+  std::vector<int> fs_idx;
+  for (int i = 0; i < n; ++i)
+    if (cd[i].h_kind == 2) fs_idx.push_back(i);
+  if (!fs_idx.empty()) {
+    const int rc = upload_fields(ctx, cd, d_cd, fs_idx, lats, temps);
+    if (rc) {
       cleanup();
-      return set_error(IHMC_E_NOMEM, "arena exhausted (field staging)");
+      return rc;
     }
-    HIPCHK(hipMemcpyAsync(t, lats[i].h, 8 * N, hipMemcpyHostToDevice, s), "h upload");
-    if (cd[i].precision == 4) k_field_setup<float><<<nblk(N), 256, 0, s>>>(d_cd, i, t, lats[i].beta);
-    else k_field_setup<double><<<nblk(N), 256, 0, s>>>(d_cd, i, t, lats[i].beta);
-    HIPCHK(hipGetLastError(), "k_field_setup");
   }
 
   // ---- per-site field constants (Kt x = h' of every such chain)
   std::vector<double*> shift(n, nullptr);
-  std::vector<int> fs_idx;
   std::vector<int64_t> fs_off;
   std::vector<const ChainDev*> fs_cd;
   int64_t fs_total = 0;
   bool translated = false;
-  for (int i = 0; i < n; ++i)
-    if (cd[i].h_kind == 2) {
-      fs_idx.push_back(i);
-      fs_off.push_back(fs_total);
-      fs_cd.push_back(&cd[i]);
-      fs_total += 4 * cd[i].N;
-      translated = translated || runs[i].form == FORM_SHIFTED;
-    }
+  for (int i : fs_idx) {
+    fs_off.push_back(fs_total);
+    fs_cd.push_back(&cd[i]);
+    fs_total += 4 * cd[i].N;
+    translated = translated || runs[i].form == FORM_SHIFTED;
+  }
   if (!fs_idx.empty()) {
     double* work = (double*)tmp_alloc(8 * (uint64_t)fs_total);
     int* didx = (int*)tmp_alloc(sizeof(int) * fs_idx.size());
@@ -639,23 +634,37 @@ int Chains::build(int32_t n_, const ihmc_lattice* lats, const ihmc_run* runs, in
   }
 
   // ---- initial field and its action
+  std::vector<StartField> start;
+  int64_t max_sites = 0;
   for (int i = 0; i < n; ++i) {
     const ihmc_run& r = runs[i];
     const int64_t N = cd[i].N;
-    const double* src = nullptr;
+    double* src = nullptr;
     if (r.psi0) {
-      double* t = (double*)tmp_alloc(8 * (uint64_t)N);
-      if (!t) {
+      src = (double*)tmp_alloc(8 * (uint64_t)N);
+      if (!src) {
         cleanup();
         return set_error(IHMC_E_NOMEM, "arena exhausted (psi0 staging)");
       }
-      HIPCHK(hipMemcpyAsync(t, r.psi0, 8 * N, hipMemcpyHostToDevice, s), "psi0 upload");
-      src = t;
+      HIPCHK(hipMemcpyAsync(src, r.psi0, 8 * N, hipMemcpyHostToDevice, s), "psi0 upload");
     }
-    if (cd[i].form == FORM_PHI && !src) k_init_phi<<<nblk(N), 256, 0, s>>>(d_cd, i);
-    else if (cd[i].precision == 4) k_init_psi<float><<<nblk(N), 256, 0, s>>>(d_cd, i, src, shift[i]);
-    else k_init_psi<double><<<nblk(N), 256, 0, s>>>(d_cd, i, src, shift[i]);
-    HIPCHK(hipGetLastError(), "k_init_psi");
+    if (cd[i].form == FORM_PHI && !src) {
+      k_init_phi<<<nblk(N), 256, 0, s>>>(d_cd, i);
+      HIPCHK(hipGetLastError(), "k_init_phi");
+      continue;
+    }
+    start.push_back(StartField{src, shift[i], i});
+    max_sites = std::max(max_sites, N);
+  }
+  if (!start.empty()) {
+    StartField* d_start = (StartField*)tmp_alloc(sizeof(StartField) * start.size());
+    if (!d_start) {
+      cleanup();
+      return set_error(IHMC_E_NOMEM, "arena exhausted (starting fields)");
+    }
+    HIPCHK(hipMemcpyAsync(d_start, start.data(), sizeof(StartField) * start.size(), hipMemcpyHostToDevice, s),
+           "start table");
+    HIPCHK(launch_start(d_cd, d_start, (int)start.size(), max_sites, s), "starting fields");
   }
   HIPCHK(launch_measure(groups, d_tiles, d_cd, s), "measure pass");
   hipError_t e = hipStreamSynchronize(s);
@@ -851,62 +860,26 @@ int Chains::restore(int32_t i, const void* buf, uint64_t bytes) {
   return IHMC_OK;
 }
 
-int Chains::result(int32_t i, ihmc_result* out) {
-  if (i < 0 || i >= n) return set_error(IHMC_E_INVAL, "chain index %d out of range", i);
-  int rc = result_from_device(ctx, cd[i], d_cd, i, out);
-  if (rc || delta[i].empty()) return rc;
-  // a translated shifted-form chain: its field and action in its own coordinates
-  const int64_t done = std::min<int64_t>(out->n_traj_done, cd[i].cap);
-  for (int64_t t = 0; t < done; ++t) {
-    if (out->H_old) out->H_old[t] += s_offset[i];
-    if (out->H_new) out->H_new[t] += s_offset[i];
+int Chains::results(int32_t first, int32_t m, ihmc_result* outs) {
+  if (first < 0 || m < 1 || first + m > n) return set_error(IHMC_E_INVAL, "chain index %d out of range", first);
+  if (!outs) return set_error(IHMC_E_INVAL, "out is NULL");
+  std::vector<int> done((size_t)m);
+  for (int k = 0; k < m; ++k) done[k] = base[first + k] + enqueued;
+  int rc = collect_results(ctx, cd, d_cd, first, m, done.data(), outs);
+  for (int k = 0; rc == IHMC_OK && k < m; ++k) {
+    const int i = first + k;
+    if (delta[i].empty()) continue;
+    // a translated shifted-form chain: its field and action in its own coordinates
+    ihmc_result* out = &outs[k];
+    const int64_t nd = std::min<int64_t>(out->n_traj_done, cd[i].cap);
+    for (int64_t t = 0; t < nd; ++t) {
+      if (out->H_old) out->H_old[t] += s_offset[i];
+      if (out->H_new) out->H_new[t] += s_offset[i];
+    }
+    if (out->psi_final)
+      for (int64_t j = 0; j < cd[i].N; ++j) out->psi_final[j] -= delta[i][(size_t)j];
   }
-  if (out->psi_final)
-    for (int64_t k = 0; k < cd[i].N; ++k) out->psi_final[k] -= delta[i][(size_t)k];
-  return IHMC_OK;
-}
-
-// Series and summary of chain ci of a device chain table (shared by the lattice
-// and dense runtimes).
-int result_from_device(ihmc_ctx* ctx, const ChainDev& c, const ChainDev* d_cd, int ci, ihmc_result* out) {
-  if (!out) return set_error(IHMC_E_INVAL, "out is NULL");
-  hipStream_t s = ctx->stream;
-  HIPCHK(hipStreamSynchronize(s), "sync");
-  ChainState st;
-  HIPCHK(hipMemcpy(&st, c.st, sizeof st, hipMemcpyDeviceToHost), "state download");
-  const int done = std::min(st.traj, c.cap);
-  std::vector<TrajRecord> rec((size_t)std::max(done, 1));
-  if (done > 0) HIPCHK(hipMemcpy(rec.data(), c.rec, sizeof(TrajRecord) * done, hipMemcpyDeviceToHost), "records");
-  for (int t = 0; t < done; ++t) {
-    const TrajRecord& r = rec[t];
-    if (out->dH) out->dH[t] = r.dH;
-    if (out->H_old) out->H_old[t] = r.H_old;
-    if (out->H_new) out->H_new[t] = r.H_new;
-    if (out->m) out->m[t] = r.m;
-    if (out->abs_m) out->abs_m[t] = r.abs_m;
-    if (out->m2c) out->m2c[t] = r.m2c;
-    if (out->beta_eps) out->beta_eps[t] = r.beta_eps;
-    if (out->accepted) out->accepted[t] = (r.flags & REC_ACCEPT) ? 1 : 0;
-    if (out->flipped) out->flipped[t] = (r.flags & REC_FLIP) ? 1 : 0;
-  }
-  out->n_traj_done = st.traj;
-  const int64_t counted = std::max(0, st.traj - c.n_therm);  // trajectories past thermalisation
-  out->acceptance = counted ? (double)st.n_acc / (double)counted : 0.0;
-  const int64_t nf = counted - st.n_nonfinite;
-  out->mean_exp_minus_dH = nf > 0 ? st.sum_exp_mdh / (double)nf : 0.0;
-  out->n_nonfinite = st.n_nonfinite;
-  out->cg_iterations = st.n_cg;
-  if (out->psi_final) {
-    double* t = (double*)ctx->arena.alloc(8 * (uint64_t)c.N);
-    if (!t) return set_error(IHMC_E_NOMEM, "arena exhausted (export)");
-    hipError_t e0 = launch_export_psi(d_cd, ci, t, c.N, c.precision, s);
-    hipError_t e = e0 == hipSuccess ? hipMemcpyAsync(out->psi_final, t, 8 * c.N, hipMemcpyDeviceToHost, s) : e0;
-    hipError_t e2 = hipStreamSynchronize(s);
-    ctx->arena.release(t);
-    if (e != hipSuccess) return hip_fail(ctx, e, "psi export");
-    if (e2 != hipSuccess) return hip_fail(ctx, e2, "psi export sync");
-  }
-  return IHMC_OK;
+  return rc;
 }
 
 // ------------------------------------------------------ checkpoint / resume ---
@@ -1166,7 +1139,8 @@ extern "C" int ihmc_chains_result(ihmc_chains* ch, int32_t i, ihmc_result* out) 
   if (!ch) return set_error(IHMC_E_INVAL, "chains is NULL");
   Chains* c = (Chains*)ch;
   CTX_OK(c->ctx);
-  return c->result(i, out);
+  if (i < 0 || i >= c->n) return set_error(IHMC_E_INVAL, "chain index %d out of range", i);
+  return c->results(i, 1, out);
 }
 
 extern "C" int ihmc_chains_checkpoint(ihmc_chains* ch, int32_t i, void* buf, uint64_t* bytes) {
@@ -1210,7 +1184,7 @@ extern "C" int ihmc_run_batch(ihmc_ctx* ctx, int32_t n, const ihmc_lattice* lats
     return set_error(IHMC_E_UNSUPPORTED, "ihmc_run_batch: chains must share n_traj");
   }
   rc = c->advance(max_traj);
-  for (int i = 0; rc == IHMC_OK && i < n; ++i) rc = c->result(i, &outs[i]);
+  if (rc == IHMC_OK) rc = c->results(0, n, outs);
   hipStreamSynchronize(ctx->stream);
   delete c;
   return rc;
@@ -1613,7 +1587,7 @@ hipError_t launch_measure(const std::vector<Group>& groups, const Tile* d_tiles,
   }
   return hipSuccess;
 }
-hipError_t setup_partials(ChainDev& c, void* block, hipStream_t s) {
+void setup_partials(ChainDev& c, void* block) {
   char* b = (char*)block;
   const uint64_t ng = part_groups(c.n_tiles);
   c.part = (uint64_t*)b;
@@ -1621,7 +1595,9 @@ hipError_t setup_partials(ChainDev& c, void* block, hipStream_t s) {
   c.gsum = (uint64_t*)b;
   b += (ng * NPART * 16 + 255) / 256 * 256;
   c.gcnt = (uint32_t*)b;
-  return hipMemsetAsync(c.gcnt, 0, 4 * ng, s);
+}
+hipError_t clear_partials(const ChainDev& c, hipStream_t s) {
+  return hipMemsetAsync(c.gcnt, 0, 4 * part_groups(c.n_tiles), s);
 }
 hipError_t launch_zero_state(ChainState* st, hipStream_t s) {
   k_zero_state<<<1, 256, 0, s>>>(st);

@@ -23,12 +23,33 @@ hipError_t launch_init_psi(const ChainDev* d_cd, int ci, const double* psi0, int
 hipError_t launch_scale(double* x, int64_t n, double by, hipStream_t s);  // x /= by
 hipError_t launch_zero_state(ChainState* st, hipStream_t s);
 // Point c.part / c.gsum / c.gcnt into `block` (partials_bytes(c.n_tiles) bytes)
-// and clear the group counters.
-hipError_t setup_partials(ChainDev& c, void* block, hipStream_t s);
+// (launch_reset or clear_partials clears the group counters).
+void setup_partials(ChainDev& c, void* block);
+hipError_t clear_partials(const ChainDev& c, hipStream_t s);
 hipError_t launch_export_psi(const ChainDev* d_cd, int ci, double* out, int64_t N, int precision, hipStream_t s);
 hipError_t launch_export_field(const ChainDev* d_cd, int ci, double* out, const void* src, int64_t N, int precision,
                                hipStream_t s);
-int result_from_device(ihmc_ctx* ctx, const ChainDev& c, const ChainDev* d_cd, int ci, ihmc_result* out);
+// Series, summary and final field of the chains first .. first + n - 1 of a
+// device chain table into outs[0 .. n) (transfer.hip); done[k] bounds the
+// trajectories that chain first + k has been asked for.  Waits for the stream's
+// work.  Uses the context's pinned buffer.
+int collect_results(ihmc_ctx* ctx, const std::vector<ChainDev>& cd, const ChainDev* d_cd, int first, int n,
+                    const int* done, ihmc_result* outs);
+// Fresh states and cleared tile counters of n chains, and (clear_values > 0, the
+// values of the largest chain) cleared fields and momenta of dense chains.
+hipError_t launch_reset(const ChainDev* d_cd, int n, int64_t clear_values, hipStream_t s);
+// Starting fields of n chains: psi0 (device, site order; null: the TAG_INIT
+// normals) plus shift (device, site order, or null).  `from` lies on the device.
+struct StartField {
+  const double* psi0;
+  const double* shift;
+  int64_t chain;
+};
+hipError_t launch_start(const ChainDev* d_cd, const StartField* from, int n, int64_t max_sites, hipStream_t s);
+// Per-site fields of the chains idx (host: lats[i].h) into their device arrays;
+// device staging of large ones is appended to temps.
+int upload_fields(ihmc_ctx* ctx, const std::vector<ChainDev>& cd, const ChainDev* d_cd, const std::vector<int>& idx,
+                  const ihmc_lattice* lats, std::vector<void*>& temps);
 // Checkpoint of one chain into a host buffer (buf NULL: size only), and its
 // restore into a chain with the same parameters (sets *traj to the
 // checkpoint's trajectory index).  `variant` names a path-specific form of the
@@ -58,6 +79,16 @@ struct Arena {
   void* alloc(uint64_t bytes);
   void release(void* p);
 };
+
+// Pinned host memory of a context, two halves that kernels read and write
+// directly (transfer.hip), each with the event of its last launch.  host is
+// null where none could be had: data then goes by copies.
+struct Stage {
+  char* host = nullptr;
+  bool tried = false;
+  hipEvent_t ev[2] = {nullptr, nullptr};
+};
+void stage_destroy(Stage& st);
 
 enum BuildFlags : int { BUILD_P_GIVEN = 1, BUILD_WRITE_P = 2, BUILD_TILED = 4 };  // TILED: never LDS-resident
 
@@ -164,7 +195,7 @@ struct Chains {
   int advance(int32_t n_traj);
   int checkpoint(int32_t i, void* buf, uint64_t* bytes);
   int restore(int32_t i, const void* buf, uint64_t bytes);
-  int result(int32_t i, ihmc_result* out);
+  int results(int32_t first, int32_t m, ihmc_result* outs);  // chains first .. first + m - 1
   ~Chains();
 };
 
@@ -194,6 +225,7 @@ struct ihmc_ctx {
   ihmc::TuneTable tune;
   int64_t resident_sites = -1;  // chains up to this many sites run LDS-resident (-1: as many as fit, 0: none)
   int32_t fuse_steps = 1;       // 2D tiled chains run two middle steps per launch
+  ihmc::Stage stage;            // pinned buffer of set-ups and results
   void* scratch = nullptr;      // this device's scratch of the allocation-free entry point
 };
 

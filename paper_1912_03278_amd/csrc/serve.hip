@@ -428,7 +428,10 @@ bool ihmc_server::admit_setup(std::vector<Request*>& fresh) {
     c.st = (ChainState*)dal(sizeof(ChainState));
     void* pblk = dal(partials_bytes(c.n_tiles));
     bool good = c.psi && c.p && c.rec && c.st && pblk;
-    if (good) e = setup_partials(c, pblk, s);
+    if (good) {
+      setup_partials(c, pblk);
+      e = clear_partials(c, s);
+    }
     if (good && !r->replay.empty()) {
       uint8_t* d = (uint8_t*)dal(r->replay.size());
       good = d != nullptr;
