@@ -1084,7 +1084,7 @@ def main():
                     help="chains that fit one workgroup's LDS run whole trajectories per launch (on) or the "
                          "tiled passes (off); results are bit-identical")
     ap.add_argument("--fuse", default="on", choices=["on", "off"],
-                    help="2D chains on the tiled passes run two middle leap-frog steps per launch (on) or one "
+                    help="2D chains on the tiled passes run up to four middle leap-frog steps per launch (on) or one "
                          "(off); results are bit-identical")
     ap.add_argument("--tiles", default="tuned", choices=["tuned", "rule"],
                     help="tile classes: autotuned per lattice shape before the run (default), or the built-in rule")

@@ -203,12 +203,12 @@ int ihmc_ctx_memory(ihmc_ctx* ctx, uint64_t* used, uint64_t* total);
  * *fp32_fit / *fp64_fit (may be NULL) receive the largest chains that fit
  * without a per-site field (a per-site field takes a fifth array). */
 int ihmc_ctx_set_resident(ihmc_ctx* ctx, int64_t max_sites, int64_t* fp32_fit, int64_t* fp64_fit);
-/* 2D chains on the tiled passes run their middle leap-frog steps two per
- * launch (on != 0, the default): the first step is evaluated on the tile plus
- * a 2-wide ring, the second on the tile, with the field read and written once
- * per pair.  The per-site arithmetic is that of one step per launch, so
- * results are bit-identical either way.  Applies to chain sets created after
- * the call, to the serving rounds that follow it, and to tuning. */
+/* 2D chains on the tiled passes run their middle leap-frog steps up to four per
+ * launch (on != 0, the default): the steps are evaluated on the tile plus a ring
+ * that narrows from step to step, with the field and the momenta read and
+ * written once per launch.  The per-site arithmetic is that of one step per
+ * launch, so results are bit-identical either way.  Applies to chain sets
+ * created after the call and to the serving rounds that follow it. */
 int ihmc_ctx_set_step_fusion(ihmc_ctx* ctx, int32_t on);
 const char* ihmc_last_error(void);
 
@@ -511,7 +511,7 @@ int ihmc_chains_group_info(ihmc_chains* chains, int32_t group, int64_t* out);
 int ihmc_chains_group_chains(ihmc_chains* chains, int32_t group, int32_t* chain_idx);
 /* Time the fused pass kind `mode` (0 = first, 1 = middle, 2 = last, 5 = two
  * middle steps in one launch, 2D groups whose chains have at least two middle
- * steps) of launch group `group`: one warm-up launch, then `reps` launches bracketed by HIP
+ * steps; a round's launches take up to four) of launch group `group`: one warm-up launch, then `reps` launches bracketed by HIP
  * events on the context stream.  Returns the mean duration per launch in
  * microseconds and the lattice sites one launch covers.  The repeated passes
  * overwrite the chains' momenta and field buffers (and a last pass closes a
@@ -551,8 +551,9 @@ int ihmc_copy_bandwidth(ihmc_ctx* ctx, uint64_t bytes, int32_t reps, double* avg
  * not NULL) = number of classes of ndim (out may be NULL to ask only that). */
 int ihmc_tile_shape(int32_t ndim, int32_t cls, int32_t* out, int32_t* n_classes);
 /* Autotune: for each distinct key among lats[0..n) (state precision
- * precision[i]), time the middle steps of every tile class (two per launch in 2D
- * when step fusion is on, see ihmc_ctx_set_step_fusion) and keep the fastest
+ * precision[i]), time the one-step middle pass of every tile class (in 2D the
+ * class sets the first and last passes; fused middle steps have tiles of their
+ * own, see ihmc_ctx_set_step_fusion) and keep the fastest
  * in the table (the built-in rule's class stays unless another is over 3 % faster).  A measurement
  * runs on the context stream over replicas of the lattice with synthetic
  * fields, about `sites` sites in all (at most 65536 replicas): the working set

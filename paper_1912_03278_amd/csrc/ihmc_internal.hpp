@@ -131,15 +131,16 @@ inline __host__ __device__ void pass_coeffs(const ChainDev& cd, int j, double& k
 }
 
 // Field buffers of a lattice chain (four): the accepted field sits in buffer
-// `cur`; launch k of a trajectory (k = 0 the first pass; a launch may fuse two
+// `cur`; launch k of a trajectory (k = 0 the first pass; a launch may fuse several
 // leap-frog steps) reads lat_in_buf and writes lat_out_buf, cycling through the
 // three other buffers, so no launch writes the buffer it reads.
+constexpr int LAT_STEPS = 4;  // middle steps a fused 2D launch takes at most
 constexpr int LAT_BUFFERS = 4;
 inline __host__ __device__ int lat_in_buf(int cur, int k) { return k == 0 ? cur : (cur + 1 + (k - 1) % 3) % 4; }
 inline __host__ __device__ int lat_out_buf(int cur, int k) { return (cur + 1 + k % 3) % 4; }
 
 // Momentum buffers of a lattice chain (two).  In 2D, launch k >= 1 reads
-// buffer lat_p_in(k) and writes lat_p_out(k): a launch that fuses two steps
+// buffer lat_p_in(k) and writes lat_p_out(k): a launch that fuses steps
 // reads the momenta of neighbouring tiles, so it must not write the buffer it
 // reads.  The first pass, the last pass and the force pass use buffer 0 (where
 // given momenta are read and final ones exported); 3D passes update buffer 0

@@ -17,13 +17,17 @@
 //             decision (Sec. 3) and writes the trajectory record;
 //   MEASURE - FP64 action and estimator sums of the accepted field (set-up);
 //   FORCE   - writes F itself (diagnostic; same arithmetic as the other passes).
-// In 2D two MIDDLE steps can also run as one launch (lattice_pass2v_pair, the
-// launch kind PASS_PAIR), with the per-site arithmetic of two passes.
+// In 2D up to four MIDDLE steps can also run as one launch (lattice_steps2v), with
+// the per-site arithmetic of single passes.
 //
 // Memory layout: rows padded to `pitch` (a multiple of 4 elements), so a thread
 // of the 2D kernel moves its four sites with 16-byte vector accesses.  Sums are
 // exact 128-bit fixed point (device_common.hpp): results do not depend on the
 // tile shape or on which chains share a launch.
+#include <algorithm>
+#include <utility>
+#include <vector>
+
 #include "chain_epilogue.hpp"
 #include "device_common.hpp"
 #include "lattice_common.hpp"
@@ -102,12 +106,11 @@ __device__ __forceinline__ int xcd_tile(int b, int n) {
 
 // A LAST launch may cover chains whose trajectories end at different passes
 // (j < 0): each block then takes its chain's own last pass j = n_pass - 1 and
-// the launch index of that pass under the round's step plan (k != 0: the
-// middle steps ran two per launch, so the last pass is launch j / 2 + 1;
-// otherwise launch j).
+// the launch index of that pass under the round's step plan (k != 0: the j - 1
+// middle steps ran LAT_STEPS per launch, after launch 0; otherwise launch j).
 __device__ __forceinline__ void chain_last_pass(const ChainDev& cd, int& j, int& k) {
   j = cd.n_pass - 1;
-  k = k ? j / 2 + 1 : j;
+  k = k ? 1 + (j - 1 + LAT_STEPS - 1) / LAT_STEPS : j;
 }
 
 // --------------------------------------------------------------------- 2D ---
@@ -342,101 +345,73 @@ __global__ __launch_bounds__(BX / 4 * BY) void lattice_pass2v(const ChainDev* __
   block_accumulate_ranks<MODE, NWAVE, NR>(cd, st, accR, bad, lat_in_buf(cur, k), tix);
 }
 
-// ------------------------------------------------------------ 2D, two steps ---
+// ------------------------------------------------------ 2D, several steps ---
 //
-// Two consecutive middle leap-frog steps j, j + 1 in one pass over a tile.
-// psi is staged with a 4-wide halo (rows y in [-4, BY+4), the x range of the
-// one-step kernel); the first step's w is evaluated on the tile plus a 3-wide
-// ring, its kick and drift on the tile plus a 2-wide ring, and the second
-// step's w on a 1-wide ring and its kick and drift on the tile.  The first
-// step on the ring repeats what the neighbouring tiles compute (about 15 %
-// more arithmetic); in exchange the pair reads psi and p and writes them once,
-// half the HBM traffic of two passes.  Per site the arithmetic is that of two
-// MIDDLE passes, operation for operation, so the results are bit-identical.
+// Up to STEPS = 4 consecutive middle leap-frog steps j, j + 1, .. in one pass
+// over a tile.  psi is staged with a halo of 2 STEPS sites; step s evaluates w on
+// the tile plus a ring of 2 (STEPS - s) - 1, and its kick and drift on the tile
+// plus a ring one narrower (the ring repeats what the neighbouring tiles compute,
+// its momenta and field read from their sites), so psi and p move through memory
+// once per launch.  Per site the arithmetic is that of single MIDDLE passes,
+// operation for operation, so the results are bit-identical.
 //
 // Positions outside the lattice (the ragged last tile of a row or column, the
 // wrap of small lattices) hold periodic images: psi, p and the field are all
 // loaded at wrapped coordinates, so every staged position evolves as the
 // lattice site it images.  The ring's momenta are read from other tiles; they
-// come from the buffer of launch k - 1 while the pair writes that of launch k,
-// so no block reads momenta another block of the launch writes.
+// come from the buffer of launch k - 1 while this launch writes that of launch k,
+// so no block reads momenta another block of the launch writes.  A chain with
+// fewer middle steps left takes those (at most max_steps) and stores its tile.
 //
-// A chain whose last middle step is step j (n_pass - 1 = j + 1) takes step j
-// only: its blocks store the first step's tile results, which are those of the
-// one-step pass, and skip the second.
+// A thread owns H consecutive rows of one 4-site chunk column (a strip) and keeps
+// their momenta, psi and field in registers for all steps; LDS holds psi and w.
+// Marching down a strip each row is read once from LDS (16 bytes) instead of three
+// times, every LDS address is a constant offset, and the two sites beside a chunk
+// come from the neighbouring lanes (a wave-wide DPP shift; the lanes at the wave's
+// ends read theirs from LDS): reading them from LDS conflicts four ways, 45 % of
+// the CU's cycles.  The tile's extent is the plan's choice (choose_steps), packed
+// into Tile::z0 as bx | by << 16; bx is a multiple of 4.
 //
-// Threads work on quads of four consecutive x: TPQ = 1 gives each thread its
-// tile quad (first-step momenta kept in registers for the second step) and at
-// most one quad of the 2-wide ring (rows -2, -1, BY, BY+1 over the whole
-// staged width, and the outer chunks of the tile rows); TPQ = 2 runs twice the
-// threads, the first half on the tile quads and the second on the ring, so a
-// launch of few tiles has more waves to hide latency with.
+// Bound by VALU issue once launches fill the chip (83 % of the cycles; 19
+// operations and two transcendentals a site and step, times the ring, 1.5 on 64 x
+// 61 tiles), by latency below that.  Per step, against two steps per launch on 64
+// x 16 tiles with one quad a thread: 4096^2 FP32 32.5 -> 23.2 us, 1024^2 3.98 ->
+// 2.64, 256^2 2.04 -> 1.30, 600 chains of 64 .. 256 sites a row with a field 36.0 ->
+// 22.1; 251 x 130 FP64 4.88 -> 2.61.  Two and three steps a launch measured 30.5 and
+// 24.8 us on 4096^2, five and six 26 and 27 on the chains.
+constexpr int STEPS = LAT_STEPS;
 
-// w = sqrt(J') tanh(sqrt(J') u) - psi on the quad in chunk c of w-row wr, from
-// psi in row wr + 1 of the staged rows (both arrays of pitch RP); the
-// expression of the one-step kernel.
-template <typename T, int RP>
-__device__ __forceinline__ void pair_w_quad(const T* __restrict__ sP, T* __restrict__ sW, int wr, int c, T Ct,
-                                            T at, T hw) {
-  const int pc = (wr + 1) * RP + 4 * c;
-  T cv[4], up[4], dn[4], w[4];
-  ld4<T>(sP + pc, cv);
-  ld4<T>(sP + pc - RP, up);
-  ld4<T>(sP + pc + RP, dn);
-  const T lft = sP[pc - 1], rgt = sP[pc + 4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const T xm = (e == 0) ? lft : cv[e - 1];
-    const T xp = (e == 3) ? rgt : cv[e + 1];
-    const T s = (xm + xp) + (up[e] + dn[e]);
-    const T u = fma_t(Ct, cv[e], s);
-    w[e] = fma_t(at, tanh_state(fma_t(at, u, hw)), -cv[e]);
-  }
-  st4<T>(sW + wr * RP + 4 * c, w);
+// Value of the lane before (wave_left) or after (wave_right) in the wave; the
+// first or last lane takes `edge`.
+template <int CTRL>
+__device__ __forceinline__ uint32_t wave_shift_u32(uint32_t edge, uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)edge, (int)v, CTRL, 0xf, 0xf, false);
 }
-
-// F = Kt w + h'/sqrt(J'), kick and drift of the quad in chunk c of w-row wr
-// (psi in row wr + 1); the new field replaces psi in LDS.
-template <typename T, int RP>
-__device__ __forceinline__ void pair_kick_drift(T* __restrict__ sP, const T* __restrict__ sW, int wr, int c, T Ct,
-                                                T kick, T drift, const T (&pq)[4], const T (&bq)[4], T (&pn)[4],
-                                                T (&pv)[4]) {
-  const int wc = wr * RP + 4 * c;
-  const int pc = (wr + 1) * RP + 4 * c;
-  T wcv[4], wup[4], wdn[4], cv[4];
-  ld4<T>(sW + wc, wcv);
-  ld4<T>(sW + wc - RP, wup);
-  ld4<T>(sW + wc + RP, wdn);
-  const T wl = sW[wc - 1], wrt = sW[wc + 4];
-  ld4<T>(sP + pc, cv);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const T wm = (e == 0) ? wl : wcv[e - 1];
-    const T wp = (e == 3) ? wrt : wcv[e + 1];
-    const T sw = (wm + wp) + (wup[e] + wdn[e]);
-    const T F = fma_t(Ct, wcv[e], sw) + bq[e];
-    pn[e] = fma_t(kick, F, pq[e]);
-    pv[e] = fma_t(drift, pn[e], cv[e]);
-  }
-  st4<T>(sP + pc, pv);
+template <int CTRL>
+__device__ __forceinline__ float wave_shift(float edge, float v) {
+  return __uint_as_float(wave_shift_u32<CTRL>(__float_as_uint(edge), __float_as_uint(v)));
 }
+template <int CTRL>
+__device__ __forceinline__ double wave_shift(double edge, double v) {
+  const uint64_t e = (uint64_t)__double_as_longlong(edge), x = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = wave_shift_u32<CTRL>((uint32_t)e, (uint32_t)x);
+  const uint32_t hi = wave_shift_u32<CTRL>((uint32_t)(e >> 32), (uint32_t)(x >> 32));
+  return __longlong_as_double((long long)((uint64_t)lo | ((uint64_t)hi << 32)));
+}
+constexpr int DPP_WAVE_SHR1 = 0x138;  // lane l - 1
+constexpr int DPP_WAVE_SHL1 = 0x130;  // lane l + 1
 
-template <typename T, int BX, int BY, int TPQ>
-__global__ __launch_bounds__(BX / 4 * BY * TPQ) void lattice_pass2v_pair(const ChainDev* __restrict__ chains,
-                                                                         const Tile* __restrict__ tiles,
-                                                                         int n_tiles, int j, int k) {
-  constexpr int QX = BX / 4;
-  constexpr int NQ = QX * BY;  // tile quads
-  constexpr int NT = NQ * TPQ;
-  constexpr int RP = BX + 8;  // staged x in [-4, BX+4)
-  constexpr int NCH = RP / 4;
-  constexpr int PR = BY + 8;  // psi rows y in [-4, BY+4)
-  constexpr int WR = BY + 6;  // w rows y in [-3, BY+3)
-  constexpr int NRING = 4 * NCH + 2 * BY;
-  static_assert(BX % 4 == 0 && NQ % 64 == 0 && NRING <= NQ && (TPQ == 1 || TPQ == 2), "tile shape");
-  __shared__ __align__(16) T sP[PR * RP];
-  __shared__ __align__(16) T sW[WR * RP];
+constexpr int MS_HX = 2 * STEPS, MS_HY = 2 * STEPS;  // staged halo (a multiple of 4 in x)
+constexpr int MS_CH = MS_HX / 4;                     // halo chunks on each side
+constexpr int MS_BX = 64;                            // widest tile
+constexpr int MS_RP = MS_BX + 2 * MS_HX;             // LDS row pitch
+static_assert(MS_HX % 4 == 0, "whole chunks of halo");
 
+template <typename T, int H>
+__global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __restrict__ chains,
+                                                        const Tile* __restrict__ tiles, int n_tiles, int j, int k,
+                                                        int max_steps) {
+  extern __shared__ __align__(16) unsigned char lds[];
   const Tile tl = tiles[xcd_tile(blockIdx.x, n_tiles)];
   const ChainDev& cd = chains[tl.chain];
   const ChainState* st = cd.st;
@@ -449,123 +424,145 @@ __global__ __launch_bounds__(BX / 4 * BY * TPQ) void lattice_pass2v_pair(const C
   gmem<T>* __restrict__ pmo = (gmem<T>*)cd.p + (int64_t)lat_p_out(k) * NP;
   const gmem<T>* __restrict__ bfield = (const gmem<T>*)cd.b;
   const bool site_field = (cd.h_kind == 2);
-  // rows y0 - 4 .. y0 + BY + 3 lie within one period of [0, L1) when L1 > BY + 3
-  const bool rows_near = (L1 > BY + 3), x_near = (L0 > BX + 2);
-  const int y0 = tl.y0;
-  auto lat_row = [&](int y) { return rows_near ? wrap_near(y0 + y, L1) : wrap_any(y0 + y, L1); };
+  const int bx = tl.z0 & 0xffff, by = tl.z0 >> 16;
+  const int nch = bx / 4 + 2 * MS_CH;             // chunks of a staged row
+  const int prow = by + 2 * MS_HY, wrow = prow - 2;  // staged rows; w rows of the first step
+  const int nst = (wrow + H - 1) / H;             // strips of a chunk column
+  const bool rows_near = (L1 >= by + MS_HY), x_near = (L0 >= bx + MS_HX);
+  auto lat_row = [&](int y) { return rows_near ? wrap_near(y, L1) : wrap_any(y, L1); };
+  T* const sP = reinterpret_cast<T*>(lds);
+  T* const sW = sP + (nst * H + 2) * MS_RP;
 
   const int t = threadIdx.x;
-  const bool has_quad = (TPQ == 1) || t < NQ;
-  const int tq = t % NQ;
-  const int qx = tq % QX, qy = tq / QX;
-  const int gx = tl.x0 + 4 * qx, gy = y0 + qy;
-  const bool quad_ok = has_quad && (gx < L0) && (gy < L1);
-
-  // ---- the thread's ring quad: row ry of the tile frame, chunk rc of the staged width
-  const int rt = (TPQ == 1) ? t : t - NQ;  // ring quad index
-  const bool has_ring = rt >= 0 && rt < NRING;
-  int ry = 0, rc = 0;
-  if (has_ring && rt < 4 * NCH) {
-    const int ri = rt / NCH;
-    ry = ri < 2 ? ri - 2 : BY + ri - 2;
-    rc = rt % NCH;
-  } else if (has_ring) {
-    const int r2 = rt - 4 * NCH;
-    ry = r2 >> 1;
-    rc = (r2 & 1) ? NCH - 1 : 0;
-  }
-
-  // ---- stage psi on the tile plus its 4-wide halo, as in the one-step kernel.
-  // The momenta and field loads are issued after the staged rows' LDS stores:
-  // loads complete in issue order, so issued before them they would hold up
-  // the wait for the staged values; issued here, their latency overlaps the
-  // barrier and the first w, and the kick is their first use
-  constexpr int RG = NT / NCH;
-  constexpr int NRPT = (PR + RG - 1) / RG;
-  const int sc = t % NCH, srg = t / NCH;
-  T v[NRPT][4];
-  if (srg < RG) {
-    const ChunkPos cp = chunk_pos(tl.x0 - 4 + 4 * sc, L0, x_near);
+  const int strip = t / nch, c = t - strip * nch;
+  const ChunkPos cp = chunk_pos(tl.x0 - MS_HX + 4 * c, L0, x_near);
+  // ---- stage psi: row r of the staged rows is lattice row y0 + r - MS_HY; each
+  // thread loads its chunk column of every nsg-th row, all loads before the stores
+  // (nsg >= nst strips, so H + 1 rows a thread cover the prow <= H nst + 2 rows)
+  {
+    const int nsg = (int)blockDim.x / nch;
+    T v[H + 1][4];
+    if (strip < nsg) {
 #pragma unroll
-    for (int q = 0; q < NRPT; ++q) {
-      const int r = srg + RG * q;
-      if (r < PR) load_chunk<T>(pin + row_offset(lat_row(r - 4), pitch), cp, v[q]);
-    }
+      for (int q = 0; q < H + 1; ++q) {
+        const int r = strip + nsg * q;
+        if (r < prow) load_chunk<T>(pin + row_offset(lat_row(tl.y0 + r - MS_HY), pitch), cp, v[q]);
+      }
 #pragma unroll
-    for (int q = 0; q < NRPT; ++q) {
-      const int r = srg + RG * q;
-      if (r < PR) st4<T>(sP + r * RP + 4 * sc, v[q]);
+      for (int q = 0; q < H + 1; ++q) {
+        const int r = strip + nsg * q;
+        if (r < prow) st4<T>(sP + r * MS_RP + 4 * c, v[q]);
+      }
     }
   }
-  // ---- momenta and field of both quads, first needed by the kick
-  T pq[4], bq[4], pr[4], br[4];
+  // ---- momenta and field of the strip's kick rows r0 .. r0 + H - 1 (row 0 is
+  // lattice row y0 - (MS_HY - 2)), issued behind the staging (loads complete in
+  // issue order) and first used by the kick
+  const bool act = strip < nst;
+  const int r0 = strip * H;
+  T pm[H][4], bq[H][4], ps[H][4];
   const T b_uniform = (T)cd.b0;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    bq[e] = b_uniform;
-    br[e] = b_uniform;
-    pq[e] = (T)0;
-    pr[e] = (T)0;
-  }
-  {
-    if (has_quad) {
-      const ChunkPos cq = chunk_pos(gx, L0, x_near);
-      const uint64_t oq = row_offset(lat_row(qy), pitch);
-      load_chunk<T>(pmi + oq, cq, pq);
-      if (site_field) load_chunk<T>(bfield + oq, cq, bq);
+  for (int i = 0; i < H; ++i) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      bq[i][e] = b_uniform;
+      pm[i][e] = (T)0;
     }
-    if (has_ring) {
-      const ChunkPos cr = chunk_pos(tl.x0 - 4 + 4 * rc, L0, x_near);
-      const uint64_t orr = row_offset(lat_row(ry), pitch);
-      load_chunk<T>(pmi + orr, cr, pr);
-      if (site_field) load_chunk<T>(bfield + orr, cr, br);
+    if (act && r0 + i < wrow - 2) {
+      const uint64_t o = row_offset(lat_row(tl.y0 + r0 + i - (MS_HY - 2)), pitch);
+      load_chunk<T>(pmi + o, cp, pm[i]);
+      if (site_field) load_chunk<T>(bfield + o, cp, bq[i]);
     }
   }
-
   lds_barrier();
 
-  const T Ct = (T)cd.C;
-  const T at = (T)cd.sqJ, hw = (T)cd.hw;
-  double kick_d = 0.0, drift_d = 0.0;
-  pass_coeffs(cd, j, kick_d, drift_d);
-  const T kick1 = (T)kick_d, drift1 = (T)drift_d;
-  pass_coeffs(cd, j + 1, kick_d, drift_d);
-  const T kick2 = (T)kick_d, drift2 = (T)drift_d;
-
-  // ---- step j: w on the rows y in [-3, BY+3) (w-row y + 3), all chunks (the
-  // outermost quad of each row holds an unused value)
-  for (int i = t; i < WR * NCH; i += NT) pair_w_quad<T, RP>(sP, sW, i / NCH, i % NCH, Ct, at, hw);
-  lds_barrier();
-  // kick and drift on the tile (momenta kept) and on the ring; each thread
-  // overwrites only the psi of its own quads, which no other thread reads now
-  T pa[4], va[4];
-  if (has_quad) pair_kick_drift<T, RP>(sP, sW, qy + 3, qx + 1, Ct, kick1, drift1, pq, bq, pa, va);
-  if (cd.n_pass - 1 == j + 1) {
-    // the chain's last middle step is step j: its results are those of the
-    // one-step pass, stored to the same buffers, and the block ends here
-    if (quad_ok) {
-      const int64_t base = gx + (int64_t)pitch * gy;
-      st4g<T>(pmo + base, pa);
-      st4g<T>(pout + base, va);
+  const T Ct = (T)cd.C, at = (T)cd.sqJ, hw = (T)cd.hw;
+  const int ns = min(max_steps, cd.n_pass - 1 - j);
+  // w row q and kick row q lie one and two rows below psi row q; the edge lanes'
+  // neighbours (others read the first lane's: one address, no conflict)
+  const int off0 = r0 * MS_RP + 4 * c;
+  const int eoff = (t & 63) == 63 ? off0 + 4 : max(0, __builtin_amdgcn_readfirstlane(off0) - 1);
+  T* const pc = sP + off0;
+  T* const wc = sW + off0;
+  const T* const pe = sP + eoff;
+  const T* const we = sW + eoff;
+  if (act) {
+#pragma unroll
+    for (int i = 0; i < H; ++i) ld4<T>(pc + (i + 2) * MS_RP, ps[i]);
+  }
+#pragma unroll 1
+  for (int s = 0; s < ns; ++s) {
+    // w on the rows the remaining steps of a full launch need
+    if (act && r0 + H > 2 * s && r0 < wrow - 2 * s) {
+      T u[4], m[4], d[4];
+      ld4<T>(pc, u);
+      ld4<T>(pc + MS_RP, m);
+#pragma unroll
+      for (int i = 0; i < H; ++i) {
+        ld4<T>(pc + (i + 2) * MS_RP, d);
+        const T edge = pe[(i + 1) * MS_RP];
+        const T lft = wave_shift<DPP_WAVE_SHR1>(edge, m[3]), rgt = wave_shift<DPP_WAVE_SHL1>(edge, m[0]);
+        T w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const T xm = (e == 0) ? lft : m[e - 1];
+          const T xp = (e == 3) ? rgt : m[e + 1];
+          const T sum = (xm + xp) + (u[e] + d[e]);
+          const T uu = fma_t(Ct, m[e], sum);
+          w[e] = fma_t(at, tanh_state(fma_t(at, uu, hw)), -m[e]);
+        }
+        st4<T>(wc + i * MS_RP, w);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          u[e] = m[e];
+          m[e] = d[e];
+        }
+      }
     }
-    return;
+    lds_barrier();
+    if (act && r0 + H > 2 * s && r0 < wrow - 2 - 2 * s) {
+      double kick_d = 0.0, drift_d = 0.0;
+      pass_coeffs(cd, j + s, kick_d, drift_d);
+      const T kick = (T)kick_d, drift = (T)drift_d;
+      T u[4], m[4], d[4];
+      ld4<T>(wc, u);
+      ld4<T>(wc + MS_RP, m);
+#pragma unroll
+      for (int i = 0; i < H; ++i) {
+        ld4<T>(wc + (i + 2) * MS_RP, d);
+        const T edge = we[(i + 1) * MS_RP];
+        const T lft = wave_shift<DPP_WAVE_SHR1>(edge, m[3]), rgt = wave_shift<DPP_WAVE_SHL1>(edge, m[0]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const T wm = (e == 0) ? lft : m[e - 1];
+          const T wp = (e == 3) ? rgt : m[e + 1];
+          const T sw = (wm + wp) + (u[e] + d[e]);
+          const T F = fma_t(Ct, m[e], sw) + bq[i][e];
+          pm[i][e] = fma_t(kick, F, pm[i][e]);
+          ps[i][e] = fma_t(drift, pm[i][e], ps[i][e]);
+        }
+        st4<T>(pc + (i + 2) * MS_RP, ps[i]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          u[e] = m[e];
+          m[e] = d[e];
+        }
+      }
+    }
+    if (s + 1 < ns) lds_barrier();
   }
-  if (has_ring) {
-    T pn[4], pv[4];
-    pair_kick_drift<T, RP>(sP, sW, ry + 3, rc, Ct, kick1, drift1, pr, br, pn, pv);
-  }
-  lds_barrier();
-
-  // ---- step j + 1: w on the rows y in [-1, BY+1), then kick and drift on the tile
-  for (int i = t; i < (BY + 2) * NCH; i += NT) pair_w_quad<T, RP>(sP, sW, 2 + i / NCH, i % NCH, Ct, at, hw);
-  lds_barrier();
-  if (!has_quad) return;
-  T pn[4], pv[4];
-  pair_kick_drift<T, RP>(sP, sW, qy + 3, qx + 1, Ct, kick2, drift2, pa, bq, pn, pv);
-  if (quad_ok) {
-    const int64_t base = gx + (int64_t)pitch * gy;
-    st4g<T>(pmo + base, pn);
-    st4g<T>(pout + base, pv);
+  const int gx = tl.x0 - MS_HX + 4 * c;
+  if (act && c >= MS_CH && c < nch - MS_CH && gx < L0) {
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const int ty = r0 + i - (MS_HY - 2), gy = tl.y0 + ty;
+      if (ty >= 0 && ty < by && gy < L1) {
+        const int64_t base = gx + (int64_t)pitch * gy;  // gx + 3 < pitch
+        st4g<T>(pmo + base, pm[i]);
+        st4g<T>(pout + base, ps[i]);
+      }
+    }
   }
 }
 
@@ -841,9 +838,88 @@ __global__ __launch_bounds__(64 * ZR, 8) void lattice_pass3t(const ChainDev* __r
 
 // ------------------------------------------------------------------ launch ---
 
-// Threads that give every SIMD of the MI355X eight waves: 256 CUs x 4 SIMDs x
-// 8 waves x 64 lanes.
-constexpr int64_t kFillThreads = 256 * 4 * 8 * 64;
+// Tile of one chain under a shape: equal tiles of at most bx x by sites, with no
+// more rows than `threads` threads can hold in strips of H.
+static void steps_tile(const StepShape& g, int L0, int L1, int& bx, int& by, int& threads, int& rows) {
+  const int nx = (L0 + g.bx - 1) / g.bx;
+  bx = ((L0 + nx - 1) / nx + 3) / 4 * 4;
+  const int nch = bx / 4 + 2 * MS_CH;
+  const int by_max = std::min(g.by, g.max_threads / nch * g.H - (2 * MS_HY - 2));
+  const int ny = (L1 + by_max - 1) / by_max;
+  by = (L1 + ny - 1) / ny;
+  const int nst = (by + 2 * MS_HY - 2 + g.H - 1) / g.H;
+  threads = (nst * nch + 63) / 64 * 64;
+  rows = nst * g.H + 2;
+}
+
+// Shape of the several-steps launches over a set of chains: the one that gives the
+// fullest CU the fewest wave-rows (waves x H, four SIMDs at a time).  Tiles of 64
+// x 64 repeat the least ring, 16 x 16 spread a small lattice over the CUs (256^2
+// FP32, per step: 1.30 us on 16 x 16, 1.41 on 32 x 16, 2.0 on 64 x 64; 1024^2:
+// 2.64 on 64 x 64 with H = 2, 2.87 with H = 3, 3.3 on 32 x 32).  Launches of more
+// than 1024 tiles keep every CU busy, so the mean counts, and workgroups of 512
+// threads at most, three of which share a CU (4096^2: H = 3 at 512 threads 23.2
+// us, H = 2 24.8, H = 3 at 768 threads 25.7).
+StepShape choose_steps(int precision, const std::vector<std::pair<int, int>>& lattices) {
+  StepShape best;
+  double best_cost = 0.0;
+  static const int kExtent[][2] = {{64, 64}, {64, 32}, {32, 32}, {32, 16}, {16, 16}};
+  for (const auto& ex : kExtent)
+    for (int H = precision == 4 ? 3 : 2; H >= 1; --H)
+      for (int cap : {512, 1024}) {
+        StepShape g;
+        g.bx = ex[0];
+        g.by = ex[1];
+        g.H = H;
+        g.max_threads = cap;
+        int64_t tiles = 0, waves = 0;
+        int wmax = 0;
+        for (const auto& l : lattices) {
+          int bx, by, thr, rows;
+          steps_tile(g, l.first, l.second, bx, by, thr, rows);
+          const int64_t n = (int64_t)((l.first + bx - 1) / bx) * ((l.second + by - 1) / by);
+          tiles += n;
+          waves += n * (thr / 64);
+          wmax = std::max(wmax, thr / 64);
+          g.threads = std::max(g.threads, thr);
+          g.rows = std::max(g.rows, rows);
+        }
+        const bool full = tiles > 1024;
+        if (full && cap == 1024 && precision == 4) continue;
+        const double cost = full ? (double)waves * H / 1024.0 : (double)(((tiles + 255) / 256 * wmax + 3) / 4 * H);
+        if (best.H == 0 || cost < best_cost) {
+          best = g;
+          best_cost = cost;
+        }
+      }
+  return best;
+}
+
+void steps_tiles(const StepShape& g, int chain, int L0, int L1, std::vector<Tile>& out) {
+  int bx, by, thr, rows;
+  steps_tile(g, L0, L1, bx, by, thr, rows);
+  for (int y = 0; y < L1; y += by)
+    for (int x = 0; x < L0; x += bx) out.push_back(Tile{chain, x, y, bx | (by << 16)});
+}
+
+hipError_t launch_lattice_steps(int precision, const StepShape& g, const ChainDev* chains, const Tile* tiles,
+                                int n_tiles, int j, int k, int max_steps, hipStream_t s) {
+  if (n_tiles <= 0) return hipSuccess;
+  if (max_steps < 1 || max_steps > STEPS || g.threads < 64 || g.threads > 1024) return hipErrorInvalidValue;
+  const size_t lds = 2 * (size_t)g.rows * MS_RP * (size_t)precision;
+  const dim3 grid((unsigned)n_tiles), block((unsigned)g.threads);
+  if (precision == 4) {
+    if (g.H == 1) lattice_steps2v<float, 1><<<grid, block, lds, s>>>(chains, tiles, n_tiles, j, k, max_steps);
+    else if (g.H == 2) lattice_steps2v<float, 2><<<grid, block, lds, s>>>(chains, tiles, n_tiles, j, k, max_steps);
+    else if (g.H == 3) lattice_steps2v<float, 3><<<grid, block, lds, s>>>(chains, tiles, n_tiles, j, k, max_steps);
+    else return hipErrorInvalidValue;
+  } else {
+    if (g.H == 1) lattice_steps2v<double, 1><<<grid, block, lds, s>>>(chains, tiles, n_tiles, j, k, max_steps);
+    else if (g.H == 2) lattice_steps2v<double, 2><<<grid, block, lds, s>>>(chains, tiles, n_tiles, j, k, max_steps);
+    else return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
 
 template <typename T, int BX, int BY>
 static hipError_t launch_mode2v(int mode, const ChainDev* chains, const Tile* tiles, int n_tiles, int j, int k,
@@ -865,15 +941,6 @@ static hipError_t launch_mode2v(int mode, const ChainDev* chains, const Tile* ti
       break;
     case PASS_FORCE:
       lattice_pass2v<T, BX, BY, PASS_FORCE><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
-      break;
-    case PASS_PAIR:
-      // a launch too small to give every SIMD eight waves with one thread per
-      // tile quad takes two threads per quad (the ring on its own threads);
-      // a large one keeps one, which leaves each thread more work in flight
-      if ((int64_t)n_tiles * block.x < kFillThreads)
-        lattice_pass2v_pair<T, BX, BY, 2><<<grid, dim3(2 * block.x), 0, s>>>(chains, tiles, n_tiles, j, k);
-      else
-        lattice_pass2v_pair<T, BX, BY, 1><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
       break;
     default:
       return hipErrorInvalidValue;

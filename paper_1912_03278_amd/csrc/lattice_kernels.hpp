@@ -3,11 +3,14 @@
 
 #include <hip/hip_runtime.h>
 
+#include <utility>
+#include <vector>
+
 #include "ihmc_internal.hpp"
 
 namespace ihmc {
 
-// PASS_PAIR: the middle steps j and j + 1 in one launch (2D tile classes only).
+// PASS_PAIR: two middle steps in one launch (2D groups; timing only).
 enum PassMode : int { PASS_FIRST = 0, PASS_MIDDLE = 1, PASS_LAST = 2, PASS_MEASURE = 3, PASS_FORCE = 4, PASS_PAIR = 5 };
 
 struct TileShape {
@@ -51,12 +54,25 @@ void resident_extend(ResidentShape& s, const ChainDev& c);
 hipError_t launch_lattice_resident(int precision, int ndim, const ResidentShape& r, const ChainDev* chains,
                                    const Tile* tiles, int n_chains, int n_traj, hipStream_t s);
 
+// Several middle steps per launch (2D): tiles of at most bx x by sites, threads
+// that own H rows of a 4-site chunk column each, workgroups of `threads` threads
+// (at most max_threads) and `rows` LDS rows per array.
+struct StepShape {
+  int bx = 0, by = 0, H = 0, max_threads = 0, threads = 0, rows = 0;
+};
+StepShape choose_steps(int precision, const std::vector<std::pair<int, int>>& lattices);
+void steps_tiles(const StepShape& g, int chain, int L0, int L1, std::vector<Tile>& out);
+// Middle steps j .. j + max_steps - 1 (at most LAT_STEPS; each chain those that it
+// has) as launch index k over n_tiles entries of steps_tiles.
+hipError_t launch_lattice_steps(int precision, const StepShape& g, const ChainDev* chains, const Tile* tiles,
+                                int n_tiles, int j, int k, int max_steps, hipStream_t s);
+
 // Launch one pass of kind `mode` (pass index j of the trajectory, which sets
 // the kick and drift; launch index k, which sets the field buffers) over n_tiles
 // consecutive entries of `tiles`; all tiles must belong to chains of the given
 // precision, dimension and tile class.  A LAST launch with j < 0 runs every
-// chain's own last pass (j = n_pass - 1), with its launch index j / 2 + 1 when
-// k != 0 (middle steps two per launch) or j when k == 0.
+// chain's own last pass (j = n_pass - 1), with the launch index that follows its
+// middle steps when k != 0 (LAT_STEPS per launch) or j when k == 0.
 hipError_t launch_lattice_pass(int precision, int ndim, int cls, int mode, const ChainDev* chains,
                                const Tile* tiles, int n_tiles, int j, int k, hipStream_t s);
 

@@ -307,6 +307,17 @@ void plan_groups(const std::vector<ChainDev>& cd, const std::vector<int>& member
       g.n_pass.push_back(c.n_pass);
     }
     g.tile_begin.push_back((int)tiles.size() - base - g.tile_off);
+    if (g.ndim == 2 && !resident) {  // tiles of the fused middle steps (and of their timing)
+      std::vector<std::pair<int, int>> ls;
+      for (int ci : g.order) ls.emplace_back(cd[ci].L0, cd[ci].L1);
+      g.steps = choose_steps(g.prec, ls);
+      g.st_off = (int)tiles.size() - base;
+      for (int ci : g.order) {
+        g.st_begin.push_back((int)tiles.size() - base - g.st_off);
+        steps_tiles(g.steps, ci, cd[ci].L0, cd[ci].L1, tiles);
+      }
+      g.st_begin.push_back((int)tiles.size() - base - g.st_off);
+    }
     g.max_pass = cd[g.order[0]].n_pass;
     groups.push_back(g);
   }
@@ -721,18 +732,20 @@ struct RoundSink {
                   hipStream_t st) {
     return pool ? launch_lattice_pass(g.prec, g.ndim, g.cls, mode, d_cd, t, n, j, k, st) : hipSuccess;
   }
+  hipError_t steps(const Group& g, const ChainDev* d_cd, const Tile* t, int n, int j, int k, hipStream_t st) {
+    return pool ? launch_lattice_steps(g.prec, g.steps, d_cd, t, n, j, k, LAT_STEPS, st) : hipSuccess;
+  }
   hipError_t resident(const Group& g, const ChainDev* d_cd, const Tile* t, int n, hipStream_t st) {
     return pool ? launch_resident_group(g, d_cd, t, n, 1, st) : hipSuccess;
   }
 };
 
 // One trajectory of every chain.  Per group: pass j = 0 (FIRST) over all
-// tiles, then MIDDLE over the chains that still have passes after j and LAST
-// over the chains whose final pass is j.  Chains are sorted by pass count, so
-// each set is a contiguous range of the tile table.  Groups run on streams of
-// their own, and the LAST launches of a group on a second stream: LAST(j) only
-// waits for launch j-1 of its group, so it overlaps MIDDLE(j) of the other
-// chains.  Captured once, the fork/join structure becomes graph edges.
+// tiles, then the middle steps over the chains that still have passes after j
+// (in 2D several steps a launch), then one LAST launch over all tiles.  Chains
+// are sorted by pass count, so each set is a contiguous range of the tile table.
+// Groups run on streams of their own.  Captured once, the fork/join structure
+// becomes graph edges.
 static hipError_t round_plan(const std::vector<Group>& groups, const Tile* d_tiles, const ChainDev* d_cd,
                              const std::vector<hipStream_t>& side, RoundSink& sk, hipStream_t s) {
   hipError_t e;
@@ -752,16 +765,15 @@ static hipError_t round_plan(const std::vector<Group>& groups, const Tile* d_til
     if ((e = sk.pass(g, PASS_FIRST, d_cd, base, g.tile_begin.back(), 0, 0, gs)) != hipSuccess) return e;
     const int nc = (int)g.order.size();
     if (g.pair) {
-      // Middle steps in pairs (1, 2), (3, 4), ...: launch k = 1 + (j - 1) / 2
-      // runs the pair starting at odd j over the chains with passes after j
-      // (chain order is descending pass count); a chain whose last middle step
-      // is j (its last pass is j + 1) takes step j alone in the same launch.
-      for (int j = 1; j < g.max_pass; j += 2) {
-        const int k = 1 + (j - 1) / 2;
+      // Middle steps LAT_STEPS at a time, from j = 1: launch k = 1 + (j - 1) /
+      // LAT_STEPS runs over the chains with passes after j (chain order is
+      // descending pass count); a chain with fewer steps left takes those.
+      for (int j = 1; j < g.max_pass; j += LAT_STEPS) {
+        const int k = 1 + (j - 1) / LAT_STEPS;
         int end = 0;
         while (end < nc && g.n_pass[end] - 1 > j) ++end;
         if (end > 0) {
-          if ((e = sk.pass(g, PASS_PAIR, d_cd, base, g.tile_begin[end], j, k, gs)) != hipSuccess) return e;
+          if ((e = sk.steps(g, d_cd, d_tiles + g.st_off, g.st_begin[end], j, k, gs)) != hipSuccess) return e;
         }
       }
     }
@@ -1492,10 +1504,14 @@ extern "C" int ihmc_chains_time_pass(ihmc_chains* ch, int32_t group, int32_t mod
   hipEvent_t e0, e1;
   HIPCHK(hipEventCreate(&e0), "event");
   HIPCHK(hipEventCreate(&e1), "event");
-  hipError_t e = launch_lattice_pass(g.prec, g.ndim, g.cls, mode, c->d_cd, c->d_tiles + g.tile_off, g.tile_begin.back(), 1, 1, s);
+  auto launch = [&]() {
+    if (mode == PASS_PAIR)
+      return launch_lattice_steps(g.prec, g.steps, c->d_cd, c->d_tiles + g.st_off, g.st_begin.back(), 1, 1, 2, s);
+    return launch_lattice_pass(g.prec, g.ndim, g.cls, mode, c->d_cd, c->d_tiles + g.tile_off, g.tile_begin.back(), 1, 1, s);
+  };
+  hipError_t e = launch();
   if (e == hipSuccess) e = hipEventRecord(e0, s);
-  for (int r = 0; e == hipSuccess && r < reps; ++r)
-    e = launch_lattice_pass(g.prec, g.ndim, g.cls, mode, c->d_cd, c->d_tiles + g.tile_off, g.tile_begin.back(), 1, 1, s);
+  for (int r = 0; e == hipSuccess && r < reps; ++r) e = launch();
   if (e == hipSuccess) e = hipEventRecord(e1, s);
   if (e == hipSuccess) e = hipEventSynchronize(e1);
   float ms = 0.f;

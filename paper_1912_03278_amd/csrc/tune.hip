@@ -177,21 +177,20 @@ static int measure_key(ihmc_ctx* ctx, const TileKey& k, int64_t sites, int reps,
   // three interleaved rounds over the classes; the minimum of the round means
   double best[kMaxTileClasses];
   for (int cls = 0; cls < kMaxTileClasses; ++cls) best[cls] = NAN;
-  const bool pair = (k.ndim == 2) && ctx->fuse_steps;
-  const int mode = pair ? PASS_PAIR : PASS_MIDDLE;
-  const double steps = pair ? 2.0 : 1.0;
+  // (fused 2D middle steps run on tiles of their own: what the class sets there is
+  // the cost of the first and last passes, which stage and update as this one does)
   for (int round = 0; round < 3; ++round) {
     for (int cls = 0; cls < ncls; ++cls) {
       const int nt = (int)tl[cls].size();
-      HIPCHK(launch_lattice_pass(k.prec, k.ndim, cls, mode, d_cd, d_tl[cls], nt, 1, 1, s), "tune warm-up");
+      HIPCHK(launch_lattice_pass(k.prec, k.ndim, cls, PASS_MIDDLE, d_cd, d_tl[cls], nt, 1, 1, s), "tune warm-up");
       HIPCHK(hipEventRecord(rel.e0, s), "event record");
       for (int i = 0; i < reps; ++i)
-        HIPCHK(launch_lattice_pass(k.prec, k.ndim, cls, mode, d_cd, d_tl[cls], nt, 1, 1, s), "tune pass");
+        HIPCHK(launch_lattice_pass(k.prec, k.ndim, cls, PASS_MIDDLE, d_cd, d_tl[cls], nt, 1, 1, s), "tune pass");
       HIPCHK(hipEventRecord(rel.e1, s), "event record");
       HIPCHK(hipEventSynchronize(rel.e1), "event sync");
       float ms = 0.f;
       HIPCHK(hipEventElapsedTime(&ms, rel.e0, rel.e1), "event time");
-      const double v = 1e6 * (double)ms / reps / (double)(R * N) / steps;
+      const double v = 1e6 * (double)ms / reps / (double)(R * N);
       if (!(best[cls] <= v)) best[cls] = v;
     }
   }
