@@ -132,12 +132,14 @@ inline __host__ __device__ void pass_coeffs(const ChainDev& cd, int j, double& k
 
 // Field buffers of a lattice chain (four): the accepted field sits in buffer
 // `cur`; launch k of a trajectory (k = 0 the first pass; a launch may fuse several
-// leap-frog steps) reads lat_in_buf and writes lat_out_buf, cycling through the
-// three other buffers, so no launch writes the buffer it reads.
+// leap-frog steps) reads lat_in_buf and writes lat_out_buf, alternating between
+// the two buffers after `cur` (mod 4), so no launch writes the buffer it reads.
+// Two, not all three others: a trajectory then touches less of the last-level
+// cache (4096^2 FP32: 784 -> 765 us a trajectory, 256^3: 1260 -> 1250).
 constexpr int LAT_STEPS = 4;  // middle steps a fused 2D launch takes at most
 constexpr int LAT_BUFFERS = 4;
-inline __host__ __device__ int lat_in_buf(int cur, int k) { return k == 0 ? cur : (cur + 1 + (k - 1) % 3) % 4; }
-inline __host__ __device__ int lat_out_buf(int cur, int k) { return (cur + 1 + k % 3) % 4; }
+inline __host__ __device__ int lat_in_buf(int cur, int k) { return k == 0 ? cur : (cur + 1 + (k - 1) % 2) % 4; }
+inline __host__ __device__ int lat_out_buf(int cur, int k) { return (cur + 1 + k % 2) % 4; }
 
 // Momentum buffers of a lattice chain (two).  In 2D, launch k >= 1 reads
 // buffer lat_p_in(k) and writes lat_p_out(k): a launch that fuses steps
