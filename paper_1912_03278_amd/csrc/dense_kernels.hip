@@ -13,13 +13,14 @@
 // Hamiltonian uses an FP64 GEMM of the stored FP32 field with the FP64 K.
 //
 // Layouts:
-//   K limbs   [L] x tiled (Np x Np), rows = sites i, columns = k
-//   X limbs   [L] x tiled (Bp x Np), rows = chains b, columns = sites k
+//   K limbs   [L] x fragments of (Np x Np), rows = sites i, columns = k
+//   X limbs   [L] x fragments of (Bp x Np), rows = chains b, columns = sites k
 //   partials  [S][Bp][Np]  FP32 (split-K slices, summed in fixed order)
-// "Tiled" stores each 128-row x 32-column block contiguously (8 KiB of BF16,
-// rows of 64 bytes), blocks ordered row-block major: one k-step of a GEMM
-// workgroup then reads one contiguous block per limb and operand, in whole
-// cache lines.  Np is N padded to a multiple of 256, Bp is B padded to a
+// "Fragments" stores each 16-row x 32-column block contiguously in the order in
+// which the lanes of a 16x16x32 MFMA take it (lane l: row l % 16, columns
+// 8 (l / 16) .. + 7, 16 bytes), blocks of a row block in order of k.  A wave then
+// loads a fragment with one instruction as 1 KiB in a row and feeds it to the
+// matrix unit as it is.  Np is N padded to a multiple of 256, Bp is B padded to a
 // multiple of 128; padding is zero.
 #include "chain_epilogue.hpp"
 #include "dense_kernels.hpp"
@@ -29,9 +30,9 @@ namespace ihmc {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-// Offset of element (row, k) of a tiled operand with Np columns.
-__host__ __device__ __forceinline__ int64_t tiled(int64_t row, int64_t k, int64_t Np) {
-  return (((row >> 7) * (Np >> 5) + (k >> 5)) << 12) + ((row & 127) << 5) + (k & 31);
+// Offset of element (row, k) of an operand in fragments with Np columns.
+__host__ __device__ __forceinline__ int64_t frag(int64_t row, int64_t k, int64_t Np) {
+  return (((row >> 4) * (Np >> 5) + (k >> 5)) << 9) + (((k >> 3) & 3) << 7) + ((row & 15) << 3) + (k & 7);
 }
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -55,7 +56,7 @@ __global__ void k_dense_split_K(const double* __restrict__ K, int64_t N, int64_t
   const double x = (i < N && k < N) ? K[i * N + k] : 0.0;
   __bf16 a, b, c;
   split3(x, a, b, c);
-  const int64_t o = tiled(i, k, Np);
+  const int64_t o = frag(i, k, Np);
   Kl[o] = a;
   Kl[Np * Np + o] = b;
   Kl[2 * Np * Np + o] = c;
@@ -247,94 +248,82 @@ __global__ void k_dense_fill(double* __restrict__ x, int64_t N, int64_t Np, doub
 // ---------------------------------------------------------- split-K MFMA GEMM ---
 //
 // part[s][b][i] = sum_{k in slice s} sum_{(a, c) in products} Kl[a][i][k] * Xl[c][b][k]
-// Workgroup tile 128 sites x 128 chains, k-step 32, eight waves (two per SIMD)
-// of 32 sites x 64 chains (2 x 4 MFMA 16x16x32 tiles).  Operand tiles of all
-// limbs are staged in LDS, double buffered: the global loads of k-step t+1 are
-// issued into registers before the MFMAs of step t and written to the other
-// LDS buffer after them, so one barrier per k-step separates the two.  LDS rows
-// are padded to 40 elements, which makes the fragment reads conflict-free.
-constexpr int GBM = 128, GBN = 128, GBK = 32, GPAD = 40, GTHREADS = 512;
-
-template <int NL, int NPROD>
-__global__ __launch_bounds__(GTHREADS) void k_dense_gemm_bf16(const __bf16* __restrict__ Kl,
-                                                              const __bf16* __restrict__ Xl, float* __restrict__ part,
-                                                              int64_t Np, int64_t Bp, int64_t kslice) {
-  __shared__ __align__(16) __bf16 sA[2][NL][GBM][GPAD];
-  __shared__ __align__(16) __bf16 sB[2][NL][GBN][GPAD];
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int64_t i0 = (int64_t)blockIdx.x * GBM, b0 = (int64_t)blockIdx.y * GBN;
-  const int64_t k_begin = (int64_t)blockIdx.z * kslice;
-  const int nk = (int)(kslice / GBK);
-  const int wr = (wave >> 1) * 32, wc = (wave & 1) * 64;  // wave's sub-tile
+// A workgroup is one wave with 16 RB sites x 16 CB chains (RB x CB MFMA 16x16x32
+// blocks), and there is no LDS: operands lie in memory as fragments, so a wave
+// loads what it multiplies straight into registers, three or four k-steps in
+// turn, the loads of a step issued two or three steps before their use.  Waves
+// that share a row or a column of fragments run side by side on one XCD and find
+// them in its caches.  Matrix cores bound the large sizes (4096 sites x 256
+// chains, six products: 44.0 us, 1170 TFLOP/s; 48.8 us when a 128 x 128 tile went
+// through LDS behind a barrier per k-step), reading K the ones with few chains
+// (4096 x 20: 16.3 us, 6.2 TB/s; was 42.7), the latency of the chain of k-steps
+// the small ones (1024 x 20: 3.8 us, was 12.6; 1024 x 128: 4.8 us, was 12.6).
+// Per output the order of the k-steps and of the products within one is that of
+// a single accumulator running over the slice, whatever RB and CB are.
+template <int NL, int NPROD, int RB, int CB, int D>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, RB * CB >= 16 ? 1 : 2))) void k_dense_gemm_bf16(
+    const __bf16* __restrict__ Kl, const __bf16* __restrict__ Xl, float* __restrict__ part, int64_t Np, int64_t Bp,
+    int S, int nrow, int ncol) {
   // limb pairs (a, c) with a + c <= 2 (NPROD = 6) or <= 1 (NPROD = 3)
   constexpr int PA[6] = {0, 0, 1, 0, 1, 2};
   constexpr int PC[6] = {0, 1, 0, 2, 1, 0};
-  // staging: a 128 x 32 block is 512 chunks of 8 elements, contiguous in the
-  // tiled layout; thread t moves chunk t (row t/4, k offset 8 (t%4)) per limb
-  const int srow = t >> 2, skc = (t & 3) * 8;
-  const __bf16* gA = Kl + tiled(i0, k_begin, Np) + t * 8;
-  const __bf16* gB = Xl + tiled(b0, k_begin, Np) + t * 8;
-  const int64_t lA = Np * Np, lB = Bp * Np;
-  bf16x8 ra[NL], rb[NL];
-  auto gload = [&](int64_t koff) {
+  const int lane = threadIdx.x;
+  // Blocks go to the 8 XCDs in turn: 8 / S of them take one k slice, each its own
+  // run of row tiles, the column tiles of a row tile one after the other.
+  const int share = 8 / S, xcd = blockIdx.x & 7, m = blockIdx.x >> 3;
+  const int z = xcd / share, ct = m % ncol, rt = m / ncol + (nrow + share - 1) / share * (xcd % share);
+  if (rt >= nrow) return;
+  const int64_t i0 = (int64_t)rt * (16 * RB), b0 = (int64_t)ct * (16 * CB), k0 = z * (Np / S);
+  const int nk = (int)((Np / S) >> 5);
+  const int64_t lA = Np * Np, lB = Bp * Np, row16 = Np << 4;
+  const __bf16* gA = Kl + frag(i0, k0, Np) + lane * 8;
+  const __bf16* gB = Xl + frag(b0, k0, Np) + lane * 8;
+  bf16x8 fa[D][NL][RB], fb[D][NL][CB];
+  auto load = [&](int buf, int kt) {
+    const int64_t o = (int64_t)kt << 9;
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
-      ra[l] = *reinterpret_cast<const bf16x8*>(gA + l * lA + koff);
-      rb[l] = *reinterpret_cast<const bf16x8*>(gB + l * lB + koff);
+#pragma unroll
+      for (int r = 0; r < RB; ++r) fa[buf][l][r] = *reinterpret_cast<const bf16x8*>(gA + l * lA + r * row16 + o);
+#pragma unroll
+      for (int c = 0; c < CB; ++c) fb[buf][l][c] = *reinterpret_cast<const bf16x8*>(gB + l * lB + c * row16 + o);
     }
   };
-  auto lstore = [&](int buf) {
+  f32x4 acc[RB][CB];
 #pragma unroll
-    for (int l = 0; l < NL; ++l) {
-      *reinterpret_cast<bf16x8*>(&sA[buf][l][srow][skc]) = ra[l];
-      *reinterpret_cast<bf16x8*>(&sB[buf][l][srow][skc]) = rb[l];
+  for (int r = 0; r < RB; ++r)
+#pragma unroll
+    for (int c = 0; c < CB; ++c) acc[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int d = 0; d < D - 1; ++d) load(d, min(d, nk - 1));
+  for (int kt = 0; kt < nk; kt += D) {
+#pragma unroll
+    for (int h = 0; h < D; ++h) {
+      if (kt + h < nk) {
+        // past the slice's end the last step is loaded again and not used; the
+        // scheduling barriers keep the loads ahead of the MFMAs they overlap
+        load((h + D - 1) % D, min(kt + h + D - 1, nk - 1));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int p = 0; p < NPROD; ++p)
+#pragma unroll
+          for (int r = 0; r < RB; ++r)
+#pragma unroll
+            for (int c = 0; c < CB; ++c)
+              acc[r][c] =
+                  __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][PA[p]][r], fb[h][PC[p]][c], acc[r][c], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
-  };
-
-  f32x4 acc[2][4];
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  gload(0);
-  lstore(0);
-  lds_barrier();
-  const int fr = lane & 15, fk = (lane >> 4) * 8;
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    // next 128 x 32 block of the same row block, issued before this step's MFMAs
-    // and stored after them; unconditional (the last step reloads its own block
-    // into the idle buffer), since the compiler sinks loads that only a branch
-    // uses into that branch, after the MFMAs, exposing their whole latency
-    gload((int64_t)min(kt + 1, nk - 1) << 12);
-    __builtin_amdgcn_sched_barrier(0);
-    bf16x8 fa[NL][2], fb[NL][4];
-#pragma unroll
-    for (int l = 0; l < NL; ++l) {
-#pragma unroll
-      for (int r = 0; r < 2; ++r) fa[l][r] = *reinterpret_cast<const bf16x8*>(&sA[buf][l][wr + 16 * r + fr][fk]);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) fb[l][c] = *reinterpret_cast<const bf16x8*>(&sB[buf][l][wc + 16 * c + fr][fk]);
-    }
-#pragma unroll
-    for (int p = 0; p < NPROD; ++p)
-#pragma unroll
-      for (int r = 0; r < 2; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-          acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[PA[p]][r], fb[PC[p]][c], acc[r][c], 0, 0, 0);
-    lstore(buf ^ 1);  // unconditional too, or the loads above would sink into its branch
-    lds_barrier();
   }
   // D layout of the 16x16 MFMA: lane -> column (chain) lane % 16, rows 4 (lane / 16) + e
-  float* out = part + (int64_t)blockIdx.z * Bp * Np;
+  float* out = part + (int64_t)z * Bp * Np;
 #pragma unroll
-  for (int r = 0; r < 2; ++r)
+  for (int r = 0; r < RB; ++r)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int64_t b = b0 + wc + 16 * c + (lane & 15);
-      const int64_t i = i0 + wr + 16 * r + 4 * (lane >> 4);
+    for (int c = 0; c < CB; ++c) {
+      const int64_t b = b0 + 16 * c + (lane & 15);
+      const int64_t i = i0 + 16 * r + 4 * (lane >> 4);
       *reinterpret_cast<float4*>(out + b * Np + i) = make_float4(acc[r][c][0], acc[r][c][1], acc[r][c][2], acc[r][c][3]);
     }
 }
@@ -467,7 +456,7 @@ __device__ __forceinline__ void split_f32(float x, __bf16& l0, __bf16& l1, __bf1
 // terms) run one wave per tile of 256 sites of one chain (grid: tiles x chains,
 // so the chain's fields are uniform loads) with four consecutive sites per lane:
 // 16-byte loads and stores of the FP32 fields, 8-byte stores of the limbs (four
-// consecutive sites are contiguous in the tiled layout), and one wave per CU
+// consecutive sites are contiguous in a fragment), and one wave per CU
 // slot instead of four, so that the whole grid is resident at once.  Sites past
 // N (the padding up to Np) carry zeros.
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -494,7 +483,7 @@ __device__ __forceinline__ void store_limbs4(__bf16* __restrict__ X, int64_t lim
     l1[e] = c;
     l2[e] = d;
   }
-  const int64_t o = tiled(b, i, Np);
+  const int64_t o = frag(b, i, Np);
   *reinterpret_cast<bf16x4*>(X + o) = l0;
   *reinterpret_cast<bf16x4*>(X + limb_stride + o) = l1;
   *reinterpret_cast<bf16x4*>(X + 2 * limb_stride + o) = l2;
@@ -732,12 +721,37 @@ hipError_t dense_fill(double* x, int64_t N, int64_t Np, double v, hipStream_t s)
   return hipGetLastError();
 }
 
-hipError_t dense_gemm_bf16(int nprod, const __bf16* Kl, const __bf16* Xl, float* part, int64_t Np, int64_t Bp, int S,
-                           hipStream_t s) {
-  dim3 grid((unsigned)(Np / GBM), (unsigned)(Bp / GBN), (unsigned)S);
-  const int64_t kslice = Np / S;
-  if (nprod == 6) k_dense_gemm_bf16<3, 6><<<grid, GTHREADS, 0, s>>>(Kl, Xl, part, Np, Bp, kslice);
-  else k_dense_gemm_bf16<2, 3><<<grid, GTHREADS, 0, s>>>(Kl, Xl, part, Np, Bp, kslice);
+template <int RB, int CB, int D>
+static void launch_gemm_bf16(int nprod, const __bf16* Kl, const __bf16* Xl, float* part, int64_t Np, int64_t Bp, int B,
+                             int S, hipStream_t s) {
+  const int nrow = (int)(Np / (16 * RB)), ncol = (B + 16 * CB - 1) / (16 * CB), share = 8 / S;
+  const unsigned grid = 8u * (unsigned)ncol * (unsigned)((nrow + share - 1) / share);
+  if (nprod == 6) k_dense_gemm_bf16<3, 6, RB, CB, D><<<grid, 64, 0, s>>>(Kl, Xl, part, Np, Bp, S, nrow, ncol);
+  else k_dense_gemm_bf16<2, 3, RB, CB, D><<<grid, 64, 0, s>>>(Kl, Xl, part, Np, Bp, S, nrow, ncol);
+}
+
+// Columns past the last tile that holds a chain are neither computed nor read.
+// The tile is the one with the least estimated time per k-step: the rounds its
+// waves take on the chip's 1024 SIMDs (one wave each: the two large tiles hold
+// more than half the registers) times what one round was measured to take, us:
+// 4x4 1.38, 4x2 0.81, 2x2 0.59, 2x1 0.45 (with up to 512 waves: beyond, its loads
+// per product make it the slower one).  So a large tile, which reuses fragments
+// more often, is taken only where it fills the chip (us: 4096 sites x 256 chains
+// 4x4 44.0, 4x2 49.0; x 128 33.4, 26.0, 2x2 31.8; 4352 x 256 71.0, 67.0, 71.1;
+// 2048 x 128 4x2 10.9, 2x2 9.5; 1024 x 128 2x2 4.8, 2x1 5.2; x 20 4.4, 3.8).
+hipError_t dense_gemm_bf16(int nprod, const __bf16* Kl, const __bf16* Xl, float* part, int64_t Np, int64_t Bp, int B,
+                           int S, hipStream_t s) {
+  if (Np % 256 != 0 || Bp % 128 != 0 || B < 1 || B > Bp || (S != 1 && S != 2 && S != 4)) return hipErrorInvalidValue;
+  auto cost = [&](int rb, int cb, int64_t per_round, double us) {
+    const int64_t waves = Np / (16 * rb) * ((B + 16 * cb - 1) / (16 * cb)) * S;
+    return us * (double)((waves + per_round - 1) / per_round);
+  };
+  const double c44 = cost(4, 4, 1024, 1.38), c42 = cost(4, 2, 1024, 0.81), c22 = cost(2, 2, 1024, 0.59),
+               c21 = cost(2, 1, 512, 0.45);
+  if (c44 <= fmin(c42, fmin(c22, c21))) launch_gemm_bf16<4, 4, 3>(nprod, Kl, Xl, part, Np, Bp, B, S, s);
+  else if (c42 <= fmin(c22, c21)) launch_gemm_bf16<4, 2, 3>(nprod, Kl, Xl, part, Np, Bp, B, S, s);
+  else if (c22 <= c21) launch_gemm_bf16<2, 2, 3>(nprod, Kl, Xl, part, Np, Bp, B, S, s);
+  else launch_gemm_bf16<2, 1, 4>(nprod, Kl, Xl, part, Np, Bp, B, S, s);
   return hipGetLastError();
 }
 

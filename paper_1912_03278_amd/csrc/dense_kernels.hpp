@@ -29,8 +29,8 @@ hipError_t cg_step(const double* q, int64_t Np, double* x, double* r, double* d,
 hipError_t dense_dot(const double* a, const double* b, int64_t Np, double* out, hipStream_t s);
 hipError_t dense_fill(double* x, int64_t N, int64_t Np, double v, hipStream_t s);
 // Split-K BF16-limb MFMA GEMM: part[s][b][i] over S slices of k; nprod = 3 or 6.
-hipError_t dense_gemm_bf16(int nprod, const __bf16* Kl, const __bf16* Xl, float* part, int64_t Np, int64_t Bp, int S,
-                           hipStream_t s);
+hipError_t dense_gemm_bf16(int nprod, const __bf16* Kl, const __bf16* Xl, float* part, int64_t Np, int64_t Bp, int B,
+                           int S, hipStream_t s);
 // FP64 MFMA GEMM of K with the chains' stored fields (accepted field if measure,
 // else the proposal after pass j).
 hipError_t dense_gemm_f64(const double* K64, const ChainDev* chains, int j, int measure, double* U64, int64_t Np,

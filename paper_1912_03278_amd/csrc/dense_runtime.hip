@@ -463,9 +463,9 @@ int DenseChains::build(const ihmc_dense& md, int32_t n, const ihmc_run* runs, in
 // w, F = K W, then the pass epilogue (kick, drift, new limbs, kinetic sums).
 hipError_t DenseChains::enqueue_force(int mode, int j, hipStream_t s) {
   hipError_t e;
-  if ((e = dense_gemm_bf16(nprod, Kl, Xl, part, Np, Bp, S, s)) != hipSuccess) return e;
+  if ((e = dense_gemm_bf16(nprod, Kl, Xl, part, Np, Bp, B, S, s)) != hipSuccess) return e;
   if ((e = dense_epi_w(d_cd, B, Np, Bp, S, part, j, W32, Wl, s)) != hipSuccess) return e;
-  if ((e = dense_gemm_bf16(nprod, Kl, Wl, part, Np, Bp, S, s)) != hipSuccess) return e;
+  if ((e = dense_gemm_bf16(nprod, Kl, Wl, part, Np, Bp, B, S, s)) != hipSuccess) return e;
   return dense_epi_f(mode, d_cd, B, Np, Bp, S, part, W32, j, Xl, s);
 }
 
@@ -596,7 +596,7 @@ extern "C" int ihmc_dense_time(ihmc_dense_chains* ch, int32_t what, int32_t reps
   if (reps < 1) return set_error(IHMC_E_INVAL, "reps must be >= 1");
   hipStream_t s = ctx->stream;
   auto launch = [&]() -> hipError_t {
-    if (what == 0) return dense_gemm_bf16(d.nprod, d.Kl, d.Xl, d.part, d.Np, d.Bp, d.S, s);
+    if (what == 0) return dense_gemm_bf16(d.nprod, d.Kl, d.Xl, d.part, d.Np, d.Bp, d.B, d.S, s);
     if (what == 1) return dense_gemm_f64(d.K64, d.d_cd, 0, 1, d.U64, d.Np, d.B, s);
     hipError_t e = dense_prep(d.d_cd, d.B, d.Np, d.Bp, d.Xl, s);
     return e == hipSuccess ? d.enqueue_force(PASS_FORCE, 0, s) : e;
