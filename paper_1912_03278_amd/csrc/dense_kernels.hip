@@ -22,6 +22,8 @@
 // loads a fragment with one instruction as 1 KiB in a row and feeds it to the
 // matrix unit as it is.  Np is N padded to a multiple of 256, Bp is B padded to a
 // multiple of 128; padding is zero.
+#include <cfloat>
+
 #include "chain_epilogue.hpp"
 #include "dense_kernels.hpp"
 #include "device_common.hpp"
@@ -70,21 +72,45 @@ __global__ void k_dense_pad_K(const double* __restrict__ K, int64_t N, int64_t N
   K64[idx] = (i < N && k < N) ? K[i * N + k] : 0.0;
 }
 
-// y = K x + C x (FP64, one block of 256 threads per row; fixed-order reduction).
-// A set `stop` flag turns the launch into a no-op (converged iterative solve).
-__global__ __launch_bounds__(256) void k_dense_gemv(const double* __restrict__ K64, int64_t Np, double C,
-                                                    const double* __restrict__ x, double* __restrict__ y,
-                                                    const int* __restrict__ stop) {
-  __shared__ double sh[4];
-  if (stop && *stop) return;
-  const int64_t i = blockIdx.x;
-  const double* row = K64 + i * Np;
-  double s = 0.0;
-  for (int64_t k = threadIdx.x; k < Np; k += 256) s += row[k] * x[k];
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+// What the set-up demands of K (N x N): finite entries, symmetric to 1e-12 of the
+// largest.  chk[0] counts non-finite entries, chk[1] holds the bits of max |K|
+// (finite entries; the bits of non-negative doubles order as integers), chk[2]
+// counts pairs that differ; all zero before.  On the host the two sweeps took
+// 3.8 ms at N = 1000, half of the set-up.
+__global__ __launch_bounds__(256) void k_dense_check(const double* __restrict__ K, int64_t n,
+                                                     unsigned long long* __restrict__ chk) {
+  double mx = 0.0;
+  bool bad = false;
+  for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < n; i += 256ll * gridDim.x) {
+    const double v = fabs(K[i]);
+    if (v <= DBL_MAX) mx = fmax(mx, v);
+    else bad = true;
+  }
+  for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
+  __shared__ double sm[4];
+  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = mx;
+  const int any = __syncthreads_or(bad);
+  if (threadIdx.x == 0) {  // one atomic per block: they all meet at one address
+    atomicMax(chk + 1, (unsigned long long)__double_as_longlong(fmax(fmax(sm[0], sm[1]), fmax(sm[2], sm[3]))));
+    if (any) atomicAdd(chk, 1ull);
+  }
+}
+
+// 32 x 32 tiles above the diagonal (and on it) against their mirror images,
+// both read in rows and one turned in LDS
+__global__ __launch_bounds__(256) void k_dense_symmetry(const double* __restrict__ K, int64_t N,
+                                                        unsigned long long* __restrict__ chk) {
+  __shared__ double sm[32][33];
+  if (blockIdx.x < blockIdx.y) return;
+  const double tol = 1e-12 * __longlong_as_double((long long)chk[1]);
+  const int64_t r0 = blockIdx.y * 32ll, c0 = blockIdx.x * 32ll;
+  const int x = threadIdx.x & 31, y0 = threadIdx.x >> 5;
+  for (int y = y0; y < 32; y += 8) sm[y][x] = (c0 + y < N && r0 + x < N) ? K[(c0 + y) * N + r0 + x] : 0.0;
   __syncthreads();
-  if (threadIdx.x == 0) y[i] = ((sh[0] + sh[1]) + (sh[2] + sh[3])) + C * x[i];
+  bool bad = false;
+  for (int y = y0; y < 32; y += 8)
+    if (r0 + y < N && c0 + x < N) bad = bad || fabs(K[(r0 + y) * N + c0 + x] - sm[x][y]) > tol;
+  if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicAdd(chk + 2, 1ull);
 }
 
 // Fixed-order sum over a 1024-thread block, broadcast to every thread.
@@ -132,101 +158,200 @@ __global__ __launch_bounds__(1024) void k_lanczos_start(double* __restrict__ q0,
 }
 
 // Step k of Lanczos with full reorthogonalisation (classical Gram-Schmidt,
-// twice): w = K q_k on entry; alpha_k = q_k.w, w is orthogonalised against
-// q_0..q_k, beta_k = |w|, q_{k+1} = w / beta_k.  One block of 1024 threads.
+// twice): w = K q_k; alpha_k = q_k.w, w is orthogonalised against q_0..q_k,
+// beta_k = |w|, q_{k+1} = w / beta_k.  Three launches of lanczos_blocks(Np) blocks,
+// each with R = Np / blocks rows of its own; what a launch needs of all rows the
+// one before left as one partial sum per block:
+//   product  q_k = w / beta_{k-1} from the norm partials, w = K q_k, partials of Q^T w
+//   orth     w -= Q c with c from those partials; first time: partials of Q^T w
+//            again, second time: partials of |w|^2
+// Bound by the latency of three dependent launches (1000 sites: 6.6 + 7.9 + 7.9 us
+// a step, 4096: 30.6 + 12.8 + 12.8, means over the run); with the orthogonalisation
+// in one block, which read the basis through a single CU four times, a step took
+// 53 and 295 us.
 constexpr int kLanczosMax = 1024;
-__global__ __launch_bounds__(1024) void k_lanczos_orth(double* __restrict__ Q, int k, double* __restrict__ w,
-                                                       double* __restrict__ alpha, double* __restrict__ beta,
-                                                       int64_t Np) {
-  __shared__ double sc[kLanczosMax];
-  __shared__ double sh[16];
+
+__device__ __forceinline__ void lanczos_dots(const double* __restrict__ Q, const double* __restrict__ w, int64_t i0,
+                                             int R, int64_t Np, int k, double* __restrict__ P) {
+  const int e = threadIdx.x & 15;
+  for (int jj = threadIdx.x >> 4; jj <= k; jj += 64) {
+    const double* q = Q + (int64_t)jj * Np + i0;
+    double s = 0.0;
+    for (int i = e; i < R; i += 16) s += q[i] * w[i0 + i];
+    for (int off = 8; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (e == 0) P[jj] = s;
+  }
+}
+
+// u: w of the previous step (k > 0; other blocks read it, so w is another buffer)
+__global__ __launch_bounds__(1024) void k_lanczos_product(const double* __restrict__ K64, double* __restrict__ Q, int k,
+                                                          const double* __restrict__ u, double* __restrict__ w,
+                                                          const double* __restrict__ npart, double* __restrict__ ab,
+                                                          double* __restrict__ P, int pstride, int64_t Np, int R) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  double a = 0.0;
-  for (int pass = 0; pass < 2; ++pass) {
-    for (int jj = wave; jj <= k; jj += 16) {
-      const double* q = Q + (int64_t)jj * Np;
-      double s = 0.0;
-      for (int64_t i = lane; i < Np; i += 64) s += q[i] * w[i];
-      for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-      if (lane == 0) sc[jj] = s;
+  const int64_t i0 = (int64_t)blockIdx.x * R;
+  double* qk = Q + (int64_t)k * Np;
+  double inv = 1.0;
+  if (k == 0) {
+    u = Q;
+  } else {
+    double ss = 0.0;
+    for (int b = lane; b < (int)gridDim.x; b += 64) ss += npart[b];
+    for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
+    const double bk = sqrt(ss);
+    inv = bk > 0.0 ? 1.0 / bk : 0.0;
+    for (int i = threadIdx.x; i < R; i += 1024) qk[i0 + i] = u[i0 + i] * inv;
+    if (blockIdx.x == 0 && threadIdx.x == 0) ab[2 * (k - 1) + 1] = bk;
+  }
+  for (int r = wave; r < R; r += 16) {
+    const double* row = K64 + (i0 + r) * Np;
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll 4
+    for (int64_t c = 2 * lane; c < Np; c += 128) {
+      const double2 kv = *reinterpret_cast<const double2*>(row + c), uv = *reinterpret_cast<const double2*>(u + c);
+      s0 += kv.x * (uv.x * inv);
+      s1 += kv.y * (uv.y * inv);
     }
+    double s = s0 + s1;
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane == 0) w[i0 + r] = s;
+  }
+  __syncthreads();  // the block's rows of w and q_k
+  lanczos_dots(Q, w, i0, R, Np, k, P + (int64_t)blockIdx.x * pstride);
+}
+
+template <bool FIRST>
+__global__ __launch_bounds__(1024) void k_lanczos_orth(const double* __restrict__ Q, int k, double* __restrict__ w,
+                                                       const double* __restrict__ P, double* __restrict__ Pnext,
+                                                       int pstride, double* __restrict__ npart, double* __restrict__ ab,
+                                                       int64_t Np, int R) {
+  __shared__ double sc[kLanczosMax], sq[4][256], red[16][16];
+  const int t = threadIdx.x, wave = t >> 6, nb4 = (int)gridDim.x >> 2;
+  const int64_t i0 = (int64_t)blockIdx.x * R;
+  for (int j0 = 0; j0 <= k; j0 += 256) {  // c: a quarter of the blocks' partials per 256 threads
+    const int q = t >> 8, jj = j0 + (t & 255);
+    double s = 0.0;
+    if (jj <= k)
+      for (int b = q * nb4; b < (q + 1) * nb4; ++b) s += P[(int64_t)b * pstride + jj];
+    sq[q][t & 255] = s;
     __syncthreads();
-    a += sc[k];
-    for (int64_t i = threadIdx.x; i < Np; i += 1024) {
-      double s = 0.0;
-      for (int jj = 0; jj <= k; ++jj) s += sc[jj] * Q[(int64_t)jj * Np + i];
-      w[i] -= s;
+    if (q == 0 && jj <= k) sc[jj] = (sq[0][t] + sq[1][t]) + (sq[2][t] + sq[3][t]);
+    __syncthreads();
+  }
+  if (blockIdx.x == 0 && t == 0) ab[2 * k] = FIRST ? sc[k] : ab[2 * k] + sc[k];
+  const int e = t & 15;
+  for (int i = e; i - e < R; i += 16) {  // 64 groups of 16 threads share the basis vectors
+    double s = 0.0;
+    if (i < R)
+      for (int jj = t >> 4; jj <= k; jj += 64) s += sc[jj] * Q[(int64_t)jj * Np + i0 + i];
+    s += __shfl_xor(s, 16, 64);
+    s += __shfl_xor(s, 32, 64);
+    if ((t & 63) < 16) red[wave][e] = s;
+    __syncthreads();
+    if (t < 16 && i < R) {
+      double d = 0.0;
+      for (int g = 0; g < 16; ++g) d += red[g][t];
+      w[i0 + i] -= d;
     }
     __syncthreads();
   }
-  double ss = 0.0;
-  for (int64_t i = threadIdx.x; i < Np; i += 1024) ss += w[i] * w[i];
-  ss = block_sum_1024(ss, sh);
-  const double bk = sqrt(ss);
-  const double inv = bk > 0.0 ? 1.0 / bk : 0.0;
-  double* qn = Q + (int64_t)(k + 1) * Np;
-  for (int64_t i = threadIdx.x; i < Np; i += 1024) qn[i] = w[i] * inv;
-  if (threadIdx.x == 0) {
-    alpha[k] = a;
-    beta[k] = bk;
+  if (FIRST) {
+    lanczos_dots(Q, w, i0, R, Np, k, Pnext + (int64_t)blockIdx.x * pstride);
+  } else {
+    double ss = 0.0;
+    for (int i = t; i < R; i += 1024) ss += w[i0 + i] * w[i0 + i];
+    ss = block_sum_1024(ss, red[0]);
+    if (t == 0) npart[blockIdx.x] = ss;
   }
 }
 
 // ---- conjugate gradients (Kt x = rhs, FP64) ---------------------------------
 //
+// One or two right-hand sides side by side, each with its own vectors and scalars
+// (the iteration is bound by launches and latency, not by K: two share them).
 // scal[0] = r.r, scal[1] = stopping threshold, scal[2] = r.r at the start;
-// it[0] counts iterations, it[1] is the stop flag read by the GEMV (1: converged,
-// 2: a direction of non-positive curvature, i.e. Kt is not positive definite).
-__global__ __launch_bounds__(1024) void k_cg_init(const double* __restrict__ rhs, int64_t Np, double rel_tol,
-                                                  double* __restrict__ x, double* __restrict__ r,
-                                                  double* __restrict__ d, double* __restrict__ scal,
-                                                  int* __restrict__ it) {
+// it[0] counts iterations, it[1] is the stop flag (1: converged, 2: a direction
+// of non-positive curvature, i.e. Kt is not positive definite).
+__global__ __launch_bounds__(1024) void k_cg_init(CgPair sys, int64_t Np, double rel_tol) {
   __shared__ double sh[16];
+  const CgSystem& c = sys.s[blockIdx.x];
   double ss = 0.0;
   for (int64_t i = threadIdx.x; i < Np; i += 1024) {
-    const double v = rhs[i];
-    x[i] = 0.0;
-    r[i] = v;
-    d[i] = v;
+    const double v = c.rhs[i];
+    c.x[i] = 0.0;
+    c.r[i] = v;
+    c.d[i] = v;
     ss += v * v;
   }
   ss = block_sum_1024(ss, sh);
   if (threadIdx.x == 0) {
-    scal[0] = ss;
-    scal[1] = rel_tol * rel_tol * ss;
-    scal[2] = ss;
-    it[0] = 0;
-    it[1] = (ss == 0.0) ? 1 : 0;
+    c.scal[0] = ss;
+    c.scal[1] = rel_tol * rel_tol * ss;
+    c.scal[2] = ss;
+    c.it[0] = 0;
+    c.it[1] = (ss == 0.0) ? 1 : 0;
   }
 }
 
-__global__ __launch_bounds__(1024) void k_cg_step(const double* __restrict__ q, int64_t Np, double* __restrict__ x,
-                                                  double* __restrict__ r, double* __restrict__ d,
-                                                  double* __restrict__ scal, int* __restrict__ it) {
+// q = K d + C d of the systems that still run: one block of 256 threads per row,
+// fixed-order reduction.
+template <int NSYS>
+__global__ __launch_bounds__(256) void k_cg_product(CgPair sys, const double* __restrict__ K64, int64_t Np, double C) {
+  __shared__ double sh[NSYS][4];
+  bool run[NSYS], any = false;
+#pragma unroll
+  for (int y = 0; y < NSYS; ++y) {
+    run[y] = sys.s[y].it[1] == 0;
+    any = any || run[y];
+  }
+  if (!any) return;
+  const int64_t i = blockIdx.x;
+  const double* row = K64 + i * Np;
+  double s[NSYS] = {};
+  for (int64_t k = threadIdx.x; k < Np; k += 256) {
+    const double v = row[k];
+#pragma unroll
+    for (int y = 0; y < NSYS; ++y) s[y] += v * sys.s[y].d[k];
+  }
+#pragma unroll
+  for (int y = 0; y < NSYS; ++y) {
+    for (int off = 32; off > 0; off >>= 1) s[y] += __shfl_xor(s[y], off, 64);
+    if ((threadIdx.x & 63) == 0) sh[y][threadIdx.x >> 6] = s[y];
+  }
+  __syncthreads();
+  const int y = threadIdx.x;
+  if (y < NSYS && run[y]) {
+    const CgSystem& c = sys.s[y];
+    c.q[i] = ((sh[y][0] + sh[y][1]) + (sh[y][2] + sh[y][3])) + C * c.d[i];
+  }
+}
+
+__global__ __launch_bounds__(1024) void k_cg_step(CgPair sys, int64_t Np) {
   __shared__ double sh[16];
-  if (it[1]) return;
-  const double rr = scal[0];
+  const CgSystem& c = sys.s[blockIdx.x];
+  if (c.it[1]) return;
+  const double rr = c.scal[0];
   double dq = 0.0;
-  for (int64_t i = threadIdx.x; i < Np; i += 1024) dq += d[i] * q[i];
+  for (int64_t i = threadIdx.x; i < Np; i += 1024) dq += c.d[i] * c.q[i];
   dq = block_sum_1024(dq, sh);
   if (!(dq > 0.0)) {  // Kt not positive definite along d (or non-finite)
-    if (threadIdx.x == 0) it[1] = 2;
+    if (threadIdx.x == 0) c.it[1] = 2;
     return;
   }
   const double alpha = rr / dq;
   double rn = 0.0;
   for (int64_t i = threadIdx.x; i < Np; i += 1024) {
-    x[i] += alpha * d[i];
-    r[i] -= alpha * q[i];
-    rn += r[i] * r[i];
+    c.x[i] += alpha * c.d[i];
+    c.r[i] -= alpha * c.q[i];
+    rn += c.r[i] * c.r[i];
   }
   rn = block_sum_1024(rn, sh);
   const double bt = rn / rr;
-  for (int64_t i = threadIdx.x; i < Np; i += 1024) d[i] = r[i] + bt * d[i];
+  for (int64_t i = threadIdx.x; i < Np; i += 1024) c.d[i] = c.r[i] + bt * c.d[i];
   if (threadIdx.x == 0) {
-    scal[0] = rn;
-    it[0] += 1;
-    if (!(rn > scal[1])) it[1] = 1;
+    c.scal[0] = rn;
+    c.it[0] += 1;
+    if (!(rn > c.scal[1])) c.it[1] = 1;
   }
 }
 
@@ -668,17 +793,21 @@ __global__ __launch_bounds__(EPI_THREADS) void k_dense_h(const ChainDev* __restr
 
 // ------------------------------------------------------------------ launch ---
 
-hipError_t dense_split_K(const double* K, int64_t N, int64_t Np, __bf16* Kl, double* K64, hipStream_t s) {
-  const int64_t n = Np * Np;
-  const unsigned g = (unsigned)((n + 255) / 256);
-  k_dense_split_K<<<g, 256, 0, s>>>(K, N, Np, Kl);
-  k_dense_pad_K<<<g, 256, 0, s>>>(K, N, Np, K64);
+hipError_t dense_split_K(const double* K, int64_t N, int64_t Np, __bf16* Kl, hipStream_t s) {
+  k_dense_split_K<<<(unsigned)((Np * Np + 255) / 256), 256, 0, s>>>(K, N, Np, Kl);
   return hipGetLastError();
 }
 
-hipError_t dense_gemv(const double* K64, int64_t Np, double C, const double* x, double* y, const int* stop,
-                      hipStream_t s) {
-  k_dense_gemv<<<(unsigned)Np, 256, 0, s>>>(K64, Np, C, x, y, stop);
+hipError_t dense_pad_K(const double* K, int64_t N, int64_t Np, double* K64, hipStream_t s) {
+  k_dense_pad_K<<<(unsigned)((Np * Np + 255) / 256), 256, 0, s>>>(K, N, Np, K64);
+  return hipGetLastError();
+}
+
+hipError_t dense_check(const double* K, int64_t N, unsigned long long* chk, hipStream_t s) {
+  const int64_t n = N * N;
+  const unsigned tiles = (unsigned)((N + 31) / 32);
+  k_dense_check<<<(unsigned)(n / 4096 < 512 ? n / 4096 + 1 : 512), 256, 0, s>>>(K, n, chk);
+  k_dense_symmetry<<<dim3(tiles, tiles), 256, 0, s>>>(K, N, chk);
   return hipGetLastError();
 }
 
@@ -693,21 +822,45 @@ hipError_t lanczos_start(double* q0, int64_t N, int64_t Np, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t lanczos_orth(double* Q, int k, double* w, double* alpha, double* beta, int64_t Np, hipStream_t s) {
-  if (k < 0 || k >= kLanczosMax) return hipErrorInvalidValue;
-  k_lanczos_orth<<<1, 1024, 0, s>>>(Q, k, w, alpha, beta, Np);
+// Blocks of a Lanczos step: 16 rows each while that gives no more than 128, whose
+// partials every block sums again.
+static int lanczos_blocks(int64_t Np) { return (int)(Np / 16 < 128 ? Np / 16 : 128); }
+
+uint64_t lanczos_work_doubles(int64_t Np, int mmax) {
+  return 2 * (uint64_t)Np + 128 + 2 * (uint64_t)(mmax + 1) + 2 * (uint64_t)lanczos_blocks(Np) * (uint64_t)(mmax + 1);
+}
+
+hipError_t lanczos_step(const double* K64, double* Q, int k, const LanczosWork& lw, int64_t Np, hipStream_t s) {
+  if (k < 0 || k >= kLanczosMax || k >= lw.mmax) return hipErrorInvalidValue;
+  const int nb = lanczos_blocks(Np), R = (int)(Np / nb), ps = lw.mmax + 1;
+  double *w = lw.w[k & 1], *P2 = lw.P + (int64_t)nb * ps;
+  k_lanczos_product<<<nb, 1024, 0, s>>>(K64, Q, k, lw.w[(k & 1) ^ 1], w, lw.npart, lw.ab, lw.P, ps, Np, R);
+  k_lanczos_orth<true><<<nb, 1024, 0, s>>>(Q, k, w, lw.P, P2, ps, lw.npart, lw.ab, Np, R);
+  k_lanczos_orth<false><<<nb, 1024, 0, s>>>(Q, k, w, P2, lw.P, ps, lw.npart, lw.ab, Np, R);
   return hipGetLastError();
 }
 
-hipError_t cg_init(const double* rhs, int64_t Np, double rel_tol, double* x, double* r, double* d, double* scal,
-                   int* it, hipStream_t s) {
-  k_cg_init<<<1, 1024, 0, s>>>(rhs, Np, rel_tol, x, r, d, scal, it);
+LanczosWork lanczos_work(double* mem, int64_t Np, int mmax) {
+  LanczosWork lw;
+  lw.npart = mem;
+  lw.n_npart = lanczos_blocks(Np);
+  lw.ab = lw.npart + 128;
+  lw.w[0] = lw.ab + 2 * (int64_t)(mmax + 1);
+  lw.w[1] = lw.w[0] + Np;
+  lw.P = lw.w[1] + Np;
+  lw.mmax = mmax;
+  return lw;
+}
+
+hipError_t cg_init(const CgPair& sys, int nsys, int64_t Np, double rel_tol, hipStream_t s) {
+  k_cg_init<<<nsys, 1024, 0, s>>>(sys, Np, rel_tol);
   return hipGetLastError();
 }
 
-hipError_t cg_step(const double* q, int64_t Np, double* x, double* r, double* d, double* scal, int* it,
-                   hipStream_t s) {
-  k_cg_step<<<1, 1024, 0, s>>>(q, Np, x, r, d, scal, it);
+hipError_t cg_iterate(const CgPair& sys, int nsys, const double* K64, int64_t Np, double C, hipStream_t s) {
+  if (nsys == 2) k_cg_product<2><<<(unsigned)Np, 256, 0, s>>>(sys, K64, Np, C);
+  else k_cg_product<1><<<(unsigned)Np, 256, 0, s>>>(sys, K64, Np, C);
+  k_cg_step<<<nsys, 1024, 0, s>>>(sys, Np);
   return hipGetLastError();
 }
 

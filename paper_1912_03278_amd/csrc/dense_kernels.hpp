@@ -8,24 +8,40 @@
 
 namespace ihmc {
 
-// K (FP64, N x N, row-major) -> three BF16 limbs and a zero-padded FP64 copy (Np x Np).
-hipError_t dense_split_K(const double* K, int64_t N, int64_t Np, __bf16* Kl, double* K64, hipStream_t s);
-// y = K x + C x in FP64 (padded length Np); a no-op once *stop is set (stop may be null).
-hipError_t dense_gemv(const double* K64, int64_t Np, double C, const double* x, double* y, const int* stop,
-                      hipStream_t s);
+// K (FP64, N x N, row-major) -> three BF16 limbs, and a zero-padded FP64 copy (Np x Np).
+hipError_t dense_split_K(const double* K, int64_t N, int64_t Np, __bf16* Kl, hipStream_t s);
+hipError_t dense_pad_K(const double* K, int64_t N, int64_t Np, double* K64, hipStream_t s);
+// Entries of K: chk[0] non-finite ones found, chk[1] bits of the largest |K|, chk[2]
+// pairs found that differ by more than 1e-12 of it (chk zero before).
+hipError_t dense_check(const double* K, int64_t N, unsigned long long* chk, hipStream_t s);
 // h' = beta h (FP64) and h'/sqrt(J') (FP32) over the padded length.
 hipError_t dense_field(const double* h, int64_t N, int64_t Np, double beta, double sqJ, double* hp, float* b,
                        hipStream_t s);
-// Lanczos with full reorthogonalisation: normalised start vector, and step k
-// (w = K q_k on entry; writes alpha[k], beta[k] and q_{k+1} = Q[k+1]).
+// Lanczos with full reorthogonalisation: normalised start vector q_0 = Q[0], and
+// step k, which writes q_k = Q[k] (k > 0), alpha_k = ab[2k], beta_{k-1} = ab[2k - 1]
+// and the n_npart partial sums of beta_k^2.
 constexpr int kLanczosMaxSteps = 1023;
+struct LanczosWork {
+  double *npart, *ab;  // npart[128], then ab[2 (mmax + 1)]
+  double *w[2], *P;
+  int n_npart, mmax;
+};
+uint64_t lanczos_work_doubles(int64_t Np, int mmax);
+LanczosWork lanczos_work(double* mem, int64_t Np, int mmax);
 hipError_t lanczos_start(double* q0, int64_t N, int64_t Np, hipStream_t s);
-hipError_t lanczos_orth(double* Q, int k, double* w, double* alpha, double* beta, int64_t Np, hipStream_t s);
-// Conjugate gradients on Kt (scal[0] = r.r, scal[1] = threshold; it[0] steps, it[1] stop flag).
-hipError_t cg_init(const double* rhs, int64_t Np, double rel_tol, double* x, double* r, double* d, double* scal,
-                   int* it, hipStream_t s);
-hipError_t cg_step(const double* q, int64_t Np, double* x, double* r, double* d, double* scal, int* it,
-                   hipStream_t s);
+hipError_t lanczos_step(const double* K64, double* Q, int k, const LanczosWork& lw, int64_t Np, hipStream_t s);
+// Conjugate gradients on Kt, one or two right-hand sides (scal[0] = r.r, scal[1] =
+// threshold, scal[2] = r.r at the start; it[0] steps, it[1] stop flag).
+struct CgSystem {
+  const double* rhs;
+  double *x, *r, *d, *q, *scal;
+  int* it;
+};
+struct CgPair {
+  CgSystem s[2];
+};
+hipError_t cg_init(const CgPair& sys, int nsys, int64_t Np, double rel_tol, hipStream_t s);
+hipError_t cg_iterate(const CgPair& sys, int nsys, const double* K64, int64_t Np, double C, hipStream_t s);
 hipError_t dense_dot(const double* a, const double* b, int64_t Np, double* out, hipStream_t s);
 hipError_t dense_fill(double* x, int64_t N, int64_t Np, double v, hipStream_t s);
 // Split-K BF16-limb MFMA GEMM: part[s][b][i] over S slices of k; nprod = 3 or 6.

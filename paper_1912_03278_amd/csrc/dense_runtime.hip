@@ -74,43 +74,56 @@ static void tridiag_min(const std::vector<double>& a, const std::vector<double>&
   *last = std::fabs(x[m - 1]);
 }
 
+// Scratch of lanczos_min: what dense_check found, then the Lanczos work space.
+constexpr int kCheckWords = 4;
+static uint64_t setup_scratch_doubles(int64_t N, int64_t Np) {
+  return kCheckWords + lanczos_work_doubles(Np, (int)std::min<int64_t>(N, kLanczosMaxSteps));
+}
+
 // FP64 Lanczos on the padded device matrix K64 (zero shift), with full
 // reorthogonalisation.  Stops when the Ritz residual |r| = beta_m |s_m| of the
 // lowest Ritz value falls below 1e-10 (|theta| + 1), at an invariant subspace,
-// or after min(N, kLanczosMaxSteps) steps.
-static int lanczos_min(ihmc_ctx* ctx, const double* K64, int64_t N, int64_t Np, double* theta, double* resid,
-                       int* steps) {
+// or after min(N, kLanczosMaxSteps) steps; with an error if the check of K's
+// entries, which comes back with the first steps, found any that may not be.
+static int lanczos_min(ihmc_ctx* ctx, const double* K64, int64_t N, int64_t Np, double* scratch, double* theta,
+                       double* resid, int* steps) {
   hipStream_t s = ctx->stream;
   const int mmax = (int)std::min<int64_t>(N, kLanczosMaxSteps);
-  double* Q = (double*)ctx->arena.alloc(8 * (uint64_t)Np * (mmax + 1));
-  double* w = (double*)ctx->arena.alloc(8 * (uint64_t)Np);
-  double* ab = (double*)ctx->arena.alloc(8 * 2 * (uint64_t)(mmax + 1));
+  const LanczosWork lw = lanczos_work(scratch + kCheckWords, Np, mmax);
+  double* Q = (double*)ctx->arena.alloc(8 * (uint64_t)Np * mmax);
   auto release = [&]() {
     hipStreamSynchronize(s);
     if (Q) ctx->arena.release(Q);
-    if (w) ctx->arena.release(w);
-    if (ab) ctx->arena.release(ab);
   };
-  if (!Q || !w || !ab) {
-    release();
-    return set_error(IHMC_E_NOMEM, "arena exhausted (Lanczos basis of %d vectors)", mmax + 1);
-  }
+  if (!Q) return set_error(IHMC_E_NOMEM, "arena exhausted (Lanczos basis of %d vectors)", mmax);
   hipError_t e = lanczos_start(Q, N, Np, s);
-  std::vector<double> a(mmax + 1), b(mmax + 1);
+  const int head = kCheckWords + 128;  // check words and norm partials lie before alpha and beta
+  std::vector<double> back(head + 2 * (mmax + 1)), a(mmax + 1), b(mmax + 1);
+  bool refused = false;
   int m = 0;
   double th = 0.0, res = 0.0;
   const int chunk = 16;
   while (e == hipSuccess && m < mmax) {
     const int m_end = std::min(mmax, m + chunk);
-    for (int k = m; k < m_end && e == hipSuccess; ++k) {
-      e = dense_gemv(K64, Np, 0.0, Q + (int64_t)k * Np, w, nullptr, s);
-      if (e == hipSuccess) e = lanczos_orth(Q, k, w, ab, ab + (mmax + 1), Np, s);
-    }
+    for (int k = m; k < m_end && e == hipSuccess; ++k) e = lanczos_step(K64, Q, k, lw, Np, s);
     if (e != hipSuccess) break;
-    if ((e = hipMemcpyAsync(a.data(), ab, 8 * (size_t)m_end, hipMemcpyDeviceToHost, s)) != hipSuccess) break;
-    if ((e = hipMemcpyAsync(b.data(), ab + (mmax + 1), 8 * (size_t)m_end, hipMemcpyDeviceToHost, s)) != hipSuccess)
+    if ((e = hipMemcpyAsync(back.data(), scratch, 8 * (size_t)(head + 2 * m_end), hipMemcpyDeviceToHost, s)) !=
+        hipSuccess)
       break;
     if ((e = hipStreamSynchronize(s)) != hipSuccess) break;
+    uint64_t chk[3];
+    std::memcpy(chk, back.data(), sizeof chk);
+    if (chk[0] || chk[2]) {
+      refused = true;
+      break;
+    }
+    double ss = 0.0;  // beta of the last step; the others are on the device
+    for (int i = 0; i < lw.n_npart; ++i) ss += back[kCheckWords + i];
+    back[head + 2 * (m_end - 1) + 1] = std::sqrt(ss);
+    for (int k = 0; k < m_end; ++k) {
+      a[k] = back[head + 2 * k];
+      b[k] = back[head + 2 * k + 1];
+    }
     m = m_end;
     double last = 0.0;
     tridiag_min(a, b, m, &th, &last);
@@ -129,6 +142,7 @@ static int lanczos_min(ihmc_ctx* ctx, const double* K64, int64_t N, int64_t Np, 
   }
   release();
   if (e != hipSuccess) return hip_fail(ctx, e, "Lanczos");
+  if (refused) return set_error(IHMC_E_INVAL, "dense: K is not symmetric or has a non-finite entry");
   if (!std::isfinite(th) || !std::isfinite(res)) return set_error(IHMC_E_INVAL, "K: Lanczos did not converge");
   *theta = th;
   *resid = res;
@@ -136,31 +150,37 @@ static int lanczos_min(ihmc_ctx* ctx, const double* K64, int64_t N, int64_t Np, 
   return IHMC_OK;
 }
 
-// x = Kt^-1 rhs by CG on the device (FP64; relative residual 1e-13, or at
-// least 1e-9 when the iteration limit is reached first).
-static int cg_solve(ihmc_ctx* ctx, const double* K64, int64_t N, int64_t Np, double C, const double* rhs, double* x,
-                    double* work, int* iters) {
+// x = Kt^-1 rhs by CG on the device for one or two right-hand sides (FP64;
+// relative residual 1e-13, or at least 1e-9 when the iteration limit is reached
+// first).  work: nsys (3 Np + 8) doubles.
+static int cg_solve(ihmc_ctx* ctx, const double* K64, int64_t N, int64_t Np, double C, int nsys,
+                    const double* const* rhs, double* const* x, double* work, int* iters) {
   hipStream_t s = ctx->stream;
-  double *r = work, *d = work + Np, *q = work + 2 * Np, *scal = work + 3 * Np;
-  int* it = (int*)(scal + 4);
-  HIPCHK(cg_init(rhs, Np, 1e-13, x, r, d, scal, it, s), "CG init");
+  CgPair sys{};
+  double* status = work;  // 8 doubles per system: scal[3], then it[2]
+  double* vec = work + 8 * nsys;
+  for (int y = 0; y < nsys; ++y, vec += 3 * Np)
+    sys.s[y] = CgSystem{rhs[y],           x[y], vec, vec + Np, vec + 2 * Np, status + 8 * y, (int*)(status + 8 * y + 4)};
+  HIPCHK(cg_init(sys, nsys, Np, 1e-13, s), "CG init");
   const int max_it = (int)std::min<int64_t>(20000, 20 * N + 100);
-  int host_it[2] = {0, 0};
+  double back[16];
+  int it[2][2] = {};
   for (int done = 0; done < max_it; done += 32) {
-    for (int k = 0; k < 32; ++k) {
-      HIPCHK(dense_gemv(K64, Np, C, d, q, it + 1, s), "CG product");
-      HIPCHK(cg_step(q, Np, x, r, d, scal, it, s), "CG step");
-    }
-    HIPCHK(hipMemcpyAsync(host_it, it, sizeof host_it, hipMemcpyDeviceToHost, s), "CG status");
+    for (int k = 0; k < 32; ++k) HIPCHK(cg_iterate(sys, nsys, K64, Np, C, s), "CG iteration");
+    HIPCHK(hipMemcpyAsync(back, status, 64 * (size_t)nsys, hipMemcpyDeviceToHost, s), "CG status");
     HIPCHK(hipStreamSynchronize(s), "CG sync");
-    if (host_it[1]) break;
+    bool run = false;
+    for (int y = 0; y < nsys; ++y) {
+      std::memcpy(it[y], back + 8 * y + 4, sizeof it[y]);
+      run = run || it[y][1] == 0;
+    }
+    if (!run) break;
   }
-  *iters = host_it[0];
-  if (host_it[1] == 2) return set_error(IHMC_E_INVAL, "dense: K + C*1 is not positive definite (CG curvature <= 0)");
-  if (host_it[1] == 0) {
-    double sc[3];
-    HIPCHK(hipMemcpy(sc, scal, sizeof sc, hipMemcpyDeviceToHost), "CG residual");
-    if (!(sc[0] <= 1e-18 * sc[2]))
+  *iters = 0;
+  for (int y = 0; y < nsys; ++y) {
+    *iters = std::max(*iters, it[y][0]);
+    if (it[y][1] == 2) return set_error(IHMC_E_INVAL, "dense: K + C*1 is not positive definite (CG curvature <= 0)");
+    if (it[y][1] == 0 && !(back[8 * y] <= 1e-18 * back[8 * y + 2]))
       return set_error(IHMC_E_INVAL, "dense: CG on K + C*1 did not converge in %d steps", max_it);
   }
   return IHMC_OK;
@@ -170,6 +190,7 @@ struct DenseChains {
   ihmc_ctx* ctx = nullptr;
   int B = 0;
   int64_t N = 0, Np = 0, Bp = 0;
+  bool auto_shift = false;  // C from the lowest Ritz value
   int S = 1, nprod = 6, n_pass = 0;
   std::vector<ChainDev> cd;
   ChainDev* d_cd = nullptr;
@@ -201,11 +222,13 @@ struct DenseChains {
     for (void* p : allocs) ctx->arena.release(p);
   }
   int build(const ihmc_dense& md, int32_t n, const ihmc_run* runs, int32_t products);
+  int build_model(const ihmc_dense& md, int32_t n, const ihmc_run* runs, int32_t products);
   hipError_t enqueue_force(int mode, int j, hipStream_t s);
   hipError_t enqueue_round(hipStream_t s);
   int advance(int32_t n_traj);
 };
 
+// All but K's entries, which the device looks at (dense_check).
 static int validate_dense(const ihmc_dense& m) {
   if (m.N < 1) return set_error(IHMC_E_INVAL, "dense: N must be >= 1");
   if (!m.K) return set_error(IHMC_E_INVAL, "dense: K is NULL");
@@ -217,6 +240,11 @@ static int validate_dense(const ihmc_dense& m) {
   if (m.h_len > 0 && !m.h) return set_error(IHMC_E_INVAL, "dense: h is NULL");
   for (int64_t i = 0; i < m.h_len; ++i)
     if (!std::isfinite(m.h[i])) return set_error(IHMC_E_INVAL, "dense: h[%lld] is not finite", (long long)i);
+  return IHMC_OK;
+}
+
+// K's entries on the host, to name the first that may not be.
+static int validate_entries(const ihmc_dense& m) {
   const int64_t N = m.N;
   double kmax = 0.0;
   for (int64_t i = 0; i < N * N; ++i) {
@@ -230,9 +258,19 @@ static int validate_dense(const ihmc_dense& m) {
   return IHMC_OK;
 }
 
+// An entry of K that may not be is reported before anything else that stands in
+// the way, so K is searched for one before another failure goes out.
 int DenseChains::build(const ihmc_dense& md, int32_t n, const ihmc_run* runs, int32_t products) {
   int rc = validate_dense(md);
   if (rc) return rc;
+  rc = build_model(md, n, runs, products);
+  if (rc == IHMC_OK) return rc;
+  const int bad = validate_entries(md);
+  return bad ? bad : rc;
+}
+
+int DenseChains::build_model(const ihmc_dense& md, int32_t n, const ihmc_run* runs, int32_t products) {
+  int rc = IHMC_OK;
   if (products == 0) products = 6;
   if (products != 3 && products != 6) return set_error(IHMC_E_INVAL, "products must be 3 or 6");
   nprod = products;
@@ -287,7 +325,9 @@ int DenseChains::build(const ihmc_dense& md, int32_t n, const ihmc_run* runs, in
                      (unsigned long long)ctx->arena.used, (unsigned long long)ctx->arena.size);
   };
 
-  // ---- K: FP64 padded copy and BF16 limbs
+  // ---- K: FP64 padded copy and BF16 limbs.  The partials of the GEMM serve as the
+  // set-up's scratch (at least S * 128 * Np floats, against about 256 (mmax + 1) + 2 Np
+  // doubles of Lanczos with mmax < 1024 and 6 Np of the conjugate gradients).
   K64 = (double*)dalloc(8 * (uint64_t)(Np * Np));
   Kl = (__bf16*)dalloc(2 * 3 * (uint64_t)(Np * Np));
   Xl = (__bf16*)dalloc(2 * 3 * (uint64_t)(Bp * Np));
@@ -296,22 +336,30 @@ int DenseChains::build(const ihmc_dense& md, int32_t n, const ihmc_run* runs, in
   part = (float*)dalloc(4 * (uint64_t)S * (uint64_t)(Bp * Np));
   U64 = (double*)dalloc(8 * (uint64_t)B * (uint64_t)Np);
   if (!K64 || !Kl || !Xl || !Wl || !W32 || !part || !U64) return nomem("dense operands");
+  if (std::max<uint64_t>(setup_scratch_doubles(N, Np), 6 * (uint64_t)Np + 16) * 2 > (uint64_t)S * (uint64_t)(Bp * Np)) {
+    cleanup();
+    return set_error(IHMC_E_NOMEM, "dense: set-up scratch too small");
+  }
   HIPCHK(hipMemsetAsync(Xl, 0, 2 * 3 * (size_t)(Bp * Np), s), "clear limbs");
   HIPCHK(hipMemsetAsync(Wl, 0, 2 * 3 * (size_t)(Bp * Np), s), "clear limbs");
   {
     double* Kh = (double*)tmp_alloc(8 * (uint64_t)(N * N));
     if (!Kh) return nomem("K staging");
     HIPCHK(hipMemcpyAsync(Kh, md.K, 8 * (size_t)(N * N), hipMemcpyHostToDevice, s), "K upload");
-    HIPCHK(dense_split_K(Kh, N, Np, Kl, K64, s), "K limbs");
+    HIPCHK(hipMemsetAsync(part, 0, 8 * kCheckWords, s), "clear check");
+    HIPCHK(dense_check(Kh, N, (unsigned long long*)part, s), "K check");
+    HIPCHK(dense_split_K(Kh, N, Np, Kl, s), "K limbs");
+    HIPCHK(dense_pad_K(Kh, N, Np, K64, s), "K copy");
   }
 
   // ---- shift: Lanczos for the lowest eigenvalue of K
-  rc = lanczos_min(ctx, K64, N, Np, &theta, &resid, &lanczos_steps);
+  rc = lanczos_min(ctx, K64, N, Np, (double*)part, &theta, &resid, &lanczos_steps);
   if (rc) {
     cleanup();
     return rc;
   }
-  if (md.C < 0.0) {
+  auto_shift = md.C < 0.0;
+  if (auto_shift) {
     C = -(theta - resid) + 0.1;
   } else {
     C = md.C;
@@ -387,33 +435,27 @@ int DenseChains::build(const ihmc_dense& md, int32_t n, const ihmc_run* runs, in
 
   // ---- estimator constants: g = Kt^-1 1, and Kt^-1 h' for a per-site field
   {
-    double* work = (double*)tmp_alloc(8 * (uint64_t)(4 * Np + 8));
     double* ones = (double*)tmp_alloc(8 * (uint64_t)Np);
     double* g = (double*)tmp_alloc(8 * (uint64_t)Np);
     double* xh = (double*)tmp_alloc(8 * (uint64_t)Np);
     double* dots = (double*)tmp_alloc(8 * 4);
-    if (!work || !ones || !g || !xh || !dots) return nomem("CG work space");
+    if (!ones || !g || !xh || !dots) return nomem("CG work space");
     HIPCHK(dense_fill(ones, N, Np, 1.0, s), "ones");
-    int it1 = 0, it2 = 0;
-    rc = cg_solve(ctx, K64, N, Np, C, ones, g, work, &it1);
+    const double* rhs[2] = {ones, hp};
+    double* x[2] = {g, xh};
+    rc = cg_solve(ctx, K64, N, Np, C, h_kind == 2 ? 2 : 1, rhs, x, (double*)part, &cg_iters);
     if (rc) {
       cleanup();
       return rc;
     }
     HIPCHK(dense_dot(ones, g, Np, dots, s), "dot");
     if (h_kind == 2) {
-      rc = cg_solve(ctx, K64, N, Np, C, hp, xh, work, &it2);
-      if (rc) {
-        cleanup();
-        return rc;
-      }
       HIPCHK(dense_dot(hp, g, Np, dots + 1, s), "dot");
       HIPCHK(dense_dot(hp, xh, Np, dots + 2, s), "dot");
     }
     double hd[4] = {0, 0, 0, 0};
     HIPCHK(hipMemcpyAsync(hd, dots, sizeof hd, hipMemcpyDeviceToHost, s), "constants");
     HIPCHK(hipStreamSynchronize(s), "constants sync");
-    cg_iters = std::max(it1, it2);
     for (int i = 0; i < B; ++i) {
       ChainDev& c = cd[i];
       c.c_v = hd[0];
@@ -570,7 +612,10 @@ extern "C" int ihmc_dense_restore(ihmc_dense_chains* ch, int32_t i, const void* 
   DenseChains& d = ch->impl;
   if (i < 0 || i >= d.B) return set_error(IHMC_E_INVAL, "chain index %d out of range", i);
   int traj = 0;
-  int rc = chain_restore(d.ctx, d.cd[i], 0x100u + (uint64_t)d.nprod, buf, bytes, &traj);
+  // a shift that comes from Lanczos may differ in its last digits where the sums
+  // of K's products run in another order
+  int rc = chain_restore(d.ctx, d.cd[i], 0x100u + (uint64_t)d.nprod, buf, bytes, &traj, nullptr,
+                         d.auto_shift ? 1e-12 : 0.0);
   if (rc) return rc;
   d.base[i] = traj - d.enqueued;
   return IHMC_OK;
@@ -703,26 +748,33 @@ extern "C" int ihmc_min_eig(ihmc_ctx* ctx, const double* K, int64_t N, double* t
   hipStream_t s = ctx->stream;
   double* K64 = (double*)ctx->arena.alloc(8 * (uint64_t)(Np * Np));
   double* Kh = (double*)ctx->arena.alloc(8 * (uint64_t)(N * N));
-  __bf16* Kl = (__bf16*)ctx->arena.alloc(2 * 3 * (uint64_t)(Np * Np));
+  double* scratch = (double*)ctx->arena.alloc(8 * setup_scratch_doubles(N, Np));
   auto release = [&]() {
     hipStreamSynchronize(s);
     if (K64) ctx->arena.release(K64);
     if (Kh) ctx->arena.release(Kh);
-    if (Kl) ctx->arena.release(Kl);
+    if (scratch) ctx->arena.release(scratch);
   };
-  if (!K64 || !Kh || !Kl) {
+  if (!K64 || !Kh || !scratch) {
     release();
-    return set_error(IHMC_E_NOMEM, "arena exhausted (K)");
+    rc = validate_entries(m);
+    return rc ? rc : set_error(IHMC_E_NOMEM, "arena exhausted (K)");
   }
   hipError_t e = hipMemcpyAsync(Kh, K, 8 * (size_t)(N * N), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = dense_split_K(Kh, N, Np, Kl, K64, s);
+  if (e == hipSuccess) e = hipMemsetAsync(scratch, 0, 8 * kCheckWords, s);
+  if (e == hipSuccess) e = dense_check(Kh, N, (unsigned long long*)scratch, s);
+  if (e == hipSuccess) e = dense_pad_K(Kh, N, Np, K64, s);
   if (e != hipSuccess) {
     release();
     return hip_fail(ctx, e, "K upload");
   }
   int st = 0;
-  rc = lanczos_min(ctx, K64, N, Np, theta, resid, &st);
+  rc = lanczos_min(ctx, K64, N, Np, scratch, theta, resid, &st);
   release();
+  if (rc) {
+    const int bad = validate_entries(m);  // names the entry, and goes before any other failure
+    return bad ? bad : rc;
+  }
   if (steps) *steps = st;
   return rc;
 }

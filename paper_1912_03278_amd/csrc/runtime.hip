@@ -1056,7 +1056,7 @@ int chain_checkpoint_host(const ChainDev& c, uint64_t fh, const ChainState& st_i
 }
 
 int chain_restore(ihmc_ctx* ctx, const ChainDev& c, uint64_t variant, const void* buf, uint64_t bytes, int* traj,
-                  hipStream_t s) {
+                  hipStream_t s, double shift_rel) {
   if (!buf) return set_error(IHMC_E_INVAL, "buf is NULL");
   if (bytes < sizeof(CkptHeader)) return set_error(IHMC_E_INVAL, "not a checkpoint (%llu bytes)", (unsigned long long)bytes);
   if (!s) s = ctx->stream;
@@ -1073,12 +1073,13 @@ int chain_restore(ihmc_ctx* ctx, const ChainDev& c, uint64_t variant, const void
   fill_identity(c, fh, variant, mine);
   // c_m, c_e and c_v follow from the fields already compared (couplings, shift,
   // field hash); another order of their sums may move the last digits
-  auto derived = [](double a, double& b) {
-    if (std::fabs(a - b) <= 1e-9 * (std::fabs(a) + std::fabs(b))) b = a;
+  auto derived = [](double a, double& b, double rel) {
+    if (std::fabs(a - b) <= rel * (std::fabs(a) + std::fabs(b))) b = a;
   };
-  derived(h.c_m, mine.c_m);
-  derived(h.c_e, mine.c_e);
-  derived(h.c_v, mine.c_v);
+  derived(h.c_m, mine.c_m, 1e-9);
+  derived(h.c_e, mine.c_e, 1e-9);
+  derived(h.c_v, mine.c_v, 1e-9);
+  if (shift_rel > 0.0) derived(h.C, mine.C, shift_rel);
   // compare the identity fields (the span between the version words and the state)
   const size_t id0 = offsetof(CkptHeader, ndim), id1 = offsetof(CkptHeader, st);
   if (std::memcmp((const char*)&h + id0, (const char*)&mine + id0, id1 - id0) != 0)

@@ -54,11 +54,12 @@ int upload_fields(ihmc_ctx* ctx, const std::vector<ChainDev>& cd, const ChainDev
 // restore into a chain with the same parameters (sets *traj to the
 // checkpoint's trajectory index).  `variant` names a path-specific form of the
 // force that must also match (0 for the lattice path).  Both wait for stream
-// s (null: the context stream) and do their copies on it.
+// s (null: the context stream) and do their copies on it.  shift_rel: how far
+// apart, relatively, the shifts C may lie (0: equal to the bit).
 int chain_checkpoint(ihmc_ctx* ctx, const ChainDev& c, uint64_t variant, void* buf, uint64_t* bytes,
                      hipStream_t s = nullptr);
 int chain_restore(ihmc_ctx* ctx, const ChainDev& c, uint64_t variant, const void* buf, uint64_t bytes, int* traj,
-                  hipStream_t s = nullptr);
+                  hipStream_t s = nullptr, double shift_rel = 0.0);
 // The same checkpoint built from host copies of a finished lattice chain: its
 // state, its accepted field in site order with the sign applied, and its
 // records; fh = field_hash_host of its h' in site order (0 without a per-site field).
