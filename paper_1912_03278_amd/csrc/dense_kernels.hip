@@ -456,113 +456,83 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, RB * CB >
 // ------------------------------------------------------------- FP64 MFMA GEMM ---
 //
 // U64[b][i] = sum_k K64[i][k] psi[b][k] with psi the stored FP32 fields (exact in
-// FP64).  Tile 64 sites x 64 chains, k-step 32, four waves of 32 x 32 (2 x 2
-// MFMA 16x16x4 FP64 tiles); LDS double buffered with register prefetch of the
-// next k-step, as in the BF16 GEMM.
+// FP64).  As in the BF16 GEMM a workgroup is one wave with 16 RB sites x 16 CB
+// chains (MFMA 16x16x4 FP64 blocks) that loads its operands straight into
+// registers, D steps of 16 k in turn: a lane holds 4 consecutive k of its row,
+// 32 and 16 bytes, and MFMA e of a step takes the e-th of every lane, so the order
+// of k within a step is 4 (lane / 16) + e.  Every output runs over k in this
+// order whatever the tile, so a chain's action does not depend on the others.
+// Few chains or sites: bound by the chain of MFMAs of an output, 64 cycles each,
+// which a wave with one block passes fastest (1024 sites x 40 chains 14.5 us,
+// 48.5 with a 64 x 64 tile per workgroup through LDS).  4096 x 256: 184 us against
+// 109 at the MFMA rate (196 through LDS); conversions of psi share the FP64 units.
 // The field of chain b is read through its state: the accepted field (with its
 // sign) for a measurement, else the buffer holding the proposal after pass j.
-constexpr int DBK = 32, DPAD = 33;
-
-__global__ __launch_bounds__(256) void k_dense_gemm_f64(const double* __restrict__ K64,
-                                                        const ChainDev* __restrict__ chains, int j, int measure,
-                                                        double* __restrict__ U64, int64_t Np, int B) {
-  __shared__ double sA[2][64][DPAD];
-  __shared__ double sB[2][64][DPAD];
-  __shared__ const float* sX[64];
-  __shared__ float sS[64];
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int64_t i0 = (int64_t)blockIdx.x * 64;
-  const int b0 = blockIdx.y * 64;
-  if (t < 64) {
-    const int b = b0 + t;
-    const float* x = nullptr;
-    float sg = 1.f;
-    if (b < B) {
-      const ChainDev& cd = chains[b];
-      const ChainState* st = cd.st;
-      const int buf = measure ? st->cur : pass_in_buf(st->cur, j);
-      x = (const float*)cd.psi + (int64_t)buf * cd.NP;
-      sg = (measure && st->sign < 0) ? -1.f : 1.f;
-    }
-    sX[t] = x;
-    sS[t] = sg;
+template <int RB, int CB, int D>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, RB * CB > 1 ? 2 : 4))) void k_dense_gemm_f64(
+    const double* __restrict__ K64, const ChainDev* __restrict__ chains, int j, int measure, double* __restrict__ U64,
+    int64_t Np, int B, int nrow, int ncol) {
+  const int lane = threadIdx.x, kq = lane >> 4;
+  // the column tiles of a row tile one after the other on one XCD
+  const int m = blockIdx.x >> 3, ct = m % ncol, rt = m / ncol * 8 + (blockIdx.x & 7);
+  if (rt >= nrow) return;
+  const int64_t i0 = (int64_t)rt * (16 * RB);
+  const int b0 = ct * (16 * CB);
+  const double* gA = K64 + (i0 + (lane & 15)) * Np + 4 * kq;
+  const float* gB[CB];
+  float sg[CB];
+#pragma unroll
+  for (int c = 0; c < CB; ++c) {
+    const ChainDev& cd = chains[min(b0 + 16 * c + (lane & 15), B - 1)];  // columns past B are not stored
+    const ChainState* st = cd.st;
+    const int buf = measure ? st->cur : pass_in_buf(st->cur, j);
+    gB[c] = (const float*)cd.psi + (int64_t)buf * cd.NP + 4 * kq;
+    sg[c] = (measure && st->sign < 0) ? -1.f : 1.f;
   }
-  __syncthreads();
-  // staging: A = 64 rows x 32 doubles as 1024 double2 chunks (4 per thread),
-  // B = 64 rows x 32 floats as 512 float4 chunks (2 per thread)
-  double2 ra[4];
-  float4 rb[2];
-  auto gload = [&](int64_t k0) {
+  f64x4 fa[D][RB];
+  f32x4 fb[D][CB];
+  auto load = [&](int s, int kt) {
+    const int64_t o = (int64_t)kt << 4;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int ch = t + 256 * q, row = ch >> 4, c2 = (ch & 15) * 2;
-      ra[q] = *reinterpret_cast<const double2*>(K64 + (i0 + row) * Np + k0 + c2);
-    }
+    for (int r = 0; r < RB; ++r) fa[s][r] = *reinterpret_cast<const f64x4*>(gA + (int64_t)(16 * r) * Np + o);
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int ch = t + 256 * q, row = ch >> 3, c4 = (ch & 7) * 4;
-      const float* x = sX[row];
-      rb[q] = x ? *reinterpret_cast<const float4*>(x + k0 + c4) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
+    for (int c = 0; c < CB; ++c) fb[s][c] = *reinterpret_cast<const f32x4*>(gB[c] + o);
   };
-  auto lstore = [&](int buf) {
+  f64x4 acc[RB][CB];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int ch = t + 256 * q, row = ch >> 4, c2 = (ch & 15) * 2;
-      sA[buf][row][c2] = ra[q].x;
-      sA[buf][row][c2 + 1] = ra[q].y;
+  for (int r = 0; r < RB; ++r)
+#pragma unroll
+    for (int c = 0; c < CB; ++c) acc[r][c] = f64x4{0.0, 0.0, 0.0, 0.0};
+  const int nk = (int)(Np >> 4);
+#pragma unroll
+  for (int d = 0; d < D - 1; ++d) load(d, min(d, nk - 1));
+  for (int kt = 0; kt < nk; kt += D) {
+#pragma unroll
+    for (int h = 0; h < D; ++h) {
+      if (kt + h < nk) {
+        load((h + D - 1) % D, min(kt + h + D - 1, nk - 1));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int r = 0; r < RB; ++r)
+#pragma unroll
+            for (int c = 0; c < CB; ++c)
+              acc[r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[h][r][e], (double)(sg[c] * fb[h][c][e]),
+                                                               acc[r][c], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int ch = t + 256 * q, row = ch >> 3, c4 = (ch & 7) * 4;
-      const float sg = sS[row];
-      sB[buf][row][c4] = (double)(sg * rb[q].x);
-      sB[buf][row][c4 + 1] = (double)(sg * rb[q].y);
-      sB[buf][row][c4 + 2] = (double)(sg * rb[q].z);
-      sB[buf][row][c4 + 3] = (double)(sg * rb[q].w);
-    }
-  };
-  const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
-  f64x4 acc[2][2];
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int c = 0; c < 2; ++c) acc[r][c] = f64x4{0.0, 0.0, 0.0, 0.0};
-  const int nk = (int)(Np / DBK);
-  gload(0);
-  lstore(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < nk) gload((int64_t)(kt + 1) * DBK);
-#pragma unroll
-    for (int ks = 0; ks < DBK; ks += 4) {
-      const int fr = lane & 15, fk = ks + (lane >> 4);
-      double fa[2], fb[2];
-#pragma unroll
-      for (int r = 0; r < 2; ++r) fa[r] = sA[buf][wr + 16 * r + fr][fk];
-#pragma unroll
-      for (int c = 0; c < 2; ++c) fb[c] = sB[buf][wc + 16 * c + fr][fk];
-#pragma unroll
-      for (int r = 0; r < 2; ++r)
-#pragma unroll
-        for (int c = 0; c < 2; ++c) acc[r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[r], fb[c], acc[r][c], 0, 0, 0);
-    }
-    if (kt + 1 < nk) lstore(buf ^ 1);
-    lds_barrier();
   }
   // D layout of the FP64 16x16 MFMA: lane -> column lane % 16, rows lane / 16 + 4 e
 #pragma unroll
-  for (int r = 0; r < 2; ++r)
+  for (int r = 0; r < RB; ++r)
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int b = b0 + wc + 16 * c + (lane & 15);
+    for (int c = 0; c < CB; ++c) {
+      const int b = b0 + 16 * c + (lane & 15);
       if (b >= B) continue;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int64_t i = i0 + wr + 16 * r + (lane >> 4) + 4 * e;
-        U64[(int64_t)b * Np + i] = acc[r][c][e];
-      }
+      for (int e = 0; e < 4; ++e) U64[(int64_t)b * Np + i0 + 16 * r + kq + 4 * e] = acc[r][c][e];
     }
 }
 
@@ -908,10 +878,29 @@ hipError_t dense_gemm_bf16(int nprod, const __bf16* Kl, const __bf16* Xl, float*
   return hipGetLastError();
 }
 
+template <int RB, int CB, int D>
+static void launch_gemm_f64(const double* K64, const ChainDev* chains, int j, int measure, double* U64, int64_t Np,
+                            int B, hipStream_t s) {
+  const int nrow = (int)(Np / (16 * RB)), ncol = (B + 16 * CB - 1) / (16 * CB);
+  k_dense_gemm_f64<RB, CB, D><<<8u * (unsigned)ncol * (unsigned)((nrow + 7) / 8), 64, 0, s>>>(K64, chains, j, measure,
+                                                                                            U64, Np, B, nrow, ncol);
+}
+
+// The tile with the least estimated time: rounds of 1024 waves (one per SIMD) times
+// what a round was measured to take at 2048 sites, us: 1x1 47, 1x2 64, 2x2 92, and
+// with at most half of the SIMDs busy 30, 59, 82.  (2048 x 128: 1x1 47, 1x2 60, 2x2
+// 81; x 256: 91, 64, 83; 4096 x 256: 341, 233, 184; 4352 x 128: 213, 188, 173.)
 hipError_t dense_gemm_f64(const double* K64, const ChainDev* chains, int j, int measure, double* U64, int64_t Np,
                           int B, hipStream_t s) {
-  dim3 grid((unsigned)(Np / 64), (unsigned)((B + 63) / 64));
-  k_dense_gemm_f64<<<grid, 256, 0, s>>>(K64, chains, j, measure, U64, Np, B);
+  if (Np % 256 != 0 || B < 1) return hipErrorInvalidValue;
+  auto cost = [&](int rb, int cb, double half, double full) {
+    const int64_t waves = Np / (16 * rb) * ((B + 16 * cb - 1) / (16 * cb));
+    return waves <= 512 ? half : full * (double)((waves + 1023) / 1024);
+  };
+  const double c11 = cost(1, 1, 30, 47), c12 = cost(1, 2, 59, 64), c22 = cost(2, 2, 82, 92);
+  if (c11 <= fmin(c12, c22)) launch_gemm_f64<1, 1, 8>(K64, chains, j, measure, U64, Np, B, s);
+  else if (c12 <= c22) launch_gemm_f64<1, 2, 4>(K64, chains, j, measure, U64, Np, B, s);
+  else launch_gemm_f64<2, 2, 4>(K64, chains, j, measure, U64, Np, B, s);
   return hipGetLastError();
 }
 
