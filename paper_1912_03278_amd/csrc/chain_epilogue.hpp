@@ -10,6 +10,12 @@
 
 namespace ihmc {
 
+// Whether the passes sum psi h' of a chain: it is zero without a field, and lattice
+// passes then leave the term out.
+__device__ __forceinline__ bool sums_psih(const ChainDev& cd) {
+  return cd.h_kind == 2 || cd.hp0 != 0.0 || cd.ndim == 0 || cd.form == FORM_PHI;
+}
+
 // Metropolis decision and record, run by one thread of the last block of a LAST
 // pass once the block has gathered the chain's accumulators (`sum`, `bad`).
 // Returns the record's flags (REC_ACCEPT, REC_FLIP, REC_NONFINITE).
@@ -57,7 +63,7 @@ __device__ __forceinline__ uint32_t finalize_trajectory(const ChainDev& cd, Chai
     cur_bad = 0;
     S = sum[T_S];
     sum_psi = fixed_to_double(sum[T_PSI]);
-    sum_psih = fixed_to_double(sum[T_PSIH]);
+    sum_psih = sums_psih(cd) ? fixed_to_double(sum[T_PSIH]) : 0.0;
     sum_ut = fixed_to_double(sum[T_UT]);
     sum_t2 = t2;
     cur = last_buf;
@@ -131,13 +137,14 @@ __device__ __forceinline__ uint32_t finalize_trajectory(const ChainDev& cd, Chai
   return flags;
 }
 
-__device__ __forceinline__ void finalize_measure(ChainState* st, const u128* sum, uint32_t bad, double t2 = 0.0) {
+__device__ __forceinline__ void finalize_measure(const ChainDev& cd, ChainState* st, const u128* sum, uint32_t bad,
+                                                 double t2 = 0.0) {
   st->cur_bad = bad ? 1 : 0;
   st->sum_t2 = t2;
   st->S_lo = sum[T_S].lo;
   st->S_hi = sum[T_S].hi;
   st->sum_psi = fixed_to_double(sum[T_PSI]);
-  st->sum_psih = fixed_to_double(sum[T_PSIH]);
+  st->sum_psih = sums_psih(cd) ? fixed_to_double(sum[T_PSIH]) : 0.0;
   st->sum_ut = fixed_to_double(sum[T_UT]);
   __hip_atomic_store(&st->bad, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __hip_atomic_store(&st->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -279,6 +286,7 @@ __device__ __forceinline__ void block_store_ranks(const ChainDev& cd, const u128
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int k = 0; k < NR; ++k) {
+    if (4 * k >= nterms) break;
     u128 v = accR[k];
     // the four lanes of each residue within a row (DPP), then across rows
     v = add128(v, dpp_u128<DPP_ROW_ROR4>(v));
@@ -319,7 +327,7 @@ template <bool kTraj, int NW>
 __device__ __forceinline__ void block_close(const ChainDev& cd, ChainState* st, int last_buf, int tix) {
   __shared__ u128 sSum[NTERM];
   __shared__ uint32_t sFlag, sLast;
-  const int a_lo = kTraj ? T_K0 : T_S;
+  const int a_lo = kTraj ? T_K0 : T_S, a_hi = sums_psih(cd) ? T_PSIH : T_UT;
   const uint32_t wmask = kTraj ? 7u : 4u;
   const int pg = part_group(cd.n_tiles);
   const int g = tix / pg;
@@ -329,26 +337,26 @@ __device__ __forceinline__ void block_close(const ChainDev& cd, ChainState* st, 
   __syncthreads();
   if (!sLast) return;
   // this block completed group g
-  gather_entries<NW>(cd.part + (int64_t)g * pg * NPART * 2, gs, a_lo, T_UT, wmask, sSum, &sFlag);
+  gather_entries<NW>(cd.part + (int64_t)g * pg * NPART * 2, gs, a_lo, a_hi, wmask, sSum, &sFlag);
   if (ng > 1) {
     if (threadIdx.x == 0) {
       __hip_atomic_store(&cd.gcnt[g], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      for (int a = a_lo; a <= T_UT; ++a) store_u128_agent(part_entry(cd.gsum, g, a), sSum[a]);
+      for (int a = a_lo; a <= a_hi; ++a) store_u128_agent(part_entry(cd.gsum, g, a), sSum[a]);
       store_flag_agent(part_entry(cd.gsum, g, NTERM), 0, sFlag);
       sLast = count_done(&st->done, (uint32_t)ng) ? 1u : 0u;
     }
     __syncthreads();
     if (!sLast) return;
     // this block completed the chain: sum the group sums (flags in word 0)
-    gather_entries<NW>(cd.gsum, ng, a_lo, T_UT, 1u, sSum, &sFlag);
+    gather_entries<NW>(cd.gsum, ng, a_lo, a_hi, 1u, sSum, &sFlag);
   }
   if (threadIdx.x == 0) {
     if (ng == 1) __hip_atomic_store(&cd.gcnt[g], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     u128 sum[NTERM];
 #pragma unroll
-    for (int a = 0; a < NTERM; ++a) sum[a] = (a >= a_lo) ? sSum[a] : u128{0ull, 0ull};
+    for (int a = 0; a < NTERM; ++a) sum[a] = (a >= a_lo && a <= a_hi) ? sSum[a] : u128{0ull, 0ull};
     if (kTraj) finalize_trajectory(cd, st, last_buf, sum, sFlag);
-    else finalize_measure(st, sum, sFlag);
+    else finalize_measure(cd, st, sum, sFlag);
   }
 }
 
@@ -364,25 +372,14 @@ __device__ __forceinline__ double quad_sum(double t0, double t1, double t2, doub
 
 // Epilogue of a lattice pass: store the block's terms (FIRST: kinetic energy of
 // the fresh momenta; LAST: final kinetic energy and the action terms; MEASURE:
-// the action terms) and close the chain where this block completes it;
-// last_buf is the buffer holding the proposal (LAST).
-template <int MODE, int NW>
-__device__ __forceinline__ void block_accumulate(const ChainDev& cd, ChainState* st, const u128* acc, uint32_t bad,
-                                                 int last_buf, int tix) {
-  constexpr int t_lo = (MODE == PASS_FIRST) ? T_K0 : ((MODE == PASS_MEASURE) ? T_S : T_K1);
-  constexpr int t_hi = (MODE == PASS_FIRST) ? T_K0 : T_UT;
-  constexpr int kind = (MODE == PASS_FIRST) ? CONTRIB_FIRST : ((MODE == PASS_MEASURE) ? CONTRIB_ACTION : CONTRIB_LAST);
-  block_store_terms<NW>(cd, acc, bad, t_lo, t_hi, kind, tix);
-  if (MODE == PASS_FIRST) return;
-  block_close<MODE == PASS_LAST, NW>(cd, st, last_buf, tix);
-}
-
-// The same with accumulators dealt over the lanes of each quad (block_store_ranks).
+// the action terms), dealt over the lanes of each quad (block_store_ranks), and
+// close the chain where this block completes it; last_buf is the buffer holding
+// the proposal (LAST).
 template <int MODE, int NW, int NR>
 __device__ __forceinline__ void block_accumulate_ranks(const ChainDev& cd, ChainState* st, const u128 (&accR)[NR],
                                                        uint32_t bad, int last_buf, int tix) {
   constexpr int t_lo = (MODE == PASS_FIRST) ? T_K0 : ((MODE == PASS_MEASURE) ? T_S : T_K1);
-  constexpr int t_hi = (MODE == PASS_FIRST) ? T_K0 : T_UT;
+  const int t_hi = (MODE == PASS_FIRST) ? T_K0 : (sums_psih(cd) ? T_PSIH : T_UT);
   constexpr int kind = (MODE == PASS_FIRST) ? CONTRIB_FIRST : ((MODE == PASS_MEASURE) ? CONTRIB_ACTION : CONTRIB_LAST);
   block_store_ranks<NW, NR>(cd, accR, bad, t_lo, t_hi - t_lo + 1, kind, tix);
   if (MODE == PASS_FIRST) return;

@@ -723,7 +723,7 @@ __global__ __launch_bounds__(EPI_THREADS) void k_dense_h(const ChainDev* __restr
   const ChainDev& cd = chains[b];
   ChainState* st = cd.st;
   const int cur = st->cur;
-  double h[4][4] = {};  // [term][site]
+  double h[4][4] = {};  // [term - T_S][site]
   if (i < cd.N) {
     const int buf = (MODE == PASS_MEASURE) ? cur : pass_in_buf(cur, j);
     f32x4 v4 = ld_f4((const float*)cd.psi + (int64_t)buf * cd.NP + i);
@@ -738,15 +738,15 @@ __global__ __launch_bounds__(EPI_THREADS) void k_dense_h(const ChainDev* __restr
         const double u = ku[e] + cd.C * v;
         const double hpx = hp4[e];
         const bool shifted = cd.form == FORM_SHIFTED;
-        // shifted form: y = sqrt(J') u + h', no linear term, h[3] = y tanh(y)
+        // shifted form: y = sqrt(J') u + h', no linear term, h[2] = y tanh(y)
         const double y = __builtin_fma(cd.sqJ, u, shifted ? hpx : 0.0);
         double lc, th;
         logcosh_tanh(y, lc, th);
         const double bx = shifted ? 0.0 : ((cd.h_kind == 2) ? hpx / cd.sqJ : cd.b0);
         h[0][e] = 0.5 * v * u - v * bx - lc;
         h[1][e] = v;
-        h[2][e] = v * hpx;
-        h[3][e] = (shifted ? y : u) * th;
+        h[2][e] = (shifted ? y : u) * th;
+        h[3][e] = v * hpx;
       }
     }
   }
@@ -757,7 +757,7 @@ __global__ __launch_bounds__(EPI_THREADS) void k_dense_h(const ChainDev* __restr
 #pragma unroll
   for (int a = 0; a < 4; ++a) acc[T_S + a] = to_fixed(quad_sum(h[a][0], h[a][1], h[a][2], h[a][3]), bad);
   // the final kinetic energy was stored by the last force epilogue
-  block_store_terms<1>(cd, acc, bad, T_S, T_UT, CONTRIB_ACTION, blockIdx.x);
+  block_store_terms<1>(cd, acc, bad, T_S, T_PSIH, CONTRIB_ACTION, blockIdx.x);
   block_close<MODE == PASS_LAST, 1>(cd, st, MODE == PASS_LAST ? pass_in_buf(cur, j) : cur, blockIdx.x);
 }
 

@@ -50,6 +50,16 @@ __device__ __forceinline__ uint4 draw(const ChainDev& cd, uint32_t i, uint32_t t
 constexpr double kLn2Head = 6.93147180369123816490e-01;
 constexpr double kLn2Tail = 1.90821492927058770002e-10;
 
+// A polynomial coefficient, with SGPR held in scalar registers.  Left to itself the
+// compiler writes a coefficient into a vector register pair for each use or keeps
+// it there: two more moves a step, or registers that cost resident waves.  Scalar
+// ones suit kernels with many waves per SIMD; a single wave waits for them.
+template <bool SGPR>
+__device__ __forceinline__ double coeff(double c) {
+  if (SGPR) asm("" : "+s"(c));
+  return c;
+}
+
 // ln u for u in (0, 1) (a 53-bit uniform): u = m 2^e with m in [sqrt(1/2),
 // sqrt 2), ln u = e ln 2 + 2 atanh(s), s = (m - 1)/(m + 1), |s| <= 0.1716, with
 // the odd Taylor series of atanh to s^23 (truncation below 1e-19 relative).
@@ -311,73 +321,64 @@ __device__ __forceinline__ double tanh_state(double x) { return tanh(x); }
 //        ln 2 + 2 atanh((e-1)/(e+3)) (e > sqrt2 - 1), so |s| <= 0.1716 and the
 //        odd series to s^23 is below 1e-18 relative.
 // Agrees with correctly rounded log cosh / tanh to a few ulp.
+template <bool SGPR>
 __device__ __forceinline__ double exp_nonpos(double x) {
-  const bool under = (x < -745.0);
-  x = under ? 0.0 : x;
+  x = fmax(x, -745.0);  // e^x < 2^-1074 below
   const double k = rint(x * 1.4426950408889634);
   double r = __builtin_fma(-k, kLn2Head, x);
   r = __builtin_fma(-k, kLn2Tail, r);
   double p = 1.6059043836821614e-10;  // 1/13!
-  p = __builtin_fma(p, r, 2.0876756987868099e-09);
-  p = __builtin_fma(p, r, 2.5052108385441720e-08);
-  p = __builtin_fma(p, r, 2.7557319223985893e-07);
-  p = __builtin_fma(p, r, 2.7557319223985888e-06);
-  p = __builtin_fma(p, r, 2.4801587301587302e-05);
-  p = __builtin_fma(p, r, 1.9841269841269841e-04);
-  p = __builtin_fma(p, r, 1.3888888888888889e-03);
-  p = __builtin_fma(p, r, 8.3333333333333332e-03);
-  p = __builtin_fma(p, r, 4.1666666666666664e-02);
-  p = __builtin_fma(p, r, 1.6666666666666666e-01);
+  p = __builtin_fma(p, r, coeff<SGPR>(2.0876756987868099e-09));
+  p = __builtin_fma(p, r, coeff<SGPR>(2.5052108385441720e-08));
+  p = __builtin_fma(p, r, coeff<SGPR>(2.7557319223985893e-07));
+  p = __builtin_fma(p, r, coeff<SGPR>(2.7557319223985888e-06));
+  p = __builtin_fma(p, r, coeff<SGPR>(2.4801587301587302e-05));
+  p = __builtin_fma(p, r, coeff<SGPR>(1.9841269841269841e-04));
+  p = __builtin_fma(p, r, coeff<SGPR>(1.3888888888888889e-03));
+  p = __builtin_fma(p, r, coeff<SGPR>(8.3333333333333332e-03));
+  p = __builtin_fma(p, r, coeff<SGPR>(4.1666666666666664e-02));
+  p = __builtin_fma(p, r, coeff<SGPR>(1.6666666666666666e-01));
   p = __builtin_fma(p, r, 0.5);
   p = __builtin_fma(p, r, 1.0);
   p = __builtin_fma(p, r, 1.0);
-  return under ? 0.0 : ldexp(p, (int)k);
+  return ldexp(p, (int)k);
 }
 
-__device__ __forceinline__ double log1p_unit(double e) {
-  const bool hi = (e > 0.41421356237309503);
-  const double s = (hi ? e - 1.0 : e) / (hi ? e + 3.0 : 2.0 + e);
-  const double off = hi ? 0.6931471805599453 : 0.0;
-  const double z = s * s;
-  double q = 1.0 / 23.0;
-  q = __builtin_fma(q, z, 1.0 / 21.0);
-  q = __builtin_fma(q, z, 1.0 / 19.0);
-  q = __builtin_fma(q, z, 1.0 / 17.0);
-  q = __builtin_fma(q, z, 1.0 / 15.0);
-  q = __builtin_fma(q, z, 1.0 / 13.0);
-  q = __builtin_fma(q, z, 1.0 / 11.0);
-  q = __builtin_fma(q, z, 1.0 / 9.0);
-  q = __builtin_fma(q, z, 1.0 / 7.0);
-  q = __builtin_fma(q, z, 1.0 / 5.0);
-  q = __builtin_fma(q, z, 1.0 / 3.0);
-  q = q * z;  // atanh(s)/s - 1
-  return off + 2.0 * __builtin_fma(s, q, s);
+// 1/d, correctly rounded, for d well inside the range of normal numbers.
+__device__ __forceinline__ double recip(double d) {
+  double q = __builtin_amdgcn_rcp(d);
+  q = __builtin_fma(q, __builtin_fma(-d, q, 1.0), q);
+  q = __builtin_fma(q, __builtin_fma(-d, q, 1.0), q);
+  return __builtin_fma(__builtin_fma(-d, q, 1.0), q, q);
 }
 
 // Both quotients, s = num/den of the log1p series and (1 - e)/(1 + e), come
 // from the one reciprocal q = 1/((1 + e) den): s = num (1 + e) q and
-// 1/(1 + e) = den q (a few ulp each, instead of two divisions).
+// 1/(1 + e) = den q (a few ulp each, instead of two divisions).  (1 + e) den lies in
+// [2, 8], so q needs none of a division's scaling: the hardware's estimate, two
+// Newton steps and the residual's correction give the correctly rounded value.
+template <bool SGPR = false>
 __device__ __forceinline__ void logcosh_tanh(double y, double& lc, double& t) {
   const double a = fabs(y);
-  const double e = exp_nonpos(-2.0 * a);
+  const double e = exp_nonpos<SGPR>(-2.0 * a);
   const bool hi = (e > 0.41421356237309503);
   const double num = hi ? e - 1.0 : e;
   const double den = hi ? e + 3.0 : 2.0 + e;
   const double g = 1.0 + e;
-  const double q = 1.0 / (g * den);
+  const double q = recip(g * den);
   const double s = (num * g) * q;
   const double z = s * s;
   double p = 1.0 / 23.0;
-  p = __builtin_fma(p, z, 1.0 / 21.0);
-  p = __builtin_fma(p, z, 1.0 / 19.0);
-  p = __builtin_fma(p, z, 1.0 / 17.0);
-  p = __builtin_fma(p, z, 1.0 / 15.0);
-  p = __builtin_fma(p, z, 1.0 / 13.0);
-  p = __builtin_fma(p, z, 1.0 / 11.0);
-  p = __builtin_fma(p, z, 1.0 / 9.0);
-  p = __builtin_fma(p, z, 1.0 / 7.0);
-  p = __builtin_fma(p, z, 1.0 / 5.0);
-  p = __builtin_fma(p, z, 1.0 / 3.0);
+  p = __builtin_fma(p, z, coeff<SGPR>(1.0 / 21.0));
+  p = __builtin_fma(p, z, coeff<SGPR>(1.0 / 19.0));
+  p = __builtin_fma(p, z, coeff<SGPR>(1.0 / 17.0));
+  p = __builtin_fma(p, z, coeff<SGPR>(1.0 / 15.0));
+  p = __builtin_fma(p, z, coeff<SGPR>(1.0 / 13.0));
+  p = __builtin_fma(p, z, coeff<SGPR>(1.0 / 11.0));
+  p = __builtin_fma(p, z, coeff<SGPR>(1.0 / 9.0));
+  p = __builtin_fma(p, z, coeff<SGPR>(1.0 / 7.0));
+  p = __builtin_fma(p, z, coeff<SGPR>(1.0 / 5.0));
+  p = __builtin_fma(p, z, coeff<SGPR>(1.0 / 3.0));
   p = p * z;  // atanh(s)/s - 1
   const double l1p = (hi ? 0.6931471805599453 : 0.0) + 2.0 * __builtin_fma(s, p, s);
   lc = (a - 0.6931471805599453) + l1p;

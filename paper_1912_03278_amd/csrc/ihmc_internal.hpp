@@ -25,8 +25,8 @@ enum Term : int {
   T_K1 = 1,    // 1/2 p^2 at the end of the trajectory (H_new)
   T_S = 2,     // action density S(psi) of the proposal
   T_PSI = 3,   // psi
-  T_PSIH = 4,  // psi h'
-  T_UT = 5,    // u tanh(sqrt(J') u), u = Kt psi
+  T_UT = 4,    // u tanh(sqrt(J') u), u = Kt psi
+  T_PSIH = 5,  // psi h' (left out by lattice passes of a chain without field, see sums_psih)
   NTERM = 6
 };
 constexpr int NPART = NTERM + 1;  // entries per tile of the partial-sum table (terms + flag words)

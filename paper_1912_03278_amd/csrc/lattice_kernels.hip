@@ -247,6 +247,7 @@ __global__ __launch_bounds__(BX / 4 * BY) void lattice_pass2v(const ChainDev* __
   const T drift = (T)drift_d;
 
   uint32_t bad = 0u;
+  const bool with_h = kH64 && sums_psih(cd);
   double qs[NTERM];  // FP64 sums of the thread's quad (0 without one)
 #pragma unroll
   for (int a = 0; a < NTERM; ++a) qs[a] = 0.0;
@@ -280,7 +281,6 @@ __global__ __launch_bounds__(BX / 4 * BY) void lattice_pass2v(const ChainDev* __
       ld4<T>(sW + wc0 + RP, wdn);
     }
     double kin[4];
-    double ht[4][4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const bool act = (gx + e < L0);
@@ -298,23 +298,36 @@ __global__ __launch_bounds__(BX / 4 * BY) void lattice_pass2v(const ChainDev* __
         const double pd = (double)((MODE == PASS_FIRST) ? pq[e] : pn[e]);
         kin[e] = act ? 0.5 * pd * pd : 0.0;
       }
-      if (kH64) {
-        const int pc = pc0 + e;
-        const double nb = ((double)sP[pc - 1] + (double)sP[pc + 1]) + ((double)sP[pc - RP] + (double)sP[pc + RP]);
-        h_terms(cd, (double)c, nb, base + e, act, ht[e]);
-      }
     }
     if (MODE == PASS_FIRST) qs[T_K0] = quad_sum(kin[0], kin[1], kin[2], kin[3]);
     if (MODE == PASS_LAST) qs[T_K1] = quad_sum(kin[0], kin[1], kin[2], kin[3]);
-    if (kH64) {
-#pragma unroll
-      for (int a = 0; a < 4; ++a) qs[T_S + a] = quad_sum(ht[0][a], ht[1][a], ht[2][a], ht[3][a]);
-    }
     if (MODE == PASS_FIRST || MODE == PASS_MIDDLE) {
       st4g<T>(pmo + base, pn);
       st4g<T>(pout + base, pv);
     } else if (MODE == PASS_FORCE || (MODE == PASS_LAST && cd.write_p_last)) {
       st4g<T>(pmo + base, pn);
+    }
+    if (kH64) {
+      // pair by pair, one site after the other: few registers, more waves
+      const bool ragged = (L0 & 3) != 0;
+#pragma unroll
+      for (int e = 0; e < 4; e += 2) {
+        SiteAction t[2];
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+          const int pc = pc0 + e + f;
+          const double nb =
+              ((double)sP[pc - 1] + (double)sP[pc + 1]) + ((double)sP[pc - RP] + (double)sP[pc + RP]);
+          t[f] = site_action<true>(cd, (double)sP[pc], nb, base + e + f);
+          if (ragged && gx + e + f >= L0) t[f] = no_site();
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        const SiteAction q{t[0].s + t[1].s, t[0].psi + t[1].psi, t[0].ut + t[1].ut, t[0].psih + t[1].psih};
+        qs[T_S] = e == 0 ? q.s : qs[T_S] + q.s;  // (t0 + t1) + (t2 + t3), as quad_sum
+        qs[T_PSI] = e == 0 ? q.psi : qs[T_PSI] + q.psi;
+        qs[T_UT] = e == 0 ? q.ut : qs[T_UT] + q.ut;
+        if (with_h) qs[T_PSIH] = e == 0 ? q.psih : qs[T_PSIH] + q.psih;
+      }
     }
   }
 
@@ -323,18 +336,22 @@ __global__ __launch_bounds__(BX / 4 * BY) void lattice_pass2v(const ChainDev* __
   // of one tile row (tile widths are multiples of 16), summed in FP64 as
   // (q0 + q1) + (q2 + q3) into every lane of the group; the group's lanes then
   // convert different terms to fixed point: the pass's terms T0 .. T0 + NU - 1
-  // in rank order, rank 4r + j by lane j into accR[r].
+  // in rank order, rank 4r + j by lane j into accR[r].  psi h' comes last: without
+  // a field LAST has four terms, one conversion and sum instead of two.
   constexpr int T0 = (MODE == PASS_FIRST) ? T_K0 : ((MODE == PASS_MEASURE) ? T_S : T_K1);
   constexpr int NU = (MODE == PASS_FIRST) ? 1 : ((MODE == PASS_MEASURE) ? 4 : 5);
   constexpr int NR = (NU + 3) / 4;
   static_assert(QX % 4 == 0, "rows of whole 16-site groups");
   const int gl = threadIdx.x & 3;
+  const int nu = (MODE != PASS_FIRST && !with_h) ? NU - 1 : NU;
   double gv[NU];
 #pragma unroll
-  for (int r = 0; r < NU; ++r) gv[r] = quad_sum_all(qs[T0 + r]);
+  for (int r = 0; r < NU; ++r) gv[r] = r < nu ? quad_sum_all(qs[T0 + r]) : 0.0;
   u128 accR[NR];
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
+    accR[r] = u128{0ull, 0ull};
+    if (4 * r >= nu) break;
     double x = 0.0;
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj)
@@ -750,6 +767,8 @@ __global__ __launch_bounds__(64 * ZR, 8) void lattice_pass3t(const ChainDev* __r
   constexpr int NR = (NU + 3) / 4;
   const int ql = threadIdx.x & 3;
   uint32_t bad = 0u;
+  const bool with_h = kH64 && sums_psih(cd);
+  const int nu = (MODE != PASS_FIRST && !with_h) ? NU - 1 : NU;
   double hs[NTERM];
   u128 accR[NR];
 #pragma unroll
@@ -804,29 +823,30 @@ __global__ __launch_bounds__(64 * ZR, 8) void lattice_pass3t(const ChainDev* __r
       if (MODE == PASS_FIRST) hs[T_K0] = hs[T_K0] + kin;
       if (MODE == PASS_LAST) hs[T_K1] = hs[T_K1] + kin;
       if (kH64) {
-        double ht[4];
         double nb = ((double)sP[c - 1] + (double)sP[c + 1]) + ((double)sP[c - RP] + (double)sP[c + RP]);
         nb = nb + ((double)sP[c - PPL] + (double)sP[c + PPL]);
-        h_terms(cd, (double)v, nb, act ? idx : 0, act, ht);
-#pragma unroll
-        for (int a = 0; a < 4; ++a) hs[T_S + a] = hs[T_S + a] + ht[a];
+        if (act) {
+          const SiteAction sa = site_action<true>(cd, (double)v, nb, idx);
+          hs[T_S] = hs[T_S] + sa.s;
+          hs[T_PSI] = hs[T_PSI] + sa.psi;
+          hs[T_UT] = hs[T_UT] + sa.ut;
+          if (with_h) hs[T_PSIH] = hs[T_PSIH] + sa.psih;
+        }
       }
     }
     // end of a slab: every lane takes part (the quad sums shuffle across the wave)
-    if (kAcc && (k & 3) == 3) {
+    if (kAcc && kk == 3) {
       double qv[NU];
 #pragma unroll
-      for (int r = 0; r < NU; ++r) {
-        qv[r] = quad_sum_all(hs[T0 + r]);
-        hs[T0 + r] = 0.0;
-      }
+      for (int r = 0; r < NU; ++r) qv[r] = r < nu ? quad_sum_all(hs[T0 + r]) : 0.0;
 #pragma unroll
       for (int kr = 0; kr < NR; ++kr) {
+        if (4 * kr >= nu) break;
         double x = 0.0;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
           if (4 * kr + j < NU) x = (ql == j) ? qv[4 * kr + j] : x;
-        accR[kr] = add128(accR[kr], to_fixed(x, bad));
+        accR[kr] = to_fixed(x, bad);
       }
     }
   }

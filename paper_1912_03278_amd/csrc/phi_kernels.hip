@@ -182,7 +182,7 @@ __global__ __launch_bounds__(PHI_THREADS) void lattice_resident_phi(const ChainD
     double t2s = 0.0;
     const uint32_t b = block_total(acc, bad, t2, sum, &t2s);
     if (tid == 0) {
-      finalize_measure(st, sum, b, t2s);
+      finalize_measure(cd, st, sum, b, t2s);
       st->n_cg += cg_iters;
     }
     return;

@@ -74,8 +74,10 @@ __device__ __forceinline__ void stv(T* p, const T (&v)[V]) {
 
 __device__ __forceinline__ uint32_t pack2(int lo, int hi) { return (uint32_t)lo | ((uint32_t)hi << 16); }
 
-// Ranks of the terms over the lanes that share a sum: K1, S, psi, psi h', u tanh
-// take ranks 0 .. 4 at the trajectory's end, K0 (drawn momenta) rank 5.
+// Ranks of the terms over the lanes that share a sum: K1, S, psi, u tanh, psi h'
+// take ranks 0 .. 4 at the trajectory's end, K0 (drawn momenta) rank 5.  psi h' is
+// zero without a field and left out then, so that the lanes of a quad convert the
+// end's terms in one go.
 constexpr int RES_RANKS = 6;
 
 template <typename T, int NDIM, int V, int NT, int NQ>
@@ -150,10 +152,12 @@ __global__ __launch_bounds__(NT, 4) void lattice_resident(const ChainDev* __rest
   // offset o and stored index gi.  Every lane takes part in every step.
   u128 accR[NR];
   uint32_t bad = 0u;
+  const bool with_h = sums_psih(cd);
   const int n16 = (L0 + 15) / 16, nq4 = (L0 + 3) / 4, nsl = (L2 + 3) / 4;
   const int nslot = (NDIM == 2) ? n16 * (16 / E) * rows : 4 * nq4 * L1 * nsl;
   auto site_sums = [&](auto nu_tag, int rank0, auto term) {
     constexpr int NU = decltype(nu_tag)::value;
+    auto left_out = [&](int rank) { return NU > 1 && rank == 4 && !with_h; };  // psi h'
     for (int s0 = 0; s0 < nslot; s0 += NT) {
       const int s = s0 + tid;
       double qv[NU];
@@ -184,6 +188,7 @@ __global__ __launch_bounds__(NT, 4) void lattice_resident(const ChainDev* __rest
         }
 #pragma unroll
         for (int a = 0; a < NU; ++a) {
+          if (left_out(rank0 + a)) continue;
           qv[a] = quad_sum_all(qv[a]);
           if constexpr (E == 1) {
             qv[a] = qv[a] + dpp_f64<DPP_ROW_HALF_MIRROR>(qv[a]);  // q0 + q1, q2 + q3
@@ -210,12 +215,14 @@ __global__ __launch_bounds__(NT, 4) void lattice_resident(const ChainDev* __rest
           }
         }
 #pragma unroll
-        for (int a = 0; a < NU; ++a) qv[a] = quad_sum_all(col[a]);
+        for (int a = 0; a < NU; ++a)
+          if (!left_out(rank0 + a)) qv[a] = quad_sum_all(col[a]);
       }
       // the sum's lanes convert one term each: rank GL r + l by lane l into accR[r]
       const int gl = lane & (GL - 1);
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
+        if (left_out(GL * r)) continue;  // the one term of its round
         double x = 0.0;
 #pragma unroll
         for (int a = 0; a < NU; ++a)
@@ -227,10 +234,11 @@ __global__ __launch_bounds__(NT, 4) void lattice_resident(const ChainDev* __rest
   auto action_term = [&](int o, int64_t gi, int xm, int xp, int ym, int yp, int zmi, int zpi, double* v) {
     double nb = ((double)sP[xm] + (double)sP[xp]) + ((double)sP[ym] + (double)sP[yp]);
     if (NDIM == 3) nb = nb + ((double)sP[zmi] + (double)sP[zpi]);
-    double h[4];
-    h_terms(cd, (double)sP[o], nb, gi, true, h);
-#pragma unroll
-    for (int a = 0; a < 4; ++a) v[a] = h[a];
+    const SiteAction sa = site_action<false>(cd, (double)sP[o], nb, gi);
+    v[0] = sa.s;
+    v[1] = sa.psi;
+    v[2] = sa.ut;
+    v[3] = sa.psih;
   };
   // the block's fixed-point totals in sSum (by rank) and flags, for thread 0
   // (the first wave, which thread 0 belongs to, adds the waves' sums)
@@ -302,7 +310,7 @@ __global__ __launch_bounds__(NT, 4) void lattice_resident(const ChainDev* __rest
       sum[T_K0] = sum[T_K1] = u128{0ull, 0ull};
 #pragma unroll
       for (int a = 0; a < 4; ++a) sum[T_S + a] = sSum[1 + a];
-      finalize_measure(cd.st, sum, b);
+      finalize_measure(cd, cd.st, sum, b);
     }
     return;
   }
