@@ -443,13 +443,13 @@ int ihmc_force(ihmc_ctx* ctx, const ihmc_lattice* lat, int32_t precision, const 
  * double) in site order, caller-owned, enqueued on `stream` (a hipStream_t;
  * NULL: the context stream) and not waited for.  The lattice may carry no
  * field or a uniform one (h_len 0 or 1; a per-site field is
- * IHMC_E_UNSUPPORTED).  It allocates nothing: the chain descriptor, tile table
- * and padded field staging live in a fixed 32 MiB device array per GPU (a
- * lattice whose staging exceeds it, about 3.9M FP32 or 1.9M FP64 sites, is
- * IHMC_E_INVAL).  Every call on one GPU uses that GPU's array, which keeps the
- * last call's contents: calls that overlap on one GPU (other streams, other
- * host threads, other contexts of the device) race and must be serialised by
- * the caller.  Same force pass and bits as ihmc_force. */
+ * IHMC_E_UNSUPPORTED).  It allocates nothing; a lattice whose padded field,
+ * force and tile table exceed 32 MiB (about 3.9M FP32 or 1.9M FP64 sites) is
+ * IHMC_E_INVAL.  Where psi and F overlap (in place, for instance) the field is
+ * staged in a fixed array of that size per GPU, which keeps the last call's
+ * contents: such calls that run at the same time on one GPU (other streams,
+ * other host threads, other contexts of the device) race and must be serialised
+ * by the caller.  Same values, to the bit, as ihmc_force. */
 int ihmc_force_noalloc(ihmc_ctx* ctx, const ihmc_lattice* lat, int32_t precision, const void* psi, void* F,
                        void* stream);
 /* Action and estimators of a host field psi: out[0] = S(psi) (FP64, eq.

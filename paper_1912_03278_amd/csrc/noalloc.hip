@@ -1,15 +1,18 @@
-// Allocation-free force evaluation (ihmc_force_noalloc): the force pass of the
-// lattice path (Sec. 3 equations of motion) on caller-owned device arrays, for
-// callers that cannot allocate device memory (code under stream capture, tight
-// serving loops).  The chain descriptor, tile table and padded field staging
-// live in one file-scope device array; each GPU holds its own copy, whose
-// address is looked up once per device when a context is created on it.
+// Allocation-free force evaluation (ihmc_force_noalloc): F = -dS/dpsi (Sec. 3
+// equations of motion) on caller-owned device arrays, for callers that cannot
+// allocate device memory (code under stream capture, tight serving loops).  One
+// launch reads the field and writes the force in the caller's site order.  Where
+// the two arrays overlap, blocks would overwrite sites that others still read, so
+// the field is staged: the chain descriptor, tile table and padded field then live
+// in one file-scope device array; each GPU holds its own copy, whose address is
+// looked up once per device when a context is created on it.
 #include <hip/hip_runtime.h>
 
 #include <cstring>
 #include <mutex>
 
 #include "device_common.hpp"
+#include "lattice_common.hpp"
 #include "lattice_kernels.hpp"
 #include "runtime_internal.hpp"
 
@@ -101,6 +104,84 @@ __global__ void k_noalloc_export(const unsigned char* base, T* __restrict__ dst)
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i < c.N) dst[i] = ((const T*)c.p)[stored_index(c, i)];
 }
+
+// The force straight from and to arrays in site order.  A block takes a tile of
+// BX x BY (x BZ) sites: psi with a halo of 2 and w = sqrt(J') tanh(sqrt(J') Kt psi) -
+// psi with a halo of 1 go through LDS, positions outside the lattice hold the
+// periodic images.  Per site the operations are those of the lattice passes' FORCE
+// mode, so the values are the same to the bit.
+//
+// Small lattices are bound by the call and its launch, so there is one launch, and
+// tiles of one site a thread spread the sites over the CUs; large ones, by the
+// passes over memory and LDS, take four sites a thread, which halves the halo (2D
+// 1.33 loads and 1.16 w a site, 3D 3.1 and 1.9).  Back-to-back calls, against
+// descriptor, import, pass and export in four launches: 48 x 40 FP32 13.5 -> 5.0
+// us, 1024^2 17.1 -> 5.2, 1900^2 31.1 -> 12.1, 100^3 19.3 -> 12.7, 150^3 34.8 ->
+// 29.9, 110^3 FP64 44.9 -> 30.7.
+template <typename T>
+struct ForceArgs {
+  T C, a, hw, b;
+  int L0, L1, L2, nx, ny;
+};
+
+__device__ __forceinline__ int wrapped(int g, int L) {
+  g = g < 0 ? g + L : g;  // at least -2, and L >= 3
+  return g < L ? g : (g - L < L ? g - L : g % L);
+}
+
+template <typename T, int NDIM, int BX, int BY, int BZ>
+__global__ __launch_bounds__(256) void k_force(ForceArgs<T> q, const T* __restrict__ psi, T* __restrict__ F) {
+  constexpr int HZ = NDIM == 3 ? 1 : 0;  // halos along z: 2 HZ and HZ
+  constexpr int PX = BX + 4, PY = BY + 4, PZ = BZ + 4 * HZ, WX = BX + 2, WY = BY + 2, WZ = BZ + 2 * HZ;
+  __shared__ T sP[PX * PY * PZ];
+  __shared__ T sW[WX * WY * WZ];
+  const int t = blockIdx.x, tx = t % q.nx, r = t / q.nx, ty = NDIM == 3 ? r % q.ny : r, tz = NDIM == 3 ? r / q.ny : 0;
+  const int x0 = tx * BX, y0 = ty * BY, z0 = tz * BZ;
+  for (int i = threadIdx.x; i < PX * PY * PZ; i += 256) {
+    const int x = i % PX, yz = i / PX, y = yz % PY, z = yz / PY;
+    const int gx = wrapped(x0 + x - 2, q.L0), gy = wrapped(y0 + y - 2, q.L1);
+    const int gz = NDIM == 3 ? wrapped(z0 + z - 2, q.L2) : 0;
+    sP[i] = psi[gx + (int64_t)q.L0 * (gy + (int64_t)q.L1 * gz)];
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < WX * WY * WZ; i += 256) {
+    const int x = i % WX, yz = i / WX, y = yz % WY, z = yz / WY;
+    const T* c = sP + (x + 1) + PX * ((y + 1) + PY * (z + HZ));
+    T n = (c[-1] + c[1]) + (c[-PX] + c[PX]);
+    if (NDIM == 3) n = n + (c[-PX * PY] + c[PX * PY]);
+    const T u = fma_t(q.C, c[0], n);
+    sW[i] = fma_t(q.a, tanh_state(fma_t(q.a, u, q.hw)), -c[0]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = threadIdx.x; i < BX * BY * BZ; i += 256) {
+    const int x = i % BX, yz = i / BX, y = yz % BY, z = yz / BY;
+    const T* w = sW + (x + 1) + WX * ((y + 1) + WY * (z + HZ));
+    T n = (w[-1] + w[1]) + (w[-WX] + w[WX]);
+    if (NDIM == 3) n = n + (w[-WX * WY] + w[WX * WY]);
+    const T f = fma_t(q.C, w[0], n) + q.b;
+    const int gx = x0 + x, gy = y0 + y, gz = z0 + z;
+    if (gx < q.L0 && gy < q.L1 && gz < q.L2)
+      F[gx + (int64_t)q.L0 * (gy + (int64_t)q.L1 * gz)] = fma_t((T)1, f, (T)0);
+  }
+}
+
+template <typename T, int NDIM, int BX, int BY, int BZ>
+hipError_t launch_force_tiles(const ChainDev& c, const void* psi, void* F, hipStream_t s) {
+  const int nx = (c.L0 + BX - 1) / BX, ny = (c.L1 + BY - 1) / BY, nz = (c.L2 + BZ - 1) / BZ;
+  const ForceArgs<T> q{(T)c.C, (T)c.sqJ, (T)c.hw, (T)c.b0, c.L0, c.L1, c.L2, nx, ny};
+  k_force<T, NDIM, BX, BY, BZ><<<(unsigned)((int64_t)nx * ny * nz), 256, 0, s>>>(q, (const T*)psi, (T*)F);
+  return hipGetLastError();
+}
+
+// Tiles of four sites a thread where they still give each CU four blocks.
+template <typename T>
+hipError_t launch_force(const ChainDev& c, const void* psi, void* F, hipStream_t s) {
+  const bool large = c.N >= 1024 * 1024;
+  if (c.ndim == 2)
+    return large ? launch_force_tiles<T, 2, 64, 16, 1>(c, psi, F, s) : launch_force_tiles<T, 2, 32, 8, 1>(c, psi, F, s);
+  return large ? launch_force_tiles<T, 3, 16, 16, 4>(c, psi, F, s) : launch_force_tiles<T, 3, 16, 4, 4>(c, psi, F, s);
+}
 }  // namespace
 
 }  // namespace ihmc
@@ -129,6 +210,12 @@ extern "C" int ihmc_force_noalloc(ihmc_ctx* ctx, const ihmc_lattice* lat, int32_
     return set_error(IHMC_E_INVAL, "lattice of %lld sites needs %llu bytes of scratch, the maximum is %llu",
                      (long long)c.N, (unsigned long long)l.end, (unsigned long long)kNoallocBytes);
   hipStream_t s = stream ? (hipStream_t)stream : ctx->stream;
+  const uint64_t bytes = (uint64_t)c.N * (uint64_t)precision;
+  const uintptr_t ip = (uintptr_t)psi, iF = (uintptr_t)F;
+  if (ip + bytes <= iF || iF + bytes <= ip) {
+    const hipError_t e = precision == 4 ? launch_force<float>(c, psi, F, s) : launch_force<double>(c, psi, F, s);
+    return e == hipSuccess ? IHMC_OK : hip_fail(ctx, e, "allocation-free force");
+  }
   unsigned char* base = (unsigned char*)ctx->scratch;
   const TileShape ts = tile_shape(c.precision, c.ndim, c.tile_cls);
   const unsigned tb = (unsigned)((c.n_tiles + 255) / 256);

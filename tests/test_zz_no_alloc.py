@@ -91,3 +91,52 @@ def test_noalloc_force_refusals(ctx):
     lat = ihmc.Lattice((8, 8), beta=0.4, C=4.1)
     psi = np.random.default_rng(3).standard_normal(64).astype(np.float32).astype(np.float64)
     assert np.array_equal(_noalloc(ctx, lat, psi, 4, False), ctx.force(lat, psi, precision=4))
+
+
+# the smallest lattices (a tile holds several periodic images), tile edges and one
+# beyond, rows of odd length, the tiles of four sites a thread and their edges
+DIRECT = [(3, 3), (3, 70), (32, 8), (33, 9), (31, 7), (130, 5), (1024, 1024), (1031, 1030),
+          (3, 3, 3), (16, 4, 4), (17, 5, 5), (5, 33, 3), (15, 9, 21), (128, 128, 64), (107, 101, 99)]
+
+
+@pytest.mark.parametrize("prec", [4, 8])
+@pytest.mark.parametrize("L", DIRECT)
+def test_noalloc_force_apart_in_place_and_unaligned(ctx, prec, L):
+    """Separate arrays (one launch) at any element alignment, in place and half
+    overlapping (staged): the bits of ihmc_force."""
+    import torch
+    from paper_1912_03278_amd import ihmc
+    dt = torch.float32 if prec == 4 else torch.float64
+    N = int(np.prod(L))
+    lat = ihmc.Lattice(L, beta=0.3, C=2 * len(L) + 0.2, h=0.03)
+    psi = np.random.default_rng(N).standard_normal(N)
+    psi = psi.astype(np.float32).astype(np.float64) if prec == 4 else psi
+    ref = ctx.force(lat, psi, precision=prec)
+    for off_p, off_F in ((0, N), (1, N + 4), (3, 2 * N + 3), (0, 0), (2, 2 + N // 2), (N // 3, 1)):
+        buf = torch.full((3 * N + 8,), float("nan"), dtype=dt, device="cuda")
+        buf[off_p:off_p + N] = torch.tensor(psi, dtype=dt, device="cuda")
+        torch.cuda.synchronize()
+        ctx.force_noalloc(lat, buf.data_ptr() + off_p * prec, buf.data_ptr() + off_F * prec, precision=prec)
+        ctx.sync()
+        got = buf[off_F:off_F + N].cpu().numpy().astype(np.float64)
+        assert np.array_equal(got, ref), (off_p, off_F)
+
+
+def test_noalloc_force_under_capture(ctx):
+    """Captured on the caller's stream and replayed on changed fields."""
+    import torch
+    from paper_1912_03278_amd import ihmc
+    lat = ihmc.Lattice((45, 37), beta=0.4, C=4.2, h=0.02)
+    rng = np.random.default_rng(8)
+    x = torch.zeros(45 * 37, dtype=torch.float64, device="cuda")
+    F = torch.zeros_like(x)
+    g, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        ctx.force_noalloc(lat, x.data_ptr(), F.data_ptr(), precision=8, stream=s.cuda_stream)
+    for _ in range(3):
+        psi = rng.standard_normal(45 * 37)
+        x.copy_(torch.tensor(psi))
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(F.cpu().numpy(), ctx.force(lat, psi, precision=8))
