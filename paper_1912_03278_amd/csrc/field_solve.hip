@@ -2,15 +2,19 @@
 // eq. phi_psi_substitution): the estimator constants h'^T Kt^-1 h' and
 // 1^T Kt^-1 h', and x itself for chains that run in translated coordinates.
 //
+// x enters the starting field of a translated chain, and a trajectory in FP64
+// amplifies a last digit of it to 1e-3 in 200 trajectories, so x comes from the
+// conjugate gradients that always gave it, operation for operation (k_field_cg),
+// and a seed keeps its trajectory.  The constants enter the estimators only.
+//
 // On the periodic lattice Kt is diagonal in the real plane waves
 // prod_d cas(2 pi k_d x_d / L_d), cas = cos + sin (the shift operators along an
 // axis come in symmetric pairs, which have cos and sin of one frequency as
 // eigenvectors of the same eigenvalue), with eigenvalues
 //     lambda(k) = C + 2 sum_d cos(2 pi k_d / L_d)
 //               = (C - 2 ndim) + sum_d 4 cos^2(pi k_d / L_d),
-// the second form exact to rounding also where C barely exceeds 2 ndim.  So the
-// solve is a separable Hartley transform H of h', a division by lambda and (for
-// x) the same transform again, over N:
+// the second form exact to rounding also where C barely exceeds 2 ndim.  So they
+// take a separable Hartley transform H of h' and a division by lambda:
 //     h'^T Kt^-1 h' = sum_k H(k)^2 / (N lambda(k)),   1^T Kt^-1 h' = H(0) / (2 ndim + C).
 //
 // One axis of all chains is one launch: out[k] = sum_j cas(2 pi j k / L) in[j],
@@ -138,18 +142,17 @@ __device__ __forceinline__ double axis_eig(int k, int L) {
   return 4.0 * (cs * cs);
 }
 
-// In array `src`: H(k) -> H(k) / (N lambda(k)); partial sums of H^2 / (N lambda)
-// over CHUNK modes each, one workgroup per chunk, in a fixed order.
-__global__ __launch_bounds__(FTHREADS) void k_fs_scale(ChainDev* __restrict__ cds, const int* __restrict__ which,
+// Partial sums of H^2 / (N lambda) of the transform in array `src`, over CHUNK modes
+// each, one workgroup per chunk, in a fixed order.
+__global__ __launch_bounds__(FTHREADS) void k_fs_sums(ChainDev* __restrict__ cds, const int* __restrict__ which,
                                                        double* work, const int64_t* __restrict__ woff, int src) {
   __shared__ double sh[FTHREADS / 64];
   ChainDev& cd = cds[which[blockIdx.y]];
   double* w = work + woff[blockIdx.y];
-  double* H = w + src * cd.N;
+  const double* H = w + src * cd.N;
   const int64_t nchunk = (cd.N + CHUNK - 1) / CHUNK;
   const double gap = cd.C - 2.0 * cd.ndim, n = (double)cd.N;
   if (blockIdx.x == 0 && threadIdx.x == 0) cd.c_m = H[0] / (2.0 * cd.ndim + cd.C);
-  __syncthreads();
   for (int64_t b = blockIdx.x; b < nchunk; b += gridDim.x) {
     double s = 0.0;
     for (int e = threadIdx.x; e < CHUNK; e += FTHREADS) {
@@ -159,9 +162,7 @@ __global__ __launch_bounds__(FTHREADS) void k_fs_scale(ChainDev* __restrict__ cd
       const int64_t r = i / cd.L0;
       double lam = gap + axis_eig(x, cd.L0) + axis_eig((int)(r % cd.L1), cd.L1);
       if (cd.ndim == 3) lam += axis_eig((int)(r / cd.L1), cd.L2);
-      const double h = H[i], y = h / (n * lam);
-      s += h * y;
-      H[i] = y;
+      s += H[i] * (H[i] / (n * lam));
     }
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
@@ -183,15 +184,96 @@ __global__ __launch_bounds__(64) void k_fs_final(ChainDev* __restrict__ cds, con
   if (threadIdx.x == 0) cd.c_e = s;
 }
 
+// Sum over a block of 256 threads in a fixed order, broadcast to all of them.
+__device__ double block_sum(double v, double* sh) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double t = 0.0;
+  for (int w = 0; w < FTHREADS / 64; ++w) t += sh[w];
+  return t;
+}
+
+// y = Kt x in site order.
+__device__ void apply_kt(const ChainDev& cd, const double* x, double* y) {
+  const int L0 = cd.L0, L1 = cd.L1, L2 = cd.L2;
+  for (int64_t s = threadIdx.x; s < cd.N; s += FTHREADS) {
+    const int gx = (int)(s % L0);
+    const int gy = (int)((s / L0) % L1);
+    const int gz = (int)(s / ((int64_t)L0 * L1));
+    auto at = [&](int a, int b, int c) { return x[a + (int64_t)L0 * (b + (int64_t)L1 * c)]; };
+    double acc = (at(gx == 0 ? L0 - 1 : gx - 1, gy, gz) + at(gx == L0 - 1 ? 0 : gx + 1, gy, gz)) +
+                 (at(gx, gy == 0 ? L1 - 1 : gy - 1, gz) + at(gx, gy == L1 - 1 ? 0 : gy + 1, gz));
+    if (cd.ndim == 3) acc += at(gx, gy, gz == 0 ? L2 - 1 : gz - 1) + at(gx, gy, gz == L2 - 1 ? 0 : gz + 1);
+    y[s] = cd.C * x[s] + acc;
+  }
+}
+
+// x = Kt^-1 h' by conjugate gradients, to a relative residual of 1e-15: one block
+// per chain, x in site order at the start of its work space.  With it the constants.
+__global__ __launch_bounds__(FTHREADS) void k_field_cg(ChainDev* __restrict__ cds, const int* __restrict__ which,
+                                                       double* work, const int64_t* __restrict__ woff) {
+  __shared__ double sh[FTHREADS / 64];
+  ChainDev& cd = cds[which[blockIdx.x]];
+  const int64_t N = cd.N;
+  double* x = work + woff[blockIdx.x];
+  double* r = x + N;
+  double* d = r + N;
+  double* q = d + N;
+  double hs = 0.0, rr = 0.0;
+  for (int64_t i = threadIdx.x; i < N; i += FTHREADS) {
+    const double v = cd.hp[stored_index(cd, i)];
+    x[i] = 0.0;
+    r[i] = v;
+    d[i] = v;
+    hs += v;
+    rr += v * v;
+  }
+  hs = block_sum(hs, sh);
+  rr = block_sum(rr, sh);
+  const double stop = 1e-30 * rr;
+  for (int it = 0; it < 20000 && rr > stop; ++it) {
+    __syncthreads();
+    apply_kt(cd, d, q);
+    __syncthreads();
+    double dq = 0.0;
+    for (int64_t i = threadIdx.x; i < N; i += FTHREADS) dq += d[i] * q[i];
+    dq = block_sum(dq, sh);
+    const double alpha = rr / dq;
+    double rn = 0.0;
+    for (int64_t i = threadIdx.x; i < N; i += FTHREADS) {
+      x[i] += alpha * d[i];
+      r[i] -= alpha * q[i];
+      rn += r[i] * r[i];
+    }
+    rn = block_sum(rn, sh);
+    const double beta = rn / rr;
+    rr = rn;
+    for (int64_t i = threadIdx.x; i < N; i += FTHREADS) d[i] = r[i] + beta * d[i];
+  }
+  __syncthreads();
+  double ce = 0.0;
+  for (int64_t i = threadIdx.x; i < N; i += FTHREADS) ce += cd.hp[stored_index(cd, i)] * x[i];
+  ce = block_sum(ce, sh);
+  if (threadIdx.x == 0) {
+    cd.c_e = ce;
+    cd.c_m = hs / (2.0 * cd.ndim + cd.C);
+  }
+}
+
 }  // namespace
 
 hipError_t launch_field_solve(ChainDev* d_cd, const std::vector<const ChainDev*>& host, const int* which, double* work,
-                              const int64_t* woff, bool need_x, hipStream_t s) {
-  if (host.empty()) return hipSuccess;
+                              const int64_t* woff, size_t plain, hipStream_t s) {
+  if (plain < host.size())
+    k_field_cg<<<(unsigned)(host.size() - plain), FTHREADS, 0, s>>>(d_cd, which + plain, work, woff + plain);
+  if (plain == 0) return hipGetLastError();
   // largest number of tiles, sites and dimensions among the chains
   int64_t tiles = 1, sites = 1;
   int nd = 2;
-  for (const ChainDev* c : host) {
+  for (size_t i = 0; i < plain; ++i) {
+    const ChainDev* c = host[i];
     const int64_t L[3] = {c->L0, c->L1, c->L2};
     for (int a = 0; a < c->ndim; ++a)
       tiles = std::max(tiles, ((L[a] + FT - 1) / FT) * ((c->N / L[a] + FT - 1) / FT));
@@ -200,18 +282,16 @@ hipError_t launch_field_solve(ChainDev* d_cd, const std::vector<const ChainDev*>
   }
   auto grid_x = [](int64_t n) { return (unsigned)std::min<int64_t>(n, MAX_GRID_X); };
   // the chains fill grid.y, at most 65535 at a time
-  for (size_t c0 = 0; c0 < host.size(); c0 += 65535) {
-    const unsigned n = (unsigned)std::min<size_t>(host.size() - c0, 65535);
+  for (size_t c0 = 0; c0 < plain; c0 += 65535) {
+    const unsigned n = (unsigned)std::min<size_t>(plain - c0, 65535);
     const int* wh = which + c0;
     const int64_t* wo = woff + c0;
     const dim3 gs(grid_x((sites + 4 * FTHREADS - 1) / (4 * FTHREADS)), n), gt(grid_x(tiles), n);
     k_fs_init<<<gs, FTHREADS, 0, s>>>(d_cd, wh, work, wo);
     for (int a = 0; a < nd; ++a) k_fs_axis<<<gt, FTHREADS, 0, s>>>(d_cd, wh, work, wo, a, a & 1);
     const int at = nd & 1;  // the array that holds the transform
-    k_fs_scale<<<dim3(grid_x((sites + CHUNK - 1) / CHUNK), n), FTHREADS, 0, s>>>(d_cd, wh, work, wo, at);
+    k_fs_sums<<<dim3(grid_x((sites + CHUNK - 1) / CHUNK), n), FTHREADS, 0, s>>>(d_cd, wh, work, wo, at);
     k_fs_final<<<n, 64, 0, s>>>(d_cd, wh, work, wo);
-    if (need_x)  // back: ends in the first array
-      for (int a = 0; a < nd; ++a) k_fs_axis<<<gt, FTHREADS, 0, s>>>(d_cd, wh, work, wo, a, (at + a) & 1);
   }
   return hipGetLastError();
 }

@@ -616,12 +616,13 @@ int Chains::build(int32_t n_, const ihmc_lattice* lats, const ihmc_run* runs, in
   std::vector<int64_t> fs_off;
   std::vector<const ChainDev*> fs_cd;
   int64_t fs_total = 0;
-  bool translated = false;
+  const size_t fs_plain =
+      std::stable_partition(fs_idx.begin(), fs_idx.end(), [&](int i) { return runs[i].form != FORM_SHIFTED; }) -
+      fs_idx.begin();
   for (int i : fs_idx) {
     fs_off.push_back(fs_total);
     fs_cd.push_back(&cd[i]);
     fs_total += 4 * cd[i].N;
-    translated = translated || runs[i].form == FORM_SHIFTED;
   }
   if (!fs_idx.empty()) {
     double* work = (double*)tmp_alloc(8 * (uint64_t)fs_total);
@@ -633,7 +634,7 @@ int Chains::build(int32_t n_, const ihmc_lattice* lats, const ihmc_run* runs, in
     }
     HIPCHK(hipMemcpyAsync(didx, fs_idx.data(), sizeof(int) * fs_idx.size(), hipMemcpyHostToDevice, s), "field solve index");
     HIPCHK(hipMemcpyAsync(doff, fs_off.data(), sizeof(int64_t) * fs_off.size(), hipMemcpyHostToDevice, s), "field solve offsets");
-    HIPCHK(launch_field_solve(d_cd, fs_cd, didx, work, doff, translated, s), "field solve");
+    HIPCHK(launch_field_solve(d_cd, fs_cd, didx, work, doff, fs_plain, s), "field solve");
     // shifted-form chains with this field: delta = Kt^-1 h' / sqrt(J') (the solve's x)
     for (size_t j = 0; j < fs_idx.size(); ++j) {
       const int i = fs_idx[j];

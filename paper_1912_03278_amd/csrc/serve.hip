@@ -407,7 +407,7 @@ bool ihmc_server::admit_setup(std::vector<Request*>& fresh) {
     return p;
   };
   std::vector<Request*> ok;
-  std::vector<int> fs_slots;
+  std::vector<int> fs_slots, fs_translated;
   std::vector<int64_t> fs_off;
   int64_t fs_total = 0;
   // the set-up runs with the device idle: the round in flight finishes first
@@ -465,9 +465,7 @@ bool ihmc_server::admit_setup(std::vector<Request*>& fresh) {
       if (!t) e = hipErrorOutOfMemory;
       if (e == hipSuccess) e = hipMemcpyAsync(t, r->h.data(), 8 * c.N, hipMemcpyHostToDevice, s);
       if (e == hipSuccess) e = launch_field_setup(d_cd, r->slot, t, r->lat.beta, c.N, c.precision, s);
-      fs_slots.push_back(r->slot);
-      fs_off.push_back(fs_total);
-      fs_total += 4 * c.N;
+      (r->run.form == FORM_SHIFTED ? fs_translated : fs_slots).push_back(r->slot);
     }
     const bool translated = r->run.form == FORM_SHIFTED && c.h_kind == 2;
     if (e == hipSuccess) {
@@ -485,7 +483,13 @@ bool ihmc_server::admit_setup(std::vector<Request*>& fresh) {
     if (e != hipSuccess) break;
     ok.push_back(r);
   }
+  const size_t fs_plain = fs_slots.size();
+  fs_slots.insert(fs_slots.end(), fs_translated.begin(), fs_translated.end());
   if (e == hipSuccess && !fs_slots.empty()) {
+    for (int k : fs_slots) {
+      fs_off.push_back(fs_total);
+      fs_total += 4 * cd_host[k].N;
+    }
     double* work = (double*)tmp(8 * (uint64_t)fs_total);
     int* which = (int*)tmp(sizeof(int) * fs_slots.size());
     int64_t* woff = (int64_t*)tmp(sizeof(int64_t) * fs_off.size());
@@ -494,9 +498,7 @@ bool ihmc_server::admit_setup(std::vector<Request*>& fresh) {
     if (e == hipSuccess) e = hipMemcpyAsync(woff, fs_off.data(), sizeof(int64_t) * fs_off.size(), hipMemcpyHostToDevice, s);
     std::vector<const ChainDev*> host;
     for (int slot : fs_slots) host.push_back(&cd_host[slot]);
-    bool translated = false;
-    for (Request* r : ok) translated = translated || (r->run.form == FORM_SHIFTED && r->cd.h_kind == 2);
-    if (e == hipSuccess) e = launch_field_solve(d_cd, host, which, work, woff, translated, s);
+    if (e == hipSuccess) e = launch_field_solve(d_cd, host, which, work, woff, fs_plain, s);
     // translated requests: delta = x / sqrt(J') (x = Kt^-1 h' of the solve), then
     // the starting field psi0 + delta, as a chain set starts it
     for (Request* r : ok) {
