@@ -291,13 +291,8 @@ __device__ __forceinline__ void block_store_ranks(const ChainDev& cd, const u128
     // the four lanes of each residue within a row (DPP), then across rows
     v = add128(v, dpp_u128<DPP_ROW_ROR4>(v));
     v = add128(v, dpp_u128<DPP_ROW_ROR8>(v));
-#pragma unroll
-    for (int off = 16; off < 64; off <<= 1) {
-      u128 o;
-      o.lo = __shfl_xor(v.lo, off, 64);
-      o.hi = __shfl_xor(v.hi, off, 64);
-      v = add128(v, o);
-    }
+    v = pair_sum128<false>(v);  // the four rows
+    v = pair_sum128<true>(v);
     const int r = 4 * k + lane;
     if (lane < 4 && r < nterms) sRedR[wave][t0 + r] = v;
   }

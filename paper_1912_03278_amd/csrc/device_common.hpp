@@ -276,6 +276,27 @@ __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int l) {
          ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l) << 32);
 }
 
+// v of the even rows (16 lanes) plus v of the odd ones beside them, and v of the
+// lower half of the wave plus v of the upper, the same value in all of them: a
+// swap of rows or halves between two registers that start as copies (VALU, no
+// LDS round trip).
+template <bool HALVES>
+__device__ __forceinline__ u128 pair_sum128(u128 v) {
+  u128 a, b;
+  auto swapped = [](uint64_t x, uint64_t& p, uint64_t& q) {
+    const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
+    const auto l = HALVES ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                          : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = HALVES ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                          : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    p = (uint64_t)l[0] | ((uint64_t)h[0] << 32);
+    q = (uint64_t)l[1] | ((uint64_t)h[1] << 32);
+  };
+  swapped(v.lo, a.lo, b.lo);
+  swapped(v.hi, a.hi, b.hi);
+  return add128(a, b);
+}
+
 // Sum over the 64 lanes of the wave, the same value in every lane; the whole
 // wave must be active.  Within each row by DPP (quads, half-rows, rows), then
 // the four row sums read out.  Integer sums: the order does not matter.

@@ -95,7 +95,7 @@ __global__ __launch_bounds__(NT, 4) void lattice_resident(const ChainDev* __rest
   __shared__ u128 sSum[RES_RANKS];
   __shared__ uint32_t sBad[NW];
   __shared__ ChainState sSt;
-  __shared__ double sAcc;
+  __shared__ double sAcc[2];  // accept uniforms, by the parity of the trajectory
   __shared__ uint32_t sFlags;
   const ChainDev& cd = chains[tiles[blockIdx.x].chain];
   const int L0 = cd.L0, L1 = cd.L1, L2 = (NDIM == 3) ? cd.L2 : 1;
@@ -250,13 +250,8 @@ __global__ __launch_bounds__(NT, 4) void lattice_resident(const ChainDev* __rest
         v = add128(v, dpp_u128<DPP_ROW_ROR4>(v));
         v = add128(v, dpp_u128<DPP_ROW_ROR8>(v));
       }
-#pragma unroll
-      for (int off = 16; off < 64; off <<= 1) {
-        u128 o;
-        o.lo = __shfl_xor(v.lo, off, 64);
-        o.hi = __shfl_xor(v.hi, off, 64);
-        v = add128(v, o);
-      }
+      v = pair_sum128<false>(v);  // the four rows
+      v = pair_sum128<true>(v);
       const int rk = GL * r + lane;
       if (lane < GL && rk < RES_RANKS) sRed[wave][rk] = v;
     }
@@ -327,17 +322,16 @@ __global__ __launch_bounds__(NT, 4) void lattice_resident(const ChainDev* __rest
   const T kick_even = (T)kd;
   const int npair = (N + 1) / 2;
 
-  for (int t = 0; t < n_traj; ++t) {
-    const int sign = sSt.sign;
-    const uint32_t traj = (uint32_t)sSt.traj;
-    load_field(sign);
-    // fresh momenta into sW, one Philox draw per site pair; one thread past the
-    // last pair draws the accept uniform
-    for (int pr = tid; pr <= npair; pr += NT) {
+  // Fresh momenta of trajectory `traj` into sW by threads t0, t0 + nt, ..: one
+  // Philox draw per site pair; the one past the last pair is the accept uniform.
+  // They need nothing of the trajectory before, so all waves but the first draw
+  // them while the first makes its Metropolis step (1.4 us of one thread).
+  auto draw_momenta = [&](uint32_t traj, int t0, int nt) {
+    for (int pr = t0; pr <= npair; pr += nt) {
       const bool mom = pr < npair;
       const uint4 w = draw(cd, mom ? (uint32_t)pr : 0u, traj, mom ? TAG_MOM : TAG_ACC);
       if (!mom) {
-        sAcc = unit53(w.x, w.y);
+        sAcc[traj & 1u] = unit53(w.x, w.y);
         continue;
       }
       double a, b;
@@ -347,6 +341,13 @@ __global__ __launch_bounds__(NT, 4) void lattice_resident(const ChainDev* __rest
       sW[r0 * PV + x0] = (T)a;
       if (2 * pr + 1 < N) sW[wrap ? (r0 + 1) * PV : r0 * PV + x0 + 1] = (T)b;
     }
+  };
+
+  draw_momenta((uint32_t)sSt.traj, tid, NT);
+  for (int t = 0; t < n_traj; ++t) {
+    const int sign = sSt.sign;
+    const uint32_t traj = (uint32_t)sSt.traj;
+    load_field(sign);
     lds_barrier();
     clear_acc();
     site_sums(NU1{}, 5, [&](int o, int64_t, int, int, int, int, int, int, double* v) {
@@ -431,7 +432,11 @@ __global__ __launch_bounds__(NT, 4) void lattice_resident(const ChainDev* __rest
       sum[T_K1] = sSum[0];
 #pragma unroll
       for (int a = 0; a < 4; ++a) sum[T_S + a] = sSum[1 + a];
-      sFlags = finalize_trajectory(cd, &sSt, cur, sum, b, 0.0, &sAcc);
+      sFlags = finalize_trajectory(cd, &sSt, cur, sum, b, 0.0, &sAcc[traj & 1u]);
+    }
+    if (t + 1 < n_traj) {
+      if (NW == 1) draw_momenta(traj + 1u, tid, NT);
+      else if (wave > 0) draw_momenta(traj + 1u, tid - 64, NT - 64);
     }
     lds_barrier();
     if (sFlags & REC_ACCEPT) {
