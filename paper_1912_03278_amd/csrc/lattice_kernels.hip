@@ -79,6 +79,14 @@ __device__ __forceinline__ ChunkPos chunk_pos(int x, int L0, bool x_near) {
   return cp;
 }
 
+// Store at device scope (sc1): the line goes on to the Infinity Cache at once.  A
+// plain store leaves it dirty in the XCD's L2, and the launch ends with a write-back of
+// all of them in one go, which nothing overlaps.
+template <typename T>
+__device__ __forceinline__ void st_through(gmem<T>* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Every lane issues the vector load (a gathering lane from the row start, and
 // discards it), so that the compiler keeps it one 16-byte access.
 template <typename T>
@@ -424,7 +432,21 @@ constexpr int MS_BX = 64;                            // widest tile
 constexpr int MS_RP = MS_BX + 2 * MS_HX;             // LDS row pitch
 static_assert(MS_HX % 4 == 0, "whole chunks of halo");
 
-template <typename T, int H>
+// The rows of a tile from p on as a raw buffer of 2 GiB (at most 64 rows of 2^20
+// values), for 16-byte stores through the L2 (see st_through).
+struct ThroughRows {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ explicit ThroughRows(gmem<float>* p)
+      : r(__builtin_amdgcn_make_buffer_rsrc((void*)(float*)p, 0, 0x7fffffff, 0x00020000)) {}
+  __device__ __forceinline__ void st4(int64_t i, const float (&v)[4]) const {
+    typedef uint32_t vu4 __attribute__((ext_vector_type(4)));
+    constexpr int SC1 = 16;
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(vu4, vf4{v[0], v[1], v[2], v[3]}), r, (int)(4 * i), 0,
+                                           SC1);
+  }
+};
+
+template <typename T, int H, bool THROUGH = false>
 __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __restrict__ chains,
                                                         const Tile* __restrict__ tiles, int n_tiles, int j, int k,
                                                         int max_steps) {
@@ -570,14 +592,20 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
     if (s + 1 < ns) lds_barrier();
   }
   const int gx = tl.x0 - MS_HX + 4 * c;
+  const int64_t base0 = (int64_t)pitch * tl.y0;  // the tile's first row
   if (act && c >= MS_CH && c < nch - MS_CH && gx < L0) {
 #pragma unroll
     for (int i = 0; i < H; ++i) {
       const int ty = r0 + i - (MS_HY - 2), gy = tl.y0 + ty;
       if (ty >= 0 && ty < by && gy < L1) {
         const int64_t base = gx + (int64_t)pitch * gy;  // gx + 3 < pitch
-        st4g<T>(pmo + base, pm[i]);
-        st4g<T>(pout + base, ps[i]);
+        if constexpr (THROUGH) {
+          ThroughRows(pmo + base0).st4(base - base0, pm[i]);
+          ThroughRows(pout + base0).st4(base - base0, ps[i]);
+        } else {
+          st4g<T>(pmo + base, pm[i]);
+          st4g<T>(pout + base, ps[i]);
+        }
       }
     }
   }
@@ -597,7 +625,7 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
 // are fetched before the staging.  Sums of the FP64 terms follow the same
 // order as in every other tiling: per column over each 4-plane slab in z order,
 // then per x-aligned quad of columns.
-template <typename T, int BX, int BY, int ZR, int MODE>
+template <typename T, int BX, int BY, int ZR, int MODE, bool THROUGH = false>
 __global__ __launch_bounds__(64 * ZR, 8) void lattice_pass3t(const ChainDev* __restrict__ chains,
                                                           const Tile* __restrict__ tiles, int n_tiles, int j,
                                                           int k) {
@@ -810,8 +838,14 @@ __global__ __launch_bounds__(64 * ZR, 8) void lattice_pass3t(const ChainDev* __r
         }
         const T pn = fma_t(kick, F, p);
         if (MODE == PASS_FIRST || MODE == PASS_MIDDLE) {
-          pmom[idx] = pn;
-          pout[idx] = fma_t(drift, pn, v);
+          const T vn = fma_t(drift, pn, v);
+          if (THROUGH) {
+            st_through(pmom + idx, pn);
+            st_through(pout + idx, vn);
+          } else {
+            pmom[idx] = pn;
+            pout[idx] = vn;
+          }
         } else if (MODE == PASS_FORCE) {
           pmom[idx] = pn;
         } else if (MODE == PASS_LAST) {
@@ -922,21 +956,34 @@ void steps_tiles(const StepShape& g, int chain, int L0, int L1, std::vector<Tile
     for (int x = 0; x < L0; x += bx) out.push_back(Tile{chain, x, y, bx | (by << 16)});
 }
 
+template <typename T, bool THROUGH>
+static void launch_steps(const StepShape& g, dim3 grid, dim3 block, size_t lds, const ChainDev* chains,
+                         const Tile* tiles, int n_tiles, int j, int k, int max_steps, hipStream_t s) {
+  if (g.H == 1) lattice_steps2v<T, 1, THROUGH><<<grid, block, lds, s>>>(chains, tiles, n_tiles, j, k, max_steps);
+  else if (g.H == 2) lattice_steps2v<T, 2, THROUGH><<<grid, block, lds, s>>>(chains, tiles, n_tiles, j, k, max_steps);
+  else if constexpr (sizeof(T) == 4)
+    lattice_steps2v<T, 3, THROUGH><<<grid, block, lds, s>>>(chains, tiles, n_tiles, j, k, max_steps);
+}
+
 hipError_t launch_lattice_steps(int precision, const StepShape& g, const ChainDev* chains, const Tile* tiles,
                                 int n_tiles, int j, int k, int max_steps, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
   if (max_steps < 1 || max_steps > STEPS || g.threads < 64 || g.threads > 1024) return hipErrorInvalidValue;
+  if (g.H < 1 || g.H > (precision == 4 ? 3 : 2)) return hipErrorInvalidValue;
   const size_t lds = 2 * (size_t)g.rows * MS_RP * (size_t)precision;
   const dim3 grid((unsigned)n_tiles), block((unsigned)g.threads);
   if (precision == 4) {
-    if (g.H == 1) lattice_steps2v<float, 1><<<grid, block, lds, s>>>(chains, tiles, n_tiles, j, k, max_steps);
-    else if (g.H == 2) lattice_steps2v<float, 2><<<grid, block, lds, s>>>(chains, tiles, n_tiles, j, k, max_steps);
-    else if (g.H == 3) lattice_steps2v<float, 3><<<grid, block, lds, s>>>(chains, tiles, n_tiles, j, k, max_steps);
-    else return hipErrorInvalidValue;
+    // Stores through the L2 where CUs hold more than one workgroup, so that others run while
+    // one stores (us a trajectory: 1024^2 88 -> 84, 1448^2 145 -> 134, 100 x 90 x 256
+    // 103 -> 97, 512^2 x 8 88 -> 83; one a CU: 100 x 90 x 64 47.0 -> 47.7, 256^2 43.9 ->
+    // 44.3), up to what the L2s hold: sets beyond write back within the launch anyway, and
+    // the parts of lines at ragged rows' ends go out twice (a set of 2048 uneven chains
+    // 3.64e11 -> 3.55e11 site-MD-steps/s).  Not in FP64, whose two 16-byte stores a chunk
+    // each cover half of every 32 bytes (512^2 x 16 566 -> 596, 2048^2 890 -> 932).
+    if (n_tiles > 256 && n_tiles <= 2048) launch_steps<float, true>(g, grid, block, lds, chains, tiles, n_tiles, j, k, max_steps, s);
+    else launch_steps<float, false>(g, grid, block, lds, chains, tiles, n_tiles, j, k, max_steps, s);
   } else {
-    if (g.H == 1) lattice_steps2v<double, 1><<<grid, block, lds, s>>>(chains, tiles, n_tiles, j, k, max_steps);
-    else if (g.H == 2) lattice_steps2v<double, 2><<<grid, block, lds, s>>>(chains, tiles, n_tiles, j, k, max_steps);
-    else return hipErrorInvalidValue;
+    launch_steps<double, false>(g, grid, block, lds, chains, tiles, n_tiles, j, k, max_steps, s);
   }
   return hipGetLastError();
 }
@@ -978,7 +1025,17 @@ static hipError_t launch_mode3t(int mode, const ChainDev* chains, const Tile* ti
       lattice_pass3t<T, BX, BY, ZR, PASS_FIRST><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
       break;
     case PASS_MIDDLE:
-      lattice_pass3t<T, BX, BY, ZR, PASS_MIDDLE><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
+      // Stores go through the L2 (see st_through) in launches of over 1M sites (n_tiles ZR
+      // 256), half of the resident boxes: below, too few blocks share a CU to hide the
+      // longer stores (FP32: 64^3 112 -> 126 us a trajectory, 96^3 153 -> 158; above,
+      // 128^3 224 -> 222, 160^3 378 -> 357, 8 chains of 64^3 217 -> 201; FP64 128^3 680
+      // -> 645).  Above the 32 MiB of the L2s' field (8M sites in FP32, 4M in FP64) most lines
+      // are written back within the launch anyway (512 chains of 24 x 21 x 30 1108 -> 1109,
+      // FP64 4000 -> 4040).  Two kernels: the choice inside one costs 1.5 % below 1M.
+      if ((int64_t)n_tiles * ZR > 4096 && (int64_t)n_tiles * ZR * (int)sizeof(T) <= 131072)
+        lattice_pass3t<T, BX, BY, ZR, PASS_MIDDLE, true><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
+      else
+        lattice_pass3t<T, BX, BY, ZR, PASS_MIDDLE><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
       break;
     case PASS_LAST:
       lattice_pass3t<T, BX, BY, ZR, PASS_LAST><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
