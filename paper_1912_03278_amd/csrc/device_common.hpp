@@ -297,6 +297,19 @@ __device__ __forceinline__ u128 pair_sum128(u128 v) {
   return add128(a, b);
 }
 
+// 16-byte store of base[i .. i + 3] at device scope (sc1): the line goes on to the
+// Infinity Cache at once.  A plain store leaves it dirty in the XCD's L2, and the
+// launch ends with a write-back of all of them in one go, which nothing overlaps.
+// base is the same in all lanes, i below 2^29.
+typedef float vec4f __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void st4_through(float* base, int64_t i, vec4f v) {
+  typedef uint32_t vec4u __attribute__((ext_vector_type(4)));
+  constexpr int SC1 = 16;
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(vec4u, v),
+                                         __builtin_amdgcn_make_buffer_rsrc(base, 0, 0x7fffffff, 0x00020000),
+                                         (int)(4 * i), 0, SC1);
+}
+
 // Sum over the 64 lanes of the wave, the same value in every lane; the whole
 // wave must be active.  Within each row by DPP (quads, half-rows, rows), then
 // the four row sums read out.  Integer sums: the order does not matter.

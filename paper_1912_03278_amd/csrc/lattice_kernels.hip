@@ -79,9 +79,7 @@ __device__ __forceinline__ ChunkPos chunk_pos(int x, int L0, bool x_near) {
   return cp;
 }
 
-// Store at device scope (sc1): the line goes on to the Infinity Cache at once.  A
-// plain store leaves it dirty in the XCD's L2, and the launch ends with a write-back of
-// all of them in one go, which nothing overlaps.
+// One value, as st4_through.
 template <typename T>
 __device__ __forceinline__ void st_through(gmem<T>* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -432,20 +430,6 @@ constexpr int MS_BX = 64;                            // widest tile
 constexpr int MS_RP = MS_BX + 2 * MS_HX;             // LDS row pitch
 static_assert(MS_HX % 4 == 0, "whole chunks of halo");
 
-// The rows of a tile from p on as a raw buffer of 2 GiB (at most 64 rows of 2^20
-// values), for 16-byte stores through the L2 (see st_through).
-struct ThroughRows {
-  __amdgpu_buffer_rsrc_t r;
-  __device__ __forceinline__ explicit ThroughRows(gmem<float>* p)
-      : r(__builtin_amdgcn_make_buffer_rsrc((void*)(float*)p, 0, 0x7fffffff, 0x00020000)) {}
-  __device__ __forceinline__ void st4(int64_t i, const float (&v)[4]) const {
-    typedef uint32_t vu4 __attribute__((ext_vector_type(4)));
-    constexpr int SC1 = 16;
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(vu4, vf4{v[0], v[1], v[2], v[3]}), r, (int)(4 * i), 0,
-                                           SC1);
-  }
-};
-
 template <typename T, int H, bool THROUGH = false>
 __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __restrict__ chains,
                                                         const Tile* __restrict__ tiles, int n_tiles, int j, int k,
@@ -600,8 +584,9 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
       if (ty >= 0 && ty < by && gy < L1) {
         const int64_t base = gx + (int64_t)pitch * gy;  // gx + 3 < pitch
         if constexpr (THROUGH) {
-          ThroughRows(pmo + base0).st4(base - base0, pm[i]);
-          ThroughRows(pout + base0).st4(base - base0, ps[i]);
+          // at most 64 rows of 2^20 values
+          st4_through((float*)(pmo + base0), base - base0, vf4{pm[i][0], pm[i][1], pm[i][2], pm[i][3]});
+          st4_through((float*)(pout + base0), base - base0, vf4{ps[i][0], ps[i][1], ps[i][2], ps[i][3]});
         } else {
           st4g<T>(pmo + base, pm[i]);
           st4g<T>(pout + base, ps[i]);
@@ -977,7 +962,7 @@ hipError_t launch_lattice_steps(int precision, const StepShape& g, const ChainDe
     // one stores (us a trajectory: 1024^2 88 -> 84, 1448^2 145 -> 134, 100 x 90 x 256
     // 103 -> 97, 512^2 x 8 88 -> 83; one a CU: 100 x 90 x 64 47.0 -> 47.7, 256^2 43.9 ->
     // 44.3), up to what the L2s hold: sets beyond write back within the launch anyway, and
-    // the parts of lines at ragged rows' ends go out twice (a set of 2048 uneven chains
+    // the parts of lines at ragged rows' ends go out twice (a set of 4096 uneven chains
     // 3.64e11 -> 3.55e11 site-MD-steps/s).  Not in FP64, whose two 16-byte stores a chunk
     // each cover half of every 32 bytes (512^2 x 16 566 -> 596, 2048^2 890 -> 932).
     if (n_tiles > 256 && n_tiles <= 2048) launch_steps<float, true>(g, grid, block, lds, chains, tiles, n_tiles, j, k, max_steps, s);
