@@ -310,6 +310,12 @@ __device__ __forceinline__ void st4_through(float* base, int64_t i, vec4f v) {
                                          (int)(4 * i), 0, SC1);
 }
 
+// One value, as st4_through.
+template <typename T>
+__device__ __forceinline__ void st_through(__attribute__((address_space(1))) T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Sum over the 64 lanes of the wave, the same value in every lane; the whole
 // wave must be active.  Within each row by DPP (quads, half-rows, rows), then
 // the four row sums read out.  Integer sums: the order does not matter.

@@ -79,12 +79,6 @@ __device__ __forceinline__ ChunkPos chunk_pos(int x, int L0, bool x_near) {
   return cp;
 }
 
-// One value, as st4_through.
-template <typename T>
-__device__ __forceinline__ void st_through(gmem<T>* p, T v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // Every lane issues the vector load (a gathering lane from the row start, and
 // discards it), so that the compiler keeps it one 16-byte access.
 template <typename T>

@@ -116,8 +116,9 @@ __global__ void k_noalloc_export(const unsigned char* base, T* __restrict__ dst)
 // passes over memory and LDS, take four sites a thread, which halves the halo (2D
 // 1.33 loads and 1.16 w a site, 3D 3.1 and 1.9).  Back-to-back calls, against
 // descriptor, import, pass and export in four launches: 48 x 40 FP32 13.5 -> 5.0
-// us, 1024^2 17.1 -> 5.2, 1900^2 31.1 -> 12.1, 100^3 19.3 -> 12.7, 150^3 34.8 ->
-// 29.9, 110^3 FP64 44.9 -> 30.7.
+// us, 1024^2 17.1 -> 5.2, 1900^2 31.1 -> 11.3, 100^3 19.3 -> 12.6, 150^3 34.8 ->
+// 28.1, 110^3 FP64 44.9 -> 29.8.  The large ones' stores go through the L2 (plainly 1900^2 12.4,
+// 150^3 30.0, 110^3 FP64 30.7).
 template <typename T>
 struct ForceArgs {
   T C, a, hw, b;
@@ -161,8 +162,11 @@ __global__ __launch_bounds__(256) void k_force(ForceArgs<T> q, const T* __restri
     if (NDIM == 3) n = n + (w[-WX * WY] + w[WX * WY]);
     const T f = fma_t(q.C, w[0], n) + q.b;
     const int gx = x0 + x, gy = y0 + y, gz = z0 + z;
-    if (gx < q.L0 && gy < q.L1 && gz < q.L2)
-      F[gx + (int64_t)q.L0 * (gy + (int64_t)q.L1 * gz)] = fma_t((T)1, f, (T)0);
+    if (gx < q.L0 && gy < q.L1 && gz < q.L2) {
+      gmem<T>* o = (gmem<T>*)F + (gx + (int64_t)q.L0 * (gy + (int64_t)q.L1 * gz));
+      if constexpr (BX * BY * BZ > 256) st_through<T>(o, fma_t((T)1, f, (T)0));
+      else *o = fma_t((T)1, f, (T)0);
+    }
   }
 }
 
