@@ -590,6 +590,15 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
   }
 }
 
+enum class StoreKind { plain, through, nontemporal };
+
+template <StoreKind ST, typename T>
+__device__ __forceinline__ void store_as(gmem<T>* p, T v) {
+  if constexpr (ST == StoreKind::through) st_through(p, v);
+  else if constexpr (ST == StoreKind::nontemporal) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
 // ------------------------------------------------------------ 3D, one phase ---
 //
 // A block owns a BX x BY x ZR box, one thread per x-y column and aligned
@@ -604,7 +613,7 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
 // are fetched before the staging.  Sums of the FP64 terms follow the same
 // order as in every other tiling: per column over each 4-plane slab in z order,
 // then per x-aligned quad of columns.
-template <typename T, int BX, int BY, int ZR, int MODE, bool THROUGH = false>
+template <typename T, int BX, int BY, int ZR, int MODE, StoreKind ST = StoreKind::plain>
 __global__ __launch_bounds__(64 * ZR, 8) void lattice_pass3t(const ChainDev* __restrict__ chains,
                                                           const Tile* __restrict__ tiles, int n_tiles, int j,
                                                           int k) {
@@ -818,13 +827,8 @@ __global__ __launch_bounds__(64 * ZR, 8) void lattice_pass3t(const ChainDev* __r
         const T pn = fma_t(kick, F, p);
         if (MODE == PASS_FIRST || MODE == PASS_MIDDLE) {
           const T vn = fma_t(drift, pn, v);
-          if (THROUGH) {
-            st_through(pmom + idx, pn);
-            st_through(pout + idx, vn);
-          } else {
-            pmom[idx] = pn;
-            pout[idx] = vn;
-          }
+          store_as<ST>(pmom + idx, pn);
+          store_as<ST>(pout + idx, vn);
         } else if (MODE == PASS_FORCE) {
           pmom[idx] = pn;
         } else if (MODE == PASS_LAST) {
@@ -994,9 +998,36 @@ static hipError_t launch_mode2v(int mode, const ChainDev* chains, const Tile* ti
   return hipGetLastError();
 }
 
+// Stores of the 3D middle pass by the memory a launch touches (four values a site,
+// two read and two written; n_tiles ZR 256 sites), against the L2s' 32 MiB together.
+// us a trajectory of 20 steps:
+// - up to 32 MiB, where no other 3D group runs beside it (sole), nontemporal: the lines
+//   leave the L2s before the launch's end, and the next one finds them in the Infinity
+//   Cache (plain, through, nontemporal: 64^3 113, 126, 113; 112^3 199, 197, 191; 128^3
+//   224, 222, 205; FP64 96^3 359, 357, 339; beside other groups 30 chains of 16^3 .. 70^3
+//   in three classes 224, -, 228);
+// - from 1M sites (two boxes a CU, which hide the longer stores) to 128 MiB through the L2
+//   (st4_through): 160^3 378, 357, 445; 256
+//   chains of 24 x 21 x 30 620, 589, 671; FP64 128^3 680, 641, 709;
+// - above plainly: most lines are written back within the launch anyway (512 chains of
+//   24 x 21 x 30 1108, 1109; FP64 4000, 4040; 256^3 nontemporal 1170 -> 1570).
+// Three kernels: a choice inside one costs small launches 1.5 %.
+template <typename T, int BX, int BY, int ZR>
+static void launch_middle3t(const ChainDev* chains, const Tile* tiles, int n_tiles, int j, int k, bool sole,
+                            hipStream_t s) {
+  const dim3 grid(n_tiles), block(64 * ZR);
+  const int64_t touched = (int64_t)n_tiles * ZR * 256 * 4 * (int)sizeof(T), l2 = 32 << 20;
+  if (touched <= l2 && sole)
+    lattice_pass3t<T, BX, BY, ZR, PASS_MIDDLE, StoreKind::nontemporal><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
+  else if ((int64_t)n_tiles * ZR > 4096 && touched <= 4 * l2)
+    lattice_pass3t<T, BX, BY, ZR, PASS_MIDDLE, StoreKind::through><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
+  else
+    lattice_pass3t<T, BX, BY, ZR, PASS_MIDDLE><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
+}
+
 template <typename T, int BX, int BY, int ZR>
 static hipError_t launch_mode3t(int mode, const ChainDev* chains, const Tile* tiles, int n_tiles, int j, int k,
-                                hipStream_t s) {
+                                bool sole, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
   dim3 grid(n_tiles), block(64 * ZR);
   switch (mode) {
@@ -1004,17 +1035,7 @@ static hipError_t launch_mode3t(int mode, const ChainDev* chains, const Tile* ti
       lattice_pass3t<T, BX, BY, ZR, PASS_FIRST><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
       break;
     case PASS_MIDDLE:
-      // Stores go through the L2 (see st_through) in launches of over 1M sites (n_tiles ZR
-      // 256), half of the resident boxes: below, too few blocks share a CU to hide the
-      // longer stores (FP32: 64^3 112 -> 126 us a trajectory, 96^3 153 -> 158; above,
-      // 128^3 224 -> 222, 160^3 378 -> 357, 8 chains of 64^3 217 -> 201; FP64 128^3 680
-      // -> 645).  Above the 32 MiB of the L2s' field (8M sites in FP32, 4M in FP64) most lines
-      // are written back within the launch anyway (512 chains of 24 x 21 x 30 1108 -> 1109,
-      // FP64 4000 -> 4040).  Two kernels: the choice inside one costs 1.5 % below 1M.
-      if ((int64_t)n_tiles * ZR > 4096 && (int64_t)n_tiles * ZR * (int)sizeof(T) <= 131072)
-        lattice_pass3t<T, BX, BY, ZR, PASS_MIDDLE, true><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
-      else
-        lattice_pass3t<T, BX, BY, ZR, PASS_MIDDLE><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
+      launch_middle3t<T, BX, BY, ZR>(chains, tiles, n_tiles, j, k, sole, s);
       break;
     case PASS_LAST:
       lattice_pass3t<T, BX, BY, ZR, PASS_LAST><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
@@ -1066,7 +1087,7 @@ TileShape tile_shape(int precision, int ndim, int cls) {
 }
 
 hipError_t launch_lattice_pass(int precision, int ndim, int cls, int mode, const ChainDev* chains,
-                               const Tile* tiles, int n_tiles, int j, int k, hipStream_t s) {
+                               const Tile* tiles, int n_tiles, int j, int k, hipStream_t s, bool sole) {
   if (cls < 0) return hipErrorInvalidValue;  // resident chains run whole trajectories (launch_resident_group)
   if (precision == 4) {
     if (ndim == 2) {
@@ -1075,10 +1096,10 @@ hipError_t launch_lattice_pass(int precision, int ndim, int cls, int mode, const
       return launch_mode2v<float, 64, 16>(mode, chains, tiles, n_tiles, j, k, s);
     }
     switch (cls) {
-      case 1: return launch_mode3t<float, 16, 16, 4>(mode, chains, tiles, n_tiles, j, k, s);
-      case 2: return launch_mode3t<float, 32, 8, 8>(mode, chains, tiles, n_tiles, j, k, s);
-      case 3: return launch_mode3t<float, 16, 16, 8>(mode, chains, tiles, n_tiles, j, k, s);
-      default: return launch_mode3t<float, 32, 8, 4>(mode, chains, tiles, n_tiles, j, k, s);
+      case 1: return launch_mode3t<float, 16, 16, 4>(mode, chains, tiles, n_tiles, j, k, sole, s);
+      case 2: return launch_mode3t<float, 32, 8, 8>(mode, chains, tiles, n_tiles, j, k, sole, s);
+      case 3: return launch_mode3t<float, 16, 16, 8>(mode, chains, tiles, n_tiles, j, k, sole, s);
+      default: return launch_mode3t<float, 32, 8, 4>(mode, chains, tiles, n_tiles, j, k, sole, s);
     }
   }
   if (ndim == 2) {
@@ -1087,10 +1108,10 @@ hipError_t launch_lattice_pass(int precision, int ndim, int cls, int mode, const
     return launch_mode2v<double, 64, 16>(mode, chains, tiles, n_tiles, j, k, s);
   }
   switch (cls) {
-    case 1: return launch_mode3t<double, 16, 16, 4>(mode, chains, tiles, n_tiles, j, k, s);
-    case 2: return launch_mode3t<double, 32, 8, 8>(mode, chains, tiles, n_tiles, j, k, s);
-    case 3: return launch_mode3t<double, 16, 16, 8>(mode, chains, tiles, n_tiles, j, k, s);
-    default: return launch_mode3t<double, 32, 8, 4>(mode, chains, tiles, n_tiles, j, k, s);
+    case 1: return launch_mode3t<double, 16, 16, 4>(mode, chains, tiles, n_tiles, j, k, sole, s);
+    case 2: return launch_mode3t<double, 32, 8, 8>(mode, chains, tiles, n_tiles, j, k, sole, s);
+    case 3: return launch_mode3t<double, 16, 16, 8>(mode, chains, tiles, n_tiles, j, k, sole, s);
+    default: return launch_mode3t<double, 32, 8, 4>(mode, chains, tiles, n_tiles, j, k, sole, s);
   }
 }
 

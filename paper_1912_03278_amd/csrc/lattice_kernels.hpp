@@ -72,8 +72,9 @@ hipError_t launch_lattice_steps(int precision, const StepShape& g, const ChainDe
 // consecutive entries of `tiles`; all tiles must belong to chains of the given
 // precision, dimension and tile class.  A LAST launch with j < 0 runs every
 // chain's own last pass (j = n_pass - 1), with the launch index that follows its
-// middle steps when k != 0 (LAT_STEPS per launch) or j when k == 0.
+// middle steps when k != 0 (LAT_STEPS per launch) or j when k == 0.  sole: no other
+// 3D launches run beside a 3D one's (its stores' kind, not its results, depends on it).
 hipError_t launch_lattice_pass(int precision, int ndim, int cls, int mode, const ChainDev* chains,
-                               const Tile* tiles, int n_tiles, int j, int k, hipStream_t s);
+                               const Tile* tiles, int n_tiles, int j, int k, hipStream_t s, bool sole = true);
 
 }  // namespace ihmc

@@ -321,6 +321,9 @@ void plan_groups(const std::vector<ChainDev>& cd, const std::vector<int>& member
     g.max_pass = cd[g.order[0]].n_pass;
     groups.push_back(g);
   }
+  int n3 = 0;
+  for (const Group& g : groups) n3 += g.ndim == 3 && g.cls >= 0;
+  for (Group& g : groups) g.sole3d = n3 <= 1;
 }
 
 // Events one round of the plan needs: the fork, and one join per group.
@@ -731,7 +734,7 @@ struct RoundSink {
   }
   hipError_t pass(const Group& g, int mode, const ChainDev* d_cd, const Tile* t, int n, int j, int k,
                   hipStream_t st) {
-    return pool ? launch_lattice_pass(g.prec, g.ndim, g.cls, mode, d_cd, t, n, j, k, st) : hipSuccess;
+    return pool ? launch_lattice_pass(g.prec, g.ndim, g.cls, mode, d_cd, t, n, j, k, st, g.sole3d) : hipSuccess;
   }
   hipError_t steps(const Group& g, const ChainDev* d_cd, const Tile* t, int n, int j, int k, hipStream_t st) {
     return pool ? launch_lattice_steps(g.prec, g.steps, d_cd, t, n, j, k, LAT_STEPS, st) : hipSuccess;

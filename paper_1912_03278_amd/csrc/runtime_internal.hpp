@@ -136,6 +136,7 @@ struct Group {
   std::vector<int> tile_begin;  // first tile of each position, relative to tile_off; size+1
   int tile_off = 0;
   int max_pass = 0;
+  bool sole3d = false;          // no other tiled 3D group in the plan
 };
 
 // Chain descriptors, launch plans and rounds shared by the resident chain sets
