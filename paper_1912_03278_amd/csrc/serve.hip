@@ -19,7 +19,6 @@
 
 #include <algorithm>
 #include <chrono>
-#include <climits>
 #include <condition_variable>
 #include <cstring>
 #include <deque>
@@ -188,18 +187,6 @@ struct ihmc_server {
   bool copy_pending[2] = {false, false};
   size_t rtile_cap = 0;
   int round_buf = 0;
-  // The last round's chains, groups and tile table (buffer plan_buf).  While the
-  // same chains go on, rounds need no new plan, and from the third on the round is
-  // replayed as a graph: 111 launches on eight streams cost the host more time
-  // (0.5 ms) than the round takes on the device (48 chains up to 64^3).  Capturing
-  // and instantiating takes about two rounds' time, so it is done only where the
-  // set has kGraphRounds rounds to go.
-  std::vector<int> plan_slots;
-  std::vector<Group> plan;
-  int plan_buf = 0;
-  bool plan_repeats = false;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t gexec = nullptr;
   double* d_export = nullptr;
   int64_t export_cap = 0;
   // statistics
@@ -214,8 +201,6 @@ struct ihmc_server {
   void loop();
   bool admit_setup(std::vector<Request*>& fresh);
   bool run_round();
-  void drop_plan();
-  void capture_plan();
   void retire(Request* r, int32_t final_state);
   void fail_all(const char* what, hipError_t e);
   bool ensure_tiles(size_t n);
@@ -579,82 +564,41 @@ bool ihmc_server::admit_setup(std::vector<Request*>& fresh) {
   return true;
 }
 
-constexpr int kGraphRounds = 8;
-
-// Forget the last round's plan: the set of chains, or a slot's chain, changes.
-// Rounds in flight may still run the graph.
-void ihmc_server::drop_plan() {
-  if (gexec) hipStreamSynchronize(s);
-  if (gexec) hipGraphExecDestroy(gexec);
-  if (graph) hipGraphDestroy(graph);
-  gexec = nullptr;
-  graph = nullptr;
-  plan_slots.clear();
-}
-
-// The plan as a graph; without one (gexec stays null) rounds are enqueued as before.
-void ihmc_server::capture_plan() {
-  hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
-  if (e == hipSuccess) {
-    e = enqueue_round_plan(plan, rd_tiles[plan_buf], d_cd, side, events, s);
-    const hipError_t e2 = hipStreamEndCapture(s, &graph);
-    if (e == hipSuccess) e = e2;
-  }
-  if (e == hipSuccess) e = hipGraphInstantiate(&gexec, graph, nullptr, nullptr, 0);
-  if (e != hipSuccess) {
-    gexec = nullptr;
-    (void)hipGetLastError();
-  }
-}
-
 // One trajectory of every resident chain that has trajectories left.
 bool ihmc_server::run_round() {
   std::vector<int> slots;
   double work = 0.0;
-  int left = INT_MAX;  // rounds until one of the chains is done
   {
     std::lock_guard<std::mutex> lk(mu);
     for (Request* r : active)
       if (!r->cancel && r->rounds < r->run.n_traj) {
         slots.push_back(r->slot);
         work += (double)r->cd.N * r->run.n_md;
-        left = std::min(left, r->run.n_traj - r->rounds);
       }
   }
   if (slots.empty()) return true;
+  std::vector<Group> g;
+  std::vector<Tile> tiles;
+  plan_groups(cd_host, slots, g, tiles, ctx->fuse_steps != 0);
   // The round is enqueued without waiting for it: the host plans and submits
   // the next round while this one runs (every request advances by exactly one
   // trajectory per round, so the host's counts do not need the device).  Only
   // retirement, admission and checkpoints wait for the rounds in flight.
-  // copy_ev[b] keeps the host at most two rounds ahead.
   const int b = round_buf;
   round_buf ^= 1;
   hipError_t e = hipSuccess;
-  const bool same = slots == plan_slots;
-  std::vector<Tile> tiles;
-  if (!same) {
-    drop_plan();
-    plan.clear();
-    plan_groups(cd_host, slots, plan, tiles, ctx->fuse_steps != 0);
-    plan_repeats = false;
-    if (!ensure_round_tiles(tiles.size()) || !ensure_streams(plan.size(), round_events(plan))) e = hipErrorOutOfMemory;
-  }
+  if (!ensure_round_tiles(tiles.size()) || !ensure_streams(g.size(), round_events(g))) e = hipErrorOutOfMemory;
   if (e == hipSuccess && copy_pending[b]) {
     e = hipEventSynchronize(copy_ev[b]);  // the upload two rounds back has read rh_tiles[b]
     copy_pending[b] = false;
   }
-  if (e == hipSuccess && !same) {
+  if (e == hipSuccess) {
     std::memcpy(rh_tiles[b], tiles.data(), sizeof(Tile) * tiles.size());
     e = hipMemcpyAsync(rd_tiles[b], rh_tiles[b], sizeof(Tile) * tiles.size(), hipMemcpyHostToDevice, s);
-    plan_buf = b;
-    plan_slots = slots;
   }
   if (e == hipSuccess) e = hipEventRecord(copy_ev[b], s);
   if (e == hipSuccess) copy_pending[b] = true;
-  if (e == hipSuccess && !graph && same && plan_repeats && left >= kGraphRounds) capture_plan();
-  plan_repeats = same;
-  if (e == hipSuccess)
-    e = gexec ? hipGraphLaunch(gexec, s) : enqueue_round_plan(plan, rd_tiles[plan_buf], d_cd, side, events, s);
+  if (e == hipSuccess) e = enqueue_round_plan(g, rd_tiles[b], d_cd, side, events, s);
   if (e != hipSuccess) {
     fail_all("round", e);
     return false;
@@ -684,7 +628,6 @@ void ihmc_server::loop() {
         if (r->cancel || r->rounds >= r->run.n_traj) finished.push_back(r);
     }
     take_checkpoints();
-    if (!finished.empty()) drop_plan();
     for (Request* r : finished) {
       retire(r, r->cancel ? REQ_CANCELLED : REQ_DONE);
       std::lock_guard<std::mutex> lk(mu);
@@ -708,7 +651,6 @@ void ihmc_server::loop() {
         continue;
       }
     }
-    if (!fresh.empty()) drop_plan();
     if (!fresh.empty() && !admit_setup(fresh)) return;
     if (!run_round()) return;
     // busy time: the iterations that had resident chains (set-up, retirement and
@@ -763,7 +705,6 @@ extern "C" int ihmc_server_destroy(ihmc_server* sv) {
   for (Request* r : sv->active)
     for (void* p : r->dev) sv->ctx->arena.release(p);
   for (auto& kv : sv->reqs) delete kv.second;
-  sv->drop_plan();
   for (hipEvent_t ev : sv->events) hipEventDestroy(ev);
   for (hipStream_t st : sv->side) hipStreamDestroy(st);
   if (sv->s) hipStreamDestroy(sv->s);
