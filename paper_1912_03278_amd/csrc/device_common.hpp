@@ -397,6 +397,9 @@ __device__ __forceinline__ double recip(double d) {
 // 1/(1 + e) = den q (a few ulp each, instead of two divisions).  (1 + e) den lies in
 // [2, 8], so q needs none of a division's scaling: the hardware's estimate, two
 // Newton steps and the residual's correction give the correctly rounded value.
+// A NaN y gives a NaN log cosh but a tanh of +-1 (exp_nonpos drops it, one operation
+// fewer): the lattice and dense action multiplies that tanh by u or y, which are NaN
+// then; where t stands alone use logcosh_tanh_nan.
 template <bool SGPR = false>
 __device__ __forceinline__ void logcosh_tanh(double y, double& lc, double& t) {
   const double a = fabs(y);
@@ -423,6 +426,12 @@ __device__ __forceinline__ void logcosh_tanh(double y, double& lc, double& t) {
   const double l1p = (hi ? 0.6931471805599453 : 0.0) + 2.0 * __builtin_fma(s, p, s);
   lc = (a - 0.6931471805599453) + l1p;
   t = copysign((1.0 - e) * (den * q), y);
+}
+
+// The same with tanh(NaN) = NaN.
+__device__ __forceinline__ void logcosh_tanh_nan(double y, double& lc, double& t) {
+  logcosh_tanh(y, lc, t);
+  t = (y != y) ? y : t;
 }
 
 template <typename T>

@@ -148,13 +148,13 @@ __global__ __launch_bounds__(PHI_THREADS) void lattice_resident_phi(const ChainD
     // t = tanh(h' + phi) into sR (free after the solve)
     for (int i = tid; i < N; i += PHI_THREADS) {
       double lc, t;
-      logcosh_tanh(sP[i] + hprime(i), lc, t);
+      logcosh_tanh_nan(sP[i] + hprime(i), lc, t);
       sR[i] = t;
     }
     __syncthreads();
     for (int i = tid; i < N; i += PHI_THREADS) {
       double lc, t;
-      logcosh_tanh(sP[i] + hprime(i), lc, t);
+      logcosh_tanh_nan(sP[i] + hprime(i), lc, t);
       s = s + (0.5 * sP[i] * sX[i] / Jp - lc);
       ts = ts + t;
       hts = hts + hprime(i) * t;
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(PHI_THREADS) void lattice_resident_phi(const ChainD
       const bool last = (j == cd.n_pass - 1);
       for (int i = tid; i < N; i += PHI_THREADS) {
         double lc, th;
-        logcosh_tanh(sP[i] + hprime(i), lc, th);
+        logcosh_tanh_nan(sP[i] + hprime(i), lc, th);
         const double F = th - sX[i] / Jp;
         const double p = __builtin_fma(kick, F, sM[i]);
         sM[i] = p;
