@@ -246,7 +246,9 @@ int ihmc_chains_destroy(ihmc_chains* chains);
  * with the checkpoint in buf (bytes long).  Chain i must have been created
  * with the same lattice and run parameters (dimensions, precision, couplings,
  * field, C, n_md, traj_len, integrator, flip_every, seed, chain_id; n_traj may
- * be larger, and must cover the trajectories already done).  A buffer that is
+ * be larger, and must cover the trajectories already done; what follows from
+ * these, the constants 1^T Kt^-1 h' and h'^T Kt^-1 h', may differ by a relative
+ * 2e-9, so that another order of their sums does not refuse a checkpoint).  A buffer that is
  * not such a checkpoint, is truncated, or belongs to a chain with other
  * parameters fails with IHMC_E_INVAL and leaves the chain unchanged.  The
  * chain then continues at the checkpoint's trajectory index; further
@@ -282,7 +284,10 @@ int ihmc_dense_advance(ihmc_dense_chains* chains, int32_t n_traj);
 int ihmc_dense_result(ihmc_dense_chains* chains, int32_t i, ihmc_result* out);
 /* Checkpoint and resume of dense chain i, as ihmc_chains_checkpoint and
  * ihmc_chains_restore (the model, the products and the run parameters of the
- * restoring chain must match; C must be the same number). */
+ * restoring chain must match, K to the bit: the checkpoint holds a checksum of
+ * it; C must be the same number, or to a relative 1e-12 where it is computed).
+ * A checkpoint of a build before the checksum is told apart by the constants
+ * 1^T Kt^-1 1, 1^T Kt^-1 h' and h'^T Kt^-1 h' instead, to a relative 2e-9. */
 int ihmc_dense_checkpoint(ihmc_dense_chains* chains, int32_t i, void* buf, uint64_t* bytes);
 int ihmc_dense_restore(ihmc_dense_chains* chains, int32_t i, const void* buf, uint64_t bytes);
 /* The shift in use and the Lanczos estimate: out[0] = C, out[1] = theta,

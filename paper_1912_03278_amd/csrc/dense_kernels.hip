@@ -75,24 +75,38 @@ __global__ void k_dense_pad_K(const double* __restrict__ K, int64_t N, int64_t N
 // What the set-up demands of K (N x N): finite entries, symmetric to 1e-12 of the
 // largest.  chk[0] counts non-finite entries, chk[1] holds the bits of max |K|
 // (finite entries; the bits of non-negative doubles order as integers), chk[2]
-// counts pairs that differ; all zero before.  On the host the two sweeps took
-// 3.8 ms at N = 1000, half of the set-up.
+// counts pairs that differ; all zero before.  chk[3] sums a mixed word of every
+// entry and its place (in any order the same), by which checkpoints tell models
+// apart.  On the host the two sweeps took 3.8 ms at N = 1000, half of the set-up.
 __global__ __launch_bounds__(256) void k_dense_check(const double* __restrict__ K, int64_t n,
                                                      unsigned long long* __restrict__ chk) {
   double mx = 0.0;
+  uint64_t mark = 0;
   bool bad = false;
   for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < n; i += 256ll * gridDim.x) {
-    const double v = fabs(K[i]);
+    const double k = K[i], v = fabs(k);
     if (v <= DBL_MAX) mx = fmax(mx, v);
     else bad = true;
+    uint64_t x = (uint64_t)__double_as_longlong(k + 0.0) + (uint64_t)i * 0x9e3779b97f4a7c15ull;  // -0 as 0
+    x = (x ^ (x >> 32)) * 0xd6e8feb86659fd93ull;
+    x = (x ^ (x >> 32)) * 0xd6e8feb86659fd93ull;
+    mark += x ^ (x >> 32);
   }
-  for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
+  for (int off = 32; off > 0; off >>= 1) {
+    mx = fmax(mx, __shfl_xor(mx, off, 64));
+    mark += __shfl_xor(mark, off, 64);
+  }
   __shared__ double sm[4];
-  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = mx;
+  __shared__ uint64_t sk[4];
+  if ((threadIdx.x & 63) == 0) {
+    sm[threadIdx.x >> 6] = mx;
+    sk[threadIdx.x >> 6] = mark;
+  }
   const int any = __syncthreads_or(bad);
   if (threadIdx.x == 0) {  // one atomic per block: they all meet at one address
     atomicMax(chk + 1, (unsigned long long)__double_as_longlong(fmax(fmax(sm[0], sm[1]), fmax(sm[2], sm[3]))));
     if (any) atomicAdd(chk, 1ull);
+    atomicAdd(chk + 3, (unsigned long long)(sk[0] + sk[1] + sk[2] + sk[3]));
   }
 }
 

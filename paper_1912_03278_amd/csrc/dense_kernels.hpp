@@ -12,7 +12,8 @@ namespace ihmc {
 hipError_t dense_split_K(const double* K, int64_t N, int64_t Np, __bf16* Kl, hipStream_t s);
 hipError_t dense_pad_K(const double* K, int64_t N, int64_t Np, double* K64, hipStream_t s);
 // Entries of K: chk[0] non-finite ones found, chk[1] bits of the largest |K|, chk[2]
-// pairs found that differ by more than 1e-12 of it (chk zero before).
+// pairs found that differ by more than 1e-12 of it, chk[3] a checksum of K (chk zero
+// before).
 hipError_t dense_check(const double* K, int64_t N, unsigned long long* chk, hipStream_t s);
 // h' = beta h (FP64) and h'/sqrt(J') (FP32) over the padded length.
 hipError_t dense_field(const double* h, int64_t N, int64_t Np, double beta, double sqJ, double* hp, float* b,

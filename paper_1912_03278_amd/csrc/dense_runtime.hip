@@ -85,8 +85,9 @@ static uint64_t setup_scratch_doubles(int64_t N, int64_t Np) {
 // lowest Ritz value falls below 1e-10 (|theta| + 1), at an invariant subspace,
 // or after min(N, kLanczosMaxSteps) steps; with an error if the check of K's
 // entries, which comes back with the first steps, found any that may not be.
+// *mark: the checksum of K from that check.
 static int lanczos_min(ihmc_ctx* ctx, const double* K64, int64_t N, int64_t Np, double* scratch, double* theta,
-                       double* resid, int* steps) {
+                       double* resid, int* steps, uint64_t* mark) {
   hipStream_t s = ctx->stream;
   const int mmax = (int)std::min<int64_t>(N, kLanczosMaxSteps);
   const LanczosWork lw = lanczos_work(scratch + kCheckWords, Np, mmax);
@@ -111,8 +112,9 @@ static int lanczos_min(ihmc_ctx* ctx, const double* K64, int64_t N, int64_t Np, 
         hipSuccess)
       break;
     if ((e = hipStreamSynchronize(s)) != hipSuccess) break;
-    uint64_t chk[3];
+    uint64_t chk[4];
     std::memcpy(chk, back.data(), sizeof chk);
+    *mark = chk[3];
     if (chk[0] || chk[2]) {
       refused = true;
       break;
@@ -205,6 +207,7 @@ struct DenseChains {
   float* bfield = nullptr;
   double C = 0.0, theta = 0.0, resid = 0.0;
   int lanczos_steps = 0, cg_iters = 0;
+  uint64_t variant = 0;  // of its checkpoints: the limb products, and a checksum of K in the upper half
   std::vector<void*> allocs;
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
@@ -353,11 +356,13 @@ int DenseChains::build_model(const ihmc_dense& md, int32_t n, const ihmc_run* ru
   }
 
   // ---- shift: Lanczos for the lowest eigenvalue of K
-  rc = lanczos_min(ctx, K64, N, Np, (double*)part, &theta, &resid, &lanczos_steps);
+  uint64_t mark = 0;
+  rc = lanczos_min(ctx, K64, N, Np, (double*)part, &theta, &resid, &lanczos_steps, &mark);
   if (rc) {
     cleanup();
     return rc;
   }
+  variant = 0x100u + (uint64_t)nprod + ((uint64_t)std::max<uint32_t>(1u, (uint32_t)(mark ^ (mark >> 32))) << 32);
   auto_shift = md.C < 0.0;
   if (auto_shift) {
     C = -(theta - resid) + 0.1;
@@ -603,7 +608,7 @@ extern "C" int ihmc_dense_checkpoint(ihmc_dense_chains* ch, int32_t i, void* buf
   CTX_OK(ch->impl.ctx);
   DenseChains& d = ch->impl;
   if (i < 0 || i >= d.B) return set_error(IHMC_E_INVAL, "chain index %d out of range", i);
-  return chain_checkpoint(d.ctx, d.cd[i], 0x100u + (uint64_t)d.nprod, buf, bytes);
+  return chain_checkpoint(d.ctx, d.cd[i], d.variant, buf, bytes);
 }
 
 extern "C" int ihmc_dense_restore(ihmc_dense_chains* ch, int32_t i, const void* buf, uint64_t bytes) {
@@ -614,8 +619,7 @@ extern "C" int ihmc_dense_restore(ihmc_dense_chains* ch, int32_t i, const void* 
   int traj = 0;
   // a shift that comes from Lanczos may differ in its last digits where the sums
   // of K's products run in another order
-  int rc = chain_restore(d.ctx, d.cd[i], 0x100u + (uint64_t)d.nprod, buf, bytes, &traj, nullptr,
-                         d.auto_shift ? 1e-12 : 0.0);
+  int rc = chain_restore(d.ctx, d.cd[i], d.variant, buf, bytes, &traj, nullptr, d.auto_shift ? 1e-12 : 0.0);
   if (rc) return rc;
   d.base[i] = traj - d.enqueued;
   return IHMC_OK;
@@ -769,7 +773,8 @@ extern "C" int ihmc_min_eig(ihmc_ctx* ctx, const double* K, int64_t N, double* t
     return hip_fail(ctx, e, "K upload");
   }
   int st = 0;
-  rc = lanczos_min(ctx, K64, N, Np, scratch, theta, resid, &st);
+  uint64_t mark = 0;
+  rc = lanczos_min(ctx, K64, N, Np, scratch, theta, resid, &st, &mark);
   release();
   if (rc) {
     const int bad = validate_entries(m);  // names the entry, and goes before any other failure

@@ -920,7 +920,7 @@ struct CkptHeader {
   int32_t h_kind, form, pad0;
   double C, sqJ, Jp, b0, hp0, eps, c_m, c_e, c_v;
   uint64_t field_hash;  // FNV-1a of the per-site h' in site order (0 without one)
-  uint64_t variant;     // path-specific form of the force (dense: limb products)
+  uint64_t variant;     // path-specific form of the force (dense: limb products, K's checksum in the upper half)
   // state
   ChainState st;
   int32_t n_rec, pad;
@@ -1075,8 +1075,10 @@ int chain_restore(ihmc_ctx* ctx, const ChainDev& c, uint64_t variant, const void
   CkptHeader mine;
   std::memset(&mine, 0, sizeof mine);
   fill_identity(c, fh, variant, mine);
-  // c_m, c_e and c_v follow from the fields already compared (couplings, shift,
-  // field hash); another order of their sums may move the last digits
+  // c_m, c_e and c_v follow from the fields compared below (couplings, shift, field
+  // hash, checksum of a dense K); another order of their sums may move the last
+  // digits.  Dense checkpoints of earlier builds carry no checksum.
+  if ((h.variant >> 32) == 0) mine.variant &= 0xffffffffull;
   auto derived = [](double a, double& b, double rel) {
     if (std::fabs(a - b) <= rel * (std::fabs(a) + std::fabs(b))) b = a;
   };

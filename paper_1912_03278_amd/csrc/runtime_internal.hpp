@@ -53,7 +53,8 @@ int upload_fields(ihmc_ctx* ctx, const std::vector<ChainDev>& cd, const ChainDev
 // Checkpoint of one chain into a host buffer (buf NULL: size only), and its
 // restore into a chain with the same parameters (sets *traj to the
 // checkpoint's trajectory index).  `variant` names a path-specific form of the
-// force that must also match (0 for the lattice path).  Both wait for stream
+// force that must also match (0 for the lattice path; an upper half of 0 in the
+// checkpoint: not compared).  Both wait for stream
 // s (null: the context stream) and do their copies on it.  shift_rel: how far
 // apart, relatively, the shifts C may lie (0: equal to the bit).
 int chain_checkpoint(ihmc_ctx* ctx, const ChainDev& c, uint64_t variant, void* buf, uint64_t* bytes,
