@@ -378,7 +378,9 @@ __global__ __launch_bounds__(BX / 4 * BY) void lattice_pass2v(const ChainDev* __
 // lattice site it images.  The ring's momenta are read from other tiles; they
 // come from the buffer of launch k - 1 while this launch writes that of launch k,
 // so no block reads momenta another block of the launch writes.  A chain with
-// fewer middle steps left takes those (at most max_steps) and stores its tile.
+// fewer middle steps left takes those (at most max_steps), on the rows that the
+// last steps of a full launch take, and stores its tile (2048^2 FP64, one step left:
+// 66 us on all rows, 58 on those).
 //
 // A thread owns H consecutive rows of one 4-site chunk column (a strip) and keeps
 // their momenta, psi and field in registers for all steps; LDS holds psi and w.
@@ -445,6 +447,8 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
   const int nch = bx / 4 + 2 * MS_CH;             // chunks of a staged row
   const int prow = by + 2 * MS_HY, wrow = prow - 2;  // staged rows; w rows of the first step
   const int nst = (wrow + H - 1) / H;             // strips of a chunk column
+  const int ns = min(max_steps, cd.n_pass - 1 - j);
+  const int skip = 2 * (STEPS - ns);              // outer rows that fewer steps leave out, on either side
   const bool rows_near = (L1 >= by + MS_HY), x_near = (L0 >= bx + MS_HX);
   auto lat_row = [&](int y) { return rows_near ? wrap_near(y, L1) : wrap_any(y, L1); };
   T* const sP = reinterpret_cast<T*>(lds);
@@ -463,12 +467,12 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
 #pragma unroll
       for (int q = 0; q < H + 1; ++q) {
         const int r = strip + nsg * q;
-        if (r < prow) load_chunk<T>(pin + row_offset(lat_row(tl.y0 + r - MS_HY), pitch), cp, v[q]);
+        if (r >= skip && r < prow - skip) load_chunk<T>(pin + row_offset(lat_row(tl.y0 + r - MS_HY), pitch), cp, v[q]);
       }
 #pragma unroll
       for (int q = 0; q < H + 1; ++q) {
         const int r = strip + nsg * q;
-        if (r < prow) st4<T>(sP + r * MS_RP + 4 * c, v[q]);
+        if (r >= skip && r < prow - skip) st4<T>(sP + r * MS_RP + 4 * c, v[q]);
       }
     }
   }
@@ -486,7 +490,7 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
       bq[i][e] = b_uniform;
       pm[i][e] = (T)0;
     }
-    if (act && r0 + i < wrow - 2) {
+    if (act && r0 + i >= skip && r0 + i < wrow - 2 - skip) {
       const uint64_t o = row_offset(lat_row(tl.y0 + r0 + i - (MS_HY - 2)), pitch);
       load_chunk<T>(pmi + o, cp, pm[i]);
       if (site_field) load_chunk<T>(bfield + o, cp, bq[i]);
@@ -495,7 +499,6 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
   lds_barrier();
 
   const T Ct = (T)cd.C, at = (T)cd.sqJ, hw = (T)cd.hw;
-  const int ns = min(max_steps, cd.n_pass - 1 - j);
   // w row q and kick row q lie one and two rows below psi row q; the edge lanes'
   // neighbours (others read the first lane's: one address, no conflict)
   const int off0 = r0 * MS_RP + 4 * c;
@@ -510,8 +513,8 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
   }
 #pragma unroll 1
   for (int s = 0; s < ns; ++s) {
-    // w on the rows the remaining steps of a full launch need
-    if (act && r0 + H > 2 * s && r0 < wrow - 2 * s) {
+    const int in = 2 * s + skip;  // rows that the remaining steps no longer need, on either side
+    if (act && r0 + H > in && r0 < wrow - in) {
       T u[4], m[4], d[4];
       ld4<T>(pc, u);
       ld4<T>(pc + MS_RP, m);
@@ -538,7 +541,7 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
       }
     }
     lds_barrier();
-    if (act && r0 + H > 2 * s && r0 < wrow - 2 - 2 * s) {
+    if (act && r0 + H > in && r0 < wrow - 2 - in) {
       double kick_d = 0.0, drift_d = 0.0;
       pass_coeffs(cd, j + s, kick_d, drift_d);
       const T kick = (T)kick_d, drift = (T)drift_d;
