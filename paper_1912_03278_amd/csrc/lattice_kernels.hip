@@ -107,10 +107,10 @@ __device__ __forceinline__ int xcd_tile(int b, int n) {
 // A LAST launch may cover chains whose trajectories end at different passes
 // (j < 0): each block then takes its chain's own last pass j = n_pass - 1 and
 // the launch index of that pass under the round's step plan (k != 0: the j - 1
-// middle steps ran LAT_STEPS per launch, after launch 0; otherwise launch j).
+// middle steps ran k per launch, after launch 0; otherwise launch j).
 __device__ __forceinline__ void chain_last_pass(const ChainDev& cd, int& j, int& k) {
   j = cd.n_pass - 1;
-  k = k ? 1 + (j - 1 + LAT_STEPS - 1) / LAT_STEPS : j;
+  k = k ? 1 + (j - 1 + k - 1) / k : j;
 }
 
 // --------------------------------------------------------------------- 2D ---
@@ -364,7 +364,7 @@ __global__ __launch_bounds__(BX / 4 * BY) void lattice_pass2v(const ChainDev* __
 
 // ------------------------------------------------------ 2D, several steps ---
 //
-// Up to STEPS = 4 consecutive middle leap-frog steps j, j + 1, .. in one pass
+// Up to STEPS (2 or 4) consecutive middle leap-frog steps j, j + 1, .. in one pass
 // over a tile.  psi is staged with a halo of 2 STEPS sites; step s evaluates w on
 // the tile plus a ring of 2 (STEPS - s) - 1, and its kick and drift on the tile
 // plus a ring one narrower (the ring repeats what the neighbouring tiles compute,
@@ -378,9 +378,10 @@ __global__ __launch_bounds__(BX / 4 * BY) void lattice_pass2v(const ChainDev* __
 // lattice site it images.  The ring's momenta are read from other tiles; they
 // come from the buffer of launch k - 1 while this launch writes that of launch k,
 // so no block reads momenta another block of the launch writes.  A chain with
-// fewer middle steps left takes those (at most max_steps), on the rows that the
-// last steps of a full launch take, and stores its tile (2048^2 FP64, one step left:
-// 66 us on all rows, 58 on those).
+// fewer middle steps left takes those (at most max_steps), on the rows that these
+// need (2 steps of halo in y), and stores its tile (2048^2 FP64, one step left on tiles
+// for four: 66 us on all rows, 58 on those).  FULL: every chain of the launch takes STEPS
+// (the number known, FP32 launches take 2 % less: 2048^2 199 -> 195 us a trajectory of 20).
 //
 // A thread owns H consecutive rows of one 4-site chunk column (a strip) and keeps
 // their momenta, psi and field in registers for all steps; LDS holds psi and w.
@@ -398,8 +399,6 @@ __global__ __launch_bounds__(BX / 4 * BY) void lattice_pass2v(const ChainDev* __
 // 2.64, 256^2 2.04 -> 1.30, 600 chains of 64 .. 256 sites a row with a field 36.0 ->
 // 22.1; 251 x 130 FP64 4.88 -> 2.61.  Two and three steps a launch measured 30.5 and
 // 24.8 us on 4096^2, five and six 26 and 27 on the chains.
-constexpr int STEPS = LAT_STEPS;
-
 // Value of the lane before (wave_left) or after (wave_right) in the wave; the
 // first or last lane takes `edge`.
 template <int CTRL>
@@ -420,16 +419,16 @@ __device__ __forceinline__ double wave_shift(double edge, double v) {
 constexpr int DPP_WAVE_SHR1 = 0x138;  // lane l - 1
 constexpr int DPP_WAVE_SHL1 = 0x130;  // lane l + 1
 
-constexpr int MS_HX = 2 * STEPS, MS_HY = 2 * STEPS;  // staged halo (a multiple of 4 in x)
-constexpr int MS_CH = MS_HX / 4;                     // halo chunks on each side
-constexpr int MS_BX = 64;                            // widest tile
-constexpr int MS_RP = MS_BX + 2 * MS_HX;             // LDS row pitch
-static_assert(MS_HX % 4 == 0, "whole chunks of halo");
+constexpr int MS_BX = 64;  // widest tile
 
-template <typename T, int H, bool THROUGH = false>
+template <typename T, int STEPS, int H, bool THROUGH, bool FULL>
 __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __restrict__ chains,
                                                         const Tile* __restrict__ tiles, int n_tiles, int j, int k,
                                                         int max_steps) {
+  constexpr int HALO = 2 * STEPS;             // staged on every side
+  constexpr int HCH = HALO / 4;               // the same in chunks
+  constexpr int RP = MS_BX + 2 * HALO;        // LDS row pitch
+  static_assert(HALO % 4 == 0, "whole chunks of halo");
   extern __shared__ __align__(16) unsigned char lds[];
   const Tile tl = tiles[xcd_tile(blockIdx.x, n_tiles)];
   const ChainDev& cd = chains[tl.chain];
@@ -444,20 +443,20 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
   const gmem<T>* __restrict__ bfield = (const gmem<T>*)cd.b;
   const bool site_field = (cd.h_kind == 2);
   const int bx = tl.z0 & 0xffff, by = tl.z0 >> 16;
-  const int nch = bx / 4 + 2 * MS_CH;             // chunks of a staged row
-  const int prow = by + 2 * MS_HY, wrow = prow - 2;  // staged rows; w rows of the first step
+  const int nch = bx / 4 + 2 * HCH;             // chunks of a staged row
+  const int ns = min(max_steps, cd.n_pass - 1 - j);  // steps taken
+  const int hy = FULL ? HALO : 2 * ns;               // rows of halo that they need
+  const int prow = by + 2 * hy, wrow = prow - 2;  // staged rows; w rows of the first step
   const int nst = (wrow + H - 1) / H;             // strips of a chunk column
-  const int ns = min(max_steps, cd.n_pass - 1 - j);
-  const int skip = 2 * (STEPS - ns);              // outer rows that fewer steps leave out, on either side
-  const bool rows_near = (L1 >= by + MS_HY), x_near = (L0 >= bx + MS_HX);
+  const bool rows_near = (L1 >= by + HALO), x_near = (L0 >= bx + HALO);
   auto lat_row = [&](int y) { return rows_near ? wrap_near(y, L1) : wrap_any(y, L1); };
   T* const sP = reinterpret_cast<T*>(lds);
-  T* const sW = sP + (nst * H + 2) * MS_RP;
+  T* const sW = sP + (nst * H + 2) * RP;
 
   const int t = threadIdx.x;
   const int strip = t / nch, c = t - strip * nch;
-  const ChunkPos cp = chunk_pos(tl.x0 - MS_HX + 4 * c, L0, x_near);
-  // ---- stage psi: row r of the staged rows is lattice row y0 + r - MS_HY; each
+  const ChunkPos cp = chunk_pos(tl.x0 - HALO + 4 * c, L0, x_near);
+  // ---- stage psi: row r of the staged rows is lattice row y0 + r - hy; each
   // thread loads its chunk column of every nsg-th row, all loads before the stores
   // (nsg >= nst strips, so H + 1 rows a thread cover the prow <= H nst + 2 rows)
   {
@@ -467,17 +466,17 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
 #pragma unroll
       for (int q = 0; q < H + 1; ++q) {
         const int r = strip + nsg * q;
-        if (r >= skip && r < prow - skip) load_chunk<T>(pin + row_offset(lat_row(tl.y0 + r - MS_HY), pitch), cp, v[q]);
+        if (r < prow) load_chunk<T>(pin + row_offset(lat_row(tl.y0 + r - hy), pitch), cp, v[q]);
       }
 #pragma unroll
       for (int q = 0; q < H + 1; ++q) {
         const int r = strip + nsg * q;
-        if (r >= skip && r < prow - skip) st4<T>(sP + r * MS_RP + 4 * c, v[q]);
+        if (r < prow) st4<T>(sP + r * RP + 4 * c, v[q]);
       }
     }
   }
   // ---- momenta and field of the strip's kick rows r0 .. r0 + H - 1 (row 0 is
-  // lattice row y0 - (MS_HY - 2)), issued behind the staging (loads complete in
+  // lattice row y0 - (hy - 2)), issued behind the staging (loads complete in
   // issue order) and first used by the kick
   const bool act = strip < nst;
   const int r0 = strip * H;
@@ -490,8 +489,8 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
       bq[i][e] = b_uniform;
       pm[i][e] = (T)0;
     }
-    if (act && r0 + i >= skip && r0 + i < wrow - 2 - skip) {
-      const uint64_t o = row_offset(lat_row(tl.y0 + r0 + i - (MS_HY - 2)), pitch);
+    if (act && r0 + i < wrow - 2) {
+      const uint64_t o = row_offset(lat_row(tl.y0 + r0 + i - (hy - 2)), pitch);
       load_chunk<T>(pmi + o, cp, pm[i]);
       if (site_field) load_chunk<T>(bfield + o, cp, bq[i]);
     }
@@ -501,7 +500,7 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
   const T Ct = (T)cd.C, at = (T)cd.sqJ, hw = (T)cd.hw;
   // w row q and kick row q lie one and two rows below psi row q; the edge lanes'
   // neighbours (others read the first lane's: one address, no conflict)
-  const int off0 = r0 * MS_RP + 4 * c;
+  const int off0 = r0 * RP + 4 * c;
   const int eoff = (t & 63) == 63 ? off0 + 4 : max(0, __builtin_amdgcn_readfirstlane(off0) - 1);
   T* const pc = sP + off0;
   T* const wc = sW + off0;
@@ -509,19 +508,19 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
   const T* const we = sW + eoff;
   if (act) {
 #pragma unroll
-    for (int i = 0; i < H; ++i) ld4<T>(pc + (i + 2) * MS_RP, ps[i]);
+    for (int i = 0; i < H; ++i) ld4<T>(pc + (i + 2) * RP, ps[i]);
   }
 #pragma unroll 1
   for (int s = 0; s < ns; ++s) {
-    const int in = 2 * s + skip;  // rows that the remaining steps no longer need, on either side
-    if (act && r0 + H > in && r0 < wrow - in) {
+    // w on the rows the remaining steps need
+    if (act && r0 + H > 2 * s && r0 < wrow - 2 * s) {
       T u[4], m[4], d[4];
       ld4<T>(pc, u);
-      ld4<T>(pc + MS_RP, m);
+      ld4<T>(pc + RP, m);
 #pragma unroll
       for (int i = 0; i < H; ++i) {
-        ld4<T>(pc + (i + 2) * MS_RP, d);
-        const T edge = pe[(i + 1) * MS_RP];
+        ld4<T>(pc + (i + 2) * RP, d);
+        const T edge = pe[(i + 1) * RP];
         const T lft = wave_shift<DPP_WAVE_SHR1>(edge, m[3]), rgt = wave_shift<DPP_WAVE_SHL1>(edge, m[0]);
         T w[4];
 #pragma unroll
@@ -532,7 +531,7 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
           const T uu = fma_t(Ct, m[e], sum);
           w[e] = fma_t(at, tanh_state(fma_t(at, uu, hw)), -m[e]);
         }
-        st4<T>(wc + i * MS_RP, w);
+        st4<T>(wc + i * RP, w);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           u[e] = m[e];
@@ -541,17 +540,17 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
       }
     }
     lds_barrier();
-    if (act && r0 + H > in && r0 < wrow - 2 - in) {
+    if (act && r0 + H > 2 * s && r0 < wrow - 2 - 2 * s) {
       double kick_d = 0.0, drift_d = 0.0;
       pass_coeffs(cd, j + s, kick_d, drift_d);
       const T kick = (T)kick_d, drift = (T)drift_d;
       T u[4], m[4], d[4];
       ld4<T>(wc, u);
-      ld4<T>(wc + MS_RP, m);
+      ld4<T>(wc + RP, m);
 #pragma unroll
       for (int i = 0; i < H; ++i) {
-        ld4<T>(wc + (i + 2) * MS_RP, d);
-        const T edge = we[(i + 1) * MS_RP];
+        ld4<T>(wc + (i + 2) * RP, d);
+        const T edge = we[(i + 1) * RP];
         const T lft = wave_shift<DPP_WAVE_SHR1>(edge, m[3]), rgt = wave_shift<DPP_WAVE_SHL1>(edge, m[0]);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -562,7 +561,7 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
           pm[i][e] = fma_t(kick, F, pm[i][e]);
           ps[i][e] = fma_t(drift, pm[i][e], ps[i][e]);
         }
-        st4<T>(pc + (i + 2) * MS_RP, ps[i]);
+        st4<T>(pc + (i + 2) * RP, ps[i]);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           u[e] = m[e];
@@ -572,12 +571,12 @@ __global__ __launch_bounds__(1024, 4) void lattice_steps2v(const ChainDev* __res
     }
     if (s + 1 < ns) lds_barrier();
   }
-  const int gx = tl.x0 - MS_HX + 4 * c;
+  const int gx = tl.x0 - HALO + 4 * c;
   const int64_t base0 = (int64_t)pitch * tl.y0;  // the tile's first row
-  if (act && c >= MS_CH && c < nch - MS_CH && gx < L0) {
+  if (act && c >= HCH && c < nch - HCH && gx < L0) {
 #pragma unroll
     for (int i = 0; i < H; ++i) {
-      const int ty = r0 + i - (MS_HY - 2), gy = tl.y0 + ty;
+      const int ty = r0 + i - (hy - 2), gy = tl.y0 + ty;
       if (ty >= 0 && ty < by && gy < L1) {
         const int64_t base = gx + (int64_t)pitch * gy;  // gx + 3 < pitch
         if constexpr (THROUGH) {
@@ -883,13 +882,34 @@ __global__ __launch_bounds__(64 * ZR, 8) void lattice_pass3t(const ChainDev* __r
 static void steps_tile(const StepShape& g, int L0, int L1, int& bx, int& by, int& threads, int& rows) {
   const int nx = (L0 + g.bx - 1) / g.bx;
   bx = ((L0 + nx - 1) / nx + 3) / 4 * 4;
-  const int nch = bx / 4 + 2 * MS_CH;
-  const int by_max = std::min(g.by, g.max_threads / nch * g.H - (2 * MS_HY - 2));
+  const int nch = bx / 4 + g.steps, ring = 4 * g.steps - 2;  // chunks of a staged row; rows a kick adds to a tile's
+  const int by_max = std::min(g.by, g.max_threads / nch * g.H - ring);
   const int ny = (L1 + by_max - 1) / by_max;
   by = (L1 + ny - 1) / ny;
-  const int nst = (by + 2 * MS_HY - 2 + g.H - 1) / g.H;
+  const int nst = (by + ring + g.H - 1) / g.H;
   threads = (nst * nch + 63) / 64 * 64;
   rows = nst * g.H + 2;
+}
+
+// What a launch over the lattices takes under a shape; sets the shape's workgroup size
+// and LDS rows.
+struct StepLoad {
+  int64_t tiles = 0, waves = 0;
+  int wmax = 0;  // waves of the largest workgroup
+};
+static StepLoad steps_load(StepShape& g, const std::vector<std::pair<int, int>>& lattices) {
+  StepLoad c;
+  for (const auto& l : lattices) {
+    int bx, by, thr, rows;
+    steps_tile(g, l.first, l.second, bx, by, thr, rows);
+    const int64_t n = (int64_t)((l.first + bx - 1) / bx) * ((l.second + by - 1) / by);
+    c.tiles += n;
+    c.waves += n * (thr / 64);
+    c.wmax = std::max(c.wmax, thr / 64);
+    g.threads = std::max(g.threads, thr);
+    g.rows = std::max(g.rows, rows);
+  }
+  return c;
 }
 
 // Shape of the several-steps launches over a set of chains: the one that gives the
@@ -900,35 +920,46 @@ static void steps_tile(const StepShape& g, int L0, int L1, int& bx, int& by, int
 // than 1024 tiles keep every CU busy, so the mean counts, and workgroups of 512
 // threads at most, three of which share a CU (4096^2: H = 3 at 512 threads 23.2
 // us, H = 2 24.8, H = 3 at 768 threads 25.7).
-StepShape choose_steps(int precision, const std::vector<std::pair<int, int>>& lattices) {
+//
+// A workgroup alone on its CU waits for LDS and transcendentals, so of equal costs there
+// the one with more waves is taken (512^2 FP32: 32 x 32 with H = 3 62.9 us a trajectory
+// of 20 steps, with H = 1 53.7).
+//
+// FP64 launches of more than 1024 tiles of 64 x 50 take two steps: the ring of four costs
+// more there than the passes over memory that it saves, and LDS leaves one workgroup a CU
+// to 64 x 64 tiles, two to 64 x 50 (us a trajectory of 20 steps, four and two a launch:
+// 2048^2 893 and 814, 3000 x 2000 1288 and 1072, 64 chains of 256^2 890 and 800; below the
+// line 1024^2 250 and 263, 256 chains of 100 x 90 524 and 557).  Smaller FP64 sets leave
+// out shapes of more than 1024 tiles, whose narrow tiles the cost flatters (1128^2 32 x 28
+// 510, 64 x 36 375).
+//
+// Chains of at most two middle steps stage the halo of two (max_middle; 520^2 FP64, n_md =
+// 3: 49.6 -> 43.7 us a trajectory, 512^2 FP32 30.2 -> 29.1).
+StepShape choose_steps(int precision, const std::vector<std::pair<int, int>>& lattices, int max_middle) {
+  if (precision == 8) {
+    StepShape g{2, 64, 64, 2, 512};
+    if (steps_load(g, lattices).tiles > 1024) return g;
+  }
+  const int steps = max_middle > 2 ? LAT_STEPS : 2;
   StepShape best;
+  StepLoad bl;
   double best_cost = 0.0;
   static const int kExtent[][2] = {{64, 64}, {64, 32}, {32, 32}, {32, 16}, {16, 16}};
   for (const auto& ex : kExtent)
     for (int H = precision == 4 ? 3 : 2; H >= 1; --H)
       for (int cap : {512, 1024}) {
-        StepShape g;
-        g.bx = ex[0];
-        g.by = ex[1];
-        g.H = H;
-        g.max_threads = cap;
-        int64_t tiles = 0, waves = 0;
-        int wmax = 0;
-        for (const auto& l : lattices) {
-          int bx, by, thr, rows;
-          steps_tile(g, l.first, l.second, bx, by, thr, rows);
-          const int64_t n = (int64_t)((l.first + bx - 1) / bx) * ((l.second + by - 1) / by);
-          tiles += n;
-          waves += n * (thr / 64);
-          wmax = std::max(wmax, thr / 64);
-          g.threads = std::max(g.threads, thr);
-          g.rows = std::max(g.rows, rows);
-        }
-        const bool full = tiles > 1024;
-        if (full && cap == 1024 && precision == 4) continue;
-        const double cost = full ? (double)waves * H / 1024.0 : (double)(((tiles + 255) / 256 * wmax + 3) / 4 * H);
-        if (best.H == 0 || cost < best_cost) {
+        StepShape g{steps, ex[0], ex[1], H, cap};
+        const StepLoad c = steps_load(g, lattices);
+        const bool full = c.tiles > 1024;
+        if (full && (cap == 1024 || (precision == 8 && (steps == 4 || ex[0] < 64)))) continue;
+        const double cost =
+            full ? (double)c.waves * H / 1024.0 : (double)(((c.tiles + 255) / 256 * c.wmax + 3) / 4 * H);
+        const int64_t rows = c.waves * H, best_rows = bl.waves * best.H;
+        const bool tie = cost == best_cost && c.tiles <= 256 && bl.tiles <= 256 &&
+                         (steps == 2 && rows != best_rows ? rows < best_rows : H < best.H);
+        if (best.H == 0 || cost < best_cost || tie) {
           best = g;
+          bl = c;
           best_cost = cost;
         }
       }
@@ -942,22 +973,28 @@ void steps_tiles(const StepShape& g, int chain, int L0, int L1, std::vector<Tile
     for (int x = 0; x < L0; x += bx) out.push_back(Tile{chain, x, y, bx | (by << 16)});
 }
 
-template <typename T, bool THROUGH>
-static void launch_steps(const StepShape& g, dim3 grid, dim3 block, size_t lds, const ChainDev* chains,
-                         const Tile* tiles, int n_tiles, int j, int k, int max_steps, hipStream_t s) {
-  if (g.H == 1) lattice_steps2v<T, 1, THROUGH><<<grid, block, lds, s>>>(chains, tiles, n_tiles, j, k, max_steps);
-  else if (g.H == 2) lattice_steps2v<T, 2, THROUGH><<<grid, block, lds, s>>>(chains, tiles, n_tiles, j, k, max_steps);
-  else if constexpr (sizeof(T) == 4)
-    lattice_steps2v<T, 3, THROUGH><<<grid, block, lds, s>>>(chains, tiles, n_tiles, j, k, max_steps);
+template <typename T, int STEPS, int H, bool THROUGH, bool FULL>
+static void launch_steps(const StepShape& g, const ChainDev* chains, const Tile* tiles, int n_tiles, int j, int k,
+                         int max_steps, hipStream_t s) {
+  const size_t lds = 2 * (size_t)g.rows * (MS_BX + 4 * STEPS) * sizeof(T);
+  lattice_steps2v<T, STEPS, H, THROUGH, FULL>
+      <<<(unsigned)n_tiles, (unsigned)g.threads, lds, s>>>(chains, tiles, n_tiles, j, k, max_steps);
+}
+
+template <typename T, int STEPS, bool THROUGH, bool FULL>
+static void launch_steps_h(const StepShape& g, const ChainDev* chains, const Tile* tiles, int n_tiles, int j, int k,
+                           int max_steps, hipStream_t s) {
+  if (g.H == 1) return launch_steps<T, STEPS, 1, THROUGH, FULL>(g, chains, tiles, n_tiles, j, k, max_steps, s);
+  if (g.H == 2) return launch_steps<T, STEPS, 2, THROUGH, FULL>(g, chains, tiles, n_tiles, j, k, max_steps, s);
+  if constexpr (sizeof(T) == 4)
+    launch_steps<T, STEPS, 3, THROUGH, FULL>(g, chains, tiles, n_tiles, j, k, max_steps, s);
 }
 
 hipError_t launch_lattice_steps(int precision, const StepShape& g, const ChainDev* chains, const Tile* tiles,
-                                int n_tiles, int j, int k, int max_steps, hipStream_t s) {
+                                int n_tiles, int j, int k, int max_steps, bool full, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-  if (max_steps < 1 || max_steps > STEPS || g.threads < 64 || g.threads > 1024) return hipErrorInvalidValue;
-  if (g.H < 1 || g.H > (precision == 4 ? 3 : 2)) return hipErrorInvalidValue;
-  const size_t lds = 2 * (size_t)g.rows * MS_RP * (size_t)precision;
-  const dim3 grid((unsigned)n_tiles), block((unsigned)g.threads);
+  if (max_steps < 1 || max_steps > g.steps || g.threads < 64 || g.threads > 1024) return hipErrorInvalidValue;
+  if ((g.steps != 2 && g.steps != 4) || g.H < 1 || g.H > (precision == 4 ? 3 : 2)) return hipErrorInvalidValue;
   if (precision == 4) {
     // Stores through the L2 where CUs hold more than one workgroup, so that others run while
     // one stores (us a trajectory: 1024^2 88 -> 84, 1448^2 145 -> 134, 100 x 90 x 256
@@ -966,10 +1003,15 @@ hipError_t launch_lattice_steps(int precision, const StepShape& g, const ChainDe
     // the parts of lines at ragged rows' ends go out twice (a set of 4096 uneven chains
     // 3.64e11 -> 3.55e11 site-MD-steps/s).  Not in FP64, whose two 16-byte stores a chunk
     // each cover half of every 32 bytes (512^2 x 16 566 -> 596, 2048^2 890 -> 932).
-    if (n_tiles > 256 && n_tiles <= 2048) launch_steps<float, true>(g, grid, block, lds, chains, tiles, n_tiles, j, k, max_steps, s);
-    else launch_steps<float, false>(g, grid, block, lds, chains, tiles, n_tiles, j, k, max_steps, s);
+    const bool through = n_tiles > 256 && n_tiles <= 2048;
+    auto launch = g.steps == 2 ? (through ? launch_steps_h<float, 2, true, false> : launch_steps_h<float, 2, false, false>)
+                  : full       ? (through ? launch_steps_h<float, 4, true, true> : launch_steps_h<float, 4, false, true>)
+                               : (through ? launch_steps_h<float, 4, true, false> : launch_steps_h<float, 4, false, false>);
+    launch(g, chains, tiles, n_tiles, j, k, max_steps, s);
+  } else if (g.steps == 4) {
+    launch_steps_h<double, 4, false, false>(g, chains, tiles, n_tiles, j, k, max_steps, s);
   } else {
-    launch_steps<double, false>(g, grid, block, lds, chains, tiles, n_tiles, j, k, max_steps, s);
+    launch_steps_h<double, 2, false, false>(g, chains, tiles, n_tiles, j, k, max_steps, s);
   }
   return hipGetLastError();
 }

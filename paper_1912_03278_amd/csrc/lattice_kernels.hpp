@@ -54,25 +54,27 @@ void resident_extend(ResidentShape& s, const ChainDev& c);
 hipError_t launch_lattice_resident(int precision, int ndim, const ResidentShape& r, const ChainDev* chains,
                                    const Tile* tiles, int n_chains, int n_traj, hipStream_t s);
 
-// Several middle steps per launch (2D): tiles of at most bx x by sites, threads
-// that own H rows of a 4-site chunk column each, workgroups of `threads` threads
-// (at most max_threads) and `rows` LDS rows per array.
+// Several middle steps per launch (2D): `steps` of them (2 or 4) on tiles of at most bx
+// x by sites, threads that own H rows of a 4-site chunk column each, workgroups of
+// `threads` threads (at most max_threads) and `rows` LDS rows per array.
 struct StepShape {
-  int bx = 0, by = 0, H = 0, max_threads = 0, threads = 0, rows = 0;
+  int steps = 0, bx = 0, by = 0, H = 0, max_threads = 0, threads = 0, rows = 0;
 };
-StepShape choose_steps(int precision, const std::vector<std::pair<int, int>>& lattices);
+// max_middle: middle steps of the chain that has most.
+StepShape choose_steps(int precision, const std::vector<std::pair<int, int>>& lattices, int max_middle);
 void steps_tiles(const StepShape& g, int chain, int L0, int L1, std::vector<Tile>& out);
-// Middle steps j .. j + max_steps - 1 (at most LAT_STEPS; each chain those that it
-// has) as launch index k over n_tiles entries of steps_tiles.
+// Middle steps j .. j + max_steps - 1 (at most g.steps; each chain those that it
+// has) as launch index k over n_tiles entries of steps_tiles.  full: max_steps is
+// g.steps and every chain of them has as many.
 hipError_t launch_lattice_steps(int precision, const StepShape& g, const ChainDev* chains, const Tile* tiles,
-                                int n_tiles, int j, int k, int max_steps, hipStream_t s);
+                                int n_tiles, int j, int k, int max_steps, bool full, hipStream_t s);
 
 // Launch one pass of kind `mode` (pass index j of the trajectory, which sets
 // the kick and drift; launch index k, which sets the field buffers) over n_tiles
 // consecutive entries of `tiles`; all tiles must belong to chains of the given
 // precision, dimension and tile class.  A LAST launch with j < 0 runs every
 // chain's own last pass (j = n_pass - 1), with the launch index that follows its
-// middle steps when k != 0 (LAT_STEPS per launch) or j when k == 0.  sole: no other
+// middle steps when k != 0 (k per launch) or j when k == 0.  sole: no other
 // 3D launches run beside a 3D one's (its stores' kind, not its results, depends on it).
 hipError_t launch_lattice_pass(int precision, int ndim, int cls, int mode, const ChainDev* chains,
                                const Tile* tiles, int n_tiles, int j, int k, hipStream_t s, bool sole = true);

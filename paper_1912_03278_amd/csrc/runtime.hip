@@ -310,7 +310,7 @@ void plan_groups(const std::vector<ChainDev>& cd, const std::vector<int>& member
     if (g.ndim == 2 && !resident) {  // tiles of the fused middle steps (and of their timing)
       std::vector<std::pair<int, int>> ls;
       for (int ci : g.order) ls.emplace_back(cd[ci].L0, cd[ci].L1);
-      g.steps = choose_steps(g.prec, ls);
+      g.steps = choose_steps(g.prec, ls, cd[g.order[0]].n_pass - 2);
       g.st_off = (int)tiles.size() - base;
       for (int ci : g.order) {
         g.st_begin.push_back((int)tiles.size() - base - g.st_off);
@@ -736,8 +736,9 @@ struct RoundSink {
                   hipStream_t st) {
     return pool ? launch_lattice_pass(g.prec, g.ndim, g.cls, mode, d_cd, t, n, j, k, st, g.sole3d) : hipSuccess;
   }
-  hipError_t steps(const Group& g, const ChainDev* d_cd, const Tile* t, int n, int j, int k, hipStream_t st) {
-    return pool ? launch_lattice_steps(g.prec, g.steps, d_cd, t, n, j, k, LAT_STEPS, st) : hipSuccess;
+  hipError_t steps(const Group& g, const ChainDev* d_cd, const Tile* t, int n, int j, int k, bool full,
+                   hipStream_t st) {
+    return pool ? launch_lattice_steps(g.prec, g.steps, d_cd, t, n, j, k, g.steps.steps, full, st) : hipSuccess;
   }
   hipError_t resident(const Group& g, const ChainDev* d_cd, const Tile* t, int n, hipStream_t st) {
     return pool ? launch_resident_group(g, d_cd, t, n, 1, st) : hipSuccess;
@@ -769,15 +770,17 @@ static hipError_t round_plan(const std::vector<Group>& groups, const Tile* d_til
     if ((e = sk.pass(g, PASS_FIRST, d_cd, base, g.tile_begin.back(), 0, 0, gs)) != hipSuccess) return e;
     const int nc = (int)g.order.size();
     if (g.pair) {
-      // Middle steps LAT_STEPS at a time, from j = 1: launch k = 1 + (j - 1) /
-      // LAT_STEPS runs over the chains with passes after j (chain order is
-      // descending pass count); a chain with fewer steps left takes those.
-      for (int j = 1; j < g.max_pass; j += LAT_STEPS) {
-        const int k = 1 + (j - 1) / LAT_STEPS;
+      // Middle steps `st` at a time, from j = 1: launch k = 1 + (j - 1) / st runs over
+      // the chains with passes after j (chain order is descending pass count); a
+      // chain with fewer steps left takes those.
+      const int st = g.steps.steps;
+      for (int j = 1; j < g.max_pass; j += st) {
+        const int k = 1 + (j - 1) / st;
         int end = 0;
         while (end < nc && g.n_pass[end] - 1 > j) ++end;
         if (end > 0) {
-          if ((e = sk.steps(g, d_cd, d_tiles + g.st_off, g.st_begin[end], j, k, gs)) != hipSuccess) return e;
+          const bool full = g.n_pass[end - 1] - 1 - j >= st;
+          if ((e = sk.steps(g, d_cd, d_tiles + g.st_off, g.st_begin[end], j, k, full, gs)) != hipSuccess) return e;
         }
       }
     }
@@ -790,7 +793,7 @@ static hipError_t round_plan(const std::vector<Group>& groups, const Tile* d_til
     }
     // the last pass of every chain of the group in one launch, each chain at
     // its own pass and buffers: no launch of the round waits on another stream
-    if ((e = sk.pass(g, PASS_LAST, d_cd, base, g.tile_begin.back(), -1, g.pair ? 1 : 0, gs)) != hipSuccess)
+    if ((e = sk.pass(g, PASS_LAST, d_cd, base, g.tile_begin.back(), -1, g.pair ? g.steps.steps : 0, gs)) != hipSuccess)
       return e;
     if ((e = sk.join(gs, s)) != hipSuccess) return e;
   }
@@ -1513,7 +1516,7 @@ extern "C" int ihmc_chains_time_pass(ihmc_chains* ch, int32_t group, int32_t mod
   HIPCHK(hipEventCreate(&e1), "event");
   auto launch = [&]() {
     if (mode == PASS_PAIR)
-      return launch_lattice_steps(g.prec, g.steps, c->d_cd, c->d_tiles + g.st_off, g.st_begin.back(), 1, 1, 2, s);
+      return launch_lattice_steps(g.prec, g.steps, c->d_cd, c->d_tiles + g.st_off, g.st_begin.back(), 1, 1, 2, false, s);
     return launch_lattice_pass(g.prec, g.ndim, g.cls, mode, c->d_cd, c->d_tiles + g.tile_off, g.tile_begin.back(), 1, 1, s);
   };
   hipError_t e = launch();

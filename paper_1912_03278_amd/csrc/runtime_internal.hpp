@@ -127,7 +127,7 @@ int tune_load(TuneTable& t, const char* path);
 // Chains of equal state precision and dimension share launches.
 struct Group {
   int prec = 4, ndim = 2, cls = 0;
-  bool pair = false;            // middle steps LAT_STEPS per launch (2D)
+  bool pair = false;            // middle steps steps.steps per launch (2D)
   StepShape steps;              // 2D groups: shape and tiles of those launches
   int st_off = 0;               // first of their tiles, relative to the plan's
   std::vector<int> st_begin;    // as tile_begin, relative to st_off
@@ -147,7 +147,7 @@ int64_t lattice_sites(const ihmc_lattice& l);
 // Descriptor of one chain whose passes use tile class `cls` (no device memory).
 void describe_chain(const ihmc_lattice& l, const ihmc_run& r, int flags, int cls, ChainDev& c);
 uint32_t chain_tile_count(const ChainDev& c);
-// fuse_steps: 2D tiled groups run their middle steps LAT_STEPS per launch.
+// fuse_steps: 2D tiled groups run several middle steps per launch.
 void plan_groups(const std::vector<ChainDev>& cd, const std::vector<int>& members, std::vector<Group>& groups,
                  std::vector<Tile>& tiles, bool fuse_steps);
 size_t round_events(const std::vector<Group>& groups);
@@ -230,7 +230,7 @@ struct ihmc_ctx {
   bool dead = false;
   ihmc::TuneTable tune;
   int64_t resident_sites = -1;  // chains up to this many sites run LDS-resident (-1: as many as fit, 0: none)
-  int32_t fuse_steps = 1;       // 2D tiled chains run LAT_STEPS middle steps per launch
+  int32_t fuse_steps = 1;       // 2D tiled chains run up to LAT_STEPS middle steps per launch
   ihmc::Stage stage;            // pinned buffer of set-ups and results
   void* scratch = nullptr;      // this device's scratch of the allocation-free entry point
 };
