@@ -178,13 +178,37 @@ hipError_t launch_force_tiles(const ChainDev& c, const void* psi, void* F, hipSt
   return hipGetLastError();
 }
 
-// Tiles of four sites a thread where they still give each CU four blocks.
+// Work of a launch on BX x BY x BZ tiles, padding included: staged values and two per
+// w, over all tiles; a quarter more where rows of four are loaded.
+double force_work(const ChainDev& c, int bx, int by, int bz) {
+  const int hz = c.ndim == 3 ? 1 : 0;
+  const double tiles = (double)((c.L0 + bx - 1) / bx) * ((c.L1 + by - 1) / by) * ((c.L2 + bz - 1) / bz);
+  const double w = tiles * ((bx + 4) * (by + 4) * (bz + 4 * hz) + 2 * (bx + 2) * (by + 2) * (bz + 2 * hz));
+  return bx == 4 ? 1.25 * w : w;
+}
+
+// The tile with the least work; those of four sites a thread where they still give each
+// CU four blocks.  Thin lattices fill little of a wide tile (FP32, on 64 x 16 or 16 x 16 x
+// 4 sites, on the tile taken, and in four launches: 4 x 500000 75, 9.7 and 33 us, 3 x 3 x
+// 200000 296, 25 and 153, 200000 x 3 x 3 68, 27 and 34, 3 x 200000 x 3 73, 25 and 56).
 template <typename T>
 hipError_t launch_force(const ChainDev& c, const void* psi, void* F, hipStream_t s) {
-  const bool large = c.N >= 1024 * 1024;
-  if (c.ndim == 2)
-    return large ? launch_force_tiles<T, 2, 64, 16, 1>(c, psi, F, s) : launch_force_tiles<T, 2, 32, 8, 1>(c, psi, F, s);
-  return large ? launch_force_tiles<T, 3, 16, 16, 4>(c, psi, F, s) : launch_force_tiles<T, 3, 16, 4, 4>(c, psi, F, s);
+  using Launch = hipError_t (*)(const ChainDev&, const void*, void*, hipStream_t);
+  struct Tile {
+    int ndim, bx, by, bz;
+    Launch launch;
+  };
+  static const Tile kTiles[] = {
+      {2, 64, 16, 1, launch_force_tiles<T, 2, 64, 16, 1>}, {2, 32, 8, 1, launch_force_tiles<T, 2, 32, 8, 1>},
+      {2, 4, 64, 1, launch_force_tiles<T, 2, 4, 64, 1>},   {3, 16, 16, 4, launch_force_tiles<T, 3, 16, 16, 4>},
+      {3, 16, 4, 4, launch_force_tiles<T, 3, 16, 4, 4>},   {3, 4, 16, 4, launch_force_tiles<T, 3, 4, 16, 4>},
+      {3, 4, 4, 16, launch_force_tiles<T, 3, 4, 4, 16>}};
+  const Tile* best = nullptr;
+  for (const Tile& t : kTiles) {
+    if (t.ndim != c.ndim || (t.bx * t.by * t.bz > 256 && c.N < 1024 * 1024)) continue;
+    if (!best || force_work(c, t.bx, t.by, t.bz) < force_work(c, best->bx, best->by, best->bz)) best = &t;
+  }
+  return best->launch(c, psi, F, s);
 }
 }  // namespace
 
