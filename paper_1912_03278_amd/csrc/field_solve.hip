@@ -5,7 +5,8 @@
 // x enters the starting field of a translated chain, and a trajectory in FP64
 // amplifies a last digit of it to 1e-3 in 200 trajectories, so x comes from the
 // conjugate gradients that always gave it, operation for operation (k_field_cg),
-// and a seed keeps its trajectory.  The constants enter the estimators only.
+// and a seed keeps its trajectory.  The constants enter the estimators only; they come
+// from a transform, except on lattices too long and thin for it (field_by_transform).
 //
 // On the periodic lattice Kt is diagonal in the real plane waves
 // prod_d cas(2 pi k_d x_d / L_d), cas = cos + sin (the shift operators along an
@@ -27,6 +28,7 @@
 // order of its own chain, so the constants do not depend on which chains share
 // the launches.
 #include <algorithm>
+#include <cmath>
 
 #include "device_common.hpp"
 #include "runtime_internal.hpp"
@@ -263,6 +265,27 @@ __global__ __launch_bounds__(FTHREADS) void k_field_cg(ChainDev* __restrict__ cd
 }
 
 }  // namespace
+
+// Which of the two gives a chain's constants, by the chain alone (so they do not depend on
+// the set): the transform fills the GPU but takes L products a site along every axis, on
+// tiles of 64 columns; the conjugate gradients take one CU and a number of iterations that
+// the extreme eigenvalues set.  The transform while its products stay below 16384 a site
+// and iteration: at the line it is 4 to 5 times as fast for one chain (3 x 3 x 60000 23
+// against 194 ms, 65536 x 8 at C = 1000 23 against 25), beyond it soon slower (2^20 x 3:
+// 9700 ms against 1280 at C = 4.1 and 175 at C = 1000), and slower from the start for
+// sets of many such chains, which the conjugate gradients solve side by side.
+bool field_by_transform(const ChainDev& c) {
+  const int64_t L[3] = {c.L0, c.L1, c.L2};
+  double products = 0.0, lo = c.C, hi = c.C;
+  for (int a = 0; a < c.ndim; ++a) {
+    products += (double)((L[a] + FT - 1) / FT) * (double)((c.N / L[a] + FT - 1) / FT) * (FT * FT) * (double)L[a];
+    lo += 2.0 * std::cos(2.0 * M_PI * (double)(L[a] / 2) / (double)L[a]);
+    hi += 2.0;
+  }
+  const double root = std::sqrt(hi / lo);
+  const double iterations = std::ceil(std::log(2e15) / std::log((root + 1.0) / (root - 1.0)));
+  return products <= 16384.0 * (double)c.N * iterations;
+}
 
 hipError_t launch_field_solve(ChainDev* d_cd, const std::vector<const ChainDev*>& host, const int* which, double* work,
                               const int64_t* woff, size_t plain, hipStream_t s) {

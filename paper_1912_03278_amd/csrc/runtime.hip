@@ -620,7 +620,7 @@ int Chains::build(int32_t n_, const ihmc_lattice* lats, const ihmc_run* runs, in
   std::vector<const ChainDev*> fs_cd;
   int64_t fs_total = 0;
   const size_t fs_plain =
-      std::stable_partition(fs_idx.begin(), fs_idx.end(), [&](int i) { return runs[i].form != FORM_SHIFTED; }) -
+      std::stable_partition(fs_idx.begin(), fs_idx.end(), [&](int i) { return runs[i].form != FORM_SHIFTED && field_by_transform(cd[i]); }) -
       fs_idx.begin();
   for (int i : fs_idx) {
     fs_off.push_back(fs_total);

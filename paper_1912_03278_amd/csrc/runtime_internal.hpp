@@ -164,9 +164,11 @@ hipError_t enqueue_round_plan(const std::vector<Group>& groups, const Tile* d_ti
 hipError_t launch_field_setup(const ChainDev* d_cd, int ci, const double* h, double beta, int64_t N, int precision,
                               hipStream_t s);
 // h'^T Kt^-1 h' and 1^T Kt^-1 h' of the chains `which` (device int array; host:
-// their descriptors in the same order), and for all but the first `plain` of them,
-// the chains that run in translated coordinates, also Kt^-1 h' in site order at the
-// start of their work space: 4 N doubles per chain at woff (field_solve.hip).
+// their descriptors in the same order), the first `plain` by the transform, the others
+// by conjugate gradients, which also leave Kt^-1 h' in site order at the start of the
+// chain's work space: 4 N doubles per chain at woff (field_solve.hip).  Chains that run
+// in translated coordinates need that; of the others, those of field_by_transform take it.
+bool field_by_transform(const ChainDev& c);
 hipError_t launch_field_solve(ChainDev* d_cd, const std::vector<const ChainDev*>& host, const int* which, double* work,
                               const int64_t* woff, size_t plain, hipStream_t s);
 hipError_t launch_measure(const std::vector<Group>& groups, const Tile* d_tiles, const ChainDev* d_cd, hipStream_t s);

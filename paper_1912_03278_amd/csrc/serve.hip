@@ -407,7 +407,7 @@ bool ihmc_server::admit_setup(std::vector<Request*>& fresh) {
     return p;
   };
   std::vector<Request*> ok;
-  std::vector<int> fs_slots, fs_translated;
+  std::vector<int> fs_slots, fs_cg;
   std::vector<int64_t> fs_off;
   int64_t fs_total = 0;
   // the set-up runs with the device idle: the round in flight finishes first
@@ -465,7 +465,7 @@ bool ihmc_server::admit_setup(std::vector<Request*>& fresh) {
       if (!t) e = hipErrorOutOfMemory;
       if (e == hipSuccess) e = hipMemcpyAsync(t, r->h.data(), 8 * c.N, hipMemcpyHostToDevice, s);
       if (e == hipSuccess) e = launch_field_setup(d_cd, r->slot, t, r->lat.beta, c.N, c.precision, s);
-      (r->run.form == FORM_SHIFTED ? fs_translated : fs_slots).push_back(r->slot);
+      (r->run.form == FORM_SHIFTED || !field_by_transform(c) ? fs_cg : fs_slots).push_back(r->slot);
     }
     const bool translated = r->run.form == FORM_SHIFTED && c.h_kind == 2;
     if (e == hipSuccess) {
@@ -484,7 +484,7 @@ bool ihmc_server::admit_setup(std::vector<Request*>& fresh) {
     ok.push_back(r);
   }
   const size_t fs_plain = fs_slots.size();
-  fs_slots.insert(fs_slots.end(), fs_translated.begin(), fs_translated.end());
+  fs_slots.insert(fs_slots.end(), fs_cg.begin(), fs_cg.end());
   if (e == hipSuccess && !fs_slots.empty()) {
     for (int k : fs_slots) {
       fs_off.push_back(fs_total);
