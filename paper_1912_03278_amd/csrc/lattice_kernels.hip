@@ -1052,19 +1052,21 @@ static hipError_t launch_mode2v(int mode, const ChainDev* chains, const Tile* ti
 //   224, 222, 205; FP64 96^3 359, 357, 339; beside other groups 30 chains of 16^3 .. 70^3
 //   in three classes 224, -, 228);
 // - from 1M sites (two boxes a CU, which hide the longer stores) to 128 MiB through the L2
-//   (st4_through): 160^3 378, 357, 445; 256
-//   chains of 24 x 21 x 30 620, 589, 671; FP64 128^3 680, 641, 709;
+//   (st4_through), where every row starts at a whole 32 bytes (aligned): 160^3 378, 357,
+//   445; 256 chains of 24 x 21 x 30 620, 589, 671; FP64 128^3 680, 641, 709.  Other rows'
+//   stores go out in halves of sectors, each twice: 132 x 128 x 128 265, 276, 249; 140^3
+//   332, 338, 351; 30 chains of 36^3 264, 274, 260; 50 of 33^3 407, 421, 402;
 // - above plainly: most lines are written back within the launch anyway (512 chains of
 //   24 x 21 x 30 1108, 1109; FP64 4000, 4040; 256^3 nontemporal 1170 -> 1570).
 // Three kernels: a choice inside one costs small launches 1.5 %.
 template <typename T, int BX, int BY, int ZR>
 static void launch_middle3t(const ChainDev* chains, const Tile* tiles, int n_tiles, int j, int k, bool sole,
-                            hipStream_t s) {
+                            bool aligned, hipStream_t s) {
   const dim3 grid(n_tiles), block(64 * ZR);
   const int64_t touched = (int64_t)n_tiles * ZR * 256 * 4 * (int)sizeof(T), l2 = 32 << 20;
   if (touched <= l2 && sole)
     lattice_pass3t<T, BX, BY, ZR, PASS_MIDDLE, StoreKind::nontemporal><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
-  else if ((int64_t)n_tiles * ZR > 4096 && touched <= 4 * l2)
+  else if (aligned && (int64_t)n_tiles * ZR > 4096 && touched <= 4 * l2)
     lattice_pass3t<T, BX, BY, ZR, PASS_MIDDLE, StoreKind::through><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
   else
     lattice_pass3t<T, BX, BY, ZR, PASS_MIDDLE><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
@@ -1072,7 +1074,7 @@ static void launch_middle3t(const ChainDev* chains, const Tile* tiles, int n_til
 
 template <typename T, int BX, int BY, int ZR>
 static hipError_t launch_mode3t(int mode, const ChainDev* chains, const Tile* tiles, int n_tiles, int j, int k,
-                                bool sole, hipStream_t s) {
+                                bool sole, bool aligned, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
   dim3 grid(n_tiles), block(64 * ZR);
   switch (mode) {
@@ -1080,7 +1082,7 @@ static hipError_t launch_mode3t(int mode, const ChainDev* chains, const Tile* ti
       lattice_pass3t<T, BX, BY, ZR, PASS_FIRST><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
       break;
     case PASS_MIDDLE:
-      launch_middle3t<T, BX, BY, ZR>(chains, tiles, n_tiles, j, k, sole, s);
+      launch_middle3t<T, BX, BY, ZR>(chains, tiles, n_tiles, j, k, sole, aligned, s);
       break;
     case PASS_LAST:
       lattice_pass3t<T, BX, BY, ZR, PASS_LAST><<<grid, block, 0, s>>>(chains, tiles, n_tiles, j, k);
@@ -1132,7 +1134,7 @@ TileShape tile_shape(int precision, int ndim, int cls) {
 }
 
 hipError_t launch_lattice_pass(int precision, int ndim, int cls, int mode, const ChainDev* chains,
-                               const Tile* tiles, int n_tiles, int j, int k, hipStream_t s, bool sole) {
+                               const Tile* tiles, int n_tiles, int j, int k, hipStream_t s, bool sole, bool aligned) {
   if (cls < 0) return hipErrorInvalidValue;  // resident chains run whole trajectories (launch_resident_group)
   if (precision == 4) {
     if (ndim == 2) {
@@ -1141,10 +1143,10 @@ hipError_t launch_lattice_pass(int precision, int ndim, int cls, int mode, const
       return launch_mode2v<float, 64, 16>(mode, chains, tiles, n_tiles, j, k, s);
     }
     switch (cls) {
-      case 1: return launch_mode3t<float, 16, 16, 4>(mode, chains, tiles, n_tiles, j, k, sole, s);
-      case 2: return launch_mode3t<float, 32, 8, 8>(mode, chains, tiles, n_tiles, j, k, sole, s);
-      case 3: return launch_mode3t<float, 16, 16, 8>(mode, chains, tiles, n_tiles, j, k, sole, s);
-      default: return launch_mode3t<float, 32, 8, 4>(mode, chains, tiles, n_tiles, j, k, sole, s);
+      case 1: return launch_mode3t<float, 16, 16, 4>(mode, chains, tiles, n_tiles, j, k, sole, aligned, s);
+      case 2: return launch_mode3t<float, 32, 8, 8>(mode, chains, tiles, n_tiles, j, k, sole, aligned, s);
+      case 3: return launch_mode3t<float, 16, 16, 8>(mode, chains, tiles, n_tiles, j, k, sole, aligned, s);
+      default: return launch_mode3t<float, 32, 8, 4>(mode, chains, tiles, n_tiles, j, k, sole, aligned, s);
     }
   }
   if (ndim == 2) {
@@ -1153,10 +1155,10 @@ hipError_t launch_lattice_pass(int precision, int ndim, int cls, int mode, const
     return launch_mode2v<double, 64, 16>(mode, chains, tiles, n_tiles, j, k, s);
   }
   switch (cls) {
-    case 1: return launch_mode3t<double, 16, 16, 4>(mode, chains, tiles, n_tiles, j, k, sole, s);
-    case 2: return launch_mode3t<double, 32, 8, 8>(mode, chains, tiles, n_tiles, j, k, sole, s);
-    case 3: return launch_mode3t<double, 16, 16, 8>(mode, chains, tiles, n_tiles, j, k, sole, s);
-    default: return launch_mode3t<double, 32, 8, 4>(mode, chains, tiles, n_tiles, j, k, sole, s);
+    case 1: return launch_mode3t<double, 16, 16, 4>(mode, chains, tiles, n_tiles, j, k, sole, aligned, s);
+    case 2: return launch_mode3t<double, 32, 8, 8>(mode, chains, tiles, n_tiles, j, k, sole, aligned, s);
+    case 3: return launch_mode3t<double, 16, 16, 8>(mode, chains, tiles, n_tiles, j, k, sole, aligned, s);
+    default: return launch_mode3t<double, 32, 8, 4>(mode, chains, tiles, n_tiles, j, k, sole, aligned, s);
   }
 }
 

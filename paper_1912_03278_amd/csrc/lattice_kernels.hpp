@@ -75,8 +75,10 @@ hipError_t launch_lattice_steps(int precision, const StepShape& g, const ChainDe
 // precision, dimension and tile class.  A LAST launch with j < 0 runs every
 // chain's own last pass (j = n_pass - 1), with the launch index that follows its
 // middle steps when k != 0 (k per launch) or j when k == 0.  sole: no other
-// 3D launches run beside a 3D one's (its stores' kind, not its results, depends on it).
+// 3D launches run beside a 3D one's; aligned: all chains' rows start at multiples of 32
+// bytes (the kind of a 3D middle launch's stores, not its results, depends on them).
 hipError_t launch_lattice_pass(int precision, int ndim, int cls, int mode, const ChainDev* chains,
-                               const Tile* tiles, int n_tiles, int j, int k, hipStream_t s, bool sole = true);
+                               const Tile* tiles, int n_tiles, int j, int k, hipStream_t s, bool sole = true,
+                               bool aligned = true);
 
 }  // namespace ihmc

@@ -305,6 +305,7 @@ void plan_groups(const std::vector<ChainDev>& cd, const std::vector<int>& member
             for (int x = 0; x < c.L0; x += ts.bx) tiles.push_back(Tile{ci, x, y, z});
       }
       g.n_pass.push_back(c.n_pass);
+      g.aligned = g.aligned && c.pitch * c.precision % 32 == 0;
     }
     g.tile_begin.push_back((int)tiles.size() - base - g.tile_off);
     if (g.ndim == 2 && !resident) {  // tiles of the fused middle steps (and of their timing)
@@ -734,7 +735,7 @@ struct RoundSink {
   }
   hipError_t pass(const Group& g, int mode, const ChainDev* d_cd, const Tile* t, int n, int j, int k,
                   hipStream_t st) {
-    return pool ? launch_lattice_pass(g.prec, g.ndim, g.cls, mode, d_cd, t, n, j, k, st, g.sole3d) : hipSuccess;
+    return pool ? launch_lattice_pass(g.prec, g.ndim, g.cls, mode, d_cd, t, n, j, k, st, g.sole3d, g.aligned) : hipSuccess;
   }
   hipError_t steps(const Group& g, const ChainDev* d_cd, const Tile* t, int n, int j, int k, bool full,
                    hipStream_t st) {
@@ -1517,7 +1518,8 @@ extern "C" int ihmc_chains_time_pass(ihmc_chains* ch, int32_t group, int32_t mod
   auto launch = [&]() {
     if (mode == PASS_PAIR)
       return launch_lattice_steps(g.prec, g.steps, c->d_cd, c->d_tiles + g.st_off, g.st_begin.back(), 1, 1, 2, false, s);
-    return launch_lattice_pass(g.prec, g.ndim, g.cls, mode, c->d_cd, c->d_tiles + g.tile_off, g.tile_begin.back(), 1, 1, s);
+    return launch_lattice_pass(g.prec, g.ndim, g.cls, mode, c->d_cd, c->d_tiles + g.tile_off, g.tile_begin.back(), 1, 1, s,
+                               g.sole3d, g.aligned);
   };
   hipError_t e = launch();
   if (e == hipSuccess) e = hipEventRecord(e0, s);

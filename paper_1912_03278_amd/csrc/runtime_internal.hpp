@@ -138,6 +138,7 @@ struct Group {
   int tile_off = 0;
   int max_pass = 0;
   bool sole3d = false;          // no other tiled 3D group in the plan
+  bool aligned = true;          // every chain's rows start at a multiple of 32 bytes
 };
 
 // Chain descriptors, launch plans and rounds shared by the resident chain sets
