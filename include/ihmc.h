@@ -556,10 +556,10 @@ int ihmc_copy_bandwidth(ihmc_ctx* ctx, uint64_t bytes, int32_t reps, double* avg
  * not NULL) = number of classes of ndim (out may be NULL to ask only that). */
 int ihmc_tile_shape(int32_t ndim, int32_t cls, int32_t* out, int32_t* n_classes);
 /* Autotune: for each distinct key among lats[0..n) (state precision
- * precision[i]), time the one-step middle pass of every tile class (in 2D the
- * class sets the first and last passes; fused middle steps have tiles of their
- * own, see ihmc_ctx_set_step_fusion) and keep the fastest
- * in the table (the built-in rule's class stays unless another is over 3 % faster).  A measurement
+ * precision[i]), time every tile class and keep the fastest in the table (the
+ * built-in rule's class stays unless another is over 3 % faster).  Timed is the
+ * one-step middle pass, or in 2D, where fused middle steps have tiles of their own
+ * (ihmc_ctx_set_step_fusion), the first and last pass together.  A measurement
  * runs on the context stream over replicas of the lattice with synthetic
  * fields, about `sites` sites in all (at most 65536 replicas): the working set
  * the choice is for, since whether the state streams from HBM or stays in the

@@ -107,7 +107,7 @@ constexpr int kMaxTileClasses = 4;
 struct TuneEntry {
   int32_t cls = 0;
   int32_t source = IHMC_TUNE_RULE;
-  double ns_site[kMaxTileClasses];  // middle-pass ns per site of each class (NaN: not measured)
+  double ns_site[kMaxTileClasses];  // ns per site of each class as measure_key times it (NaN: not measured)
 };
 struct TuneTable {
   std::mutex mu;

@@ -2,11 +2,14 @@
 //
 // Every tile class gives bitwise the same trajectories (sums are formed per
 // x-aligned quad of sites and per 4-plane column, then added in exact fixed
-// point), so the class is a pure speed choice.  The tuner times the middle
-// pass -- the pass a trajectory repeats n_md - 1 times -- of each class on
-// replicas of a lattice shape with synthetic fields, and keeps the fastest in
-// the context's table; chains take their class from the table when they are
-// created.  The table can be saved to and loaded from a JSON file.
+// point), so the class is a pure speed choice.  The tuner times what a trajectory
+// runs on the class's tiles on replicas of a lattice shape with synthetic fields: the
+// middle pass, which it repeats n_md - 1 times, or, in 2D where middle steps run
+// several a launch on tiles of their own, the first and the last pass.  These are
+// bound by FP64 and random numbers, not by staging as the middle pass is: the class
+// fastest there was up to 33 % slower in them (1M sites of 200^2: 64 x 16 35.8 us, 32 x
+// 32 26.8).  It keeps the fastest in the context's table; chains take their class from
+// the table when they are created.  The table can be saved to and loaded from a JSON file.
 
 #include <hip/hip_runtime.h>
 
@@ -78,13 +81,32 @@ __global__ void k_tune_states(ChainState* st, int n) {
 }
 
 static inline uint64_t r256(uint64_t b) { return (b + 255ull) & ~255ull; }
+static inline uint64_t r64(uint64_t b) { return (b + 63ull) & ~63ull; }
+
+// Bytes of the partial sums that FIRST and LAST passes of n_tiles tiles need, and the
+// replicas' pointers into theirs (at byte `at` of each replica's block of `stride` bytes).
+static uint64_t tune_partials(uint32_t n_tiles) {
+  return r64(16ull * NPART * (n_tiles + part_groups(n_tiles)) + 4ull * part_groups(n_tiles));
+}
+__global__ void k_tune_partials(ChainDev* cd, int n, char* blocks, uint64_t stride, uint64_t at, uint32_t n_tiles) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  char* b = blocks + (uint64_t)i * stride + at;
+  const uint64_t ng = part_groups(n_tiles);
+  ChainDev& c = cd[i];
+  c.n_tiles = n_tiles;
+  c.part = (uint64_t*)b;
+  c.gsum = (uint64_t*)(b + 16ull * NPART * n_tiles);
+  c.gcnt = (uint32_t*)(b + 16ull * NPART * (n_tiles + ng));
+  for (uint64_t g = 0; g < ng; ++g) c.gcnt[g] = 0u;
+}
 
 constexpr int64_t kTuneMinSites = int64_t(1) << 20;  // a launch this large fills the GPU
 constexpr int64_t kTuneMaxSites = int64_t(1) << 26;
 constexpr int64_t kTuneMaxReplicas = 65536;
 
-// Nanoseconds per site and middle step of every class of key k (timed on the
-// two-step launch for 2D when the context fuses steps): replicas of the
+// Nanoseconds per site of every class of key k, for a middle step, or for the first and
+// last pass together in 2D when the context fuses steps: replicas of the
 // lattice, each with its own fields, `sites` sites in all (the working set the
 // choice is for: whether it streams from HBM or stays in the last-level cache
 // decides which tile is fastest), one launch over all their tiles.
@@ -109,11 +131,24 @@ static int measure_key(ihmc_ctx* ctx, const TileKey& k, int64_t sites, int reps,
   r.precision = k.prec;
   ChainDev c0;
   describe_chain(l, r, 0, 0, c0);
-  const int64_t R = std::min(kTuneMaxReplicas, std::max<int64_t>(1, (sites + N / 2) / N));
+  const int64_t R0 = std::min(kTuneMaxReplicas, std::max<int64_t>(1, (sites + N / 2) / N));
   const int ncls = tile_class_count(k.ndim);
   const uint64_t pb = (uint64_t)k.prec;
-  const uint64_t fb =
-      r256(((uint64_t)LAT_BUFFERS + (uint64_t)LAT_P_BUFFERS + (uint64_t)k.site_field) * (uint64_t)c0.NP * pb);
+  // a replica's block: the field buffers (FIRST reads 0 and writes 1, LAST reads 1 and the
+  // states are reset after it), the momenta, the field, and for FIRST and LAST the field in
+  // FP64 and the partial sums
+  const bool ends = k.ndim == 2 && ctx->fuse_steps;
+  const uint64_t nb = ends ? 2 : LAT_BUFFERS, np = ends ? 1 : LAT_P_BUFFERS;
+  const uint64_t all = r256(((uint64_t)LAT_BUFFERS + (uint64_t)LAT_P_BUFFERS + (uint64_t)k.site_field) * (uint64_t)c0.NP * pb);
+  const uint64_t at_hp = r64((nb + np + (uint64_t)k.site_field) * (uint64_t)c0.NP * pb);
+  const uint64_t at_part = at_hp + (ends && k.site_field ? r64(8 * (uint64_t)c0.NP) : 0);
+  uint32_t most_tiles = 0;
+  for (int cls = 0; cls < ncls; ++cls) {
+    const TileShape ts = tile_shape(k.prec, k.ndim, cls);
+    most_tiles = std::max(most_tiles, (uint32_t)((k.L0 + ts.bx - 1) / ts.bx * ((k.L1 + ts.by - 1) / ts.by)));
+  }
+  const uint64_t fb = ends ? at_part + tune_partials(most_tiles) : all;
+  const int64_t R = std::max<int64_t>(1, std::min<int64_t>(R0, (int64_t)(R0 * all / fb)));  // within the memory of all buffers
 
   std::vector<std::vector<Tile>> tl(ncls);
   for (int cls = 0; cls < ncls; ++cls) {
@@ -123,7 +158,7 @@ static int measure_key(ihmc_ctx* ctx, const TileKey& k, int64_t sites, int reps,
         for (int y = 0; y < k.L1; y += ts.by)
           for (int x = 0; x < k.L0; x += ts.bx) tl[cls].push_back(Tile{(int32_t)q, x, y, z});
   }
-  uint64_t total = R * fb + r256(R * sizeof(ChainState)) + r256(R * sizeof(ChainDev));
+  uint64_t total = R0 * all + r256(R * sizeof(ChainState)) + r256(R * sizeof(ChainDev));  // (the fields' share of either form)
   for (int cls = 0; cls < ncls; ++cls) total += r256(tl[cls].size() * sizeof(Tile));
   char* blk = (char*)ctx->arena.alloc(total);
   if (!blk)
@@ -143,7 +178,7 @@ static int measure_key(ihmc_ctx* ctx, const TileKey& k, int64_t sites, int reps,
   } rel{ctx, blk};
 
   char* fields = blk;
-  ChainState* st = (ChainState*)(fields + R * fb);
+  ChainState* st = (ChainState*)(fields + R0 * all);
   ChainDev* d_cd = (ChainDev*)((char*)st + r256(R * sizeof(ChainState)));
   char* tp = (char*)d_cd + r256(R * sizeof(ChainDev));
   std::vector<Tile*> d_tl(ncls);
@@ -156,8 +191,10 @@ static int measure_key(ihmc_ctx* ctx, const TileKey& k, int64_t sites, int reps,
   for (int64_t q = 0; q < R; ++q) {
     char* f = fields + q * fb;
     cd[q].psi = f;
-    cd[q].p = f + LAT_BUFFERS * c0.NP * pb;
-    cd[q].b = k.site_field ? (const void*)(f + (LAT_BUFFERS + LAT_P_BUFFERS) * c0.NP * pb) : nullptr;
+    cd[q].p = f + nb * c0.NP * pb;
+    cd[q].b = k.site_field ? (const void*)(f + (nb + np) * c0.NP * pb) : nullptr;
+    cd[q].hp = ends && k.site_field ? (double*)(f + at_hp) : nullptr;
+    cd[q].cap = 0;  // no records
     cd[q].st = st + q;
   }
   const int64_t nel = (int64_t)(R * fb / pb);
@@ -165,7 +202,8 @@ static int measure_key(ihmc_ctx* ctx, const TileKey& k, int64_t sites, int reps,
   if (k.prec == 4) k_tune_fill<float><<<fgrid, 256, 0, s>>>((float*)fields, nel);
   else k_tune_fill<double><<<fgrid, 256, 0, s>>>((double*)fields, nel);
   HIPCHK(hipGetLastError(), "k_tune_fill");
-  k_tune_states<<<(unsigned)((R + 255) / 256), 256, 0, s>>>(st, (int)R);
+  const unsigned rgrid = (unsigned)((R + 255) / 256);
+  k_tune_states<<<rgrid, 256, 0, s>>>(st, (int)R);
   HIPCHK(hipGetLastError(), "k_tune_states");
   HIPCHK(hipMemcpyAsync(d_cd, cd.data(), R * sizeof(ChainDev), hipMemcpyHostToDevice, s), "tune chain upload");
   for (int cls = 0; cls < ncls; ++cls)
@@ -177,15 +215,28 @@ static int measure_key(ihmc_ctx* ctx, const TileKey& k, int64_t sites, int reps,
   // three interleaved rounds over the classes; the minimum of the round means
   double best[kMaxTileClasses];
   for (int cls = 0; cls < kMaxTileClasses; ++cls) best[cls] = NAN;
-  // (fused 2D middle steps run on tiles of their own: what the class sets there is
-  // the cost of the first and last passes, which stage and update as this one does)
+  const bool aligned = c0.pitch * k.prec % 32 == 0;
+  auto pass = [&](int cls, int mode) {
+    return launch_lattice_pass(k.prec, k.ndim, cls, mode, d_cd, d_tl[cls], (int)tl[cls].size(), mode != PASS_FIRST,
+                               mode != PASS_FIRST, s, true, aligned);
+  };
+  auto timed = [&](int cls) {
+    if (!ends) return pass(cls, PASS_MIDDLE);
+    hipError_t e = pass(cls, PASS_FIRST);
+    if (e == hipSuccess) e = pass(cls, PASS_LAST);
+    if (e != hipSuccess) return e;
+    k_tune_states<<<rgrid, 256, 0, s>>>(st, (int)R);
+    return hipGetLastError();
+  };
   for (int round = 0; round < 3; ++round) {
     for (int cls = 0; cls < ncls; ++cls) {
-      const int nt = (int)tl[cls].size();
-      HIPCHK(launch_lattice_pass(k.prec, k.ndim, cls, PASS_MIDDLE, d_cd, d_tl[cls], nt, 1, 1, s), "tune warm-up");
+      if (ends) {
+        k_tune_partials<<<rgrid, 256, 0, s>>>(d_cd, (int)R, fields, fb, at_part, (uint32_t)(tl[cls].size() / (size_t)R));
+        HIPCHK(hipGetLastError(), "k_tune_partials");
+      }
+      HIPCHK(timed(cls), "tune warm-up");
       HIPCHK(hipEventRecord(rel.e0, s), "event record");
-      for (int i = 0; i < reps; ++i)
-        HIPCHK(launch_lattice_pass(k.prec, k.ndim, cls, PASS_MIDDLE, d_cd, d_tl[cls], nt, 1, 1, s), "tune pass");
+      for (int i = 0; i < reps; ++i) HIPCHK(timed(cls), "tune pass");
       HIPCHK(hipEventRecord(rel.e1, s), "event record");
       HIPCHK(hipEventSynchronize(rel.e1), "event sync");
       float ms = 0.f;
