@@ -174,13 +174,17 @@ struct ihmc_server {
   ChainDev* d_cd = nullptr;
   std::vector<ChainDev> cd_host;  // slot table
   std::vector<int> free_slots;
-  Tile* d_tiles = nullptr;
+  // Tile tables and the export buffer take arena space that the budget does not count.
+  // Where there is none left for them they stay in pinned host memory, which the launches
+  // read and write directly, and where a request finds none they make room for it
+  // (shed_tables): no request fails for them.
+  Tile* d_tiles = nullptr;  // null: launches read h_tiles
   Tile* h_tiles = nullptr;  // pinned staging of the tile table (set-up of admitted chains)
   size_t tile_cap = 0;
   // the rounds' tile tables, two of each: a round is enqueued while the one
   // before it still runs, so its table goes to the other buffer; copy_ev[b]
-  // marks the upload from rh_tiles[b], which the host waits for before it
-  // writes that staging buffer again
+  // marks the upload from rh_tiles[b] (rd_tiles[b] null: the launches that read it),
+  // which the host waits for before it writes that staging buffer again
   Tile* rd_tiles[2] = {nullptr, nullptr};
   Tile* rh_tiles[2] = {nullptr, nullptr};
   hipEvent_t copy_ev[2] = {nullptr, nullptr};
@@ -205,6 +209,7 @@ struct ihmc_server {
   void fail_all(const char* what, hipError_t e);
   bool ensure_tiles(size_t n);
   bool ensure_round_tiles(size_t n);
+  void shed_tables();
   bool ensure_streams(size_t n_groups, size_t n_events);
   void take_checkpoints();
   void resume_requests(std::vector<Request*>& ok);
@@ -295,21 +300,21 @@ void ihmc_server::fail_all(const char* what, hipError_t e) {
 }
 
 bool ihmc_server::ensure_tiles(size_t n) {
-  if (n <= tile_cap) return true;
+  if (n <= tile_cap) {
+    if (!d_tiles) d_tiles = (Tile*)ctx->arena.alloc(sizeof(Tile) * tile_cap);
+    return true;
+  }
   const size_t cap = std::max<size_t>(n, 2 * tile_cap);
   if (d_tiles) ctx->arena.release(d_tiles);
   if (h_tiles) hipHostFree(h_tiles);
   d_tiles = nullptr;
   h_tiles = nullptr;
   tile_cap = 0;
-  d_tiles = (Tile*)ctx->arena.alloc(sizeof(Tile) * cap);
-  if (!d_tiles) return false;
   if (hipHostMalloc((void**)&h_tiles, sizeof(Tile) * cap, 0) != hipSuccess) {
     h_tiles = nullptr;
-    ctx->arena.release(d_tiles);
-    d_tiles = nullptr;
     return false;
   }
+  d_tiles = (Tile*)ctx->arena.alloc(sizeof(Tile) * cap);
   tile_cap = cap;
   return true;
 }
@@ -317,7 +322,10 @@ bool ihmc_server::ensure_tiles(size_t n) {
 // Both round tile tables with room for n tiles.  Growing them waits for the
 // rounds in flight, which read the old ones.
 bool ihmc_server::ensure_round_tiles(size_t n) {
-  if (n <= rtile_cap) return true;
+  if (n <= rtile_cap) {
+    if (!rd_tiles[round_buf]) rd_tiles[round_buf] = (Tile*)ctx->arena.alloc(sizeof(Tile) * rtile_cap);
+    return true;
+  }
   if (hipStreamSynchronize(s) != hipSuccess) return false;
   const size_t cap = std::max<size_t>(n, 2 * rtile_cap);
   for (int b = 0; b < 2; ++b) {
@@ -330,15 +338,25 @@ bool ihmc_server::ensure_round_tiles(size_t n) {
   rtile_cap = 0;
   for (int b = 0; b < 2; ++b) {
     if (!copy_ev[b] && hipEventCreateWithFlags(&copy_ev[b], hipEventDisableTiming) != hipSuccess) return false;
-    rd_tiles[b] = (Tile*)ctx->arena.alloc(sizeof(Tile) * cap);
-    if (!rd_tiles[b]) return false;
     if (hipHostMalloc((void**)&rh_tiles[b], sizeof(Tile) * cap, 0) != hipSuccess) {
       rh_tiles[b] = nullptr;
       return false;
     }
+    rd_tiles[b] = (Tile*)ctx->arena.alloc(sizeof(Tile) * cap);
   }
   rtile_cap = cap;
   return true;
+}
+
+// Tables and export buffer out of the arena; the stream is idle.
+void ihmc_server::shed_tables() {
+  for (Tile** t : {&d_tiles, &rd_tiles[0], &rd_tiles[1]}) {
+    if (*t) ctx->arena.release(*t);
+    *t = nullptr;
+  }
+  if (d_export) ctx->arena.release(d_export);
+  d_export = nullptr;
+  export_cap = 0;
 }
 
 bool ihmc_server::ensure_streams(size_t n_groups, size_t n_events) {
@@ -373,11 +391,21 @@ void ihmc_server::retire(Request* r, int32_t final_state) {
       d_export = (double*)ctx->arena.alloc(8 * (uint64_t)c.N);
       export_cap = d_export ? c.N : 0;
     }
+    r->psi.resize(c.N);
     if (d_export) {
-      r->psi.resize(c.N);
       e = launch_export_psi(d_cd, r->slot, d_export, c.N, c.precision, s);
       if (e == hipSuccess) e = hipMemcpyAsync(r->psi.data(), d_export, 8 * c.N, hipMemcpyDeviceToHost, s);
       if (e == hipSuccess) e = hipStreamSynchronize(s);
+    } else {
+      double* h = nullptr;
+      e = hipHostMalloc((void**)&h, 8 * (uint64_t)c.N, 0);
+      if (e == hipSuccess) {
+        e = launch_export_psi(d_cd, r->slot, h, c.N, c.precision, s);
+        const hipError_t e2 = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = e2;
+        if (e == hipSuccess) std::memcpy(r->psi.data(), h, 8 * (size_t)c.N);
+        hipHostFree(h);
+      }
     }
   }
   for (void* p : r->dev) ctx->arena.release(p);
@@ -403,6 +431,10 @@ bool ihmc_server::admit_setup(std::vector<Request*>& fresh) {
   std::vector<void*> temps;
   auto tmp = [&](uint64_t b) {
     void* p = ctx->arena.alloc(b);
+    if (!p) {
+      shed_tables();
+      p = ctx->arena.alloc(b);
+    }
     if (p) temps.push_back(p);
     return p;
   };
@@ -422,26 +454,37 @@ bool ihmc_server::admit_setup(std::vector<Request*>& fresh) {
       if (p) r->dev.push_back(p);
       return p;
     };
-    c.psi = dal((uint64_t)LAT_BUFFERS * c.NP * pb);
-    c.p = dal((uint64_t)LAT_P_BUFFERS * c.NP * pb);
-    c.rec = (TrajRecord*)dal(sizeof(TrajRecord) * (uint64_t)std::max(1, r->run.n_traj));
-    c.st = (ChainState*)dal(sizeof(ChainState));
-    void* pblk = dal(partials_bytes(c.n_tiles));
-    bool good = c.psi && c.p && c.rec && c.st && pblk;
+    void* pblk = nullptr;
+    uint8_t* replay = nullptr;
+    auto take_memory = [&]() {
+      c.psi = dal((uint64_t)LAT_BUFFERS * c.NP * pb);
+      c.p = dal((uint64_t)LAT_P_BUFFERS * c.NP * pb);
+      c.rec = (TrajRecord*)dal(sizeof(TrajRecord) * (uint64_t)std::max(1, r->run.n_traj));
+      c.st = (ChainState*)dal(sizeof(ChainState));
+      pblk = dal(partials_bytes(c.n_tiles));
+      bool good = c.psi && c.p && c.rec && c.st && pblk;
+      if (good && !r->replay.empty()) good = (replay = (uint8_t*)dal(r->replay.size())) != nullptr;
+      if (good && c.h_kind == 2) {
+        c.hp = (double*)dal(8 * (uint64_t)c.NP);
+        c.b = dal((uint64_t)c.NP * pb);
+        good = c.hp && c.b;
+      }
+      if (good) return true;
+      for (void* p : r->dev) ctx->arena.release(p);
+      r->dev.clear();
+      return false;
+    };
+    bool good = take_memory();
+    if (!good) {
+      shed_tables();
+      good = take_memory();
+    }
     if (good) {
       setup_partials(c, pblk);
       e = clear_partials(c, s);
-    }
-    if (good && !r->replay.empty()) {
-      uint8_t* d = (uint8_t*)dal(r->replay.size());
-      good = d != nullptr;
-      if (good) e = hipMemcpyAsync(d, r->replay.data(), r->replay.size(), hipMemcpyHostToDevice, s);
-      c.replay = d;
-    }
-    if (good && c.h_kind == 2) {
-      c.hp = (double*)dal(8 * (uint64_t)c.NP);
-      c.b = dal((uint64_t)c.NP * pb);
-      good = c.hp && c.b;
+      c.replay = replay;
+      if (e == hipSuccess && replay)
+        e = hipMemcpyAsync(replay, r->replay.data(), r->replay.size(), hipMemcpyHostToDevice, s);
     }
     if (!good || e != hipSuccess) {
       for (void* p : r->dev) ctx->arena.release(p);
@@ -522,8 +565,8 @@ bool ihmc_server::admit_setup(std::vector<Request*>& fresh) {
       e = hipErrorOutOfMemory;
     } else {
       std::memcpy(h_tiles, tiles.data(), sizeof(Tile) * tiles.size());
-      e = hipMemcpyAsync(d_tiles, h_tiles, sizeof(Tile) * tiles.size(), hipMemcpyHostToDevice, s);
-      if (e == hipSuccess) e = launch_measure(g, d_tiles, d_cd, s);
+      if (d_tiles) e = hipMemcpyAsync(d_tiles, h_tiles, sizeof(Tile) * tiles.size(), hipMemcpyHostToDevice, s);
+      if (e == hipSuccess) e = launch_measure(g, d_tiles ? d_tiles : h_tiles, d_cd, s);
     }
   }
   if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -585,20 +628,25 @@ bool ihmc_server::run_round() {
   // trajectory per round, so the host's counts do not need the device).  Only
   // retirement, admission and checkpoints wait for the rounds in flight.
   const int b = round_buf;
-  round_buf ^= 1;
   hipError_t e = hipSuccess;
   if (!ensure_round_tiles(tiles.size()) || !ensure_streams(g.size(), round_events(g))) e = hipErrorOutOfMemory;
+  round_buf ^= 1;
   if (e == hipSuccess && copy_pending[b]) {
     e = hipEventSynchronize(copy_ev[b]);  // the upload two rounds back has read rh_tiles[b]
     copy_pending[b] = false;
   }
   if (e == hipSuccess) {
     std::memcpy(rh_tiles[b], tiles.data(), sizeof(Tile) * tiles.size());
-    e = hipMemcpyAsync(rd_tiles[b], rh_tiles[b], sizeof(Tile) * tiles.size(), hipMemcpyHostToDevice, s);
+    if (rd_tiles[b]) {
+      e = hipMemcpyAsync(rd_tiles[b], rh_tiles[b], sizeof(Tile) * tiles.size(), hipMemcpyHostToDevice, s);
+      if (e == hipSuccess) e = hipEventRecord(copy_ev[b], s);
+      if (e == hipSuccess) e = enqueue_round_plan(g, rd_tiles[b], d_cd, side, events, s);
+    } else {
+      e = enqueue_round_plan(g, rh_tiles[b], d_cd, side, events, s);
+      if (e == hipSuccess) e = hipEventRecord(copy_ev[b], s);
+    }
   }
-  if (e == hipSuccess) e = hipEventRecord(copy_ev[b], s);
   if (e == hipSuccess) copy_pending[b] = true;
-  if (e == hipSuccess) e = enqueue_round_plan(g, rd_tiles[b], d_cd, side, events, s);
   if (e != hipSuccess) {
     fail_all("round", e);
     return false;
