@@ -506,9 +506,24 @@ Chains::~Chains() {
   for (hipEvent_t ev : events) hipEventDestroy(ev);
   for (hipStream_t st : side) hipStreamDestroy(st);
   for (void* p : allocs) ctx->arena.release(p);
+  for (void* p : pinned) hipHostFree(p);
 }
 
-
+// A table of `bytes` bytes that launches read, in the arena (listed in `blocks`), or where
+// that has no room left for it in pinned host memory: tables are no reason to refuse a set.
+void* Chains::table(uint64_t bytes, const void* from, std::vector<void*>& blocks, hipError_t* e) {
+  void* p = ctx->arena.alloc(bytes);
+  if (p) {
+    blocks.push_back(p);
+    *e = hipMemcpyAsync(p, from, bytes, hipMemcpyHostToDevice, ctx->stream);
+    return p;
+  }
+  *e = hipHostMalloc(&p, bytes, 0);
+  if (*e != hipSuccess) return nullptr;
+  pinned.push_back(p);
+  std::memcpy(p, from, bytes);
+  return p;
+}
 
 int Chains::build(int32_t n_, const ihmc_lattice* lats, const ihmc_run* runs, int flags) {
   n = n_;
@@ -593,13 +608,13 @@ int Chains::build(int32_t n_, const ihmc_lattice* lats, const ihmc_run* runs, in
       events.push_back(ev);
     }
   }
-  d_tiles = (Tile*)dalloc(sizeof(Tile) * all_tiles.size());
+  hipError_t te = hipSuccess;
+  d_tiles = (Tile*)table(sizeof(Tile) * all_tiles.size(), all_tiles.data(), allocs, &te);
   if (!d_tiles) {
     cleanup();
     return set_error(IHMC_E_NOMEM, "arena exhausted (tile table)");
   }
-  HIPCHK(hipMemcpyAsync(d_tiles, all_tiles.data(), sizeof(Tile) * all_tiles.size(), hipMemcpyHostToDevice, s),
-         "tile upload");
+  HIPCHK(te, "tile upload");
   HIPCHK(hipMemcpyAsync(d_cd, cd.data(), sizeof(ChainDev) * (uint64_t)n, hipMemcpyHostToDevice, s), "chain upload");
   HIPCHK(launch_reset(d_cd, n, 0, s), "chain states");
 
@@ -673,13 +688,12 @@ int Chains::build(int32_t n_, const ihmc_lattice* lats, const ihmc_run* runs, in
     max_sites = std::max(max_sites, N);
   }
   if (!start.empty()) {
-    StartField* d_start = (StartField*)tmp_alloc(sizeof(StartField) * start.size());
+    const StartField* d_start = (const StartField*)table(sizeof(StartField) * start.size(), start.data(), temps, &te);
     if (!d_start) {
       cleanup();
       return set_error(IHMC_E_NOMEM, "arena exhausted (starting fields)");
     }
-    HIPCHK(hipMemcpyAsync(d_start, start.data(), sizeof(StartField) * start.size(), hipMemcpyHostToDevice, s),
-           "start table");
+    HIPCHK(te, "start table");
     HIPCHK(launch_start(d_cd, d_start, (int)start.size(), max_sites, s), "starting fields");
   }
   HIPCHK(launch_measure(groups, d_tiles, d_cd, s), "measure pass");

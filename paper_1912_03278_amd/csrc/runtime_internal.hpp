@@ -184,6 +184,7 @@ struct Chains {
   Tile* d_tiles = nullptr;
   std::vector<Group> groups;
   std::vector<void*> allocs;
+  std::vector<void*> pinned;       // tables that found no room in the arena
   std::vector<hipStream_t> side;   // one per launch group
   std::vector<hipEvent_t> events;  // fork/join points of one round
   int enqueued = 0;
@@ -199,6 +200,7 @@ struct Chains {
   hipGraphExec_t gexec = nullptr;
 
   void* dalloc(uint64_t bytes);
+  void* table(uint64_t bytes, const void* from, std::vector<void*>& blocks, hipError_t* e);
   int build(int32_t n, const ihmc_lattice* lats, const ihmc_run* runs, int flags);
   hipError_t enqueue_round(hipStream_t s);
   int advance(int32_t n_traj);
