@@ -279,6 +279,119 @@ __global__ __launch_bounds__(1024) void k_lanczos_orth(const double* __restrict_
   }
 }
 
+// Steps k0 .. k1 - 1 of a small matrix (Np = 256) in one workgroup and one launch: the
+// sums of the three launches, in their order (16 rows a partial sum, rows past N are
+// zero), so the results are the same to the bit.  Three launches a step are what bounds
+// the smallest (lowest eigenvalue of 16 sites 0.27 ms, of 64 0.83; in one launch per 16
+// steps 0.18 and 0.66); one CU's reads of K and of the basis soon cost more: 100 sites 0.85
+// and 0.79 ms, 128 1.16 and 1.22, 160 1.10 and 1.32.
+constexpr int kLanczosSmall = 64;       // steps that it takes
+constexpr int64_t kLanczosSmallN = 112;  // and sites
+
+__global__ __launch_bounds__(1024) void k_lanczos_small(const double* __restrict__ K64, double* __restrict__ Q, int k0,
+                                                        int k1, double* __restrict__ wa, double* __restrict__ wb,
+                                                        double* __restrict__ npart, double* __restrict__ ab, int N) {
+  constexpr int NP = 256, NB = NP / 16;
+  __shared__ double sw[NP], sP[NB][kLanczosSmall], sc[kLanczosSmall], sA[16][NP], sn[NB];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, row = t & (NP - 1), q4 = t >> 8;
+  const int nb = (N + 15) / 16;
+  if (t < NB) sn[t] = k0 > 0 ? npart[t] : 0.0;
+  if (t < NP) sw[t] = 0.0;
+  __syncthreads();
+  // c = Q^T w: partial sums over 16 rows, then over these
+  auto coefficients = [&](int k) {
+#pragma unroll 4
+    for (int p = t >> 4; p < nb * (k + 1); p += 64) {
+      const int b = p % nb, j = p / nb, i = 16 * b + (t & 15);
+      double s = Q[(int64_t)j * NP + i] * sw[i];
+      for (int off = 8; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+      if ((t & 15) == 0) sP[b][j] = s;
+    }
+    __syncthreads();
+    if (t <= k) {
+      double q[4];
+      for (int a = 0; a < 4; ++a) {
+        q[a] = 0.0;
+        for (int b = 4 * a; b < min(4 * a + 4, nb); ++b) q[a] += sP[b][t];
+      }
+      sc[t] = (q[0] + q[1]) + (q[2] + q[3]);
+    }
+    __syncthreads();
+  };
+  // w -= Q c: four terms, then the sixteen sums of four in turn
+  auto orthogonalise = [&](int k) {
+    double q[16];
+#pragma unroll
+    for (int a = 0; a < 16; ++a) q[a] = Q[(int64_t)min(16 * q4 + a, k) * NP + row];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      double x[4];
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const int j = 16 * q4 + 4 * v + a;
+        x[a] = j <= k ? 0.0 + sc[j] * q[4 * v + a] : 0.0;
+      }
+      sA[4 * q4 + v][row] = (x[0] + x[1]) + (x[2] + x[3]);
+    }
+    __syncthreads();
+    if (t < NP) {
+      double d = 0.0;
+      for (int v = 0; v < 16; ++v) d += sA[v][t];
+      sw[t] -= d;
+    }
+    __syncthreads();
+  };
+  for (int k = k0; k < k1; ++k) {
+    const double* u = k == 0 ? Q : ((k & 1) ? wa : wb);  // w of the step before
+    double* w = (k & 1) ? wb : wa;
+    double inv = 1.0;
+    if (k > 0) {
+      double ss = lane < NB ? sn[lane] : 0.0;
+      for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
+      const double bk = sqrt(ss);
+      inv = bk > 0.0 ? 1.0 / bk : 0.0;
+      if (t < NP) Q[(int64_t)k * NP + t] = u[t] * inv;
+      if (t == 0) ab[2 * (k - 1) + 1] = bk;
+    }
+    double2 uv[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      uv[h] = *reinterpret_cast<const double2*>(u + 2 * lane + 128 * h);
+      uv[h].x *= inv;
+      uv[h].y *= inv;
+    }
+#pragma unroll 4
+    for (int r = wave; r < N; r += 16) {
+      const double* kr = K64 + (int64_t)r * NP + 2 * lane;
+      double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const double2 kv = *reinterpret_cast<const double2*>(kr + 128 * h);
+        s0 += kv.x * uv[h].x;
+        s1 += kv.y * uv[h].y;
+      }
+      double s = s0 + s1;
+      for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+      if (lane == 0) sw[r] = s;
+    }
+    __syncthreads();  // w and q_k
+    coefficients(k);
+    const double alpha = sc[k];
+    orthogonalise(k);
+    coefficients(k);
+    if (t == 0) ab[2 * k] = alpha + sc[k];
+    orthogonalise(k);
+    if (t < NP) {
+      w[t] = sw[t];
+      double ss = sw[t] * sw[t];
+      for (int off = 8; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
+      if ((t & 15) == 0) sn[t >> 4] = ss;
+    }
+    __syncthreads();
+  }
+  if (t < NB) npart[t] = sn[t];
+}
+
 // ---- conjugate gradients (Kt x = rhs, FP64) ---------------------------------
 //
 // One or two right-hand sides side by side, each with its own vectors and scalars
@@ -816,7 +929,7 @@ uint64_t lanczos_work_doubles(int64_t Np, int mmax) {
   return 2 * (uint64_t)Np + 128 + 2 * (uint64_t)(mmax + 1) + 2 * (uint64_t)lanczos_blocks(Np) * (uint64_t)(mmax + 1);
 }
 
-hipError_t lanczos_step(const double* K64, double* Q, int k, const LanczosWork& lw, int64_t Np, hipStream_t s) {
+static hipError_t lanczos_step(const double* K64, double* Q, int k, const LanczosWork& lw, int64_t Np, hipStream_t s) {
   if (k < 0 || k >= kLanczosMax || k >= lw.mmax) return hipErrorInvalidValue;
   const int nb = lanczos_blocks(Np), R = (int)(Np / nb), ps = lw.mmax + 1;
   double *w = lw.w[k & 1], *P2 = lw.P + (int64_t)nb * ps;
@@ -824,6 +937,20 @@ hipError_t lanczos_step(const double* K64, double* Q, int k, const LanczosWork& 
   k_lanczos_orth<true><<<nb, 1024, 0, s>>>(Q, k, w, lw.P, P2, ps, lw.npart, lw.ab, Np, R);
   k_lanczos_orth<false><<<nb, 1024, 0, s>>>(Q, k, w, P2, lw.P, ps, lw.npart, lw.ab, Np, R);
   return hipGetLastError();
+}
+
+hipError_t lanczos_steps(const double* K64, double* Q, int k0, int k1, const LanczosWork& lw, int64_t N, int64_t Np,
+                         hipStream_t s) {
+  if (k0 < 0 || k1 > lw.mmax) return hipErrorInvalidValue;
+  if (Np == 256 && N <= kLanczosSmallN && k1 <= kLanczosSmall) {
+    k_lanczos_small<<<1, 1024, 0, s>>>(K64, Q, k0, k1, lw.w[0], lw.w[1], lw.npart, lw.ab, (int)N);
+    return hipGetLastError();
+  }
+  for (int k = k0; k < k1; ++k) {
+    const hipError_t e = lanczos_step(K64, Q, k, lw, Np, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 LanczosWork lanczos_work(double* mem, int64_t Np, int mmax) {

@@ -19,8 +19,8 @@ hipError_t dense_check(const double* K, int64_t N, unsigned long long* chk, hipS
 hipError_t dense_field(const double* h, int64_t N, int64_t Np, double beta, double sqJ, double* hp, float* b,
                        hipStream_t s);
 // Lanczos with full reorthogonalisation: normalised start vector q_0 = Q[0], and
-// step k, which writes q_k = Q[k] (k > 0), alpha_k = ab[2k], beta_{k-1} = ab[2k - 1]
-// and the n_npart partial sums of beta_k^2.
+// steps k0 .. k1 - 1; step k writes q_k = Q[k] (k > 0), alpha_k = ab[2k], beta_{k-1} =
+// ab[2k - 1] and the n_npart partial sums of beta_k^2.
 constexpr int kLanczosMaxSteps = 1023;
 struct LanczosWork {
   double *npart, *ab;  // npart[128], then ab[2 (mmax + 1)]
@@ -30,7 +30,8 @@ struct LanczosWork {
 uint64_t lanczos_work_doubles(int64_t Np, int mmax);
 LanczosWork lanczos_work(double* mem, int64_t Np, int mmax);
 hipError_t lanczos_start(double* q0, int64_t N, int64_t Np, hipStream_t s);
-hipError_t lanczos_step(const double* K64, double* Q, int k, const LanczosWork& lw, int64_t Np, hipStream_t s);
+hipError_t lanczos_steps(const double* K64, double* Q, int k0, int k1, const LanczosWork& lw, int64_t N, int64_t Np,
+                         hipStream_t s);
 // Conjugate gradients on Kt, one or two right-hand sides (scal[0] = r.r, scal[1] =
 // threshold, scal[2] = r.r at the start; it[0] steps, it[1] stop flag).
 struct CgSystem {

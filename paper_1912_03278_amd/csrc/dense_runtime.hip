@@ -106,8 +106,7 @@ static int lanczos_min(ihmc_ctx* ctx, const double* K64, int64_t N, int64_t Np, 
   const int chunk = 16;
   while (e == hipSuccess && m < mmax) {
     const int m_end = std::min(mmax, m + chunk);
-    for (int k = m; k < m_end && e == hipSuccess; ++k) e = lanczos_step(K64, Q, k, lw, Np, s);
-    if (e != hipSuccess) break;
+    if ((e = lanczos_steps(K64, Q, m, m_end, lw, N, Np, s)) != hipSuccess) break;
     if ((e = hipMemcpyAsync(back.data(), scratch, 8 * (size_t)(head + 2 * m_end), hipMemcpyDeviceToHost, s)) !=
         hipSuccess)
       break;
