@@ -11,9 +11,8 @@
 // holds only the two arrays that neighbours read, psi and w, in rows padded to
 // whole vectors.  A leap-frog step is then two phases (w; kick and drift) of
 // four to six 16-byte LDS reads per vector with a barrier after each.  The
-// accepted field stays in its global buffer (read at the start of a
-// trajectory, written when a proposal is accepted; chains with few registers
-// per thread keep it in registers).
+// accepted field stays in registers too, and goes back to its buffer once, at the
+// launch's end.
 //
 // The per-site arithmetic and the grouping of the FP64 sums (in 2D 16 x-aligned
 // sites as four quads; in 3D x-aligned quads of columns, each column first
@@ -39,9 +38,10 @@
 namespace ihmc {
 
 // Largest resident chain: what four (five with a per-site field) logical
-// arrays of a chain may take.  The two padded LDS arrays of such a chain, with
-// the reduction scratch, stay below 64 KiB for every row length (rows of five
-// FP32 sites are padded most, 8/5).
+// arrays of a chain may take (5088 FP32 or 2544 FP64 sites, 4070 or 2035 with a
+// field).  The two padded LDS arrays take at most 65 088 bytes (FP32 rows of five
+// sites are padded most, 8/5: 5 x 1017), the reduction scratch under 2 KiB, of the
+// CU's 160 KiB.
 constexpr int RES_FIT_BYTES = 81408;
 
 int resident_max_sites(int precision, bool site_field) { return RES_FIT_BYTES / ((site_field ? 5 : 4) * precision); }
@@ -89,7 +89,6 @@ __global__ __launch_bounds__(NT, 4) void lattice_resident(const ChainDev* __rest
   // lanes that share one sum and deal its conversions
   constexpr int GL = (NDIM == 2 && E == 1) ? 16 : 4;
   constexpr int NR = (RES_RANKS + GL - 1) / GL;
-  constexpr bool KEEP = NQ * V * (int)sizeof(T) <= 32;  // accepted field in registers
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ u128 sRed[NW][RES_RANKS];
   __shared__ u128 sSum[RES_RANKS];
@@ -118,7 +117,7 @@ __global__ __launch_bounds__(NT, 4) void lattice_resident(const ChainDev* __rest
   int own[NQ], last[NQ], gix[NQ];
   uint32_t updn[NQ], zmzp[NQ], lfrt[NQ];
   bool act[NQ];
-  T ps[NQ][V], pm[NQ][V], ww[NQ][V], bq[NQ][V], keep[KEEP ? NQ : 1][V];
+  T ps[NQ][V], pm[NQ][V], ww[NQ][V], bq[NQ][V], keep[NQ][V];  // keep: the accepted field
 #pragma unroll
   for (int k = 0; k < NQ; ++k) {
     const int q = tid + NT * k;
@@ -139,7 +138,7 @@ __global__ __launch_bounds__(NT, 4) void lattice_resident(const ChainDev* __rest
       pm[k][e] = (T)0;
       const bool in = act[k] && e <= last[k];
       if (cd.h_kind == 2 && in) bq[k][e] = ((const gmem<T>*)cd.b)[gix[k] + e];
-      if (KEEP) keep[KEEP ? k : 0][e] = in ? gpsi[gix[k] + e] : (T)0;
+      keep[k][e] = in ? gpsi[gix[k] + e] : (T)0;
     }
   }
   // right neighbour of element e: the next one, or the site right of the last
@@ -281,12 +280,7 @@ __global__ __launch_bounds__(NT, 4) void lattice_resident(const ChainDev* __rest
     for (int k = 0; k < NQ; ++k) {
       if (!act[k]) continue;
 #pragma unroll
-      for (int e = 0; e < V; ++e) {
-        T v = (T)0;
-        if (KEEP) v = keep[KEEP ? k : 0][e];
-        else if (e <= last[k]) v = gpsi[gix[k] + e];
-        ps[k][e] = neg_if(v, sign);
-      }
+      for (int e = 0; e < V; ++e) ps[k][e] = neg_if(keep[k][e], sign);
       stv<T, V>(sP + own[k], ps[k]);
     }
   };
@@ -444,21 +438,16 @@ __global__ __launch_bounds__(NT, 4) void lattice_resident(const ChainDev* __rest
       for (int k = 0; k < NQ; ++k) {
         if (!act[k]) continue;
 #pragma unroll
-        for (int e = 0; e < V; ++e) {
-          if (KEEP) keep[KEEP ? k : 0][e] = ps[k][e];
-          else if (e <= last[k]) gpsi[gix[k] + e] = ps[k][e];
-        }
+        for (int e = 0; e < V; ++e) keep[k][e] = ps[k][e];
       }
     }
   }
   // the accepted field back to its buffer and the state (finalize kept cur)
-  if (KEEP) {
 #pragma unroll
-    for (int k = 0; k < NQ; ++k)
+  for (int k = 0; k < NQ; ++k)
 #pragma unroll
-      for (int e = 0; e < V; ++e)
-        if (act[k] && e <= last[k]) gpsi[gix[k] + e] = keep[KEEP ? k : 0][e];
-  }
+    for (int e = 0; e < V; ++e)
+      if (act[k] && e <= last[k]) gpsi[gix[k] + e] = keep[k][e];
   if (tid < (int)(sizeof(ChainState) / 8)) ((uint64_t*)cd.st)[tid] = ((const uint64_t*)&sSt)[tid];
 }
 
