@@ -115,10 +115,10 @@ def tune_tiles(ctx, lats, args, sites=0):
     return {"tile_classes": "autotuned", "tuned_shapes": n, "tune_s": round(dt, 2)}
 
 
-def group_rows(chains, reps, modes=(1,), pair=False):
+def group_rows(chains, reps, modes=(1,), fused=False):
     """Per launch group: tile shape, sites and HIP-event time of the pass kinds
-    (with pair: also the two-step launch of the groups that have one, as
-    pair_us)."""
+    (with fused: also the launch of several middle steps of the groups that have
+    one, as fused_us, and its steps per site)."""
     from paper_1912_03278_amd import ihmc
     rows = []
     for g in range(chains.groups()):
@@ -132,9 +132,10 @@ def group_rows(chains, reps, modes=(1,), pair=False):
         for m in modes:
             name = ("first_us", "middle_us", "last_us")[m]
             row[name] = chains.time_pass(g, mode=m, reps=reps if m == 1 else max(10, reps // 5))["us"]
-        if pair:
-            try:  # groups without two-step launches refuse the mode
-                row["pair_us"] = chains.time_pass(g, mode=ihmc.PAIR, reps=reps)["us"]
+        if fused:
+            try:  # groups without such launches refuse the mode
+                t = chains.time_pass(g, mode=ihmc.FUSED, reps=reps)
+                row["fused_us"], row["fused_steps"] = t["us"], t["sites"] / row["sites"]
             except ihmc.IhmcError:
                 pass
         rows.append(row)
@@ -221,17 +222,17 @@ def streaming_point(args, copy_gbs):
     dt = time.perf_counter() - t0
     acc = ch.result(0, want_psi=False)["acceptance"]
     mid = ch.time_pass(0, mode=1, reps=max(5, args.timing_reps // 5))
-    pair = ch.time_pass(0, mode=ihmc.PAIR, reps=max(5, args.timing_reps // 5)) if args.fuse_steps else None
+    fused = ch.time_pass(0, mode=ihmc.FUSED, reps=max(5, args.timing_reps // 5)) if args.fuse_steps else None
     ch.close()
     ctx.close()
     gbs = BYTES_MIDDLE_F32 * mid["sites"] / (mid["us"] * 1e-6) / 1e9
     print(f"bench: streaming point 8192^2 middle pass {mid['us']:.1f} us = {gbs:.0f} GB/s", file=sys.stderr,
           flush=True)
     extra = {}
-    if pair:
-        pgbs = BYTES_MIDDLE_F32 * pair["sites"] / (pair["us"] * 1e-6) / 1e9
-        extra = {"two_step_pass_us": round(pair["us"], 2), "two_step_achieved_GBs": round(pgbs, 1),
-                 "two_step_traffic": traffic_bytes("stream_2d_pair", sites=pair["sites"])}
+    if fused:
+        fgbs = BYTES_MIDDLE_F32 * mid["sites"] / (fused["us"] * 1e-6) / 1e9
+        extra = {"fused_pass_us": round(fused["us"], 2), "fused_steps": fused["sites"] / mid["sites"],
+                 "fused_achieved_GBs": round(fgbs, 1), "fused_traffic": traffic_bytes("stream_2d_fused", sites=mid["sites"])}
     return {"label": "extra point, not the configured workload: one 2D 8192^2 chain at beta_c, FP32, n_md=20",
             "site_md_steps_per_s": 4 * L * L * 20 / dt, "acceptance": acc,
             "middle_pass_us": round(mid["us"], 2), "bytes_per_launch": BYTES_MIDDLE_F32 * mid["sites"],
@@ -349,18 +350,18 @@ def run_batched(args):
         print(f"bench: plain form on {len(sample)} chains, bitwise equal: {identical}", file=sys.stderr, flush=True)
     acc = [chains.result(i, want_psi=False)["acceptance"] for i in range(0, len(ws), max(1, len(ws) // 64))]
 
-    # launch groups (all chains FP32 2D): HIP-event times of the one-step and
-    # two-step launches; a launch moves 20 B per site (psi, p and the field
-    # read, p and psi written) for one or two MD steps
-    kern = group_rows(chains, args.timing_reps, pair=args.fuse_steps)
+    # launch groups (all chains FP32 2D): HIP-event times of the one-step launch and of
+    # the rounds' launches of several; a launch moves 20 B per site (psi, p and the
+    # field read, p and psi written) for all its MD steps
+    kern = group_rows(chains, args.timing_reps, fused=args.fuse_steps)
     for k in kern:
-        for name in ("middle", "pair"):
+        for name in ("middle", "fused"):
             if f"{name}_us" in k:
                 k[f"{name}_physical_GBs"] = round(20 * k["sites"] / (k[f"{name}_us"] * 1e-6) / 1e9, 1)
                 k[f"{name}_us"] = round(k[f"{name}_us"], 2)
-    key = "pair_us" if args.fuse_steps else "middle_us"
+    key = "fused_us" if args.fuse_steps else "middle_us"
     gi, dom = max(((g, k) for g, k in enumerate(kern) if key in k), key=lambda t: t[1]["sites"])
-    steps_per_launch = 2 if args.fuse_steps else 1
+    steps_per_launch = round(dom["fused_steps"]) if args.fuse_steps else 1
     # algorithmic bytes of one launch: (20 + 8/n_md) B per site-MD-step, per
     # chain of the group, times the site-MD-steps the launch advances
     dom_chains = [ws[i] for i in chains.group_chains(gi)]
@@ -370,7 +371,7 @@ def run_batched(args):
     achieved_phys = phys_bytes / (dom[key] * 1e-6) / 1e9
     copy_bytes = 512 << 20
     copy_gbs = 2 * copy_bytes / (ctx.copy_bandwidth(copy_bytes, reps=10) * 1e-6) / 1e9
-    cls_traffic = traffic_bytes("batched_pair" if args.fuse_steps else "batched_middle", sites=dom["sites"],
+    cls_traffic = traffic_bytes("batched_fused" if args.fuse_steps else "batched_middle", sites=dom["sites"],
                                 tiles=dom["tiles"])
     line = {
         "metric": METRIC, "value": value, "unit": "site-MD-steps/s", "n_gpus": 1, "steps": K,
@@ -381,11 +382,11 @@ def run_batched(args):
                                "one step = one trajectory of every chain",
                    "chains": len(ws), "sites": sum(int(math.prod(w["L"])) for w in ws),
                    "execution_form": "one HIP graph per round (per-pass launches of every tile-class group on "
-                                     "streams of their own; chains of at most 5024 sites as LDS-resident whole-"
+                                     "streams of their own; chains of at most 5088 sites as LDS-resident whole-"
                                      "trajectory launches beside them), replayed per round; not a single persistent "
                                      "kernel with a device work queue",
                    **tiles, "resident": args.resident, "fuse_steps": args.fuse},
-        "roofline": {"bound": "hbm", "kernel": ("two-step " if args.fuse_steps else "") +
+        "roofline": {"bound": "hbm", "kernel": (f"{steps_per_launch}-step " if args.fuse_steps else "") +
                                                f"fused middle pass, 2D, per-site field, {dom['tiles']}-tile group "
                                                f"({dom['chains']} chains, {dom['sites']} sites)",
                      "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -943,16 +944,16 @@ def run_large(args, K=None, W=None):
 
     # ---- roofline of the dominant kernel: HIP-event timing of each fused pass kind
     # groups are ordered (precision, ndim, tile class): the 2D chain, then the 3D one
-    # per group, the launch kind that carries most of its middle steps: the
-    # two-step launch of a fused 2D group (plus one single step for an odd
-    # number of middle steps), else the one-step pass; both move 16 B per site
-    kern = group_rows(chains, args.timing_reps, modes=(1, 0, 2), pair=args.fuse_steps)
+    # per group, the launch kind that carries most of its middle steps: the launch
+    # of several steps of a fused 2D group (what is left over counted in full), else
+    # the one-step pass; both move 16 B per site
+    kern = group_rows(chains, args.timing_reps, modes=(1, 0, 2), fused=args.fuse_steps)
     for g, k in enumerate(kern):
         n_mid = ws[g]["n_md"] - 1
-        if "pair_us" in k:
-            k["kind"], k["kind_us"] = "two-step middle pass", k["pair_us"]
-            k["middle_share_us"] = (n_mid // 2) * k["pair_us"] + (n_mid % 2) * k["middle_us"]
-            k["steps_per_launch"] = 2
+        if "fused_us" in k:
+            n = k["steps_per_launch"] = round(k["fused_steps"])
+            k["kind"], k["kind_us"] = f"{n}-step middle pass", k["fused_us"]
+            k["middle_share_us"] = math.ceil(n_mid / n) * k["fused_us"]
         else:
             k["kind"], k["kind_us"] = "middle pass", k["middle_us"]
             k["middle_share_us"] = n_mid * k["middle_us"]
@@ -965,7 +966,7 @@ def run_large(args, K=None, W=None):
     achieved_phys = phys_bytes / (dom["kind_us"] * 1e-6) / 1e9
     dom_kind, dom_us, dom_steps = dom["kind"], dom["kind_us"], dom["steps_per_launch"]
     for k in kern:
-        for name in ("middle", "pair"):
+        for name in ("middle", "fused"):
             if f"{name}_us" in k:
                 k[f"{name}_physical_GBs"] = round(BYTES_MIDDLE_F32 * k["sites"] / (k[f"{name}_us"] * 1e-6) / 1e9, 1)
                 k[f"{name}_us"] = round(k[f"{name}_us"], 3)
@@ -993,7 +994,7 @@ def run_large(args, K=None, W=None):
             "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4),
             "traffic": traffic_bytes(("large_3d_" if dom["ndim"] == 3 else "large_2d_") +
-                                     ("pair" if dom_kind.startswith("two") else "middle"),
+                                     ("fused" if dom_steps > 1 else "middle"),
                                      sites=dom["sites"], tiles=dom["tiles"]),
             "algorithmic_bytes_per_launch": int(alg_bytes),
             "algorithmic_basis": f"(16 + 4/n_md) B per site-MD-step x {dom_steps} MD step(s) "

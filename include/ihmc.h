@@ -515,10 +515,12 @@ int ihmc_chains_group_info(ihmc_chains* chains, int32_t group, int64_t* out);
  * entries). */
 int ihmc_chains_group_chains(ihmc_chains* chains, int32_t group, int32_t* chain_idx);
 /* Time the fused pass kind `mode` (0 = first, 1 = middle, 2 = last, 5 = two
- * middle steps in one launch, 2D groups whose chains have at least two middle
- * steps; a round's launches take up to four) of launch group `group`: one warm-up launch, then `reps` launches bracketed by HIP
+ * middle steps in one launch, 6 = as many as a round's launches take, two or four;
+ * 5 and 6 in 2D groups whose chains have at least two middle steps) of launch group
+ * `group`: one warm-up launch, then `reps` launches bracketed by HIP
  * events on the context stream.  Returns the mean duration per launch in
- * microseconds and the lattice sites one launch covers.  The repeated passes
+ * microseconds and the lattice sites one launch covers (mode 6: each counted once
+ * for every step that it takes).  The repeated passes
  * overwrite the chains' momenta and field buffers (and a last pass closes a
  * trajectory of every chain in the group): call it only when the chains'
  * results have been fetched or are no longer needed. */

@@ -10,8 +10,17 @@
 
 namespace ihmc {
 
-// PASS_PAIR: two middle steps in one launch (2D groups; timing only).
-enum PassMode : int { PASS_FIRST = 0, PASS_MIDDLE = 1, PASS_LAST = 2, PASS_MEASURE = 3, PASS_FORCE = 4, PASS_PAIR = 5 };
+// PASS_PAIR, PASS_FUSED: two middle steps in one launch, and as many as a round's launches
+// take (2D groups; timing only).
+enum PassMode : int {
+  PASS_FIRST = 0,
+  PASS_MIDDLE = 1,
+  PASS_LAST = 2,
+  PASS_MEASURE = 3,
+  PASS_FORCE = 4,
+  PASS_PAIR = 5,
+  PASS_FUSED = 6
+};
 
 struct TileShape {
   int bx, by, bz;

@@ -1509,29 +1509,33 @@ extern "C" int ihmc_chains_time_pass(ihmc_chains* ch, int32_t group, int32_t mod
   ihmc_ctx* ctx = c->ctx;
   CTX_OK(ctx);
   if (group < 0 || group >= (int32_t)c->groups.size()) return set_error(IHMC_E_INVAL, "group out of range");
-  if (mode != PASS_FIRST && mode != PASS_MIDDLE && mode != PASS_LAST && mode != PASS_PAIR)
-    return set_error(IHMC_E_INVAL, "only FIRST, MIDDLE, LAST and PAIR passes can be timed");
+  const bool fused = mode == PASS_PAIR || mode == PASS_FUSED;
+  if (mode != PASS_FIRST && mode != PASS_MIDDLE && mode != PASS_LAST && !fused)
+    return set_error(IHMC_E_INVAL, "only FIRST, MIDDLE, LAST, PAIR and FUSED passes can be timed");
   if (reps < 1) return set_error(IHMC_E_INVAL, "reps must be >= 1");
   const Group& g = c->groups[group];
   if (g.cls < 0)
     return set_error(IHMC_E_UNSUPPORTED, "group %d runs LDS-resident whole trajectories, not passes", group);
-  if (mode == PASS_PAIR && g.ndim != 2)
-    return set_error(IHMC_E_UNSUPPORTED, "group %d: two-step launches are 2D only", group);
+  if (fused && g.ndim != 2)
+    return set_error(IHMC_E_UNSUPPORTED, "group %d: launches of several steps are 2D only", group);
   for (int ci : g.order) {
     if (mode == PASS_MIDDLE && c->cd[ci].n_pass < 3)
       return set_error(IHMC_E_INVAL, "chain %d has no middle pass", ci);
-    if (mode == PASS_PAIR && c->cd[ci].n_pass < 4)
+    if (fused && c->cd[ci].n_pass < 4)
       return set_error(IHMC_E_INVAL, "chain %d has fewer than two middle steps", ci);
   }
+  // FUSED counts a site once for every step that it takes
+  const int steps = mode == PASS_FUSED ? g.steps.steps : 2;
   int64_t nsite = 0;
-  for (int ci : g.order) nsite += c->cd[ci].N;
+  for (int ci : g.order) nsite += c->cd[ci].N * (mode == PASS_FUSED ? std::min(steps, c->cd[ci].n_pass - 2) : 1);
+  const bool full = mode == PASS_FUSED && g.n_pass.back() - 2 >= steps;
   hipStream_t s = ctx->stream;
   hipEvent_t e0, e1;
   HIPCHK(hipEventCreate(&e0), "event");
   HIPCHK(hipEventCreate(&e1), "event");
   auto launch = [&]() {
-    if (mode == PASS_PAIR)
-      return launch_lattice_steps(g.prec, g.steps, c->d_cd, c->d_tiles + g.st_off, g.st_begin.back(), 1, 1, 2, false, s);
+    if (fused)
+      return launch_lattice_steps(g.prec, g.steps, c->d_cd, c->d_tiles + g.st_off, g.st_begin.back(), 1, 1, steps, full, s);
     return launch_lattice_pass(g.prec, g.ndim, g.cls, mode, c->d_cd, c->d_tiles + g.tile_off, g.tile_begin.back(), 1, 1, s,
                                g.sole3d, g.aligned);
   };

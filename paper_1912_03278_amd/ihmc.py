@@ -23,7 +23,7 @@ F32, F64 = 4, 8
 LEAPFROG, OMELYAN = 0, 1
 FORM_PSI, FORM_PHI = 0, 1  # the substituted field (the hot path) / the inverse formulation (A/B baseline)
 FORM_SHIFTED = 2  # the substitution phi = sqrt(J') Kt psi: h' inside the log cosh
-FIRST, MIDDLE, LAST, PAIR = 0, 1, 2, 5  # pass kinds of Chains.time_pass
+FIRST, MIDDLE, LAST, PAIR, FUSED = 0, 1, 2, 5, 6  # pass kinds of Chains.time_pass
 TAG_INIT, TAG_MOM, TAG_ACC, TAG_FLIP = 1, 2, 3, 4
 
 EXPORTS = (
@@ -668,7 +668,8 @@ class Chains:
 
     def time_pass(self, group, mode=1, reps=50):
         """Mean duration (us) of one fused pass launch of a group, timed with HIP events
-        (mode 0 first, 1 middle, 2 last, PAIR = two middle steps, 2D only)."""
+        (mode 0 first, 1 middle, 2 last; 2D only: PAIR two middle steps, FUSED as many
+        as a round's launches take, "sites" then times the steps)."""
         us, sites, nd, pr = C.c_double(), C.c_int64(), C.c_int32(), C.c_int32()
         _check(load().ihmc_chains_time_pass(self.h, int(group), int(mode), int(reps), C.byref(us),
                                             C.byref(sites), C.byref(nd), C.byref(pr)))

@@ -30,3 +30,26 @@ def test_equal_one_step_a_launch(L, n, prec, n_md):
     for a, b in zip(*out):
         for k in ("dH", "H_old", "H_new", "m", "beta_eps", "accepted", "psi_final"):
             assert np.array_equal(a[k], b[k], equal_nan=True), k
+
+
+@pytest.mark.parametrize("L,n,prec,n_md,steps", [
+    ((64, 50), 3, 4, (9,), 4), ((30, 25), 1100, 8, (9,), 2), ((64, 50), 4, 4, (9, 4), (4 + 3) / 2),
+])
+def test_timed_launch_is_the_rounds_own(L, n, prec, n_md, steps):
+    """The timed launch takes as many steps as a round's, at most what a chain has,
+    counts a site once for each, and leaves the chains' results as they are."""
+    from paper_1912_03278_amd import ihmc
+    lats = [ihmc.Lattice(L, beta=0.42, C=4.1) for _ in range(n)]
+    runs = [ihmc.Run(n_md=n_md[i % len(n_md)], n_traj=2, precision=prec, seed=4, chain_id=i) for i in range(n)]
+    with ihmc.Context(arena_bytes=2 << 30, resident=0) as ctx:
+        ref = ctx.run_batch(lats, runs)
+        ch = ihmc.Chains(ctx, lats, runs)
+        t = ch.time_pass(0, mode=ihmc.FUSED, reps=3)
+        assert t["us"] > 0 and t["sites"] == steps * n * L[0] * L[1]
+        ch.advance(2)
+        for i, a in enumerate(ref):
+            b = ch.result(i)
+            assert np.array_equal(a["dH"], b["dH"]) and np.array_equal(a["m"], b["m"])
+        with pytest.raises(ihmc.IhmcError):
+            ch.time_pass(0, mode=ihmc.FUSED + 1, reps=1)
+        ch.close()
