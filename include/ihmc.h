@@ -203,7 +203,7 @@ int ihmc_ctx_memory(ihmc_ctx* ctx, uint64_t* used, uint64_t* total);
  * *fp32_fit / *fp64_fit (may be NULL) receive the largest chains that fit
  * without a per-site field (a per-site field takes a fifth array). */
 int ihmc_ctx_set_resident(ihmc_ctx* ctx, int64_t max_sites, int64_t* fp32_fit, int64_t* fp64_fit);
-/* 2D chains on the tiled passes run their middle leap-frog steps up to four per
+/* 2D chains on the tiled passes run their middle leap-frog steps two or four per
  * launch (on != 0, the default): the steps are evaluated on the tile plus a ring
  * that narrows from step to step, with the field and the momenta read and
  * written once per launch.  The per-site arithmetic is that of one step per
@@ -568,8 +568,9 @@ int ihmc_tile_shape(int32_t ndim, int32_t cls, int32_t* out, int32_t* n_classes)
  * last-level cache decides which tile is fastest.  sites = 0 takes the total
  * sites of lats[0..n), repeats included (pass the lattices of the chains that
  * will run together); the value is clamped to [2^20, 2^26].  Per class, `reps`
- * launches (0: 10, or 4 above 2^23 sites) after a warm-up, in three rounds
- * interleaved across the classes, keeping the least mean.  The arena must hold
+ * launches (0: 10, or 4 above 2^23 sites; of a first and last pass a quarter as many)
+ * after a warm-up, in three rounds interleaved across the classes, keeping the least
+ * mean.  The arena must hold
  * the replicas (6 state fields, 7 with a per-site field, each replica) for the
  * duration of one key.  Keys with a measured entry are skipped unless flags has
  * IHMC_TUNE_FORCE; pinned keys are always skipped.  Synchronous; *n_measured
