@@ -9,9 +9,9 @@ of every chain; the metric is site-MD-steps/s = (sites x MD steps) per second
 over the timed steps.  Beside it the line carries
 
   * the roofline of the dominant launch kind (HIP-event timed on the library's
-    stream): the algorithmic fraction (20 + 8/n_md bytes per site-MD-step times
-    the site-MD-steps one launch advances) and the physical one (20 bytes per
-    site and launch);
+    stream): the fraction of the HBM peak by the bytes a launch has to move (20 per
+    site, whatever its MD steps), and beside it that by the bytes the same steps
+    take one a launch (20 + 8/n_md per site-MD-step), which may exceed one;
   * the plain form: a sample of the same chains run one at a time, its rate and
     whether every result is bitwise equal to the batched run;
   * the FP64 CPU oracle on a 64-chain sample of the workload (5 trajectories
@@ -52,23 +52,23 @@ KERNEL_SOURCES = ("lattice_kernels.hip", "lattice_kernels.hpp", "chain_epilogue.
                   "ihmc_internal.hpp", "dense_kernels.hip", "dense_kernels.hpp")
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 TRAFFIC = {
-    "large_2d_middle": {"sources": "b2a10c053ede82e0", "tiles": "64x16", "sites": 1048576,
+    "large_2d_middle": {"sources": "14db994acd5fd456", "tiles": "64x16", "sites": 1048576,
                         "fetch_kib": 4207.0, "write_kib": 8192.0},
-    "large_2d_pair": {"sources": "b2a10c053ede82e0", "tiles": "64x16", "sites": 1048576,
-                      "fetch_kib": 4353.5, "write_kib": 8192.0},
-    "large_3d_middle": {"sources": "b2a10c053ede82e0", "tiles": "32x8x8", "sites": 2097152,
+    "large_2d_fused": {"sources": "14db994acd5fd456", "tiles": "64x16", "sites": 1048576,
+                       "fetch_kib": 4805.5, "write_kib": 8192.0},
+    "large_3d_middle": {"sources": "14db994acd5fd456", "tiles": "32x8x8", "sites": 2097152,
                         "fetch_kib": 9279.0, "write_kib": 16384.0},
-    "stream_2d_middle": {"sources": "b2a10c053ede82e0", "tiles": "64x16", "sites": 67108864,
-                         "fetch_kib": 263729.3, "write_kib": 524288.0},
-    "stream_2d_pair": {"sources": "b2a10c053ede82e0", "tiles": "64x16", "sites": 67108864,
-                       "fetch_kib": 264983.6, "write_kib": 524288.0},
+    "stream_2d_middle": {"sources": "14db994acd5fd456", "tiles": "64x16", "sites": 67108864,
+                         "fetch_kib": 263716.8, "write_kib": 524288.0},
+    "stream_2d_fused": {"sources": "14db994acd5fd456", "tiles": "64x16", "sites": 67108864,
+                        "fetch_kib": 326522.6, "write_kib": 524288.1},
     # the tuner's choices set which chains form the group, so a launch of the
     # default run may hold a few more or fewer sites: per-site scaling
-    "batched_middle": {"sources": "b2a10c053ede82e0", "tiles": "64x16", "sites": 28718719, "scale_by_sites": True,
-                       "fetch_kib": 170626.8, "write_kib": 226601.3},
-    "batched_pair": {"sources": "b2a10c053ede82e0", "tiles": "64x16", "sites": 28718719, "scale_by_sites": True,
-                     "fetch_kib": 170776.5, "write_kib": 227465.4},
-    "dense_gemm_bf16": {"sources": "b2a10c053ede82e0", "fetch_kib": 73752.0, "write_kib": 16384.0},
+    "batched_middle": {"sources": "14db994acd5fd456", "tiles": "64x16", "sites": 22375693, "scale_by_sites": True,
+                       "fetch_kib": 132909.5, "write_kib": 176679.7},
+    "batched_fused": {"sources": "14db994acd5fd456", "tiles": "64x16", "sites": 22375693, "scale_by_sites": True,
+                      "fetch_kib": 132978.1, "write_kib": 177440.7},
+    "dense_gemm_bf16": {"sources": "14db994acd5fd456", "fetch_kib": 55359.0, "write_kib": 16384.0},
 }
 
 
@@ -389,14 +389,16 @@ def run_batched(args):
         "roofline": {"bound": "hbm", "kernel": (f"{steps_per_launch}-step " if args.fuse_steps else "") +
                                                f"fused middle pass, 2D, per-site field, {dom['tiles']}-tile group "
                                                f"({dom['chains']} chains, {dom['sites']} sites)",
-                     "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": cls_traffic,
+                     "achieved": round(achieved_phys, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                     "frac": round(achieved_phys / HBM_PEAK_GBS, 4), "traffic": cls_traffic,
                      "traffic_basis": None if cls_traffic is None else
                      "FETCH_SIZE x 2 + WRITE_SIZE x 1 (copy-kernel calibration) of the full-group launch, "
                      "per site of the profiled launch times this launch's sites",
                      "algorithmic_bytes_per_launch": int(alg_bytes),
                      "algorithmic_basis": f"(20 + 8/n_md) B per site-MD-step x {steps_per_launch} MD step(s) per "
                                           "site and launch, summed over the group's chains",
+                     "achieved_algorithmic": round(achieved, 1),
+                     "frac_algorithmic": round(achieved / HBM_PEAK_GBS, 4),
                      "physical_bytes_per_launch": phys_bytes, "achieved_physical": round(achieved_phys, 1),
                      "frac_physical": round(achieved_phys / HBM_PEAK_GBS, 4),
                      "avg_launch_us": dom[key], "timing": "HIP events on the library stream, launches back to back",
@@ -991,14 +993,15 @@ def run_large(args, K=None, W=None):
         },
         "roofline": {
             "bound": "hbm", "kernel": f"fused {dom_kind}, {dom['ndim']}D",
-            "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": round(achieved / HBM_PEAK_GBS, 4),
+            "achieved": round(achieved_phys, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": round(achieved_phys / HBM_PEAK_GBS, 4),
             "traffic": traffic_bytes(("large_3d_" if dom["ndim"] == 3 else "large_2d_") +
                                      ("fused" if dom_steps > 1 else "middle"),
                                      sites=dom["sites"], tiles=dom["tiles"]),
             "algorithmic_bytes_per_launch": int(alg_bytes),
             "algorithmic_basis": f"(16 + 4/n_md) B per site-MD-step x {dom_steps} MD step(s) "
                                  "per site and launch",
+            "achieved_algorithmic": round(achieved, 1), "frac_algorithmic": round(achieved / HBM_PEAK_GBS, 4),
             "physical_bytes_per_launch": phys_bytes, "achieved_physical": round(achieved_phys, 1),
             "frac_physical": round(achieved_phys / HBM_PEAK_GBS, 4),
             "avg_launch_us": round(dom_us, 3),
@@ -1085,7 +1088,7 @@ def main():
                     help="chains that fit one workgroup's LDS run whole trajectories per launch (on) or the "
                          "tiled passes (off); results are bit-identical")
     ap.add_argument("--fuse", default="on", choices=["on", "off"],
-                    help="2D chains on the tiled passes run up to four middle leap-frog steps per launch (on) or one "
+                    help="2D chains on the tiled passes run two or four middle leap-frog steps per launch (on) or one "
                          "(off); results are bit-identical")
     ap.add_argument("--tiles", default="tuned", choices=["tuned", "rule"],
                     help="tile classes: autotuned per lattice shape before the run (default), or the built-in rule")

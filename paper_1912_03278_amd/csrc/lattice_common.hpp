@@ -94,7 +94,7 @@ __device__ __forceinline__ void st4<double>(double* __restrict__ p, const double
 // sites take no_site().
 //
 // These terms and their sums bound the last pass on large lattices by VALU issue
-// (981 operations a wave of 256 sites, 97 % of the cycles at 4096^2; an FP64
+// (914 instructions a wave of 256 sites, 91 % of the cycles on 8192^2 FP32, h = 0; an FP64
 // operation holds a SIMD for five cycles, a move or select for three to five).  So
 // no division is scaled, a term that is zero for the chain is left out, a site's
 // terms are added up before the next one starts (65 registers instead of 84: seven

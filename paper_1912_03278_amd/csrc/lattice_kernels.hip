@@ -17,7 +17,7 @@
 //             decision (Sec. 3) and writes the trajectory record;
 //   MEASURE - FP64 action and estimator sums of the accepted field (set-up);
 //   FORCE   - writes F itself (diagnostic; same arithmetic as the other passes).
-// In 2D up to four MIDDLE steps can also run as one launch (lattice_steps2v), with
+// In 2D two or four MIDDLE steps can also run as one launch (lattice_steps2v), with
 // the per-site arithmetic of single passes.
 //
 // Memory layout: rows padded to `pitch` (a multiple of 4 elements), so a thread
@@ -392,9 +392,10 @@ __global__ __launch_bounds__(BX / 4 * BY) void lattice_pass2v(const ChainDev* __
 // the CU's cycles.  The tile's extent is the plan's choice (choose_steps), packed
 // into Tile::z0 as bx | by << 16; bx is a multiple of 4.
 //
-// Bound by VALU issue once launches fill the chip (83 % of the cycles; 19
-// operations and two transcendentals a site and step, times the ring, 1.5 on 64 x
-// 61 tiles), by latency below that.  Per step, against two steps per launch on 64
+// Bound by VALU issue once launches fill the chip (99 % of the cycles on 8192^2, 80 %
+// on 698 chains with a field; 42 VALU instructions a site and step there, 26 of them
+// FP32 arithmetic, 3 transcendental, the ring's included), by latency below that
+// (1024^2: 5.7 us of issue in 10.0).  Per step, against two steps per launch on 64
 // x 16 tiles with one quad a thread: 4096^2 FP32 32.5 -> 23.2 us, 1024^2 3.98 ->
 // 2.64, 256^2 2.04 -> 1.30, 600 chains of 64 .. 256 sites a row with a field 36.0 ->
 // 22.1; 251 x 130 FP64 4.88 -> 2.61.  Two and three steps a launch measured 30.5 and
@@ -1051,7 +1052,8 @@ static hipError_t launch_mode2v(int mode, const ChainDev* chains, const Tile* ti
 //   leave the L2s before the launch's end, and the next one finds them in the Infinity
 //   Cache (plain, through, nontemporal: 64^3 113, 126, 113; 112^3 199, 197, 191; 128^3
 //   224, 222, 205; FP64 96^3 359, 357, 339; beside other groups 30 chains of 16^3 .. 70^3
-//   in three classes 224, -, 228);
+//   in three classes 224, -, 228).  The lead ends a little above the L2s (128 x 128 x 136,
+//   34 MiB, 256, 254, 236; 136 x 136 x 128 290, 291, 286; 140^3, 42 MiB, 332, 338, 351);
 // - from 1M sites (two boxes a CU, which hide the longer stores) to 128 MiB through the L2
 //   (st4_through), where every row starts at a whole 32 bytes (aligned): 160^3 378, 357,
 //   445; 256 chains of 24 x 21 x 30 620, 589, 671; FP64 128^3 680, 641, 709.  Other rows'

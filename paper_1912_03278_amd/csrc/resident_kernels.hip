@@ -21,12 +21,12 @@
 // n_traj = 0 measures S and the estimator sums of the accepted field (the
 // set-up pass) instead.
 //
-// Bound by VALU issue on the chain's one CU: a 64 x 64 FP32 step is 0.83 us (16
-// waves, ~125 VALU instructions a wave) against 6.4 us for the scalar form it
-// replaces (one site per LDS access, five LDS arrays, 256 threads, neighbour
-// addresses worked out at every step); momenta, FP64 sums and the Metropolis
-// step of a trajectory take 13.4 us there (26 before), 4.5 us for 15 x 15
-// (15.4).  1024 such chains of 64 x 64: 105 us a trajectory of 15 steps (294).
+// Bound by VALU issue on the chain's one CU: a 64 x 64 FP32 step is 0.83 us on 16
+// waves (87 VALU instructions a wave, 79 % of the cycles; the rest of a trajectory
+// 94 %; 15 x 15 waits, 24 %) against 6.4 us for the scalar form it replaces (one site per LDS access, five
+// LDS arrays, 256 threads, neighbour addresses worked out at every step); momenta,
+// FP64 sums and the Metropolis step of a trajectory take 13.4 us there (26 before),
+// 4.5 us for 15 x 15 (15.4).  1024 such chains of 64 x 64: 105 us a trajectory of 15 steps (294).
 #include <algorithm>
 #include <type_traits>
 

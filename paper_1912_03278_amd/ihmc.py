@@ -393,7 +393,7 @@ class Context:
         return f32.value, f64.value
 
     def set_step_fusion(self, on=True):
-        """2D chains on the tiled passes run their middle steps up to four per launch
+        """2D chains on the tiled passes run their middle steps two or four per launch
         (bit-identical results); applies to chain sets created afterwards."""
         _check(load().ihmc_ctx_set_step_fusion(self.h, 1 if on else 0))
 
