@@ -52,23 +52,23 @@ KERNEL_SOURCES = ("lattice_kernels.hip", "lattice_kernels.hpp", "chain_epilogue.
                   "ihmc_internal.hpp", "dense_kernels.hip", "dense_kernels.hpp")
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 TRAFFIC = {
-    "large_2d_middle": {"sources": "14db994acd5fd456", "tiles": "64x16", "sites": 1048576,
+    "large_2d_middle": {"sources": "0a51d92e28c4e4d2", "tiles": "64x16", "sites": 1048576,
                         "fetch_kib": 4207.0, "write_kib": 8192.0},
-    "large_2d_fused": {"sources": "14db994acd5fd456", "tiles": "64x16", "sites": 1048576,
+    "large_2d_fused": {"sources": "0a51d92e28c4e4d2", "tiles": "64x16", "sites": 1048576,
                        "fetch_kib": 4805.5, "write_kib": 8192.0},
-    "large_3d_middle": {"sources": "14db994acd5fd456", "tiles": "32x8x8", "sites": 2097152,
+    "large_3d_middle": {"sources": "0a51d92e28c4e4d2", "tiles": "32x8x8", "sites": 2097152,
                         "fetch_kib": 9279.0, "write_kib": 16384.0},
-    "stream_2d_middle": {"sources": "14db994acd5fd456", "tiles": "64x16", "sites": 67108864,
+    "stream_2d_middle": {"sources": "0a51d92e28c4e4d2", "tiles": "64x16", "sites": 67108864,
                          "fetch_kib": 263716.8, "write_kib": 524288.0},
-    "stream_2d_fused": {"sources": "14db994acd5fd456", "tiles": "64x16", "sites": 67108864,
+    "stream_2d_fused": {"sources": "0a51d92e28c4e4d2", "tiles": "64x16", "sites": 67108864,
                         "fetch_kib": 326522.6, "write_kib": 524288.1},
     # the tuner's choices set which chains form the group, so a launch of the
     # default run may hold a few more or fewer sites: per-site scaling
-    "batched_middle": {"sources": "14db994acd5fd456", "tiles": "64x16", "sites": 22375693, "scale_by_sites": True,
+    "batched_middle": {"sources": "0a51d92e28c4e4d2", "tiles": "64x16", "sites": 22375693, "scale_by_sites": True,
                        "fetch_kib": 132909.5, "write_kib": 176679.7},
-    "batched_fused": {"sources": "14db994acd5fd456", "tiles": "64x16", "sites": 22375693, "scale_by_sites": True,
+    "batched_fused": {"sources": "0a51d92e28c4e4d2", "tiles": "64x16", "sites": 22375693, "scale_by_sites": True,
                       "fetch_kib": 132978.1, "write_kib": 177440.7},
-    "dense_gemm_bf16": {"sources": "14db994acd5fd456", "fetch_kib": 55359.0, "write_kib": 16384.0},
+    "dense_gemm_bf16": {"sources": "0a51d92e28c4e4d2", "fetch_kib": 55359.0, "write_kib": 16384.0},
 }
 
 

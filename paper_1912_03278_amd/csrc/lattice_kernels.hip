@@ -380,8 +380,9 @@ __global__ __launch_bounds__(BX / 4 * BY) void lattice_pass2v(const ChainDev* __
 // so no block reads momenta another block of the launch writes.  A chain with
 // fewer middle steps left takes those (at most max_steps), on the rows that these
 // need (2 steps of halo in y), and stores its tile (2048^2 FP64, one step left on tiles
-// for four: 66 us on all rows, 58 on those).  FULL: every chain of the launch takes STEPS
-// (the number known, FP32 launches take 2 % less: 2048^2 199 -> 195 us a trajectory of 20).
+// for four: 66 us on all rows, 58 on those).  FULL: on all rows whatever is left (their
+// number known, FP32 launches take 2 % less: 2048^2 199 -> 195 us a trajectory of 20; a
+// body for each number in one kernel costs small launches 1 to 2 %).
 //
 // A thread owns H consecutive rows of one 4-site chunk column (a strip) and keeps
 // their momenta, psi and field in registers for all steps; LDS holds psi and w.

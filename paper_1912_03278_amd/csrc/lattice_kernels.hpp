@@ -73,8 +73,8 @@ struct StepShape {
 StepShape choose_steps(int precision, const std::vector<std::pair<int, int>>& lattices, int max_middle);
 void steps_tiles(const StepShape& g, int chain, int L0, int L1, std::vector<Tile>& out);
 // Middle steps j .. j + max_steps - 1 (at most g.steps; each chain those that it
-// has) as launch index k over n_tiles entries of steps_tiles.  full: max_steps is
-// g.steps and every chain of them has as many.
+// has) as launch index k over n_tiles entries of steps_tiles.  full: on all rows
+// of halo, whatever a chain has left (any choice gives the same values).
 hipError_t launch_lattice_steps(int precision, const StepShape& g, const ChainDev* chains, const Tile* tiles,
                                 int n_tiles, int j, int k, int max_steps, bool full, hipStream_t s);
 

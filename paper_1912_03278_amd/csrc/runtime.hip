@@ -760,6 +760,17 @@ struct RoundSink {
   }
 };
 
+// Whether a launch of several steps from pass j over the group's first `end` chains takes
+// the form with all rows of halo: where three quarters of its tiles have all steps or all
+// but one left, whose own saving is less than what the rows of each chain cost the others
+// (200 lattices of 72 .. 256 sites a row, 8 .. 32 steps: 261 us a trajectory, with a launch
+// in this form only where every chain has all left; 257).
+static bool all_rows(const Group& g, int j, int end) {
+  int most = 0;
+  while (most < end && g.n_pass[most] - 1 - j >= g.steps.steps - 1) ++most;
+  return 4ll * g.st_begin[most] >= 3ll * g.st_begin[end];
+}
+
 // One trajectory of every chain.  Per group: pass j = 0 (FIRST) over all
 // tiles, then the middle steps over the chains that still have passes after j
 // (in 2D several steps a launch), then one LAST launch over all tiles.  Chains
@@ -794,7 +805,7 @@ static hipError_t round_plan(const std::vector<Group>& groups, const Tile* d_til
         int end = 0;
         while (end < nc && g.n_pass[end] - 1 > j) ++end;
         if (end > 0) {
-          const bool full = g.n_pass[end - 1] - 1 - j >= st;
+          const bool full = all_rows(g, j, end);
           if ((e = sk.steps(g, d_cd, d_tiles + g.st_off, g.st_begin[end], j, k, full, gs)) != hipSuccess) return e;
         }
       }
@@ -1528,7 +1539,7 @@ extern "C" int ihmc_chains_time_pass(ihmc_chains* ch, int32_t group, int32_t mod
   const int steps = mode == PASS_FUSED ? g.steps.steps : 2;
   int64_t nsite = 0;
   for (int ci : g.order) nsite += c->cd[ci].N * (mode == PASS_FUSED ? std::min(steps, c->cd[ci].n_pass - 2) : 1);
-  const bool full = mode == PASS_FUSED && g.n_pass.back() - 2 >= steps;
+  const bool full = mode == PASS_FUSED && all_rows(g, 1, (int)g.order.size());
   hipStream_t s = ctx->stream;
   hipEvent_t e0, e1;
   HIPCHK(hipEventCreate(&e0), "event");

@@ -1,7 +1,7 @@
 """2D launches of two and of four steps, full and with fewer steps left, equal one step a launch.
 
 Two steps a launch: FP64 sets of more than 1024 tiles, and chains of at most two middle
-steps.  A four-step launch knows the number where every chain of it has four left.
+steps.  Where most chains have all steps or all but one left, a launch works on all rows.
 """
 import numpy as np
 import pytest
@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
     ((300, 40), 5, 4, (3, 2)), ((300, 40), 5, 8, (3, 2)),
     ((1256, 1250), 1, 8, (3,)), ((1024, 900), 1, 4, (3,)), ((3, 5), 7, 4, (3, 1)),
     ((70, 66), 40, 4, (9,)), ((70, 66), 40, 4, (9, 10, 6)), ((512, 512), 1, 4, (10,)),
+    ((70, 66), 40, 4, (9, 9, 9, 9, 6)), ((33, 40), 60, 4, (9, 9, 9, 9, 9, 7)), ((5, 7), 30, 4, (5, 5, 5, 5, 3)),  # few with fewer left
 ])
 def test_equal_one_step_a_launch(L, n, prec, n_md):
     from paper_1912_03278_amd import ihmc
