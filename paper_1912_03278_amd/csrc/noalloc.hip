@@ -204,9 +204,14 @@ hipError_t launch_force(const ChainDev& c, const void* psi, void* F, hipStream_t
       {3, 16, 4, 4, launch_force_tiles<T, 3, 16, 4, 4>},   {3, 4, 16, 4, launch_force_tiles<T, 3, 4, 16, 4>},
       {3, 4, 4, 16, launch_force_tiles<T, 3, 4, 4, 16>}};
   const Tile* best = nullptr;
+  double least = 0.0;
   for (const Tile& t : kTiles) {
     if (t.ndim != c.ndim || (t.bx * t.by * t.bz > 256 && c.N < 1024 * 1024)) continue;
-    if (!best || force_work(c, t.bx, t.by, t.bz) < force_work(c, best->bx, best->by, best->bz)) best = &t;
+    const double w = force_work(c, t.bx, t.by, t.bz);
+    if (!best || w < least) {
+      best = &t;
+      least = w;
+    }
   }
   return best->launch(c, psi, F, s);
 }
